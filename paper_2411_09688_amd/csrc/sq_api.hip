@@ -89,6 +89,11 @@ int check_device(const char *fn)
     return SQ_OK;
 }
 
+sq::Shape to_shape(const sq_shape_t *sh)
+{
+    return sq::Shape{sh->B, sh->H, sh->L, sh->C, sh->Lq, sh->U, sh->sm_scale, sh->causal_user};
+}
+
 size_t align256(size_t n) { return (n + 255) & ~(size_t)255; }
 
 // Carves consecutive 256-byte aligned regions out of a workspace.
@@ -373,6 +378,7 @@ sq::UserAttn make_user_pieces(const sq_shape_t *sh, int G, const void *q, const 
 struct PrefillSharedWs {
     sq::DecodePlan plan;
     int32_t *key_idx;
+    float *partials;
 };
 
 PrefillSharedWs carve_prefill_shared(Carver &cv, const sq_shape_t *sh)
@@ -384,13 +390,30 @@ PrefillSharedWs carve_prefill_shared(Carver &cv, const sq_shape_t *sh)
     w.plan.rec = cv.take<int4>(rows * sh->C);
     w.plan.hdr = cv.take<int2>(rows);
     w.key_idx = cv.take<int32_t>(rows * sh->L);
+    w.partials = cv.take<float>(sq::prefill_partial_floats(true, to_shape(sh)));
+    return w;
+}
+
+// Workspace of the masked prefill attention: key -> cluster map, block table, partial results.
+struct PrefillAttnWs {
+    int32_t *key_cid, *blk_info;
+    float *partials;
+};
+
+PrefillAttnWs carve_prefill_attn(Carver &cv, const sq_shape_t *sh)
+{
+    PrefillAttnWs w{};
+    w.key_cid = cv.take<int32_t>((size_t)sh->H * sh->L);
+    w.blk_info = cv.take<int32_t>(sq::prefill_blk_info_ints(sh->H, sh->L));
+    w.partials = cv.take<float>(sq::prefill_partial_floats(false, to_shape(sh)));
     return w;
 }
 
 // Workspace of the whole prefill steps.
 struct PrefillStepWs {
     uint32_t *mask;
-    int32_t *n_ranges, *n_keys, *key_cid, *blk_info;
+    int32_t *n_ranges, *n_keys;
+    PrefillAttnWs att;
 };
 
 PrefillStepWs carve_prefill_step(Carver &cv, const sq_shape_t *sh)
@@ -400,8 +423,7 @@ PrefillStepWs carve_prefill_step(Carver &cv, const sq_shape_t *sh)
     w.mask = cv.take<uint32_t>(rows * ((sh->C + 31) / 32));
     w.n_ranges = cv.take<int32_t>(rows);
     w.n_keys = cv.take<int32_t>(rows);
-    w.key_cid = cv.take<int32_t>((size_t)sh->H * sh->L);
-    w.blk_info = cv.take<int32_t>(sq::prefill_blk_info_ints(sh->H, sh->L));
+    w.att = carve_prefill_attn(cv, sh);
     return w;
 }
 
@@ -475,11 +497,6 @@ int check_ws(const char *fn, const sq_shape_t *sh, int which, void *ws, size_t w
     return SQ_OK;
 }
 
-sq::Shape to_shape(const sq_shape_t *sh)
-{
-    return sq::Shape{sh->B, sh->H, sh->L, sh->C, sh->Lq, sh->U, sh->sm_scale, sh->causal_user};
-}
-
 }  // namespace
 
 extern "C" {
@@ -502,8 +519,7 @@ size_t sq_workspace_bytes(const sq_shape_t *sh, int which)
         else carve_step(cv, sh);
         return cv.off;
     case SQ_CALL_ATTN_PREFILL:
-        cv.take<int32_t>((size_t)sh->H * sh->L);
-        cv.take<int32_t>(sq::prefill_blk_info_ints(sh->H, sh->L));
+        carve_prefill_attn(cv, sh);
         return cv.off;
     case SQ_CALL_SELECT_MEAN:
         cv.take<float>((size_t)sh->B * sh->H * sq::mean_parts_for(sh->Lq) * sh->C);
@@ -844,10 +860,9 @@ int sq_sparse_attn_prefill(const sq_shape_t *sh, const void *q, const void *K_fi
     if (int rc = check_ws(__func__, sh, SQ_CALL_ATTN_PREFILL, ws, ws_bytes)) return rc;
     if (int rc = check_device(__func__)) return rc;
     Carver cv(ws);
-    int32_t *key_cid = cv.take<int32_t>((size_t)sh->H * sh->L);
-    int32_t *blk_info = cv.take<int32_t>(sq::prefill_blk_info_ints(sh->H, sh->L));
-    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, keep_mask, offsets, key_cid, blk_info, out, lse,
-                                   to_shape(sh), static_cast<hipStream_t>(stream)));
+    PrefillAttnWs w = carve_prefill_attn(cv, sh);
+    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, keep_mask, offsets, w.key_cid, w.blk_info,
+                                   w.partials, out, lse, to_shape(sh), static_cast<hipStream_t>(stream)));
     g_err[0] = 0;
     return SQ_OK;
 }
@@ -907,7 +922,7 @@ int sq_sparse_attn_prefill_shared(const sq_shape_t *sh, const void *q, const voi
     Carver cv(ws);
     PrefillSharedWs w = carve_prefill_shared(cv, sh);
     SQ_HIP(sq::launch_ranges_to_rec(ranges, n_ranges, w.plan, sh->B * sh->H, sh->C, s));
-    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.plan, w.key_idx, out, lse,
+    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.plan, w.key_idx, w.partials, out, lse,
                                           to_shape(sh), s));
     g_err[0] = 0;
     return SQ_OK;
@@ -946,7 +961,8 @@ int sq_prefill_step(const sq_shape_t *sh, const void *q, const void *centroids, 
     uint32_t *mask = keep_mask ? keep_mask : w.mask;
     SQ_HIP(sq::launch_prefill_lookup(q, centroids, sizes, thresh, mask, w.n_ranges, n_keys ? n_keys : w.n_keys, nullptr,
                                      false, sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s));
-    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask, offsets, w.key_cid, w.blk_info, out, lse,
+    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask, offsets, w.att.key_cid, w.att.blk_info,
+                                   w.att.partials, out, lse,
                                    to_shape(sh), s));
     g_err[0] = 0;
     return SQ_OK;
@@ -973,7 +989,7 @@ int sq_prefill_mean_step(const sq_shape_t *sh, const void *q, const void *centro
     // the selection writes the kept ranges' records straight into the attention's plan
     SQ_HIP(sq::launch_select(w.part_sum, nullptr, nullptr, true, thresh, sizes, offsets, keep_mask, nullptr, w.n_ranges,
                              n_keys ? n_keys : w.n_keys, w.att.plan, false, 0, opt, rows, sh->H, 1, sh->C, s));
-    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.att.plan, w.att.key_idx, out, lse,
+    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.att.plan, w.att.key_idx, w.att.partials, out, lse,
                                           to_shape(sh), s));
     g_err[0] = 0;
     return SQ_OK;
@@ -1241,7 +1257,8 @@ int sq_hier_prefill_step(const sq_shape_t *sh, int32_t C1, const void *q, const 
     SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, mask2, w.step.n_ranges,
                                      n_keys ? n_keys : w.step.n_keys, nullptr, false, sh->B, sh->H, sh->Lq, sh->C,
                                      sh->sm_scale, s, nullptr, nullptr, w.parent, w.mask1, C1));
-    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask2, offsets2, w.step.key_cid, w.step.blk_info,
+    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask2, offsets2, w.step.att.key_cid, w.step.att.blk_info,
+                                   w.step.att.partials,
                                    out, lse, to_shape(sh), s));
     g_err[0] = 0;
     return SQ_OK;
@@ -1302,7 +1319,7 @@ int sq_hier_prefill_mean_step(const sq_shape_t *sh, int32_t C1, const void *q, c
     SQ_HIP(sq::launch_select(w.step.part_sum, nullptr, nullptr, true, thresh2, sizes2, offsets2, keep_mask2, nullptr,
                              w.step.n_ranges, n_keys ? n_keys : w.step.n_keys, w.step.att.plan, false, 0, opt2, rows,
                              sh->H, 1, sh->C, s));
-    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.step.att.plan, w.step.att.key_idx, out,
+    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.step.att.plan, w.step.att.key_idx, w.step.att.partials, out,
                                           lse, to_shape(sh), s));
     g_err[0] = 0;
     return SQ_OK;

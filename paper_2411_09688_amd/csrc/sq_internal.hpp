@@ -173,13 +173,20 @@ inline size_t prefill_blk_info_ints(int H, int L) { return prefill_skip_count_at
 // (the key -> cluster map and the block table).
 hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                const uint32_t *keep_mask, const int32_t *offsets, int32_t *key_cid, int32_t *blk_info,
-                               void *out, float *lse, const Shape &sh, hipStream_t s);
+                               float *partials, void *out, float *lse, const Shape &sh, hipStream_t s);
 
 // Prefill attention with ONE kept set per (sequence, head): plan.rec / plan.hdr hold the kept ranges' records
 // (from launch_ranges_to_rec); key_idx [B*H, L] is workspace for the list of kept key rows.
 hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
-                                      DecodePlan plan, int32_t *key_idx, void *out, float *lse, const Shape &sh,
-                                      hipStream_t s);
+                                      DecodePlan plan, int32_t *key_idx, float *partials, void *out, float *lse,
+                                      const Shape &sh, hipStream_t s);
+
+// Both forms deal a unit's key blocks to prefill_splits() workgroups where (heads x query blocks) alone do not fill the
+// chip; their partial results (m, l, -, -, o[128]) per (query row, share) go through `partials`
+// (prefill_partial_floats() floats, 0 without a split) to a merge launch.
+constexpr int PF_MAX_SPLIT = 64;
+int prefill_splits(bool shared, const Shape &sh);
+size_t prefill_partial_floats(bool shared, const Shape &sh);
 
 // Offline clustering (sq_kmeans.hip).  hn: [heads * C] floats; hist: [heads * parts * C] ints with
 // parts = ceil(L / kmeans_part_len(L)).

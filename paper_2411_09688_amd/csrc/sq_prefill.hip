@@ -194,7 +194,8 @@ __global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void p
     const _Float16 *__restrict__ q, const _Float16 *__restrict__ Kf, const _Float16 *__restrict__ Vf,
     const _Float16 *__restrict__ Ku, const _Float16 *__restrict__ Vu, const uint32_t *__restrict__ keep_mask,
     const int32_t *__restrict__ key_cid, const int32_t *__restrict__ blk_info, _Float16 *__restrict__ out,
-    float *__restrict__ lse, int B, int H, int L, int C, int Lq, int U, int causal_user, float sm_scale)
+    float *__restrict__ lse, float *__restrict__ partials, int n_split, int B, int H, int L, int C, int Lq, int U,
+    int causal_user, float sm_scale)
 {
     constexpr int QT = PF_QT, BM = pf_bm(SHARED);
     constexpr int PF_THREADS = 64 * pf_waves(SHARED);
@@ -210,8 +211,12 @@ __global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void p
     // one L2 fetches a head's keys once for all of its query blocks.
     const int nqb = (Lq + BM - 1) / BM;
     const int per_xcd = gridDim.x >> 3;                   // grid is a multiple of 8
-    const int unit = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if (unit >= nqb * B * H) return;
+    const int piece = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+    if (piece >= nqb * B * H * n_split) return;
+    // With few (head, query block) units the key blocks of a unit are dealt to n_split workgroups: block positions
+    // split, split + n_split, ... of the unit's walking order (interleaved, so that a run of blocks nobody kept or the
+    // causal end of the user keys is shared out evenly).
+    const int unit = piece / n_split, split = piece - unit * n_split;
     if constexpr (!SHARED) {
         // Which of the two masked kernels does the work: the listed one iff enough (workgroup, block) pairs can be skipped.
         const int nblk_all = (L + PF_BN - 1) / PF_BN;
@@ -405,15 +410,21 @@ __global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void p
         return i < n_list ? (LISTED ? __builtin_amdgcn_readfirstlane((int)s_list[i]) : i) : nblk_fixed + (i - n_list);
     };
 
+    // This workgroup's share: positions at(0), at(1), ... of the walking order; n_mine of them, the first n_mine_fixed
+    // of which are fixed blocks.
+    auto at = [&](int i) { return split + i * n_split; };
+    const int n_mine = (max(n_seq - split, 0) + n_split - 1) / n_split;
+    const int n_mine_fixed = (max(n_list - split, 0) + n_split - 1) / n_split;
+
     int info_cur = 0;
-    if (n_seq > 0) {                                      // (no kept key and no user key: nothing to stage)
-        fetch_idx(0);
+    if (n_mine > 0) {                                     // (no kept key and no user key: nothing to stage)
+        fetch_idx(at(0));
         take_idx();
-        fetch_idx(1);
-        aim(blk_at(0));
+        fetch_idx(at(1));
+        aim(blk_at(at(0)));
         fetch_rest(0, stage[0]);
         info_cur = pinfo;
-        commit(blk_at(0), stage[0]);
+        commit(blk_at(at(0)), stage[0]);
     }
     loads_landed();
     __syncthreads();
@@ -425,14 +436,15 @@ __global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void p
     // plain loop (823 us against 896-929 us unrolled: twice the code for a body that already holds five variants of
     // the block), so the body is kept in a file of its own and included in each loop.
     if constexpr (SHARED) {
-        auto one_block = [&](int blk, auto par) {
+        auto one_block = [&](int it, auto par) {
+            const int blk = at(it);
             PfStage &st = stage[par];
             PfStage &st_next = stage[par ^ 1];
 #define PF_USER(b) ((b) >= nblk_fixed)
 #define PF_NEXT_STAGE st_next
-#define PF_HAS_NEXT (blk + 1 < nblk)
-#define PF_NEXT_BLK (blk + 1)
-#define PF_FETCH_IDX_AHEAD if (blk + 2 < nblk) fetch_idx(blk + 2)
+#define PF_HAS_NEXT (it + 1 < n_mine)
+#define PF_NEXT_BLK at(it + 1)
+#define PF_FETCH_IDX_AHEAD if (it + 2 < n_mine) fetch_idx(at(it + 2))
 #define PF_OPERANDS_AHEAD 0
 #include "sq_prefill_block.inc"
 #undef PF_OPERANDS_AHEAD
@@ -442,17 +454,18 @@ __global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void p
 #undef PF_NEXT_STAGE
 #undef PF_USER
         };
-        for (int blk = 0; blk < nblk; blk += 2) {
-            one_block(blk, std::integral_constant<int, 0>{});
-            if (blk + 1 < nblk) one_block(blk + 1, std::integral_constant<int, 1>{});
+        for (int it = 0; it < n_mine; it += 2) {
+            one_block(it, std::integral_constant<int, 0>{});
+            if (it + 1 < n_mine) one_block(it + 1, std::integral_constant<int, 1>{});
         }
     } else if constexpr (!LISTED) {
-        for (int blk = 0; blk < nblk; ++blk) {
-            PfStage &st = stage[blk & 1];
+        for (int it = 0; it < n_mine; ++it) {
+            const int blk = at(it);
+            PfStage &st = stage[it & 1];
 #define PF_USER(b) ((b) >= nblk_fixed)
-#define PF_NEXT_STAGE stage[(blk + 1) & 1]
-#define PF_HAS_NEXT (blk + 1 < nblk)
-#define PF_NEXT_BLK (blk + 1)
+#define PF_NEXT_STAGE stage[(it + 1) & 1]
+#define PF_HAS_NEXT (it + 1 < n_mine)
+#define PF_NEXT_BLK (blk + n_split)
 #define PF_FETCH_IDX_AHEAD (void)0
 #define PF_OPERANDS_AHEAD 3
 #include "sq_prefill_block.inc"
@@ -468,15 +481,16 @@ __global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void p
         // other needs (base pointers, lengths) is not kept in registers through it.
         // (The list is read two blocks ahead and made scalar only after the block: the entry heads the address chain
         // of the next block's loads, and nothing in front of the block's own work waits for it.)
-        int blk_cur = n_list > 0 ? blk_at(0) : 0, blk_ahead = n_seq > 1 ? blk_at(1) : 0;
-        for (int it = 0; it < n_list; ++it) {
+        int blk_cur = n_mine > 0 ? blk_at(at(0)) : 0, blk_ahead = n_mine > 1 ? blk_at(at(1)) : 0;
+        for (int it = 0; it < n_mine_fixed; ++it) {
             const int blk = blk_cur, blk_nx = blk_ahead;
             int ahead_v = 0;
-            if (it + 2 < n_seq) ahead_v = it + 2 < n_list ? (int)s_list[it + 2] : nblk_fixed + (it + 2 - n_list);
+            const int pos2 = at(it + 2);
+            if (pos2 < n_seq) ahead_v = pos2 < n_list ? (int)s_list[pos2] : nblk_fixed + (pos2 - n_list);
             PfStage &st = stage[it & 1];
 #define PF_USER(b) false
 #define PF_NEXT_STAGE stage[(it + 1) & 1]
-#define PF_HAS_NEXT (it + 1 < n_seq)
+#define PF_HAS_NEXT (it + 1 < n_mine)
 #define PF_NEXT_BLK blk_nx
 #define PF_FETCH_IDX_AHEAD (void)0
 #define PF_OPERANDS_AHEAD 3
@@ -490,13 +504,13 @@ __global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void p
             blk_cur = blk_nx;
             blk_ahead = __builtin_amdgcn_readfirstlane(ahead_v);
         }
-        for (int it = n_list; it < n_seq; ++it) {
-            const int blk = nblk_fixed + (it - n_list);
+        for (int it = n_mine_fixed; it < n_mine; ++it) {
+            const int blk = nblk_fixed + (at(it) - n_list);
             PfStage &st = stage[it & 1];
 #define PF_USER(b) true
 #define PF_NEXT_STAGE stage[(it + 1) & 1]
-#define PF_HAS_NEXT (it + 1 < n_seq)
-#define PF_NEXT_BLK (blk + 1)
+#define PF_HAS_NEXT (it + 1 < n_mine)
+#define PF_NEXT_BLK (blk + n_split)
 #define PF_FETCH_IDX_AHEAD (void)0
 #define PF_OPERANDS_AHEAD 3
 #include "sq_prefill_block.inc"
@@ -514,6 +528,16 @@ __global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void p
     for (int qt = 0; qt < QT; ++qt) {
         const float lt = cross16_sum(l_run[qt]);
         if (nq[qt] >= Lq) continue;
+        if (n_split > 1) {                                // this share's (m, l, o) for the merge launch; m in natural units
+            float *pr = partials + ((row0 + nq[qt]) * (size_t)n_split + split) * PART_STRIDE;
+#pragma unroll
+            for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<f4 *>(pr + 4 + dt * 16 + kg * 4) = o[qt][dt];
+            if (kg == 0) {
+                pr[0] = m_run[qt] * sm_scale;
+                pr[1] = lt;
+            }
+            continue;
+        }
         const bool empty = !(lt > 0.0f);
         const float inv = empty ? 0.0f : 1.0f / lt;
         _Float16 *orow = out + (row0 + nq[qt]) * D;
@@ -528,13 +552,77 @@ __global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void p
     }
 }
 
+// Merges the n_split partial results of a query row: one wave per row, two dimensions per lane.  Bound by the partials'
+// bytes (528 per row and share, just written: mostly still in the caches).
+__global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restrict__ partials, _Float16 *__restrict__ out,
+                                                            float *__restrict__ lse, int n_split, size_t rows)
+{
+    const size_t row = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+    if (row >= rows) return;
+    const float *pr = partials + row * (size_t)n_split * PART_STRIDE;
+    float M = SQ_NEG_INF;
+    for (int s = lane; s < n_split; s += 64) M = fmaxf(M, pr[(size_t)s * PART_STRIDE]);
+    M = wave_max(M);
+    float l = 0.0f, o0 = 0.0f, o1 = 0.0f;
+#pragma unroll 4
+    for (int s = 0; s < n_split; ++s) {
+        const float *p = pr + (size_t)s * PART_STRIDE;
+        const float w = p[0] == SQ_NEG_INF ? 0.0f : expf(p[0] - M);
+        const float2 v = *reinterpret_cast<const float2 *>(p + 4 + 2 * lane);
+        l = fmaf(w, p[1], l);
+        o0 = fmaf(w, v.x, o0);
+        o1 = fmaf(w, v.y, o1);
+    }
+    const bool empty = !(l > 0.0f);
+    const float inv = empty ? 0.0f : 1.0f / l;
+    *reinterpret_cast<h2 *>(out + row * D + 2 * lane) = h2{(_Float16)(o0 * inv), (_Float16)(o1 * inv)};
+    if (lse && lane == 0) lse[row] = empty ? SQ_NEG_INF : M + logf(l);
+}
+
+// Workgroups a unit's key blocks are dealt to.  SLOTS workgroups run at a time (two per compute unit in the masked
+// form, one in the shared-set form), so with u units and s shares the launch takes ceil(u s / SLOTS) rounds of
+// ceil(blocks / s) blocks each plus a fixed part (prologue, first loads, partial results: about four blocks' time), and
+// the merge launch costs its own start and the partials' bytes.  In the shared-set form the number of kept keys is not
+// known on the host: an eighth of the context is assumed (the rule only moves time, not results).  Measured, whole
+// steps, without -> with shares: masked form, 2 x 12 heads x 333 tokens x 9001 keys (144 units, 3 shares) 203 -> 105 us,
+// 20 heads x 17 tokens x 22682 keys (20 units) 491 -> 83 us; shared-set form, 20 heads x 150 tokens x 20011 keys
+// (40 units) 92 -> 53 us, two-level step of 8 heads x 512 tokens x 262144 keys (32 units) 616 -> 250 us.
+int prefill_splits(bool shared, const Shape &sh)
+{
+    const long long slots = shared ? 256 : 512;
+    const long long bm = pf_bm(shared), rows = (long long)sh.B * sh.H * sh.Lq;
+    const long long units = (long long)sh.B * sh.H * ((sh.Lq + bm - 1) / bm);
+    const long long fixed = ((long long)(shared ? (sh.L + 7) / 8 : sh.L) + PF_BN - 1) / PF_BN;
+    const long long nblk = fixed + (sh.U + PF_BN - 1) / PF_BN;
+    int best = 1;
+    double best_cost = 0.0;
+    for (int s = 1; s <= PF_MAX_SPLIT && s <= nblk; ++s) {
+        if (s > 1 && units * s > 2 * slots) break;
+        const double rounds = (double)((units * s + slots - 1) / slots);
+        const double cost = rounds * ((double)((nblk + s - 1) / s) + 4.0) + (s > 1 ? 3.0 + 1.5e-4 * (double)rows * s : 0.0);
+        if (s == 1 || cost < best_cost) {
+            best = s;
+            best_cost = cost;
+        }
+    }
+    return best;
+}
+
+size_t prefill_partial_floats(bool shared, const Shape &sh)
+{
+    const int s = prefill_splits(shared, sh);
+    return s > 1 ? (size_t)sh.B * sh.H * sh.Lq * s * PART_STRIDE : 0;
+}
+
 namespace {
 
 // ev0 / ev1: profiling events recorded in front of / behind the launch (either may be null).
 template <bool SHARED, bool LISTED>
 hipError_t launch_prefill_kernel(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                  const uint32_t *keep_mask, const int32_t *key_cid, const int32_t *blk_info, void *out,
-                                 float *lse, const Shape &sh, hipStream_t s, hipEvent_t ev0, hipEvent_t ev1)
+                                 float *lse, float *partials, const Shape &sh, hipStream_t s, hipEvent_t ev0,
+                                 hipEvent_t ev1)
 {
     const size_t smem = 2 * sizeof(PfStage) + (LISTED ? PF_LIST_BYTES : 0);
     static bool attr_set = false;   // one GPU per process in this build
@@ -545,18 +633,29 @@ hipError_t launch_prefill_kernel(const void *q, const void *Kf, const void *Vf, 
         attr_set = true;
     }
     constexpr int PF_BM = pf_bm(SHARED), PF_THREADS = 64 * pf_waves(SHARED);
-    const int units = ((sh.Lq + PF_BM - 1) / PF_BM) * sh.H * sh.B;
+    const int n_split = prefill_splits(SHARED, sh);
+    const int units = ((sh.Lq + PF_BM - 1) / PF_BM) * sh.H * sh.B * n_split;
     dim3 grid((units + 7) / 8 * 8);
     if (ev0 || ev1)
         hipExtLaunchKernelGGL((prefill_attn_kernel<SHARED, LISTED>), grid, dim3(PF_THREADS), (uint32_t)smem, s, ev0, ev1,
                               0, (const _Float16 *)q, (const _Float16 *)Kf, (const _Float16 *)Vf, (const _Float16 *)Ku,
-                              (const _Float16 *)Vu, keep_mask, key_cid, blk_info, (_Float16 *)out, lse, sh.B, sh.H, sh.L,
-                              sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale);
+                              (const _Float16 *)Vu, keep_mask, key_cid, blk_info, (_Float16 *)out, lse, partials, n_split,
+                              sh.B, sh.H, sh.L, sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale);
     else
         hipLaunchKernelGGL((prefill_attn_kernel<SHARED, LISTED>), grid, dim3(PF_THREADS), smem, s, (const _Float16 *)q,
                            (const _Float16 *)Kf, (const _Float16 *)Vf, (const _Float16 *)Ku, (const _Float16 *)Vu,
-                           keep_mask, key_cid, blk_info, (_Float16 *)out, lse, sh.B, sh.H, sh.L, sh.C, sh.Lq, sh.U,
-                           sh.causal_user, sh.sm_scale);
+                           keep_mask, key_cid, blk_info, (_Float16 *)out, lse, partials, n_split, sh.B, sh.H, sh.L,
+                           sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale);
+    return hipGetLastError();
+}
+
+hipError_t launch_prefill_merge(bool shared, const float *partials, void *out, float *lse, const Shape &sh, hipStream_t s)
+{
+    const int n_split = prefill_splits(shared, sh);
+    if (n_split == 1) return hipSuccess;
+    const size_t rows = (size_t)sh.B * sh.H * sh.Lq;
+    hipLaunchKernelGGL(prefill_merge_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, partials, (_Float16 *)out,
+                       lse, n_split, rows);
     return hipGetLastError();
 }
 
@@ -564,7 +663,7 @@ hipError_t launch_prefill_kernel(const void *q, const void *Kf, const void *Vf, 
 
 hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                const uint32_t *keep_mask, const int32_t *offsets, int32_t *key_cid, int32_t *blk_info,
-                               void *out, float *lse, const Shape &sh, hipStream_t s)
+                               float *partials, void *out, float *lse, const Shape &sh, hipStream_t s)
 {
     const int nblk = (sh.L + PF_BN - 1) / PF_BN;
     hipLaunchKernelGGL(key_cluster_kernel, dim3(64, sh.H), dim3(256), 0, s, offsets, key_cid, sh.C, sh.L);
@@ -584,11 +683,13 @@ hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, co
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    e = launch_prefill_kernel<false, false>(q, Kf, Vf, Ku, Vu, keep_mask, key_cid, blk_info, out, lse, sh, s, ev0,
+    e = launch_prefill_kernel<false, false>(q, Kf, Vf, Ku, Vu, keep_mask, key_cid, blk_info, out, lse, partials, sh, s, ev0,
                                             may_list ? nullptr : ev1);
-    if (e != hipSuccess || !may_list) return e;
-    return launch_prefill_kernel<false, true>(q, Kf, Vf, Ku, Vu, keep_mask, key_cid, blk_info, out, lse, sh, s, nullptr,
-                                              ev1);
+    if (e == hipSuccess && may_list)
+        e = launch_prefill_kernel<false, true>(q, Kf, Vf, Ku, Vu, keep_mask, key_cid, blk_info, out, lse, partials, sh, s,
+                                               nullptr, ev1);
+    if (e != hipSuccess) return e;
+    return launch_prefill_merge(false, partials, out, lse, sh, s);
 }
 
 hipError_t launch_expand_ranges(DecodePlan plan, int32_t *idx, int rows, int L, hipStream_t s)
@@ -598,16 +699,18 @@ hipError_t launch_expand_ranges(DecodePlan plan, int32_t *idx, int rows, int L, 
 }
 
 hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
-                                      DecodePlan plan, int32_t *key_idx, void *out, float *lse, const Shape &sh,
-                                      hipStream_t s)
+                                      DecodePlan plan, int32_t *key_idx, float *partials, void *out, float *lse,
+                                      const Shape &sh, hipStream_t s)
 {
     hipLaunchKernelGGL(expand_ranges_kernel, dim3(sh.B * sh.H, EXPAND_SLICES), dim3(256), 0, s, plan, key_idx, sh.L);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     profile_pair(&ev0, &ev1);
-    return launch_prefill_kernel<true, false>(q, Kf, Vf, Ku, Vu, nullptr, key_idx,
-                                              reinterpret_cast<const int32_t *>(plan.hdr), out, lse, sh, s, ev0, ev1);
+    e = launch_prefill_kernel<true, false>(q, Kf, Vf, Ku, Vu, nullptr, key_idx,
+                                           reinterpret_cast<const int32_t *>(plan.hdr), out, lse, partials, sh, s, ev0, ev1);
+    if (e != hipSuccess) return e;
+    return launch_prefill_merge(true, partials, out, lse, sh, s);
 }
 
 }  // namespace sq

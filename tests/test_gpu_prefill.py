@@ -342,6 +342,23 @@ def test_prefill_mean_step_small(sq, oracle, case):
     compare_prefill_mean(oracle, w, P, got, stats, f"prefill-mean-step{case}")
 
 
+@pytest.mark.parametrize("case", [
+    dict(B=1, H=1, L=64 * 70 + 1, C=90, Lq=17, U=3, keep_frac=0.2, causal_user=False),    # more shares than one round of the merge
+    dict(B=1, H=1, L=60, C=5, Lq=129, U=129, keep_frac=0.5, causal_user=True),            # one fixed block: shares of user blocks only
+    dict(B=2, H=3, L=700, C=11, Lq=1, U=0, keep_frac=0.1, causal_user=False),             # shares without a kept key, no user keys
+    dict(B=1, H=5, L=64 * 9, C=40, Lq=257, U=65, keep_frac=0.3, causal_user=False),       # blocks not a multiple of the shares
+])
+def test_prefill_split_shares(sq, oracle, case):
+    """Few (head, query block) units: their key blocks are dealt to several workgroups and merged."""
+    w = wl.calibrate(wl.make_workload("prefill_split", seed=31, threads=2, **case), oracle.scores)
+    P = sq.upload(w)
+    run_prefill_step(sq, w, P)
+    compare_prefill(oracle, w, P, f"prefill-split{case}", logits=False)
+    w.thresh, stats = mean_thresholds(oracle, w)
+    P = sq.upload(w)
+    compare_prefill_mean(oracle, w, P, run_prefill_mean_step(sq, w, P), stats, f"prefill-mean-split{case}")
+
+
 def test_prefill_step_queries_alike_within_a_block(sq, oracle):
     """The whole step on queries that resemble their neighbours (each block of 64 tokens shares a direction, as
     consecutive tokens of a prompt do): the selections of a block overlap, most key blocks are kept by no token of it,
