@@ -394,17 +394,18 @@ PrefillSharedWs carve_prefill_shared(Carver &cv, const sq_shape_t *sh)
     return w;
 }
 
-// Workspace of the masked prefill attention: key -> cluster map, block table, partial results.
+// Workspace of the masked prefill attention: block table, partial results.
 struct PrefillAttnWs {
-    int32_t *key_cid, *blk_info;
+    uint32_t *runs;
+    int32_t *blk_info;
     float *partials;
 };
 
 PrefillAttnWs carve_prefill_attn(Carver &cv, const sq_shape_t *sh)
 {
     PrefillAttnWs w{};
-    w.key_cid = cv.take<int32_t>((size_t)sh->H * sh->L);
-    w.blk_info = cv.take<int32_t>(sq::prefill_blk_info_ints(sh->H, sh->L));
+    w.runs = cv.take<uint32_t>(sq::prefill_table_words(sh->H, sh->L));
+    w.blk_info = cv.take<int32_t>(sq::prefill_blocks(sh->H, sh->L));
     w.partials = cv.take<float>(sq::prefill_partial_floats(false, to_shape(sh)));
     return w;
 }
@@ -861,7 +862,7 @@ int sq_sparse_attn_prefill(const sq_shape_t *sh, const void *q, const void *K_fi
     if (int rc = check_device(__func__)) return rc;
     Carver cv(ws);
     PrefillAttnWs w = carve_prefill_attn(cv, sh);
-    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, keep_mask, offsets, w.key_cid, w.blk_info,
+    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, keep_mask, offsets, w.runs, w.blk_info,
                                    w.partials, out, lse, to_shape(sh), static_cast<hipStream_t>(stream)));
     g_err[0] = 0;
     return SQ_OK;
@@ -961,7 +962,7 @@ int sq_prefill_step(const sq_shape_t *sh, const void *q, const void *centroids, 
     uint32_t *mask = keep_mask ? keep_mask : w.mask;
     SQ_HIP(sq::launch_prefill_lookup(q, centroids, sizes, thresh, mask, w.n_ranges, n_keys ? n_keys : w.n_keys, nullptr,
                                      false, sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s));
-    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask, offsets, w.att.key_cid, w.att.blk_info,
+    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask, offsets, w.att.runs, w.att.blk_info,
                                    w.att.partials, out, lse,
                                    to_shape(sh), s));
     g_err[0] = 0;
@@ -1257,7 +1258,7 @@ int sq_hier_prefill_step(const sq_shape_t *sh, int32_t C1, const void *q, const 
     SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, mask2, w.step.n_ranges,
                                      n_keys ? n_keys : w.step.n_keys, nullptr, false, sh->B, sh->H, sh->Lq, sh->C,
                                      sh->sm_scale, s, nullptr, nullptr, w.parent, w.mask1, C1));
-    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask2, offsets2, w.step.att.key_cid, w.step.att.blk_info,
+    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask2, offsets2, w.step.att.runs, w.step.att.blk_info,
                                    w.step.att.partials,
                                    out, lse, to_shape(sh), s));
     g_err[0] = 0;

@@ -89,6 +89,20 @@ __device__ __forceinline__ float cross16_max(float v)
     return fmaxf(a, b);
 }
 
+// The same over the two halves of the wave (lanes l, l^32).
+__device__ __forceinline__ float cross32_max(float v)
+{
+    float a, b;
+    swap32(v, a, b);
+    return fmaxf(a, b);
+}
+__device__ __forceinline__ float cross32_sum(float v)
+{
+    float a, b;
+    swap32(v, a, b);
+    return a + b;
+}
+
 // Sum over the 64 lanes of a wave as an xor butterfly (partners 1, 2, 4, 8, 16, 32 lanes away, in that order);
 // every lane gets the same bits.  Entirely in the vector ALU: the first two steps are quad permutes; after them
 // the four lanes of a quad agree, so mirroring a half row (lane i <-> 7 - i) pairs the same values as xor 4, and

@@ -1,37 +1,39 @@
 // Prefill-time sparse attention (Section 4.2) with per-query selection: every query token attends to the
 // keys of the clusters set in its own keep mask, plus the (causal) user keys, one softmax over the union.
 //
-// Layout of the computation (FlashAttention-2 style: grid over heads x query blocks, loop over key blocks,
-// online softmax), written for CDNA4 matrix cores:
-//   * a workgroup = 4 waves x 16 queries, two workgroups per compute unit (shared-set form: 8 waves, one
-//     workgroup); all waves walk the same 64-key blocks, whose K and V tiles are staged row-major in LDS once per
-//     workgroup (two LDS buffers; the next block's rows go from global memory straight into the other buffer with the
-//     load-to-LDS instruction, issued a piece at a time behind the steps of the current block's score products);
-//   * scores are computed TRANSPOSED, S^T = K Q^T, with 16x16x32 fp16 MFMA tiles (A = 16 keys, B = 16
-//     queries).  In the accumulator layout a lane then owns ONE query column for the whole kernel (and four
-//     keys per tile), so the running maximum, the running sum and the rescaling of the output are per-lane
-//     scalars, and P^T is repacked into the B operand of the next product in registers, with no
-//     cross-lane traffic;
+// Layout of the computation (FlashAttention-2 style: grid over heads x query blocks x shares of the key blocks, loop over
+// key blocks, online softmax), written for CDNA4 matrix cores:
+//   * a wave owns 32 queries; a workgroup of eight (or four) waves walks the same 64-key blocks, whose K and V tiles are
+//     staged row-major in LDS once per workgroup, straight from global memory with the load-to-LDS instruction;
+//   * scores are computed TRANSPOSED, S^T = K Q^T, with 32x32x16 fp16 MFMA tiles (A = 32 keys, B = 32 queries).  In the
+//     accumulator layout a lane then owns ONE query column for the whole kernel (and 16 keys per tile; lanes l and l + 32
+//     share a column), so the reference maximum, the running sum and the rescaling of the output are per-lane scalars, and
+//     P^T is packed into the B operand of the next product in registers, with no cross-lane traffic;
 //   * O^T = V^T P^T uses A = V^T tiles read from the row-major V tile with the transposing LDS read
 //     (ds_read_b64_tr_b16), so V needs no transposition on its way into LDS;
-//   * the per-query keep masks are applied per (query, key): a small pre-kernel expands the cluster offsets
-//     into a key -> cluster map, each key block brings, for every query of the workgroup, the window of mask
-//     bits that covers its clusters, the bit of a (query, key) pair is spread over a word with one signed
-//     bit-field extract and blended into the score with one bit-select, and a wave skips the products of a
-//     block none of its queries kept.  The mask arithmetic is issued behind the S^T products, in the same
-//     straight-line block, so the vector ALU works while the matrix cores do;
-//   * the masked form exists twice: a kernel that walks every key block, and one that first lists, per workgroup, the
-//     blocks in which at least one of its queries kept a cluster and walks only those.  A counting launch decides which
-//     of the two does the work (see PF_LIST_MIN_SHARE).
+//   * the loop is pipelined inside a wave: while the softmax of block i runs on the vector ALU, the products S^T of block
+//     i + 1 and O^T of block i are issued between its instructions (the order is laid out by hand, a pair of scores at a
+//     time).  Two waves per SIMD that run their phases one after the other overlap little of them on this chip, and a wave
+//     issues at most one vector instruction per five cycles, so both the overlap and the instruction count matter;
+//   * masks cost no vector arithmetic per score: a lane's visible keys of a block are two words (one AND/OR pair per run of
+//     keys of one cluster, prepared by a table launch), and the score products start from 0 (visible) or -inf (hidden),
+//     four start values per LDS read from a 16-entry table.
+// What it is bound by at 32 heads x 1024 tokens x 32K keys (549 GFLOP executed): about 3600 cycles per block and pair of waves
+// against 2050 of matrix work, at the 1.9 GHz the chip holds under this load -- 1.06 PFLOP/s in the kernel, where the
+// library's large fp16 product reaches 1.18 on the same card.  The form before it (16 queries per wave, masks and maxima on
+// every score, phases one after the other): 755 us; 32 queries per wave in that order 595; this order 515.  Timing-only builds
+// of it: without loads -9 %, without LDS operand reads -11 %, without exponentials -12 %, without products -25 %
+// (sum of nothing dominates).
 // The user block is causal when causal_user is set (query t sees user keys 0..t); the fixed context is
 // always fully visible.
 //
 // SHARED variant (selection on averaged scores, Appendix D "Prefill Stage"): all query tokens of a (sequence,
 // head) attend to ONE kept set.  The kept ranges are expanded into a list of key rows (the key-index tensor of
-// Section 4.2); the kernel walks that list 64 keys at a time, gathering K and V rows by index (the indices of
-// the block after next travel in registers ahead of the rows), with no per-query masks: only the tail of the
-// last block and the causal user keys are masked, so every executed tile is useful work.
+// Section 4.2); the kernel walks that list 64 keys at a time, gathering K and V rows by index (the indices travel in
+// registers ahead of the rows), with no per-query masks: only the tail of the last block and the causal user keys are
+// hidden, so every executed tile is useful work.
 #include <type_traits>
+#include <utility>
 
 #include "sq_common.hpp"
 #include "sq_internal.hpp"
@@ -44,44 +46,86 @@ constexpr int PF_BN = 64;                 // keys per block
 // instead of padded so that the operand reads stay free of bank conflicts: the 16-byte chunk c of row r sits at slot
 // c ^ swz(r).  The swizzle is applied on the global side (lane = slot: it fetches chunk slot ^ swz(r)).
 //   K (16-byte reads, 16 rows at one chunk index per group of lanes): swz = r % 16 -- the 16 rows land in 16 slots.
-//   V (transposing 8-byte reads, 16 rows x 32 bytes per instruction): swz = 2 * (r % 8) -- a pair of chunks stays
-//   adjacent and the 8 rows of half a wave land in 8 different pairs.
+//   V (transposing 8-byte reads, 4 rows x 64 bytes per half wave): swz = 4 * (r % 4) -- the four chunks of a row stay
+//   together and the four rows land in four different quarters of the banks.
 __device__ __forceinline__ int pf_k_swz(int row) { return row & 15; }
-__device__ __forceinline__ int pf_v_swz(int row) { return (row & 7) << 1; }
+__device__ __forceinline__ int pf_v_swz(int row) { return (row & 3) << 2; }
 
-// key -> cluster id map of every head (clusters are contiguous key ranges).  Keys that no cluster covers (before
-// offsets[0] or from offsets[C] on) get the "no cluster" id 0x7fffffff, which no query keeps.
-__global__ __launch_bounds__(256) void key_cluster_kernel(const int32_t *__restrict__ offsets, int32_t *__restrict__ cid,
-                                                          int C, int L)
+// Block table of the masked form: per (head, 64-key block) the runs of keys that share a cluster (clusters are contiguous
+// key ranges, so a block is a few runs: three at 32 keys per cluster).
+//   runs[h, blk, i]   cluster | first key of the run in the block << 16 | (keys - 1) << 22, ascending
+//   rows[h, blk]      the same for up to PF_ROW_RUNS runs in the form the attention kernel uses, groups of four runs, PF_ROW_GROUP
+//                     words each: [0..3] cluster relative to the block's first (31, a window bit that is never set, for none),
+//                     [4..7] / [8..11] the run's keys for lanes 0..31: bit 8 a + i = key 32 t + 8 a + i, t = 0 / 1,
+//                     [12..15] / [16..19] for lanes 32..63: key 32 t + 8 a + 4 + i (i < 4: see the accumulator layout there)
+//   blk_info[h, blk]  first cluster | min(span of cluster ids, 30) << 16 | n runs << 21 | wide << 31; wide: the span does
+//                     not fit the 31-bit window of mask bits (a block that crosses many empty clusters)
+// Keys that no cluster covers (before offsets[0] or from offsets[C] on) belong to no run.  One wave per block: a 64-way
+// search for the first key's cluster, then the keys are placed among the next 64 cluster starts.
+constexpr int PF_ROW_RUNS = 12, PF_ROW_GROUP = 20, PF_ROW_WORDS = 64;
+__global__ __launch_bounds__(256) void block_table_kernel(const int32_t *__restrict__ offsets, uint32_t *__restrict__ runs,
+                                                          uint32_t *__restrict__ rows, int32_t *__restrict__ blk_info, int C,
+                                                          int L, int nblk)
 {
-    const int h = blockIdx.y;
-    const int32_t *off = offsets + (size_t)h * (C + 1);
-    if (blockIdx.x == 0) {
-        const int head = max(0, min(L, off[0])), tail = max(0, min(L, off[C]));
-        for (int j = threadIdx.x; j < head; j += 256) cid[(size_t)h * L + j] = 0x7fffffff;
-        for (int j = tail + threadIdx.x; j < L; j += 256) cid[(size_t)h * L + j] = 0x7fffffff;
-    }
-    for (int c = blockIdx.x * 4 + (threadIdx.x >> 6); c < C; c += gridDim.x * 4) {
-        const int a = max(0, off[c]), b = min(L, off[c + 1]);
-        for (int j = a + (threadIdx.x & 63); j < b; j += 64) cid[(size_t)h * L + j] = c;
-    }
-}
-
-// Per 64-key block of the fixed context: the cluster of its first key, how many cluster ids it spans, and
-// whether that span fits the 31-bit window of mask bits staged per query (it always does unless the block
-// crosses a long run of empty clusters).  blk_info[h, blk] = first | span << 16 | wide << 31.
-__global__ __launch_bounds__(256) void block_info_kernel(const int32_t *__restrict__ cid, int32_t *__restrict__ blk_info,
-                                                         int C, int L, int nblk)
-{
-    const int h = blockIdx.y;
-    const int blk = blockIdx.x * 256 + threadIdx.x;
-    if (h == 0 && blk == 0)                              // the count of skippable (workgroup, block) pairs, behind the table
-        *reinterpret_cast<unsigned long long *>(blk_info + prefill_skip_count_at((int)gridDim.y, L)) = 0ull;
+    const int h = blockIdx.y, lane = threadIdx.x & 63, blk = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (blk >= nblk) return;
-    const int first = max(0, min(cid[(size_t)h * L + blk * PF_BN], C - 1));
-    const int last = max(first, min(cid[(size_t)h * L + min(L, (blk + 1) * PF_BN) - 1], C - 1));
-    const int span = last - first;
-    blk_info[(size_t)h * nblk + blk] = first | (min(span, 30) << 16) | (span >= 31 ? (int)0x80000000 : 0);
+    const int32_t *off = offsets + (size_t)h * (C + 1);
+    const int j0 = blk * PF_BN, j = j0 + lane;
+    int lo = -1, hi = C + 1;                             // the last c with off[c] <= j0 (-1: none) lies in [lo, hi)
+    while (hi - lo > 1) {
+        const int step = (hi - lo + 63) >> 6, at = lo + (lane + 1) * step;
+        const bool le = at < hi && off[min(at, C)] <= j0;
+        lo += __popcll(__ballot(le)) * step;
+        hi = min(hi, lo + step);
+    }
+    const int nx = lo + 1 + lane;
+    const int start = nx <= C ? off[nx] : 0x7fffffff;    // starts of the 64 clusters after it
+    int pos = 0;                                         // how many of them are at or before this lane's key
+#pragma unroll
+    for (int step = 32; step > 0; step >>= 1)
+        if (__shfl(start, pos + step - 1) <= j) pos += step;
+    if (__shfl(start, pos) <= j) ++pos;
+    int c = lo + pos;
+    if (__ballot(pos == 64) != 0ull) {                   // more than 64 cluster starts in the block: search for each key
+        int a = lo, b = C + 1;
+        while (b - a > 1) {
+            const int mid = (a + b) >> 1;
+            if (off[mid] <= j) a = mid;
+            else b = mid;
+        }
+        c = a;
+    }
+    const bool covered = c >= 0 && c < C && j < L;
+    if (!covered) c = 0x7fffffff;
+    const int before = __shfl_up(c, 1);
+    const bool change = lane == 0 || c != before;
+    const unsigned long long cuts = __ballot(change), heads = __ballot(change && covered);
+    const int n = __popcll(heads);
+    const unsigned long long later = lane == 63 ? 0ull : cuts >> (lane + 1);
+    const int len = later ? __ffsll((long long)later) : 64 - lane;   // keys up to the next cut
+    uint32_t *dst = runs + ((size_t)h * nblk + blk) * PF_BN;
+    const unsigned long long in = __ballot(covered);
+    const int first = n ? __shfl(c, __ffsll((long long)heads) - 1) : 0;
+    const int last = n ? __shfl(c, 63 - __clzll((long long)in)) : 0;
+    uint32_t *row = rows + ((size_t)h * nblk + blk) * PF_ROW_WORDS;
+    auto put = [&](int slot, uint32_t rel, unsigned long long keys) {
+        uint32_t *g = row + (slot >> 2) * PF_ROW_GROUP + (slot & 3);
+        g[0] = rel;
+        g[4] = (uint32_t)keys & 0x0f0f0f0fu;
+        g[8] = (uint32_t)(keys >> 32) & 0x0f0f0f0fu;
+        g[12] = (uint32_t)(keys >> 4) & 0x0f0f0f0fu;
+        g[16] = (uint32_t)(keys >> 36) & 0x0f0f0f0fu;
+    };
+    if (change && covered) {
+        const int slot = __popcll(heads & ((1ull << lane) - 1ull));
+        dst[slot] = (uint32_t)c | (uint32_t)lane << 16 | (uint32_t)(len - 1) << 22;
+        if (slot < PF_ROW_RUNS) put(slot, (uint32_t)min(c - first, 31), (~0ull >> (64 - len)) << lane);
+    }
+    if (lane >= n && lane < PF_ROW_RUNS) put(lane, 31u, 0ull);
+    if (lane == 0) {
+        const int span = max(last - first, 0);
+        blk_info[(size_t)h * nblk + blk] = first | (min(span, 30) << 16) | (n << 21) | (span >= 31 ? (int)0x80000000 : 0);
+    }
 }
 
 // Kept ranges of every (sequence, head) row -> list of key rows: record (first key, count, keys before) writes
@@ -100,17 +144,8 @@ __global__ __launch_bounds__(256) void expand_ranges_kernel(DecodePlan plan, int
     }
 }
 
-// Masked form, two kernels for the same work.  The plain one walks every fixed-context block (a wave still skips the
-// products of a block none of its queries kept).  The listed one first builds, in LDS, the ordered list of the blocks in
-// which at least one query of the workgroup kept a cluster and walks only those (Section 4.2: the work follows the kept
-// set, not the context length): blocks nobody kept are neither fetched nor staged nor waited for at a barrier.  Walking
-// through the list costs about 6% when nothing can be skipped (883 against 833 us at 32 heads x 1024 tokens x 32K keys,
-// 1/8 kept per query), so a counting launch in front adds up the (workgroup, block) pairs that can be skipped; both
-// kernels are then launched and each returns at once unless the count picks it (listed: an eighth of the pairs or more).
-constexpr int PF_LIST_CAP = 4096;         // blocks (256K keys); longer contexts take the plain kernel
+constexpr int PF_LIST_CAP = 4096;         // fixed blocks per workgroup (the split keeps a share within it)
 constexpr int PF_UMASK_WORDS = SELECT_MAX_C / 32;
-constexpr size_t PF_LIST_BYTES = PF_UMASK_WORDS * 4 + PF_LIST_CAP * 2;
-constexpr int PF_LIST_MIN_SHARE = 8;      // listed kernel iff skippable pairs * 8 >= all pairs
 
 // s_um[0..W) |= keep masks of queries q0 .. q0+bm-1 (those below Lq) of query rows row0...; s_um zeroed by the caller,
 // barrier after it by the caller.  A mask word of eight queries per item: eight independent loads, one LDS atomic.
@@ -128,58 +163,27 @@ __device__ __forceinline__ void pf_union_mask(uint32_t *s_um, const uint32_t *__
 }
 
 // Does a workgroup whose queries' masks OR to s_um need the block with table entry bi?  (A block that spans more
-// cluster ids than the staged window is not decided here: needed.)
+// cluster ids than the window is not decided here: needed.)
 __device__ __forceinline__ bool pf_block_needed(int bi, const uint32_t *s_um, int W)
 {
     if (bi < 0) return true;
+    if (((bi >> 21) & 127) == 0) return false;                 // no key of the block lies in a cluster
     const int first = bi & 0xffff, w0 = first >> 5;
     const unsigned long long two = ((unsigned long long)(w0 + 1 < W ? s_um[w0 + 1] : 0u) << 32) | s_um[w0];
     const uint32_t present = (2u << ((bi >> 16) & 31)) - 1u;   // local clusters that occur in the block
     return ((uint32_t)(two >> (first & 31)) & present) != 0u;
 }
 
-// The counting launch: one workgroup per query block of the masked kernels, *skip_count += blocks it can skip.
-__global__ __launch_bounds__(256) void prefill_need_kernel(const uint32_t *__restrict__ keep_mask,
-                                                           const int32_t *__restrict__ blk_info,
-                                                           unsigned long long *__restrict__ skip_count, int B, int H,
-                                                           int L, int C, int Lq, int bm)
-{
-    __shared__ uint32_t s_um[PF_UMASK_WORDS];
-    __shared__ int s_cnt;
-    const int tid = threadIdx.x;
-    const int nqb = (Lq + bm - 1) / bm, unit = blockIdx.x;
-    const int h = unit / (nqb * B), b = (unit / nqb) % B, q0 = (unit % nqb) * bm;
-    const int W = (C + 31) >> 5, nblk = (L + PF_BN - 1) / PF_BN;
-    const size_t row0 = ((size_t)b * H + h) * Lq;
-    for (int w = tid; w < W; w += 256) s_um[w] = 0u;
-    if (tid == 0) s_cnt = 0;
-    __syncthreads();
-    pf_union_mask(s_um, keep_mask, row0, q0, bm, Lq, W, tid, 256);
-    __syncthreads();
-    int skip = 0;
-    for (int bb = tid; bb < nblk; bb += 256) skip += pf_block_needed(blk_info[(size_t)h * nblk + bb], s_um, W) ? 0 : 1;
-    for (int o = 32; o; o >>= 1) skip += __shfl_xor(skip, o);
-    if ((tid & 63) == 0 && skip) atomicAdd(&s_cnt, skip);
-    __syncthreads();
-    if (tid == 0 && s_cnt) atomicAdd(skip_count, (unsigned long long)s_cnt);
-}
+constexpr int PF_AHEAD = 4;                                 // operands requested from LDS ahead of their product
+constexpr int pf_bm(int waves) { return 32 * waves; }       // queries per workgroup
 
-constexpr int PF_QT = 1;                  // 16-query tiles per wave
-// Waves per workgroup (all walk the same staged key blocks).  Measured at the 32-head, 1024-token shape: the masked
-// form is fastest with 4 (1.10 ms against 1.17 with 8: the two workgroups of a compute unit cover each other's
-// barriers), the shared-set form with 8 (155 us against 171: half the global->LDS staging per product).
-constexpr int pf_waves(bool shared) { return shared ? 8 : 4; }
-constexpr int pf_bm(bool shared) { return 16 * PF_QT * pf_waves(shared); }   // queries per workgroup
-constexpr int PF_BM_MAX = pf_bm(true);
-
-struct PfStage {                          // one LDS buffer of a key block
-    _Float16 K[PF_BN * D];
-    _Float16 V[PF_BN * D];
-    int cid[PF_BN];                       // cluster of each key (0x7fffffff past the end)
-    int sh[PF_BN];                        // bit of the key's cluster in the staged window: cluster - first cluster of
-                                          // the block (31, a bit that is never set, for keys past the end)
-    uint32_t qbits[PF_BM_MAX];            // per query: mask bits of clusters first .. first+30, bit 31 clear
-};
+// Key blocks staged in LDS (K and V tiles each).  Two: a barrier per block (with four waves two workgroups share a compute
+// unit's LDS).  Four in the masked form with eight waves: a barrier per pair of blocks, and the loads have a pair's time to
+// land (32 heads x 1024 tokens x 32K keys: 593 -> 583 us per step); the shared-set form's shares are a tenth as long and lose
+// as much in the longer prologue (171 -> 174 us).
+constexpr int pf_bufs(bool shared, int waves) { return waves == 8 && !shared ? 4 : 2; }
+constexpr uint32_t PF_TILE = PF_BN * D * 2;                 // bytes of a K or V tile
+constexpr int PF_TABS = 4;                // block table rows in LDS: the block's whose start values are made and the next ones
 
 // (mask & a) | (~mask & b) on the bit patterns of floats: one v_bfi_b32.
 __device__ __forceinline__ float select_bits(uint32_t mask, float a, float b)
@@ -187,212 +191,110 @@ __device__ __forceinline__ float select_bits(uint32_t mask, float a, float b)
     return __builtin_bit_cast(float, (mask & __builtin_bit_cast(uint32_t, a)) | (~mask & __builtin_bit_cast(uint32_t, b)));
 }
 
-// SHARED: key_cid is the key-row list [B*H, L] and blk_info the per-row (records, kept keys) headers; keep_mask is
-// not used.
-template <bool SHARED, bool LISTED>
-__global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void prefill_attn_kernel(
+// f(0), f(1), ... f(N - 1) with the index a compile-time constant.
+template <int N, typename F, int... I>
+__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F &&f)
+{
+    static_for_impl<N>(f, std::make_integer_sequence<int, N>{});
+}
+#define PF_INLINE __attribute__((always_inline))          // (a lambda left as a call would put what it captures in memory)
+
+// SHARED: table is the key-row list [B*H, L] and blk_info the per-row (records, kept keys) headers; keep_mask is not
+// used.  Otherwise table / rows / blk_info are the block table (block_table_kernel).
+template <bool SHARED, int PF_WAVES>
+__global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kernel(
     const _Float16 *__restrict__ q, const _Float16 *__restrict__ Kf, const _Float16 *__restrict__ Vf,
     const _Float16 *__restrict__ Ku, const _Float16 *__restrict__ Vu, const uint32_t *__restrict__ keep_mask,
-    const int32_t *__restrict__ key_cid, const int32_t *__restrict__ blk_info, _Float16 *__restrict__ out,
-    float *__restrict__ lse, float *__restrict__ partials, int n_split, int B, int H, int L, int C, int Lq, int U,
-    int causal_user, float sm_scale)
+    const uint32_t *__restrict__ table, const uint32_t *__restrict__ rows, const int32_t *__restrict__ blk_info,
+    _Float16 *__restrict__ out, float *__restrict__ lse, float *__restrict__ partials, int n_split, int B, int H, int L,
+    int C, int Lq, int U, int causal_user, float sm_scale)
 {
-    constexpr int QT = PF_QT, BM = pf_bm(SHARED);
-    constexpr int PF_THREADS = 64 * pf_waves(SHARED);
-    constexpr int PF_RP = PF_THREADS / 16;    // rows of a key block the workgroup moves per pass (16 lanes per row)
-    constexpr int PF_NP = PF_BN / PF_RP;      // passes per block
-    extern __shared__ __align__(16) unsigned char smem[];
-    PfStage *stage = reinterpret_cast<PfStage *>(smem);   // [2]
+    constexpr int PF_BM = pf_bm(PF_WAVES), PF_THREADS = 64 * PF_WAVES;
+    constexpr int PF_RP = PF_THREADS / 16;                  // rows of a key block the workgroup moves per pass (16 lanes per row)
+    constexpr int PF_NP = PF_BN / PF_RP;                    // passes per block
+    static_assert(PF_RP % 16 == 0, "the staging swizzles take the row modulo 16 from the thread alone");
+    constexpr int NB = pf_bufs(SHARED, PF_WAVES), LV = NB / 2, LK = LV + 1;   // iteration it fetches V of block it + LV, K of block it + LK
+    __shared__ __align__(16) unsigned char stage[2 * NB * PF_TILE];   // NB tiles of K, then NB tiles of V
+    __shared__ __align__(16) uint32_t s_tab[SHARED ? 1 : PF_TABS * PF_ROW_WORDS];
+    __shared__ uint32_t s_um[SHARED ? 1 : PF_UMASK_WORDS];  // OR of the keep masks of the workgroup's queries
+    __shared__ uint16_t s_list[SHARED ? 1 : PF_LIST_CAP];   // the fixed blocks this workgroup walks
+    __shared__ int s_wc[PF_WAVES];
+    __shared__ __align__(16) float s_hide[16 * 4];          // entry n: the start values of four scores whose visibility bits are n
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int col = lane & 15, kg = lane >> 4;
-    // Workgroup -> (head, sequence, query block).  Workgroups are dealt to the 8 XCDs round-robin by their
+    const int col = lane & 31, g = lane >> 5, l16 = lane & 15;
+    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
+    if (tid < 64) s_hide[tid] = ((tid >> 2) >> (tid & 3)) & 1 ? 0.0f : SQ_NEG_INF;   // (read behind the barriers below)
+    // Workgroup -> (head, sequence, query block, share).  Workgroups are dealt to the 8 XCDs round-robin by their
     // linear id; units that share a head (and so stream the same K/V) are made to land on the same XCD, so
     // one L2 fetches a head's keys once for all of its query blocks.
-    const int nqb = (Lq + BM - 1) / BM;
-    const int per_xcd = gridDim.x >> 3;                   // grid is a multiple of 8
+    const int nqb = (Lq + PF_BM - 1) / PF_BM;
+    const int per_xcd = gridDim.x >> 3;                     // grid is a multiple of 8
     const int piece = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
     if (piece >= nqb * B * H * n_split) return;
-    // With few (head, query block) units the key blocks of a unit are dealt to n_split workgroups: block positions
-    // split, split + n_split, ... of the unit's walking order (interleaved, so that a run of blocks nobody kept or the
-    // causal end of the user keys is shared out evenly).
+    // With few (head, query block) units the key blocks of a unit are dealt to n_split workgroups: blocks split,
+    // split + n_split, ... (interleaved, so that a run of blocks nobody kept or the causal end of the user keys is shared
+    // out evenly).
     const int unit = piece / n_split, split = piece - unit * n_split;
-    if constexpr (!SHARED) {
-        // Which of the two masked kernels does the work: the listed one iff enough (workgroup, block) pairs can be skipped.
-        const int nblk_all = (L + PF_BN - 1) / PF_BN;
-        const unsigned long long skip = *reinterpret_cast<const unsigned long long *>(blk_info + prefill_skip_count_at(H, L));
-        const bool by_list = nblk_all <= PF_LIST_CAP && skip > 0ull &&
-                             skip * PF_LIST_MIN_SHARE >= (unsigned long long)(nqb * B * H) * (unsigned long long)nblk_all;
-        if (by_list != LISTED) return;
-    }
     const int h = unit / (nqb * B), b = (unit / nqb) % B;
-    const int q0 = (unit % nqb) * BM;                     // first query of the workgroup
+    const int q0 = (unit % nqb) * PF_BM;                    // first query of the workgroup
     const int W = (C + 31) >> 5;
-    const size_t row0 = ((size_t)b * H + h) * Lq;         // query-row index of query 0 of this (b, h)
-    const float c2 = sm_scale * 1.44269504088896341f;     // exp(sm_scale * s) = exp2(c2 * s)
+    const size_t row0 = ((size_t)b * H + h) * Lq;           // query-row index of query 0 of this (b, h)
+    const float c2 = sm_scale * 1.44269504088896341f;       // exp(sm_scale * s) = exp2(c2 * s)
 
-    // Queries of this lane: n[qt] = q0 + wave*16*QT + qt*16 + col; B operand of S^T = K Q^T.
-    h8 bq[QT][4];
-    int nq[QT];
+    // This lane's query column (a column past the end repeats the last query and is not stored).
+    const int q0w = q0 + wave_u * 32, nq = q0w + col, nqc = min(nq, Lq - 1);
+    const bool wave_on = q0w < Lq;                          // (wave-uniform)
+    h8 bq[8];                                               // B operand of S^T = K Q^T
+    {
+        const h8 *qp = reinterpret_cast<const h8 *>(q + (row0 + nqc) * D);
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        nq[qt] = q0 + wave * 16 * QT + qt * 16 + col;
-        const int nc = min(nq[qt], Lq - 1);
-        const h8 *qp = reinterpret_cast<const h8 *>(q + (row0 + nc) * D);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) bq[qt][s] = qp[s * 4 + kg];
+        for (int s = 0; s < 8; ++s) bq[s] = qp[s * 2 + g];
     }
-
-    float m_run[QT], l_run[QT];                           // running max (raw logit units) and sum per query column
-    f4 o[QT][8];
+    float m_ref = SQ_NEG_INF, m_lim = SQ_NEG_INF, mneg = 0.0f, l_run = 0.0f;
+    f16v o[4];
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        m_run[qt] = SQ_NEG_INF;
-        l_run[qt] = 0.0f;
+    for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) o[qt][dt] = f4{0.f, 0.f, 0.f, 0.f};
-    }
+        for (int r = 0; r < 16; ++r) o[dt][r] = 0.0f;
 
-    const _Float16 *Kfh = Kf + (size_t)h * L * D, *Vfh = Vf + (size_t)h * L * D;
-    const _Float16 *Kuh = Ku + ((size_t)b * H + h) * (size_t)U * D, *Vuh = Vu + ((size_t)b * H + h) * (size_t)U * D;
+    const char *Kfh = reinterpret_cast<const char *>(Kf + (size_t)h * L * D), *Vfh = reinterpret_cast<const char *>(Vf + (size_t)h * L * D);
+    const char *Kuh = reinterpret_cast<const char *>(Ku + ((size_t)b * H + h) * (size_t)U * D);
+    const char *Vuh = reinterpret_cast<const char *>(Vu + ((size_t)b * H + h) * (size_t)U * D);
     // keys of the fixed context this (sequence, head) walks: all of them, or the kept ones through the row list
     const int n_fixed = SHARED ? min(blk_info[2 * ((size_t)b * H + h) + 1], L) : L;
-    const int32_t *idx_bh = key_cid + ((size_t)b * H + h) * (size_t)L;   // SHARED only
+    const int32_t *idx_bh = reinterpret_cast<const int32_t *>(table) + ((size_t)b * H + h) * (size_t)L;   // SHARED only
     const int nblk_fixed = (n_fixed + PF_BN - 1) / PF_BN;
     // Causal user block: queries of this workgroup see user keys 0 .. min(U, q0 + BM) - 1 at most.
-    const int u_vis = causal_user ? min(U, q0 + BM) : U;
-    const int nblk = nblk_fixed + (u_vis + PF_BN - 1) / PF_BN;
-    const int32_t *binfo = blk_info + (size_t)h * ((L + PF_BN - 1) / PF_BN);
-    const int32_t *cid_h = key_cid + (size_t)h * L;
-    // Mask row of the query this thread stages bits for (threads 0..BM-1).
-    const int my_q = q0 + tid;
-    const uint32_t *my_mrow = keep_mask + (row0 + min(my_q, Lq - 1)) * W;
+    const int u_vis = causal_user ? min(U, q0 + PF_BM) : U;
+    const int nblk_user = (u_vis + PF_BN - 1) / PF_BN;
+    const int nblk_all = (L + PF_BN - 1) / PF_BN;
+    const int32_t *binfo = blk_info + (size_t)h * nblk_all;
+    const uint32_t *mrow = keep_mask + (row0 + nqc) * W;    // mask row of this lane's query
 
-    // Registers that carry the next block's ids and mask words from global memory to LDS (its K and V rows go to LDS
-    // directly).
-    int pcid = 0, pinfo = 0;
-    uint32_t pw_lo = 0u, pw_hi = 0u;
-    // This thread's pieces of a 64-key block: piece i = key i*PF_RP + tid/16 (rows of 256 B), LDS slot tid%16 of that
-    // row, i.e. the 16-byte chunk (tid%16) ^ swz(row) of the row in memory; row % 16 = (tid/16) % 16 for every piece.
-    const uint32_t r_off = (uint32_t)(tid >> 4) * 256u;
-    const uint32_t k_ch = (uint32_t)((tid & 15) ^ pf_k_swz(tid >> 4)) * 16u, v_ch = (uint32_t)((tid & 15) ^ pf_v_swz(tid >> 4)) * 16u;
-    const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-    // SHARED: rows of this thread's pieces (keys i*16 + tid/16) of a fixed block; the indices of block b+2 are
-    // loaded while block b is computed and used when block b+1's rows are fetched.
-    int ik_n[PF_NP] = {}, ik_c[PF_NP] = {};
-    auto fetch_idx = [&](int blk) {
-        if (!SHARED || blk >= nblk_fixed) return;
-        const int j0 = blk * PF_BN, last = n_fixed - 1;
-#pragma unroll
-        for (int i = 0; i < PF_NP; ++i) ik_n[i] = idx_bh[min(j0 + i * PF_RP + (tid >> 4), last)];
-    };
-    // The loads of the next block are issued in PF_NP pieces (one K and one V row chunk per thread each).  `aim` points
-    // them at block `blk` and issues the block's small loads (ids, mask words); `fetch_piece` is then called from inside
-    // the block body, one piece behind each step of the S^T products, so that the four waves of a workgroup do not queue
-    // at the address unit all at once while the matrix cores idle.
-    const char *nKb = reinterpret_cast<const char *>(Kfh), *nVb = reinterpret_cast<const char *>(Vfh);   // uniform bases
-    uint32_t noff[PF_NP];                 // per-thread byte offsets of the pieces' rows, the same for K and V
-#pragma unroll
-    for (int i = 0; i < PF_NP; ++i) noff[i] = 0u;
-    auto aim = [&](int blk) {
-        const bool user = blk >= nblk_fixed;
-        const int j0 = (user ? blk - nblk_fixed : blk) * PF_BN;
-        const int nkeys = user ? U : L;
-        if (SHARED && !user) {            // gathered rows (slots past the kept keys repeat the last kept row)
-            nKb = reinterpret_cast<const char *>(Kfh);
-            nVb = reinterpret_cast<const char *>(Vfh);
-#pragma unroll
-            for (int i = 0; i < PF_NP; ++i) noff[i] = (uint32_t)ik_c[i] * 256u;
-            return;
-        }
-        nKb = reinterpret_cast<const char *>(user ? Kuh : Kfh) + (size_t)j0 * 256;
-        nVb = reinterpret_cast<const char *>(user ? Vuh : Vfh) + (size_t)j0 * 256;
-        if (j0 + PF_BN <= nkeys) {        // full block
-#pragma unroll
-            for (int i = 0; i < PF_NP; ++i) noff[i] = r_off + (uint32_t)i * (PF_RP * 256u);
-        } else {                          // last block of a tensor: rows past the end re-read the last row
-            const int last = nkeys - 1 - j0;
-#pragma unroll
-            for (int i = 0; i < PF_NP; ++i)
-                noff[i] = (uint32_t)min(i * PF_RP + (tid >> 4), last) * 256u;
-        }
-        if (!user && !SHARED) {
-            pinfo = binfo[blk];
-            if (tid < PF_BN) pcid = j0 + tid < L ? cid_h[j0 + tid] : 0x7fffffff;
-            if (tid < BM) {
-                const int w0 = (pinfo & 0xffff) >> 5;
-                pw_lo = my_mrow[w0];
-                pw_hi = w0 + 1 < W ? my_mrow[w0 + 1] : 0u;
-            }
-        }
-    };
-    typedef __attribute__((address_space(1))) const void *gptr_t;
-    typedef __attribute__((address_space(3))) void *lptr_t;
-    auto fetch_piece = [&](int i, PfStage &dst) {   // i: compile-time constant at every call
-        // this wave's four rows of the piece: 1 KB of the tile, lane l at byte 16 l
-        _Float16 *lk = dst.K + (i * PF_RP + wave_u * 4) * D, *lv = dst.V + (i * PF_RP + wave_u * 4) * D;
-        if constexpr (SHARED) {
-            __builtin_amdgcn_global_load_lds((gptr_t)(nKb + (noff[i] + k_ch)), (lptr_t)lk, 16, 0, 0);
-            __builtin_amdgcn_global_load_lds((gptr_t)(nVb + (noff[i] + v_ch)), (lptr_t)lv, 16, 0, 0);
-        } else {
-            // Written as instructions: through the builtin the compiler makes the first V read of the CURRENT buffer wait
-            // for these loads into the OTHER buffer (it cannot tell the two apart).  Masked form at 32 heads x 1024 tokens x
-            // 32K keys: 1042 us with the builtin, 825 us this way; the shared-set form, whose V reads come later, is faster
-            // with the builtin (133 against 147 us: the asm statements pin the compiler's schedule).
-            const uint32_t ak = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t)lk);
-            const uint32_t av = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t)lv);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(ak), "v"(noff[i] + k_ch), "s"(nKb) : "m0");
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(av), "v"(noff[i] + v_ch), "s"(nVb) : "m0");
-        }
-    };
-    auto fetch_rest = [&](int from, PfStage &dst) {
-#pragma unroll
-        for (int i = 0; i < PF_NP; ++i)
-            if (i >= from) fetch_piece(i, dst);
-    };
-    // The loads to LDS are not tracked by the compiler: before the barrier that publishes a block, every wave waits
-    // for all of its outstanding memory operations itself.
-    auto loads_landed = [&]() { __builtin_amdgcn_s_waitcnt(0x0f70); };   // vmcnt(0)
-    auto commit = [&](int blk, PfStage &st) {   // registers -> LDS (ids, mask bits)
-        const bool user = blk >= nblk_fixed;
-        if (!user && !SHARED) {
-            const int first = pinfo & 0xffff;
-            if (tid < PF_BN) {
-                st.cid[tid] = pcid;
-                st.sh[tid] = (unsigned)(pcid - first) >= 31u ? 31 : pcid - first;   // (no cluster, or outside the window: bit 31 is never set)
-            }
-            if (tid < BM) {
-                const unsigned long long two = ((unsigned long long)pw_hi << 32) | pw_lo;
-                st.qbits[tid] = my_q < Lq ? ((uint32_t)(two >> (first & 31)) & 0x7fffffffu) : 0u;
-            }
-        }
-    };
-
-    auto take_idx = [&]() {
-#pragma unroll
-        for (int i = 0; i < PF_NP; ++i) ik_c[i] = ik_n[i];
-    };
-    // ---- listed form: the blocks this workgroup has to walk, in order ------------------------------------------------
-    // s_um = OR of the keep masks of the workgroup's queries; s_list = the fixed blocks it needs.
-    uint32_t *s_um = reinterpret_cast<uint32_t *>(smem + 2 * sizeof(PfStage));
-    uint16_t *s_list = reinterpret_cast<uint16_t *>(s_um + PF_UMASK_WORDS);
-    int n_list = nblk_fixed;
-    if constexpr (LISTED) {
-        __shared__ int s_wc[PF_THREADS / 64];
+    // ---- the blocks of this share, in order: fixed blocks (masked form: those in which a query of the workgroup kept a
+    // cluster; nobody's blocks are neither fetched nor staged), then user blocks ------------------------------------------
+    int n_list = (max(nblk_fixed - split, 0) + n_split - 1) / n_split;
+    if constexpr (!SHARED) {
         for (int w = tid; w < W; w += PF_THREADS) s_um[w] = 0u;
         __syncthreads();
-        pf_union_mask(s_um, keep_mask, row0, q0, BM, Lq, W, tid, PF_THREADS);
+        pf_union_mask(s_um, keep_mask, row0, q0, PF_BM, Lq, W, tid, PF_THREADS);
         __syncthreads();
         int base = 0;
-        for (int b0 = 0; b0 < nblk_fixed; b0 += PF_THREADS) {   // in order: a ballot per wave, the waves' counts in LDS
-            const int bb = b0 + tid;
-            const bool need = bb < nblk_fixed && pf_block_needed(binfo[bb], s_um, W);
+        for (int i0 = 0; i0 < n_list; i0 += PF_THREADS) {   // in order: a ballot per wave, the waves' counts in LDS
+            const int bb = split + (i0 + tid) * n_split;
+            const bool need = i0 + tid < n_list && pf_block_needed(binfo[bb], s_um, W);
             const unsigned long long bal = __ballot(need);
             if (lane == 0) s_wc[wave] = __popcll(bal);
             __syncthreads();
             int before = 0, total = 0;
 #pragma unroll
-            for (int w = 0; w < PF_THREADS / 64; ++w) {
+            for (int w = 0; w < PF_WAVES; ++w) {
                 if (w < wave) before += s_wc[w];
                 total += s_wc[w];
             }
@@ -403,153 +305,418 @@ __global__ __launch_bounds__(64 * pf_waves(SHARED), 8 / pf_waves(SHARED)) void p
         }
         n_list = __builtin_amdgcn_readfirstlane(base);
     }
-    // The blocks in walking order: the (listed) fixed blocks, then the user blocks.
-    const int n_seq = n_list + (nblk - nblk_fixed);
-    // (the same in every lane: made scalar, or every address and branch that hangs on it would be done per lane)
-    auto blk_at = [&](int i) {
-        return i < n_list ? (LISTED ? __builtin_amdgcn_readfirstlane((int)s_list[i]) : i) : nblk_fixed + (i - n_list);
+    const int u_first = (split + n_split - nblk_fixed % n_split) % n_split;   // first user block of the share
+    const int n_mine = n_list + (max(nblk_user - u_first, 0) + n_split - 1) / n_split;
+    // The walk's next entries, one per lane: lane i holds position t_base + i (past the end: the last one again) as block | user
+    // flag << 31, and a fixed block's table entry.  Read with v_readlane, refilled every few dozen blocks: scalar values that
+    // cost one instruction each.
+    int t_base = 0, t_ent = 0, t_info = 0;
+    auto fill_entries = [&](int base) PF_INLINE {
+        t_base = base;
+        const int i = min(base + lane, n_mine - 1);
+        const bool user = i >= n_list;
+        const int blk = user ? u_first + (i - n_list) * n_split : SHARED ? split + i * n_split : (int)s_list[i];
+        t_ent = user ? blk | (int)0x80000000 : blk;
+        if (!SHARED) t_info = binfo[user ? 0 : blk];
+    };
+    constexpr int T_KEEP = 56;                              // entries used of a fill: the loop looks up to seven ahead
+
+    // ---- staging -----------------------------------------------------------------------------------------------------------
+    // This thread's pieces of a 64-key block: piece i = key i*PF_RP + tid/16 (rows of 256 B), LDS slot tid%16 of that
+    // row, i.e. the 16-byte chunk (tid%16) ^ swz(row) of the row in memory; row % 16 = (tid/16) % 16 for every piece.
+    const int trow = tid >> 4;
+    const uint32_t k_ch = (uint32_t)((tid & 15) ^ pf_k_swz(trow)) * 16u, v_ch = (uint32_t)((tid & 15) ^ pf_v_swz(trow)) * 16u;
+    const uint32_t k_at = (uint32_t)trow * 256u + k_ch, v_at = (uint32_t)trow * 256u + v_ch;
+    // Where a block's rows are: base addresses and `end`, 16 bytes before the end of its rows (contiguous rows).
+    struct Aim {
+        const char *k, *v;
+        uint32_t end;
+    };
+    auto aim_at = [&](int e) PF_INLINE {
+        const bool user = e < 0;
+        const int j0 = (e & 0x7fffffff) * PF_BN;
+        const size_t at = SHARED && !user ? 0 : (size_t)j0 * 256;
+        return Aim{(user ? Kuh : Kfh) + at, (user ? Vuh : Vfh) + at, (uint32_t)min((user ? U : L) - j0, PF_BN) * 256u - 16u};
+    };
+    // SHARED: the gathered rows of this thread's pieces (for a user block the list is not used).
+    struct Rows {
+        int r[SHARED ? PF_NP : 1];
+    };
+    auto rows_of = [&](int e) PF_INLINE {
+        Rows x{};
+        if constexpr (SHARED) {
+            const int j0 = e < 0 ? 0 : e * PF_BN, last = max(n_fixed - 1, 0);
+#pragma unroll
+            for (int k = 0; k < PF_NP; ++k) x.r[k] = idx_bh[min(j0 + k * PF_RP + trow, last)];
+        }
+        return x;
+    };
+    typedef __attribute__((address_space(3))) void *lptr_t;
+    auto lds_at = [&](const void *p) PF_INLINE { return __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t)p); };
+    // Written as instructions: through the builtin the compiler may make a read of the CURRENT buffer wait for these
+    // loads into the OTHER buffer.  The waves wait for their own loads themselves before the barrier that publishes a block.
+    // Contiguous rows: rows past the end of the tensor read some chunk in front of it (what lands there is hidden).
+    const uint32_t lds_w = lds_at(stage) + (uint32_t)wave_u * 1024u;      // a wave's four rows of a pass: 1 KB, lane l at byte 16 l
+    auto fetch_piece = [&](int i, const char *base, uint32_t end, bool gathered, const Rows &rw, uint32_t at, uint32_t ch, uint32_t tile) PF_INLINE {
+        uint32_t off = min(at + (uint32_t)i * (PF_RP * 256u), end);
+        if constexpr (SHARED) off = gathered ? (uint32_t)rw.r[i] * 256u + ch : off;
+        asm volatile("s_add_u32 m0, %0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %2, %3" ::"s"(lds_w),
+                     "i"(tile + (uint32_t)i * (PF_RP * 256u)), "v"(off), "s"(base) : "m0", "scc");
+    };
+    constexpr uint32_t V_AT = NB * PF_TILE;                 // byte offset of the V tiles
+    auto loads_landed = [&]() PF_INLINE { __builtin_amdgcn_s_waitcnt(0x0f70); };   // vmcnt(0)
+
+    // Masked form: what decides the visible keys travels ahead of the block: its table row to LDS (one wave fetches it), and
+    // the two mask words of this lane's query that hold the block's window of clusters (loaded when the window moves to
+    // another word, every few blocks).
+    auto fetch_tab = [&](int pos, int e) PF_INLINE {
+        if (SHARED || wave_u != 0) return;
+        const uint32_t *p = rows + ((size_t)h * nblk_all + (e < 0 ? 0 : e)) * PF_ROW_WORDS;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_at(s_tab) + (uint32_t)(pos & (PF_TABS - 1)) * (PF_ROW_WORDS * 4)),
+                     "v"(lane * 4), "s"(p) : "m0");
+    };
+    uint32_t mw_lo = 0u, mw_hi = 0u;
+    int mw_at = -1;
+    auto fetch_words = [&](int info) PF_INLINE {
+        if (SHARED) return;
+        const int w0 = (info & 0xffff) >> 5;
+        if (w0 != mw_at) {
+            mw_at = w0;
+            mw_lo = mrow[min(w0, W - 1)];
+            mw_hi = w0 + 1 < W ? mrow[w0 + 1] : 0u;
+        }
+    };
+    // Keys of the block at walk position pos (entry e, table entry info) that this lane's query sees, as the accumulators
+    // hold them: bit 8 a + i of w[t] = key 32 t + 8 a + 4 g + i (i < 4).
+    auto visible = [&](int pos, int e, int info, uint32_t wl, uint32_t wh, uint32_t (&w)[2]) PF_INLINE {
+        if (SHARED || e < 0) {
+            // user keys: those at or before the query (causal); one kept set: all but the slots past the kept keys
+            const int n = (e >= 0 ? n_fixed : causal_user ? min(U, nqc + 1) : U) - (e & 0x7fffffff) * PF_BN;
+            const unsigned long long m = n >= 64 ? ~0ull : (1ull << max(n, 0)) - 1ull;
+            w[0] = (uint32_t)(m >> (4 * g)) & 0x0f0f0f0fu;
+            w[1] = (uint32_t)(m >> 32 >> (4 * g)) & 0x0f0f0f0fu;
+            return;
+        }
+        w[0] = w[1] = 0u;
+        const int n = (info >> 21) & 127, first = info & 0xffff;
+        if (info >= 0 && n <= PF_ROW_RUNS) {
+            // bit (cluster - first cluster of the block) of the query's window, spread over the keys of its run
+            const uint32_t qb = __builtin_amdgcn_alignbit(wh, wl, (uint32_t)first & 31u) & 0x7fffffffu;
+            const uint32_t *row = s_tab + (pos & (PF_TABS - 1)) * PF_ROW_WORDS;
+            auto group = [&](int k) PF_INLINE {
+                const uint4 rel = *reinterpret_cast<const uint4 *>(row + k * PF_ROW_GROUP);
+                const uint4 k0 = *reinterpret_cast<const uint4 *>(row + k * PF_ROW_GROUP + 4 + 8 * g);
+                const uint4 k1 = *reinterpret_cast<const uint4 *>(row + k * PF_ROW_GROUP + 8 + 8 * g);
+                auto add = [&](uint32_t r, uint32_t a, uint32_t b) PF_INLINE {
+                    const uint32_t on = (uint32_t)__builtin_amdgcn_sbfe((int)qb, r, 1u);
+                    w[0] |= on & a;
+                    w[1] |= on & b;
+                };
+                add(rel.x, k0.x, k1.x);
+                add(rel.y, k0.y, k1.y);
+                add(rel.z, k0.z, k1.z);
+                add(rel.w, k0.w, k1.w);
+            };
+            group(0);
+            if (n > 4) {
+                group(1);
+                group(2);
+            }
+        } else {                                            // many runs, or more than 31 cluster ids: every run's bit from the mask itself
+            const uint32_t *rp = table + ((size_t)h * nblk_all + e) * PF_BN;
+            for (int i = 0; i < n; ++i) {
+                const uint32_t r = __builtin_amdgcn_readfirstlane(rp[i]), c = r & 0xffffu;
+                const unsigned long long ks = (~0ull >> (63 - (int)((r >> 22) & 63u))) << ((r >> 16) & 63u);
+                const uint32_t on = 0u - ((mrow[c >> 5] >> (c & 31u)) & 1u);
+                w[0] |= on & (uint32_t)(ks >> (4 * g)) & 0x0f0f0f0fu;
+                w[1] |= on & (uint32_t)(ks >> 32 >> (4 * g)) & 0x0f0f0f0fu;
+            }
+        }
     };
 
-    // This workgroup's share: positions at(0), at(1), ... of the walking order; n_mine of them, the first n_mine_fixed
-    // of which are fixed blocks.
-    auto at = [&](int i) { return split + i * n_split; };
-    const int n_mine = (max(n_seq - split, 0) + n_split - 1) / n_split;
-    const int n_mine_fixed = (max(n_list - split, 0) + n_split - 1) / n_split;
-
-    int info_cur = 0;
-    if (n_mine > 0) {                                     // (no kept key and no user key: nothing to stage)
-        fetch_idx(at(0));
-        take_idx();
-        fetch_idx(at(1));
-        aim(blk_at(at(0)));
-        fetch_rest(0, stage[0]);
-        info_cur = pinfo;
-        commit(blk_at(at(0)), stage[0]);
-    }
-    loads_landed();
-    __syncthreads();
-
-    // The key blocks, alternating between the two LDS buffers.  The shared-set form runs the loop unrolled over the
-    // buffers, so that which buffer is read and which is filled are compile-time constants: the compiler can then tell
-    // them apart (no wait for the loads to LDS in front of the V reads) and the swizzled operand addresses are
-    // loop-invariant -- 133 -> 117 us at 32 heads x 1024 tokens, 1/8 of 32K keys kept.  The masked form is faster as a
-    // plain loop (823 us against 896-929 us unrolled: twice the code for a body that already holds five variants of
-    // the block), so the body is kept in a file of its own and included in each loop.
-    if constexpr (SHARED) {
-        auto one_block = [&](int it, auto par) {
-            const int blk = at(it);
-            PfStage &st = stage[par];
-            PfStage &st_next = stage[par ^ 1];
-#define PF_USER(b) ((b) >= nblk_fixed)
-#define PF_NEXT_STAGE st_next
-#define PF_HAS_NEXT (it + 1 < n_mine)
-#define PF_NEXT_BLK at(it + 1)
-#define PF_FETCH_IDX_AHEAD if (it + 2 < n_mine) fetch_idx(at(it + 2))
-#define PF_OPERANDS_AHEAD 0
-#include "sq_prefill_block.inc"
-#undef PF_OPERANDS_AHEAD
-#undef PF_FETCH_IDX_AHEAD
-#undef PF_NEXT_BLK
-#undef PF_HAS_NEXT
-#undef PF_NEXT_STAGE
-#undef PF_USER
-        };
-        for (int it = 0; it < n_mine; it += 2) {
-            one_block(it, std::integral_constant<int, 0>{});
-            if (it + 1 < n_mine) one_block(it + 1, std::integral_constant<int, 1>{});
-        }
-    } else if constexpr (!LISTED) {
-        for (int it = 0; it < n_mine; ++it) {
-            const int blk = at(it);
-            PfStage &st = stage[it & 1];
-#define PF_USER(b) ((b) >= nblk_fixed)
-#define PF_NEXT_STAGE stage[(it + 1) & 1]
-#define PF_HAS_NEXT (it + 1 < n_mine)
-#define PF_NEXT_BLK (blk + n_split)
-#define PF_FETCH_IDX_AHEAD (void)0
-#define PF_OPERANDS_AHEAD 3
-#include "sq_prefill_block.inc"
-#undef PF_OPERANDS_AHEAD
-#undef PF_FETCH_IDX_AHEAD
-#undef PF_NEXT_BLK
-#undef PF_HAS_NEXT
-#undef PF_NEXT_STAGE
-#undef PF_USER
-        }
-    } else {
-        // Two loops, fixed blocks then user blocks: each then holds only its own forms of the block, and what only the
-        // other needs (base pointers, lengths) is not kept in registers through it.
-        // (The list is read two blocks ahead and made scalar only after the block: the entry heads the address chain
-        // of the next block's loads, and nothing in front of the block's own work waits for it.)
-        int blk_cur = n_mine > 0 ? blk_at(at(0)) : 0, blk_ahead = n_mine > 1 ? blk_at(at(1)) : 0;
-        for (int it = 0; it < n_mine_fixed; ++it) {
-            const int blk = blk_cur, blk_nx = blk_ahead;
-            int ahead_v = 0;
-            const int pos2 = at(it + 2);
-            if (pos2 < n_seq) ahead_v = pos2 < n_list ? (int)s_list[pos2] : nblk_fixed + (pos2 - n_list);
-            PfStage &st = stage[it & 1];
-#define PF_USER(b) false
-#define PF_NEXT_STAGE stage[(it + 1) & 1]
-#define PF_HAS_NEXT (it + 1 < n_mine)
-#define PF_NEXT_BLK blk_nx
-#define PF_FETCH_IDX_AHEAD (void)0
-#define PF_OPERANDS_AHEAD 3
-#include "sq_prefill_block.inc"
-#undef PF_OPERANDS_AHEAD
-#undef PF_FETCH_IDX_AHEAD
-#undef PF_NEXT_BLK
-#undef PF_HAS_NEXT
-#undef PF_NEXT_STAGE
-#undef PF_USER
-            blk_cur = blk_nx;
-            blk_ahead = __builtin_amdgcn_readfirstlane(ahead_v);
-        }
-        for (int it = n_mine_fixed; it < n_mine; ++it) {
-            const int blk = nblk_fixed + (at(it) - n_list);
-            PfStage &st = stage[it & 1];
-#define PF_USER(b) true
-#define PF_NEXT_STAGE stage[(it + 1) & 1]
-#define PF_HAS_NEXT (it + 1 < n_mine)
-#define PF_NEXT_BLK (blk + n_split)
-#define PF_FETCH_IDX_AHEAD (void)0
-#define PF_OPERANDS_AHEAD 3
-#include "sq_prefill_block.inc"
-#undef PF_OPERANDS_AHEAD
-#undef PF_FETCH_IDX_AHEAD
-#undef PF_NEXT_BLK
-#undef PF_HAS_NEXT
-#undef PF_NEXT_STAGE
-#undef PF_USER
-        }
-    }
-
-    // ---- normalise and store: lane holds query column nq[qt], dims dt*16 + kg*4 + v ---------------------------
+    // Operand addresses in LDS, of the first stage's tiles (the swizzles depend on the lane alone); hidden from the compiler,
+    // which would otherwise add their two parts again in front of every read.
+    uint32_t k_lds[8], v_lds[4];
 #pragma unroll
-    for (int qt = 0; qt < QT; ++qt) {
-        const float lt = cross16_sum(l_run[qt]);
-        if (nq[qt] >= Lq) continue;
-        if (n_split > 1) {                                // this share's (m, l, o) for the merge launch; m in natural units
-            float *pr = partials + ((row0 + nq[qt]) * (size_t)n_split + split) * PART_STRIDE;
+    for (int i = 0; i < 8; ++i) {
+        k_lds[i] = (uint32_t)(size_t)(lptr_t)stage + (uint32_t)(col * D + ((2 * i + g) ^ pf_k_swz(l16)) * 8) * 2u;
+        asm volatile("" : "+v"(k_lds[i]));
+    }
 #pragma unroll
-            for (int dt = 0; dt < 8; ++dt) *reinterpret_cast<f4 *>(pr + 4 + dt * 16 + kg * 4) = o[qt][dt];
-            if (kg == 0) {
-                pr[0] = m_run[qt] * sm_scale;
-                pr[1] = lt;
+    for (int i = 0; i < 4; ++i) {
+        const int row = 4 * g + (l16 >> 2), chunk = i * 4 + 2 * ((lane >> 4) & 1) + ((l16 & 3) >> 1);
+        v_lds[i] = (uint32_t)(size_t)(lptr_t)stage + V_AT + (uint32_t)(row * D + (chunk ^ pf_v_swz(row)) * 8 + (l16 & 1) * 4) * 2u;
+        asm volatile("" : "+v"(v_lds[i]));
+    }
+    typedef __attribute__((address_space(3))) const h8 *lds_h8_t;
+    typedef __attribute__((address_space(3))) tr_h4 *lds_tr_t;
+    auto k_operand = [&](uint32_t st, int m) PF_INLINE {              // product m: keys (m & 1) * 32 .. + 31, dimensions 16 (m >> 1) .. + 15
+        return *(lds_h8_t)(k_lds[m >> 1] + st + (uint32_t)(m & 1) * (32u * D * 2u));
+    };
+    auto v_operand = [&](uint32_t st, int m) PF_INLINE {              // product m: keys 16 (m >> 2) .. + 15, dimensions 32 (m & 3) .. + 31
+        const uint32_t at = v_lds[m & 3] + st + (uint32_t)(m >> 2) * (16u * D * 2u);
+        const h4 a0 = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_tr_t)at));
+        const h4 a1 = __builtin_bit_cast(h4, __builtin_amdgcn_ds_read_tr16_b64_v4f16((lds_tr_t)(at + 8u * D * 2u)));
+        return h8{a0[0], a0[1], a0[2], a0[3], a1[0], a1[1], a1[2], a1[3]};
+    };
+    // A block's score products start from 0 for a pair that is visible and -inf for one that is hidden: masks cost no vector
+    // arithmetic, four start values come with one LDS read.  Group gi = 4 t + a: keys 32 t + 8 a + 4 g + (0..3).
+    auto start_group = [&](f16v (&sa)[2], const uint32_t (&w)[2], int gi) PF_INLINE {
+        const int t = gi >> 2, a = gi & 3;
+        const f4 v = *reinterpret_cast<const f4 *>(s_hide + ((w[t] >> (8 * a)) & 0xffu) * 4);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) sa[t][4 * a + k] = v[k];
+    };
+    auto max_pair = [&](float mx, const f16v (&sa)[2], int i) PF_INLINE {    // (propagates NaN: see new_max)
+        const int t = i >> 3, r = 2 * (i & 7);
+        return __builtin_elementwise_maximum(__builtin_elementwise_maximum(mx, sa[t][r]), sa[t][r + 1]);
+    };
+    // The reference maximum moves only when a score passes it by 2^8 (probabilities then stay below 2^8, far inside
+    // fp16's range, at the same relative rounding): the output is rarely rescaled.  A hidden key with an infinite or NaN
+    // component makes its score NaN instead of -inf: such a block's hidden scores are set again here (w0, w1: its visible
+    // keys), and the maximum is then taken without regard to NaN.
+    auto new_max = [&](float mx, f16v (&sa)[2], uint32_t w0, uint32_t w1) PF_INLINE {
+        if (__ballot(!(mx <= m_lim)) != 0ull) {
+            if (__ballot(mx != mx) != 0ull) {
+                mx = SQ_NEG_INF;
+#pragma unroll
+                for (int t = 0; t < 2; ++t)
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        sa[t][r] = ((t ? w1 : w0) >> (8 * (r >> 2) + (r & 3))) & 1u ? sa[t][r] : SQ_NEG_INF;
+                        mx = fmaxf(mx, sa[t][r]);
+                    }
             }
-            continue;
-        }
-        const bool empty = !(lt > 0.0f);
-        const float inv = empty ? 0.0f : 1.0f / lt;
-        _Float16 *orow = out + (row0 + nq[qt]) * D;
+            const float m_new = fmaxf(m_ref, cross32_max(mx));
+            const float alpha = m_new == m_ref ? 1.0f : __builtin_amdgcn_exp2f((m_ref - m_new) * c2);
+            m_ref = m_new;
+            m_lim = m_new + 8.0f / c2;
+            mneg = m_new == SQ_NEG_INF ? 0.0f : -m_new * c2;       // nothing seen yet: exp2(-inf) = 0
+            l_run *= alpha;
 #pragma unroll
-        for (int dt = 0; dt < 8; ++dt) {
+            for (int dt = 0; dt < 4; ++dt) o[dt] *= alpha;
+        }
+    };
+
+    if (n_mine > 0) {                                       // (no kept key and no user key: nothing to do)
+        fill_entries(0);
+        auto ent = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_ent, i - t_base); };
+        auto inf = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_info, i - t_base); };
+        f16v s_cur[2], s_nxt[2];
+        uint32_t vis0 = 0u, vis1 = 0u;                      // visible keys of the block whose start values were made last
+        uint2 w2{}, w3{};                                   // mask words of blocks it + 2, it + 3
+        bool any_cur = true, any_nxt = true;                // does this wave see a key of block it, it + 1?
+        // Start values of the scores of the block at position i; nothing visible past the end of the walk.
+        auto start_scores = [&](f16v (&sa)[2], int i, uint2 words) PF_INLINE {
+            uint32_t w[2] = {0u, 0u};
+            if (i < n_mine) visible(i, ent(i), inf(i), words.x, words.y, w);
+            vis0 = w[0];
+            vis1 = w[1];
+#pragma unroll
+            for (int gi = 0; gi < 8; ++gi) start_group(sa, w, gi);
+            return __ballot((w[0] | w[1]) != 0u) != 0ull;
+        };
+        auto words_of = [&](int i) PF_INLINE {
+            fetch_words(inf(i));
+            return uint2{mw_lo, mw_hi};
+        };
+        Aim aim_v{};                                        // of block it + LV (computed with its K, one iteration before)
+        Rows rv = rows_of(ent(LV)), rk = rows_of(ent(LK)), rk1 = rows_of(ent(LK + 1));   // blocks it + LV, it + LK, it + LK + 1
+#pragma unroll
+        for (int b = 0; b < LK; ++b) {
+            const int e = ent(b);
+            aim_v = aim_at(e);
+            const Rows r = rows_of(e);
+#pragma unroll
+            for (int i = 0; i < PF_NP; ++i) {
+                fetch_piece(i, aim_v.k, aim_v.end, e >= 0, r, k_at, k_ch, b * PF_TILE);
+                if (b < LV) fetch_piece(i, aim_v.v, aim_v.end, e >= 0, r, v_at, v_ch, V_AT + b * PF_TILE);
+            }
+        }
+#pragma unroll
+        for (int b = 0; b < PF_TABS; ++b) fetch_tab(b, ent(b));
+        const uint2 w0 = words_of(0), w1 = words_of(1);
+        w2 = words_of(2);
+        w3 = words_of(3);
+        loads_landed();
+        __syncthreads();
+        if (wave_on) {                                      // scores of the first block
+            any_cur = start_scores(s_cur, 0, w0);
+#pragma unroll
+            for (int m = 0; m < 16; ++m)
+                s_cur[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(k_operand(0u, m), bq[m >> 1], s_cur[m & 1], 0, 0, 0);
+            float mx = SQ_NEG_INF;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) mx = max_pair(mx, s_cur, i);
+            new_max(mx, s_cur, vis0, vis1);
+            any_nxt = start_scores(s_nxt, 1, w1);
+        }
+        __syncthreads();                                    // K of the first block is read: its buffer may be filled again
+
+        // Iteration it: softmax of block it (scores ready, maximum known), S^T = K Q^T of block it + 1, O^T += V^T P^T of block
+        // it, then the maximum of block it + 1 and the start values of block it + 2.  Matrix and vector work are laid out
+        // alternating in the instruction stream: 24 products between the 16 pairs of exponentials, 8 between the rest; the
+        // scalar work that aims the next loads goes behind the first products.
+        // masked: std::bool_constant; false: the blocks up to it + LK are full blocks of kept keys, every pair visible.
+        auto walk = [&](int it, auto par, f16v (&sc)[2], f16v (&sn)[2], auto masked) PF_INLINE {
+            constexpr bool MASKED = decltype(masked)::value;
+            constexpr uint32_t at_v = par * PF_TILE, at_k = (par + 1) % NB * PF_TILE;
+            constexpr uint32_t to_v = V_AT + (par + LV) % NB * PF_TILE, to_k = (par + LK) % NB * PF_TILE;
+            Aim aim_k{};
+            bool gk = true, gv = true;
+            Rows rk2{};
+            uint2 w4{};
+            auto look_ahead = [&]() PF_INLINE {
+                const int e = ent(it + LK);
+                aim_k = aim_at(e);
+                if (MASKED) {
+                    gk = e >= 0;
+                    gv = ent(it + LV) >= 0;
+                }
+            };
+            auto look_further = [&]() PF_INLINE {
+                rk2 = rows_of(ent(it + LK + 2));
+                fetch_tab(it + 4, ent(it + 4));
+                w4 = words_of(it + 4);
+            };
+            auto fetch_kv = [&](int x) PF_INLINE {                    // 2 PF_NP pieces; the tiles they fill were read one pass ago or earlier
+                if (x & 1) fetch_piece(x >> 1, aim_v.v, aim_v.end, gv, rv, v_at, v_ch, to_v);
+                else fetch_piece(x >> 1, aim_k.k, aim_k.end, gk, rk, k_at, k_ch, to_k);
+            };
+            // A wave that sees no key of the three blocks at hand has nothing to do: hidden scores stay -inf, whatever block they
+            // belong to.  (Where selections follow the position, most waves skip most of the workgroup's blocks.  32 heads x 1024 tokens x
+            // 32K keys, every 256 / 64 tokens sharing a band of 1/8 of the clusters: 123 / 317 us without this, 126 / 248 with it;
+            // the form before, which listed blocks per 64 queries, 168 / 197.)
+            bool any_new = true, on = wave_on;
+            if (MASKED && on && !any_cur && !any_nxt) {
+                uint32_t w[2] = {0u, 0u};
+                if (it + 2 < n_mine) visible(it + 2, ent(it + 2), inf(it + 2), w2.x, w2.y, w);
+                any_new = on = __ballot((w[0] | w[1]) != 0u) != 0ull;
+            }
+            if (on) {
+                h8 op[PF_AHEAD];
+                auto operand = [&](int m) PF_INLINE { return m < 16 ? k_operand(at_k, m) : v_operand(at_v, m - 16); };
+#pragma unroll
+                for (int m = 0; m < PF_AHEAD; ++m) op[m] = operand(m);
+                h8 bp[4];
+                float ps0 = 0.0f, ps1 = 0.0f, mx = SQ_NEG_INF;
+                const uint32_t v0 = MASKED ? vis0 : ~0u, v1 = MASKED ? vis1 : ~0u;
+                uint32_t w[2] = {0u, 0u};
+                __builtin_amdgcn_sched_barrier(0);
+                static_for<32>([&](auto ic) PF_INLINE {
+                    constexpr int i = ic;
+                    if constexpr (i < 16) {                 // two probabilities of block it
+                        constexpr int t = i >> 3, r = 2 * (i & 7);
+                        const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[t][r], c2, mneg));
+                        const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[t][r + 1], c2, mneg));
+                        ps0 += p0;
+                        ps1 += p1;
+                        bp[2 * t + (r >> 3)][r & 7] = (_Float16)p0;
+                        bp[2 * t + (r >> 3)][(r & 7) + 1] = (_Float16)p1;
+                        asm volatile("" : "+v"(ps0), "+v"(ps1));   // (the sums stay here, between the products)
+                        if constexpr (i == 1) look_ahead();
+                        if constexpr (i >= 2 && i < 2 + 2 * PF_NP) fetch_kv(i - 2);
+                        if constexpr (i == 11) look_further();
+                    } else {                                // two scores of block it + 1, four start values of block it + 2
+                        mx = max_pair(mx, sn, i - 16);
+                        asm volatile("" : "+v"(mx));
+                        if constexpr (MASKED) {
+                            if constexpr (i == 16) {
+                                if (it + 2 < n_mine) visible(it + 2, ent(it + 2), inf(it + 2), w2.x, w2.y, w);
+                                vis0 = w[0];
+                                vis1 = w[1];
+                                any_new = __ballot((w[0] | w[1]) != 0u) != 0ull;
+                            }
+                            if constexpr (i & 1) start_group(sc, w, (i - 16) >> 1);
+                        }
+                    }
+                    constexpr int m0 = i < 16 ? 3 * i / 2 : 24 + (i - 16) / 2, m1 = i < 16 ? 3 * (i + 1) / 2 : 24 + (i - 15) / 2;
+                    static_for<m1 - m0>([&](auto mc) PF_INLINE {
+                        constexpr int m = m0 + mc;
+                        const h8 a = op[m % PF_AHEAD];
+                        if constexpr (m < 2 && !MASKED) {
+                            f16v z;
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) z[r] = 0.0f;
+                            sn[m] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bq[0], z, 0, 0, 0);
+                        } else if constexpr (m < 16)
+                            sn[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bq[m >> 1], sn[m & 1], 0, 0, 0);
+                        else
+                            o[m & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bp[(m - 16) >> 2], o[m & 3], 0, 0, 0);
+                        if constexpr (m + PF_AHEAD < 32) op[m % PF_AHEAD] = operand(m + PF_AHEAD);
+                    });
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+                l_run += ps0 + ps1;
+                new_max(mx, sn, v0, v1);
+            } else {
+                look_ahead();
+#pragma unroll
+                for (int x = 0; x < 2 * PF_NP; ++x) fetch_kv(x);
+                look_further();
+            }
+            any_cur = any_nxt;
+            any_nxt = any_new;
+            aim_v = aim_k;
+            rv = rk;
+            rk = rk1;
+            rk1 = rk2;
+            w2 = w3;
+            w3 = w4;
+            if (it + 1 - t_base >= T_KEEP) fill_entries(it + 1);
+            if (NB == 2 || (par & 1)) {
+                loads_landed();
+                __syncthreads();
+            }
+        };
+        // Unrolled over the LDS buffers: which one is read and which is filled are compile-time constants, so the swizzled
+        // operand addresses are loop-invariant plus an immediate.
+        int it = 0;
+        auto walks = [&](auto masked) PF_INLINE {
+            walk(it, std::integral_constant<int, 0>{}, s_cur, s_nxt, masked);
+            if (!masked || it + 1 < n_mine) walk(it + 1, std::integral_constant<int, 1>{}, s_nxt, s_cur, masked);
+            if constexpr (NB == 4) {
+                if (!masked || it + 2 < n_mine) walk(it + 2, std::integral_constant<int, 2>{}, s_cur, s_nxt, masked);
+                if (!masked || it + 3 < n_mine) walk(it + 3, std::integral_constant<int, 3>{}, s_nxt, s_cur, masked);
+            }
+        };
+        if constexpr (SHARED) {                             // while the blocks fetched ahead are full blocks of kept keys: no start values
+            const int n_full = (max(n_fixed / PF_BN - split, 0) + n_split - 1) / n_split;
+            for (; it + NB - 1 + LK < n_full; it += NB) walks(std::false_type{});
+            if (it > 0 && wave_on) any_nxt = start_scores(s_nxt, it + 1, uint2{0u, 0u});
+        }
+        for (; it < n_mine; it += NB) walks(std::true_type{});
+    }
+
+    // ---- normalise and store: lane holds query column nq, dims dt*32 + 8*a + 4*g + (0..3) --------------------------------
+    const float lt = cross32_sum(l_run);
+    if (nq >= Lq) return;
+    if (n_split > 1) {                                      // this share's (m, l, o) for the merge launch; m in natural units
+        float *pr = partials + ((row0 + nq) * (size_t)n_split + split) * PART_STRIDE;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+            for (int a = 0; a < 4; ++a)
+                *reinterpret_cast<f4 *>(pr + 4 + dt * 32 + 8 * a + 4 * g) = f4{o[dt][4 * a], o[dt][4 * a + 1], o[dt][4 * a + 2], o[dt][4 * a + 3]};
+        if (g == 0) {
+            pr[0] = m_ref * sm_scale;
+            pr[1] = lt;
+        }
+        return;
+    }
+    const bool empty = !(lt > 0.0f);
+    const float inv = empty ? 0.0f : 1.0f / lt;
+    _Float16 *orow = out + (row0 + nq) * D;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+        for (int a = 0; a < 4; ++a) {
             h4 hv;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) hv[v] = (_Float16)(o[qt][dt][v] * inv);
-            *reinterpret_cast<h4 *>(orow + dt * 16 + kg * 4) = hv;
+            for (int v = 0; v < 4; ++v) hv[v] = (_Float16)(o[dt][4 * a + v] * inv);
+            *reinterpret_cast<h4 *>(orow + dt * 32 + 8 * a + 4 * g) = hv;
         }
-        if (lse && kg == 0) lse[row0 + nq[qt]] = empty ? SQ_NEG_INF : m_run[qt] * sm_scale + logf(lt);
-    }
+    if (lse && g == 0) lse[row0 + nq] = empty ? SQ_NEG_INF : m_ref * sm_scale + logf(lt);
 }
 
 // Merges the n_split partial results of a query row: one wave per row, two dimensions per lane.  Bound by the partials'
@@ -580,34 +747,45 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
     if (lse && lane == 0) lse[row] = empty ? SQ_NEG_INF : M + logf(l);
 }
 
-// Workgroups a unit's key blocks are dealt to.  SLOTS workgroups run at a time (two per compute unit in the masked
-// form, one in the shared-set form), so with u units and s shares the launch takes ceil(u s / SLOTS) rounds of
-// ceil(blocks / s) blocks each plus a fixed part (prologue, first loads, partial results: about four blocks' time), and
-// the merge launch costs its own start and the partials' bytes.  In the shared-set form the number of kept keys is not
-// known on the host: an eighth of the context is assumed (the rule only moves time, not results).  Measured, whole
-// steps, without -> with shares: masked form, 2 x 12 heads x 333 tokens x 9001 keys (144 units, 3 shares) 203 -> 105 us,
-// 20 heads x 17 tokens x 22682 keys (20 units) 491 -> 83 us; shared-set form, 20 heads x 150 tokens x 20011 keys
-// (40 units) 92 -> 53 us, two-level step of 8 heads x 512 tokens x 262144 keys (32 units) 616 -> 250 us.
-int prefill_splits(bool shared, const Shape &sh)
+// Waves per workgroup and the number of workgroups a unit's key blocks are dealt to.  A compute unit holds eight waves: one
+// workgroup of eight (256 queries, half the staging per product) or two of four (128 queries, less padding of short or odd
+// query blocks).  With u units and s shares the launch takes ceil(u s / slots) rounds of ceil(blocks / s) blocks each plus
+// a fixed part (prologue, first loads, partial results: about six blocks' time), and the merge launch costs its own start
+// and the partials' bytes.  In the shared-set form the number of kept keys is not known on the host: an eighth of the context
+// is assumed (the rule only moves time, not results).  Eight waves unless four promise a tenth less.  Measured, whole steps:
+//   eight / four waves  32 heads x 1024 tokens x 32K keys 582 / 605 us, 2 x 12 heads x 333 tokens x 9001 keys 84 / 76 us;
+//   one / several shares  20 heads x 17 tokens x 22682 keys (20 units) 491 / 82 us, averaged selection 20 heads x 150 tokens x
+//   20011 keys (40 units) 92 / 56 us, two-level step of 8 heads x 512 tokens x 262144 keys 664 / 270 us.
+namespace {
+struct PfPlan {
+    int waves, n_split;
+};
+PfPlan prefill_plan(bool shared, const Shape &sh)
 {
-    const long long slots = shared ? 256 : 512;
-    const long long bm = pf_bm(shared), rows = (long long)sh.B * sh.H * sh.Lq;
-    const long long units = (long long)sh.B * sh.H * ((sh.Lq + bm - 1) / bm);
+    const long long rows = (long long)sh.B * sh.H * sh.Lq;
     const long long fixed = ((long long)(shared ? (sh.L + 7) / 8 : sh.L) + PF_BN - 1) / PF_BN;
     const long long nblk = fixed + (sh.U + PF_BN - 1) / PF_BN;
-    int best = 1;
+    // (the masked form lists the blocks of a share in LDS)
+    const int least = shared ? 1 : (int)((fixed + PF_LIST_CAP - 1) / PF_LIST_CAP);
+    PfPlan best{8, least};
     double best_cost = 0.0;
-    for (int s = 1; s <= PF_MAX_SPLIT && s <= nblk; ++s) {
-        if (s > 1 && units * s > 2 * slots) break;
-        const double rounds = (double)((units * s + slots - 1) / slots);
-        const double cost = rounds * ((double)((nblk + s - 1) / s) + 4.0) + (s > 1 ? 3.0 + 1.5e-4 * (double)rows * s : 0.0);
-        if (s == 1 || cost < best_cost) {
-            best = s;
-            best_cost = cost;
+    for (int waves = 8; waves >= 4; waves -= 4) {
+        const long long slots = 256 * 8 / waves, bm = pf_bm(waves);
+        const long long units = (long long)sh.B * sh.H * ((sh.Lq + bm - 1) / bm);
+        for (int s = least; s <= least || (s <= PF_MAX_SPLIT && s <= nblk && units * s <= 2 * slots); ++s) {
+            const double rounds = (double)((units * s + slots - 1) / slots);
+            const double cost = rounds * ((double)((nblk + s - 1) / s) + 6.0) + (s > 1 ? 3.0 + 1.5e-4 * (double)rows * s : 0.0);
+            if (best_cost == 0.0 || cost < (waves < best.waves ? 0.9 * best_cost : best_cost)) {
+                best = PfPlan{waves, s};
+                best_cost = cost;
+            }
         }
     }
     return best;
 }
+}  // namespace
+
+int prefill_splits(bool shared, const Shape &sh) { return prefill_plan(shared, sh).n_split; }
 
 size_t prefill_partial_floats(bool shared, const Shape &sh)
 {
@@ -617,79 +795,61 @@ size_t prefill_partial_floats(bool shared, const Shape &sh)
 
 namespace {
 
-// ev0 / ev1: profiling events recorded in front of / behind the launch (either may be null).
-template <bool SHARED, bool LISTED>
+template <bool SHARED, int WAVES>
 hipError_t launch_prefill_kernel(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
-                                 const uint32_t *keep_mask, const int32_t *key_cid, const int32_t *blk_info, void *out,
-                                 float *lse, float *partials, const Shape &sh, hipStream_t s, hipEvent_t ev0,
-                                 hipEvent_t ev1)
+                                 const uint32_t *keep_mask, const uint32_t *table, const uint32_t *rows,
+                                 const int32_t *blk_info, void *out, float *lse, float *partials, int n_split,
+                                 const Shape &sh, hipStream_t s)
 {
-    const size_t smem = 2 * sizeof(PfStage) + (LISTED ? PF_LIST_BYTES : 0);
-    static bool attr_set = false;   // one GPU per process in this build
-    if (!attr_set) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(prefill_attn_kernel<SHARED, LISTED>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-    }
-    constexpr int PF_BM = pf_bm(SHARED), PF_THREADS = 64 * pf_waves(SHARED);
-    const int n_split = prefill_splits(SHARED, sh);
-    const int units = ((sh.Lq + PF_BM - 1) / PF_BM) * sh.H * sh.B * n_split;
-    dim3 grid((units + 7) / 8 * 8);
-    if (ev0 || ev1)
-        hipExtLaunchKernelGGL((prefill_attn_kernel<SHARED, LISTED>), grid, dim3(PF_THREADS), (uint32_t)smem, s, ev0, ev1,
-                              0, (const _Float16 *)q, (const _Float16 *)Kf, (const _Float16 *)Vf, (const _Float16 *)Ku,
-                              (const _Float16 *)Vu, keep_mask, key_cid, blk_info, (_Float16 *)out, lse, partials, n_split,
-                              sh.B, sh.H, sh.L, sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale);
+    constexpr int BM = pf_bm(WAVES);
+    const int units = ((sh.Lq + BM - 1) / BM) * sh.H * sh.B * n_split;
+    const dim3 grid((units + 7) / 8 * 8), block(64 * WAVES);
+    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    if (profile_pair(&ev0, &ev1))
+        hipExtLaunchKernelGGL((prefill_attn_kernel<SHARED, WAVES>), grid, block, 0, s, ev0, ev1, 0, (const _Float16 *)q,
+                              (const _Float16 *)Kf, (const _Float16 *)Vf, (const _Float16 *)Ku, (const _Float16 *)Vu,
+                              keep_mask, table, rows, blk_info, (_Float16 *)out, lse, partials, n_split, sh.B, sh.H, sh.L,
+                              sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale);
     else
-        hipLaunchKernelGGL((prefill_attn_kernel<SHARED, LISTED>), grid, dim3(PF_THREADS), smem, s, (const _Float16 *)q,
+        hipLaunchKernelGGL((prefill_attn_kernel<SHARED, WAVES>), grid, block, 0, s, (const _Float16 *)q,
                            (const _Float16 *)Kf, (const _Float16 *)Vf, (const _Float16 *)Ku, (const _Float16 *)Vu,
-                           keep_mask, key_cid, blk_info, (_Float16 *)out, lse, partials, n_split, sh.B, sh.H, sh.L,
+                           keep_mask, table, rows, blk_info, (_Float16 *)out, lse, partials, n_split, sh.B, sh.H, sh.L,
                            sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale);
     return hipGetLastError();
 }
 
-hipError_t launch_prefill_merge(bool shared, const float *partials, void *out, float *lse, const Shape &sh, hipStream_t s)
+// The attention launch and, where the blocks are split, the merge launch.
+template <bool SHARED>
+hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
+                                  const uint32_t *keep_mask, const uint32_t *table, const uint32_t *rows,
+                                  const int32_t *blk_info, void *out, float *lse, float *partials, const Shape &sh,
+                                  hipStream_t s)
 {
-    const int n_split = prefill_splits(shared, sh);
-    if (n_split == 1) return hipSuccess;
-    const size_t rows = (size_t)sh.B * sh.H * sh.Lq;
-    hipLaunchKernelGGL(prefill_merge_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, s, partials, (_Float16 *)out,
-                       lse, n_split, rows);
+    const PfPlan plan = prefill_plan(SHARED, sh);
+    const hipError_t e = plan.waves == 8 ? launch_prefill_kernel<SHARED, 8>(q, Kf, Vf, Ku, Vu, keep_mask, table, rows, blk_info,
+                                                                            out, lse, partials, plan.n_split, sh, s)
+                                         : launch_prefill_kernel<SHARED, 4>(q, Kf, Vf, Ku, Vu, keep_mask, table, rows, blk_info,
+                                                                            out, lse, partials, plan.n_split, sh, s);
+    if (e != hipSuccess || plan.n_split == 1) return e;
+    const size_t n = (size_t)sh.B * sh.H * sh.Lq;
+    hipLaunchKernelGGL(prefill_merge_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, partials, (_Float16 *)out, lse,
+                       plan.n_split, n);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
-                               const uint32_t *keep_mask, const int32_t *offsets, int32_t *key_cid, int32_t *blk_info,
+                               const uint32_t *keep_mask, const int32_t *offsets, uint32_t *runs, int32_t *blk_info,
                                float *partials, void *out, float *lse, const Shape &sh, hipStream_t s)
 {
     const int nblk = (sh.L + PF_BN - 1) / PF_BN;
-    hipLaunchKernelGGL(key_cluster_kernel, dim3(64, sh.H), dim3(256), 0, s, offsets, key_cid, sh.C, sh.L);
-    hipLaunchKernelGGL(block_info_kernel, dim3((nblk + 255) / 256, sh.H), dim3(256), 0, s, key_cid, blk_info, sh.C,
+    uint32_t *rows = runs + prefill_blocks(sh.H, sh.L) * PF_BN;
+    hipLaunchKernelGGL(block_table_kernel, dim3((nblk + 3) / 4, sh.H), dim3(256), 0, s, offsets, runs, rows, blk_info, sh.C,
                        sh.L, nblk);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
-    profile_pair(&ev0, &ev1);                            // (the pair brackets both attention launches)
-    const bool may_list = nblk <= PF_LIST_CAP;           // else the count stays 0 and the plain kernel does the work
-    if (may_list) {
-        constexpr int BM = pf_bm(false);
-        const int units = ((sh.Lq + BM - 1) / BM) * sh.H * sh.B;
-        hipLaunchKernelGGL(prefill_need_kernel, dim3(units), dim3(256), 0, s, keep_mask, blk_info,
-                           reinterpret_cast<unsigned long long *>(blk_info + prefill_skip_count_at(sh.H, sh.L)), sh.B, sh.H,
-                           sh.L, sh.C, sh.Lq, BM);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    e = launch_prefill_kernel<false, false>(q, Kf, Vf, Ku, Vu, keep_mask, key_cid, blk_info, out, lse, partials, sh, s, ev0,
-                                            may_list ? nullptr : ev1);
-    if (e == hipSuccess && may_list)
-        e = launch_prefill_kernel<false, true>(q, Kf, Vf, Ku, Vu, keep_mask, key_cid, blk_info, out, lse, partials, sh, s,
-                                               nullptr, ev1);
-    if (e != hipSuccess) return e;
-    return launch_prefill_merge(false, partials, out, lse, sh, s);
+    return launch_prefill_kernels<false>(q, Kf, Vf, Ku, Vu, keep_mask, runs, rows, blk_info, out, lse, partials, sh, s);
 }
 
 hipError_t launch_expand_ranges(DecodePlan plan, int32_t *idx, int rows, int L, hipStream_t s)
@@ -705,12 +865,8 @@ hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void 
     hipLaunchKernelGGL(expand_ranges_kernel, dim3(sh.B * sh.H, EXPAND_SLICES), dim3(256), 0, s, plan, key_idx, sh.L);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
-    profile_pair(&ev0, &ev1);
-    e = launch_prefill_kernel<true, false>(q, Kf, Vf, Ku, Vu, nullptr, key_idx,
-                                           reinterpret_cast<const int32_t *>(plan.hdr), out, lse, partials, sh, s, ev0, ev1);
-    if (e != hipSuccess) return e;
-    return launch_prefill_merge(true, partials, out, lse, sh, s);
+    return launch_prefill_kernels<true>(q, Kf, Vf, Ku, Vu, nullptr, reinterpret_cast<const uint32_t *>(key_idx), nullptr,
+                                        reinterpret_cast<const int32_t *>(plan.hdr), out, lse, partials, sh, s);
 }
 
 }  // namespace sq

@@ -160,6 +160,69 @@ def test_prefill_masks_that_follow_position(sq, oracle, case):
     print(f"banded {case}: skippable pairs {skip}/{tot}, max-abs err {err:.2e}", flush=True)
 
 
+def random_masks(w, rng, share):
+    gk = rng.random((w.B, w.H, w.Lq, w.C)) < share
+    W = (w.C + 31) // 32
+    bits = np.zeros((w.B, w.H, w.Lq, W * 32), bool); bits[..., :w.C] = gk
+    words = (bits.reshape(w.B, w.H, w.Lq, W, 32) * (1 << np.arange(32, dtype=np.uint64))).sum(-1).astype(np.uint32)
+    return gk, torch.from_numpy(words.view(np.int32))
+
+
+def run_masked(sq, P):
+    sq.sq_sparse_attn_prefill(P.shape, P.q, P.K_fixed, P.V_fixed, P.offsets, P.keep_mask, P.K_user, P.V_user, P.out,
+                              P.lse, sq.workspace(P.shape, sq.SQ_CALL_ATTN_PREFILL, P.q.device))
+    torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("case", [
+    dict(B=1, H=2, L=1000, C=130, Lq=33, U=64),       # 5 to 12 runs of one cluster per 64-key block
+    dict(B=1, H=2, L=1500, C=400, Lq=70, U=0),        # more runs than a table row holds, cluster ids within the window
+    dict(B=2, H=1, L=1300, C=1500, Lq=257, U=5),      # more cluster ids than the window
+    dict(B=1, H=1, L=63, C=2, Lq=300, U=63),          # tensors shorter than a block
+    dict(B=1, H=3, L=64 * 40, C=3, Lq=31, U=1),       # whole blocks of one cluster
+])
+@pytest.mark.parametrize("gap", [0, 70])
+def test_prefill_block_tables(sq, oracle, case, gap):
+    """Explicit random masks over blocks of few and many clusters; `gap`: the first and last keys belong to no cluster."""
+    w = wl.make_workload("prefill_runs", seed=33, threads=2, keep_frac=0.3, causal_user=case["U"] > 1, **case)
+    gk, words = random_masks(w, np.random.default_rng(3), 0.4)
+    off = np.clip(w.offsets, gap, max(gap, w.L - gap)).astype(np.int32)
+    sizes = np.diff(off, axis=1).astype(np.int32)
+    P = sq.upload(w)
+    P.keep_mask.copy_(words)
+    P.offsets.copy_(torch.from_numpy(off))
+    run_masked(sq, P)
+    R = (w.B, w.H, w.Lq)
+    cap = int(gk.sum(-1).max()) + 1
+    ranges = np.zeros((*R, cap, 2), np.int32); n_r = np.zeros(R, np.int32)
+    for b, h, t in np.ndindex(*R):
+        ranges[b, h, t], n_r[b, h, t] = ranges_from_keep(gk[b, h, t], off[h], sizes[h], cap)
+    out, lse = oracle.sparse_attn(w.q, w.K_fixed, w.V_fixed, ranges, n_r, w.K_user, w.V_user, w.sm_scale,
+                                  causal_user=w.causal_user)
+    assert np.abs(P.out.cpu().numpy().astype(np.float64) - out).max() <= ATTN_ATOL
+    np.testing.assert_allclose(P.lse.cpu().numpy(), lse, atol=2e-4, rtol=1e-5)
+
+
+def test_prefill_hidden_keys_may_be_infinite(sq):
+    """A key a query does not keep has no influence on it, whatever its components are; a query that keeps it sees it."""
+    w = wl.make_workload("prefill_inf", seed=34, threads=1, B=1, H=2, L=900, C=30, Lq=200, U=70, keep_frac=0.3,
+                         causal_user=True)
+    gk, words = random_masks(w, np.random.default_rng(4), 0.4)
+    P = sq.upload(w)
+    P.keep_mask.copy_(words)
+    run_masked(sq, P)
+    out, lse = P.out.clone(), P.lse.clone()
+    c = 11                                                 # one cluster's keys become inf, another's NaN
+    for h in range(w.H):
+        P.K_fixed[h, w.offsets[h, c]:w.offsets[h, c + 1]] = float("inf")
+        P.K_fixed[h, w.offsets[h, c + 9]:w.offsets[h, c + 10]] = float("nan")
+    run_masked(sq, P)
+    hidden = torch.from_numpy(~(gk[..., c] | gk[..., c + 9])).to(out.device)
+    assert hidden.any() and torch.equal(P.out[hidden], out[hidden]) and torch.equal(P.lse[hidden], lse[hidden])
+    seen = torch.from_numpy(gk[..., c + 9]).to(out.device)
+    assert torch.isnan(P.out[seen]).all()
+
+
 def test_cfg4_sparse_prefill_32k(sq, oracle):
     print("cfg4: generating", flush=True)
     w = wl.calibrate(wl.make_config("cfg4_prefill_32k", threads=16), oracle.scores)
