@@ -399,6 +399,11 @@ struct PrefillAttnWs {
     uint32_t *runs;
     int32_t *blk_info;
     float *partials;
+    sq::BlockTable table(const sq_shape_t *sh, const int32_t *offsets) const
+    {
+        return sq::BlockTable{offsets, runs, runs + sq::prefill_blocks(sh->H, sh->L) * sq::PF_BN, blk_info,
+                              sh->C, sh->L, (sh->L + sq::PF_BN - 1) / sq::PF_BN};
+    }
 };
 
 PrefillAttnWs carve_prefill_attn(Carver &cv, const sq_shape_t *sh)
@@ -413,7 +418,7 @@ PrefillAttnWs carve_prefill_attn(Carver &cv, const sq_shape_t *sh)
 // Workspace of the whole prefill steps.
 struct PrefillStepWs {
     uint32_t *mask;
-    int32_t *n_ranges, *n_keys;
+    float *stats;
     PrefillAttnWs att;
 };
 
@@ -422,14 +427,13 @@ PrefillStepWs carve_prefill_step(Carver &cv, const sq_shape_t *sh)
     const size_t rows = (size_t)sh->B * sh->H * sh->Lq;
     PrefillStepWs w{};
     w.mask = cv.take<uint32_t>(rows * ((sh->C + 31) / 32));
-    w.n_ranges = cv.take<int32_t>(rows);
-    w.n_keys = cv.take<int32_t>(rows);
+    w.stats = cv.take<float>(sq::lookup_stat_floats(sh->B * sh->H, sh->Lq, sh->C));
     w.att = carve_prefill_attn(cv, sh);
     return w;
 }
 
 struct PrefillMeanStepWs {
-    float *part_sum;
+    float *stats, *part_sum;
     int32_t *n_ranges, *n_keys;
     PrefillSharedWs att;
 };
@@ -438,7 +442,8 @@ PrefillMeanStepWs carve_prefill_mean_step(Carver &cv, const sq_shape_t *sh)
 {
     const size_t rows = (size_t)sh->B * sh->H;
     PrefillMeanStepWs w{};
-    w.part_sum = cv.take<float>(rows * sq::lookup_parts_for(sh->Lq) * sh->C);
+    w.stats = cv.take<float>(sq::lookup_stat_floats((int)rows, sh->Lq, sh->C));
+    w.part_sum = cv.take<float>(sq::lookup_part_floats((int)rows, sh->Lq, sh->C));
     w.n_ranges = cv.take<int32_t>(rows);
     w.n_keys = cv.take<int32_t>(rows);
     w.att = carve_prefill_shared(cv, sh);
@@ -446,11 +451,11 @@ PrefillMeanStepWs carve_prefill_mean_step(Carver &cv, const sq_shape_t *sh)
 }
 
 // Workspace of the hierarchical prefill step with per-query selection: the one-level step's, plus the level-1 masks
-// and counts per token and the parent of every fine cluster.
+// per token and the parent of every fine cluster.
 struct HierPrefillWs {
     PrefillStepWs step;
     uint32_t *mask1;
-    int32_t *nr1, *nk1, *parent;
+    int32_t *parent;
 };
 
 HierPrefillWs carve_hier_prefill(Carver &cv, const sq_shape_t *sh)
@@ -459,8 +464,6 @@ HierPrefillWs carve_hier_prefill(Carver &cv, const sq_shape_t *sh)
     HierPrefillWs w{};
     w.step = carve_prefill_step(cv, sh);
     w.mask1 = cv.take<uint32_t>(rows * 32);                 // at most 1024 coarse clusters
-    w.nr1 = cv.take<int32_t>(rows);
-    w.nk1 = cv.take<int32_t>(rows);
     w.parent = cv.take<int32_t>((size_t)sh->H * sh->C);
     return w;
 }
@@ -862,8 +865,10 @@ int sq_sparse_attn_prefill(const sq_shape_t *sh, const void *q, const void *K_fi
     if (int rc = check_device(__func__)) return rc;
     Carver cv(ws);
     PrefillAttnWs w = carve_prefill_attn(cv, sh);
-    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, keep_mask, offsets, w.runs, w.blk_info,
-                                   w.partials, out, lse, to_shape(sh), static_cast<hipStream_t>(stream)));
+    const sq::BlockTable bt = w.table(sh, offsets);
+    SQ_HIP(sq::launch_block_table(bt, sh->H, static_cast<hipStream_t>(stream)));
+    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, keep_mask, bt, w.partials, out, lse, to_shape(sh),
+                                   static_cast<hipStream_t>(stream)));
     g_err[0] = 0;
     return SQ_OK;
 }
@@ -960,11 +965,10 @@ int sq_prefill_step(const sq_shape_t *sh, const void *q, const void *centroids, 
     Carver cv(ws);
     PrefillStepWs w = carve_prefill_step(cv, sh);
     uint32_t *mask = keep_mask ? keep_mask : w.mask;
-    SQ_HIP(sq::launch_prefill_lookup(q, centroids, sizes, thresh, mask, w.n_ranges, n_keys ? n_keys : w.n_keys, nullptr,
-                                     false, sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s));
-    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask, offsets, w.att.runs, w.att.blk_info,
-                                   w.att.partials, out, lse,
-                                   to_shape(sh), s));
+    const sq::BlockTable bt = w.att.table(sh, offsets);
+    SQ_HIP(sq::launch_prefill_lookup(q, centroids, sizes, thresh, w.stats, mask, n_keys, nullptr, false, sh->B, sh->H, sh->Lq,
+                                     sh->C, sh->sm_scale, s, nullptr, nullptr, nullptr, nullptr, 0, &bt));
+    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask, bt, w.att.partials, out, lse, to_shape(sh), s));
     g_err[0] = 0;
     return SQ_OK;
 }
@@ -982,10 +986,10 @@ int sq_prefill_mean_step(const sq_shape_t *sh, const void *q, const void *centro
     Carver cv(ws);
     PrefillMeanStepWs w = carve_prefill_mean_step(cv, sh);
     const int rows = sh->B * sh->H;
-    SQ_HIP(sq::launch_prefill_lookup(q, centroids, sizes, thresh, nullptr, nullptr, nullptr, w.part_sum, true, sh->B,
+    SQ_HIP(sq::launch_prefill_lookup(q, centroids, sizes, thresh, w.stats, nullptr, nullptr, w.part_sum, true, sh->B,
                                      sh->H, sh->Lq, sh->C, sh->sm_scale, s));
     sq::SelectOpts opt{};
-    opt.mean_parts = sq::lookup_parts_for(sh->Lq);
+    opt.mean_parts = sq::lookup_parts(rows, sh->Lq, sh->C);
     opt.mean_div = (float)sh->Lq;
     // the selection writes the kept ranges' records straight into the attention's plan
     SQ_HIP(sq::launch_select(w.part_sum, nullptr, nullptr, true, thresh, sizes, offsets, keep_mask, nullptr, w.n_ranges,
@@ -1252,15 +1256,14 @@ int sq_hier_prefill_step(const sq_shape_t *sh, int32_t C1, const void *q, const 
     uint32_t *mask2 = keep_mask2 ? keep_mask2 : w.step.mask;
     // Level 1 (Eq. 2) per token over the coarse centroids; then every fine cluster's parent; then level 2 (Eq. 3) per
     // token over the children of the coarse clusters that token kept.
-    SQ_HIP(sq::launch_prefill_lookup(q, centroids1, sizes1, thresh1, w.mask1, w.nr1, w.nk1, nullptr, false, sh->B, sh->H,
-                                     sh->Lq, C1, sh->sm_scale, s));
+    const sq::BlockTable bt = w.step.att.table(sh, offsets2);
+    SQ_HIP(sq::launch_prefill_lookup(q, centroids1, sizes1, thresh1, w.step.stats, w.mask1, nullptr, nullptr, false, sh->B,
+                                     sh->H, sh->Lq, C1, sh->sm_scale, s));
     SQ_HIP(sq::launch_child_parent(child_offsets, w.parent, sh->H, C1, sh->C, s));
-    SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, mask2, w.step.n_ranges,
-                                     n_keys ? n_keys : w.step.n_keys, nullptr, false, sh->B, sh->H, sh->Lq, sh->C,
-                                     sh->sm_scale, s, nullptr, nullptr, w.parent, w.mask1, C1));
-    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask2, offsets2, w.step.att.runs, w.step.att.blk_info,
-                                   w.step.att.partials,
-                                   out, lse, to_shape(sh), s));
+    SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, w.step.stats, mask2, n_keys, nullptr, false, sh->B, sh->H,
+                                     sh->Lq, sh->C, sh->sm_scale, s, nullptr, nullptr, w.parent, w.mask1, C1, &bt));
+    SQ_HIP(sq::launch_prefill_attn(q, K_fixed, V_fixed, K_user, V_user, mask2, bt, w.step.att.partials, out, lse,
+                                   to_shape(sh), s));
     g_err[0] = 0;
     return SQ_OK;
 }
@@ -1300,19 +1303,20 @@ int sq_hier_prefill_mean_step(const sq_shape_t *sh, int32_t C1, const void *q, c
     HierPrefillMeanWs w = carve_hier_prefill_mean(cv, sh);
     const int rows = sh->B * sh->H;
     sq::SelectOpts opt{};
-    opt.mean_parts = sq::lookup_parts_for(sh->Lq);
+    opt.mean_parts = sq::lookup_parts(rows, sh->Lq, sh->C);
     opt.mean_div = (float)sh->Lq;
     // Level 1 (Eq. 2 averaged over the tokens): the kept coarse clusters' child ranges become records ...
-    SQ_HIP(sq::launch_prefill_lookup(q, centroids1, sizes1, thresh1, nullptr, nullptr, nullptr, w.step.part_sum, true,
+    SQ_HIP(sq::launch_prefill_lookup(q, centroids1, sizes1, thresh1, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
                                      sh->B, sh->H, sh->Lq, C1, sh->sm_scale, s));
     sq::SelectOpts opt1 = opt;
     opt1.len_from_offsets = 1;
+    opt1.mean_parts = sq::lookup_parts(rows, sh->Lq, C1);
     SQ_HIP(sq::launch_select(w.step.part_sum, nullptr, nullptr, true, thresh1, sizes1, child_offsets, nullptr, nullptr,
                              w.nr1, w.nk1, w.cand, false, 0, opt1, rows, sh->H, 1, C1, s));
     // ... which expand to the list of candidate fine clusters of each (sequence, head).
     SQ_HIP(sq::launch_expand_ranges(w.cand, w.cand_id, rows, sh->C, s));
     // Level 2 (Eq. 3 per token over the candidates, averaged over the tokens): scores and selection in candidate order.
-    SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, nullptr, nullptr, nullptr, w.step.part_sum, true,
+    SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
                                      sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s, w.cand_id, w.cand.hdr));
     sq::SelectOpts opt2 = opt;
     opt2.cand_id = w.cand_id;

@@ -103,6 +103,13 @@ __device__ __forceinline__ float cross32_sum(float v)
     return a + b;
 }
 
+__device__ __forceinline__ uint32_t cross32_or(uint32_t v)
+{
+    float a, b;
+    swap32(__builtin_bit_cast(float, v), a, b);
+    return __builtin_bit_cast(uint32_t, a) | __builtin_bit_cast(uint32_t, b);
+}
+
 // Sum over the 64 lanes of a wave as an xor butterfly (partners 1, 2, 4, 8, 16, 32 lanes away, in that order);
 // every lane gets the same bits.  Entirely in the vector ALU: the first two steps are quad permutes; after them
 // the four lanes of a quad agree, so mirroring a half row (lane i <-> 7 - i) pairs the same values as xor 4, and

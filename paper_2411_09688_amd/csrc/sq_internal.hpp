@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "sq_block_table.hpp"
 #include "sq_common.hpp"
 
 namespace sq {
@@ -60,16 +61,22 @@ constexpr int MEAN_ROWS = 64;
 inline int mean_parts_for(int Lq) { return (Lq + MEAN_ROWS - 1) / MEAN_ROWS; }
 hipError_t launch_mean_score(const float *logits, const float *row_max, const float *denom, float *part_sum, int BH,
                              int Lq, int C, hipStream_t s);
-// Fused prefill lookup (scores, statistics and the per-token decision in one kernel, nothing materialised): one
-// wave handles LOOKUP_ROWS query tokens.  mean == false writes keep_mask [B*H*Lq, ceil(C/32)] and the per-token
-// counts; mean == true writes part_sum [B*H, lookup_parts_for(Lq), C] for the selection on averaged scores.
-constexpr int LOOKUP_ROWS = 16;
-__host__ __device__ inline int lookup_parts_for(int Lq) { return (Lq + LOOKUP_ROWS - 1) / LOOKUP_ROWS; }
+// Prefill lookup (scores, normalisers and the per-token decision, nothing of size [queries x clusters] materialised).
+// stats: lookup_stat_floats() floats of workspace.  mean == false writes keep_mask [B*H*Lq, ceil(C/32)] and, if given, the
+// per-token key counts n_keys; mean == true writes part_sum [B*H, lookup_parts(), C] for the selection on averaged scores
+// (lookup_part_floats() floats).
+constexpr int LK_MAX_SLICES = 32;
+int lookup_slices(int BH, int Lq, int C);
+int lookup_parts(int BH, int Lq, int C);
+size_t lookup_part_floats(int BH, int Lq, int C);
+inline size_t lookup_stat_floats(int BH, int Lq, int C) { return (size_t)BH * Lq * lookup_slices(BH, Lq, C) * 2; }
 hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int32_t *sizes, const float *thresh,
-                                 uint32_t *keep_mask, int32_t *n_ranges, int32_t *n_keys, float *part_sum, bool mean,
+                                 float *stats, uint32_t *keep_mask, int32_t *n_keys, float *part_sum, bool mean,
                                  int B, int H, int Lq, int C, float sm_scale, hipStream_t s,
                                  const int32_t *cand_id = nullptr, const int2 *cand_hdr = nullptr,
-                                 const int32_t *parent = nullptr, const uint32_t *mask1 = nullptr, int C1 = 0);
+                                 const int32_t *parent = nullptr, const uint32_t *mask1 = nullptr, int C1 = 0,
+                                 const BlockTable *table = nullptr);
+// (table given, per-query mode: the first launch also makes the attention's block table.)
 // (parent [H, C] / mask1 [B*H*Lq, ceil(C1/32)] given, per-query mode: a cluster counts for a token only if the token's
 // level-1 mask holds its parent: level 2 of a hierarchical lookup with per-token candidates; C1 <= 1024.)
 hipError_t launch_child_parent(const int32_t *child_offsets, int32_t *parent, int H, int C1, int C2, hipStream_t s);
@@ -164,13 +171,14 @@ hipError_t launch_decode_attn_shared(const void *q, const void *Kf, const void *
                                      DecodePlan plan, float *partials, void *out, float *lse, const Shape &sh,
                                      hipStream_t s);
 
-// Prefill attention with per-query keep masks; runs [prefill_table_words(H, L)] and blk_info [prefill_blocks(H, L)] are
-// workspace (the block table: the runs of keys of one cluster in every 64-key block, see block_table_kernel).
-inline size_t prefill_blocks(int H, int L) { return (size_t)H * (((size_t)L + 63) / 64); }
-inline size_t prefill_table_words(int H, int L) { return prefill_blocks(H, L) * 128; }
+// Prefill attention with per-query keep masks.  The block table is workspace (prefill_table_words(H, L) words for runs and
+// rows, prefill_blocks(H, L) for info), made by launch_block_table or by the first launch of the lookup.
+inline size_t prefill_blocks(int H, int L) { return (size_t)H * (((size_t)L + PF_BN - 1) / PF_BN); }
+inline size_t prefill_table_words(int H, int L) { return prefill_blocks(H, L) * (PF_BN + PF_ROW_WORDS); }
+hipError_t launch_block_table(const BlockTable &bt, int H, hipStream_t s);
 hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
-                               const uint32_t *keep_mask, const int32_t *offsets, uint32_t *runs, int32_t *blk_info,
-                               float *partials, void *out, float *lse, const Shape &sh, hipStream_t s);
+                               const uint32_t *keep_mask, const BlockTable &bt, float *partials, void *out, float *lse,
+                               const Shape &sh, hipStream_t s);
 
 // Prefill attention with ONE kept set per (sequence, head): plan.rec / plan.hdr hold the kept ranges' records
 // (from launch_ranges_to_rec); key_idx [B*H, L] is workspace for the list of kept key rows.

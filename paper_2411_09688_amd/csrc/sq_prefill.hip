@@ -35,12 +35,12 @@
 #include <type_traits>
 #include <utility>
 
+#include "sq_block_table.hpp"
 #include "sq_common.hpp"
 #include "sq_internal.hpp"
 
 namespace sq {
 
-constexpr int PF_BN = 64;                 // keys per block
 // K and V tiles in LDS: unpadded rows of 256 B, filled straight from global memory by the load-to-LDS instruction
 // (global_load_lds_dwordx4: the 64 lanes of a wave write 64 x 16 contiguous bytes = four whole rows), and swizzled
 // instead of padded so that the operand reads stay free of bank conflicts: the 16-byte chunk c of row r sits at slot
@@ -51,81 +51,10 @@ constexpr int PF_BN = 64;                 // keys per block
 __device__ __forceinline__ int pf_k_swz(int row) { return row & 15; }
 __device__ __forceinline__ int pf_v_swz(int row) { return (row & 3) << 2; }
 
-// Block table of the masked form: per (head, 64-key block) the runs of keys that share a cluster (clusters are contiguous
-// key ranges, so a block is a few runs: three at 32 keys per cluster).
-//   runs[h, blk, i]   cluster | first key of the run in the block << 16 | (keys - 1) << 22, ascending
-//   rows[h, blk]      the same for up to PF_ROW_RUNS runs in the form the attention kernel uses, groups of four runs, PF_ROW_GROUP
-//                     words each: [0..3] cluster relative to the block's first (31, a window bit that is never set, for none),
-//                     [4..7] / [8..11] the run's keys for lanes 0..31: bit 8 a + i = key 32 t + 8 a + i, t = 0 / 1,
-//                     [12..15] / [16..19] for lanes 32..63: key 32 t + 8 a + 4 + i (i < 4: see the accumulator layout there)
-//   blk_info[h, blk]  first cluster | min(span of cluster ids, 30) << 16 | n runs << 21 | wide << 31; wide: the span does
-//                     not fit the 31-bit window of mask bits (a block that crosses many empty clusters)
-// Keys that no cluster covers (before offsets[0] or from offsets[C] on) belong to no run.  One wave per block: a 64-way
-// search for the first key's cluster, then the keys are placed among the next 64 cluster starts.
-constexpr int PF_ROW_RUNS = 12, PF_ROW_GROUP = 20, PF_ROW_WORDS = 64;
-__global__ __launch_bounds__(256) void block_table_kernel(const int32_t *__restrict__ offsets, uint32_t *__restrict__ runs,
-                                                          uint32_t *__restrict__ rows, int32_t *__restrict__ blk_info, int C,
-                                                          int L, int nblk)
+// The block table of a call that has no lookup launch to make it in (sq_sparse_attn_prefill): see sq_block_table.hpp.
+__global__ __launch_bounds__(256) void block_table_kernel(BlockTable bt)
 {
-    const int h = blockIdx.y, lane = threadIdx.x & 63, blk = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (blk >= nblk) return;
-    const int32_t *off = offsets + (size_t)h * (C + 1);
-    const int j0 = blk * PF_BN, j = j0 + lane;
-    int lo = -1, hi = C + 1;                             // the last c with off[c] <= j0 (-1: none) lies in [lo, hi)
-    while (hi - lo > 1) {
-        const int step = (hi - lo + 63) >> 6, at = lo + (lane + 1) * step;
-        const bool le = at < hi && off[min(at, C)] <= j0;
-        lo += __popcll(__ballot(le)) * step;
-        hi = min(hi, lo + step);
-    }
-    const int nx = lo + 1 + lane;
-    const int start = nx <= C ? off[nx] : 0x7fffffff;    // starts of the 64 clusters after it
-    int pos = 0;                                         // how many of them are at or before this lane's key
-#pragma unroll
-    for (int step = 32; step > 0; step >>= 1)
-        if (__shfl(start, pos + step - 1) <= j) pos += step;
-    if (__shfl(start, pos) <= j) ++pos;
-    int c = lo + pos;
-    if (__ballot(pos == 64) != 0ull) {                   // more than 64 cluster starts in the block: search for each key
-        int a = lo, b = C + 1;
-        while (b - a > 1) {
-            const int mid = (a + b) >> 1;
-            if (off[mid] <= j) a = mid;
-            else b = mid;
-        }
-        c = a;
-    }
-    const bool covered = c >= 0 && c < C && j < L;
-    if (!covered) c = 0x7fffffff;
-    const int before = __shfl_up(c, 1);
-    const bool change = lane == 0 || c != before;
-    const unsigned long long cuts = __ballot(change), heads = __ballot(change && covered);
-    const int n = __popcll(heads);
-    const unsigned long long later = lane == 63 ? 0ull : cuts >> (lane + 1);
-    const int len = later ? __ffsll((long long)later) : 64 - lane;   // keys up to the next cut
-    uint32_t *dst = runs + ((size_t)h * nblk + blk) * PF_BN;
-    const unsigned long long in = __ballot(covered);
-    const int first = n ? __shfl(c, __ffsll((long long)heads) - 1) : 0;
-    const int last = n ? __shfl(c, 63 - __clzll((long long)in)) : 0;
-    uint32_t *row = rows + ((size_t)h * nblk + blk) * PF_ROW_WORDS;
-    auto put = [&](int slot, uint32_t rel, unsigned long long keys) {
-        uint32_t *g = row + (slot >> 2) * PF_ROW_GROUP + (slot & 3);
-        g[0] = rel;
-        g[4] = (uint32_t)keys & 0x0f0f0f0fu;
-        g[8] = (uint32_t)(keys >> 32) & 0x0f0f0f0fu;
-        g[12] = (uint32_t)(keys >> 4) & 0x0f0f0f0fu;
-        g[16] = (uint32_t)(keys >> 36) & 0x0f0f0f0fu;
-    };
-    if (change && covered) {
-        const int slot = __popcll(heads & ((1ull << lane) - 1ull));
-        dst[slot] = (uint32_t)c | (uint32_t)lane << 16 | (uint32_t)(len - 1) << 22;
-        if (slot < PF_ROW_RUNS) put(slot, (uint32_t)min(c - first, 31), (~0ull >> (64 - len)) << lane);
-    }
-    if (lane >= n && lane < PF_ROW_RUNS) put(lane, 31u, 0ull);
-    if (lane == 0) {
-        const int span = max(last - first, 0);
-        blk_info[(size_t)h * nblk + blk] = first | (min(span, 30) << 16) | (n << 21) | (span >= 31 ? (int)0x80000000 : 0);
-    }
+    block_table_part(bt, blockIdx.y, blockIdx.x);
 }
 
 // Kept ranges of every (sequence, head) row -> list of key rows: record (first key, count, keys before) writes
@@ -839,17 +768,17 @@ hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf,
 
 }  // namespace
 
-hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
-                               const uint32_t *keep_mask, const int32_t *offsets, uint32_t *runs, int32_t *blk_info,
-                               float *partials, void *out, float *lse, const Shape &sh, hipStream_t s)
+hipError_t launch_block_table(const BlockTable &bt, int H, hipStream_t s)
 {
-    const int nblk = (sh.L + PF_BN - 1) / PF_BN;
-    uint32_t *rows = runs + prefill_blocks(sh.H, sh.L) * PF_BN;
-    hipLaunchKernelGGL(block_table_kernel, dim3((nblk + 3) / 4, sh.H), dim3(256), 0, s, offsets, runs, rows, blk_info, sh.C,
-                       sh.L, nblk);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_prefill_kernels<false>(q, Kf, Vf, Ku, Vu, keep_mask, runs, rows, blk_info, out, lse, partials, sh, s);
+    hipLaunchKernelGGL(block_table_kernel, dim3(block_table_groups(bt.nblk), H), dim3(256), 0, s, bt);
+    return hipGetLastError();
+}
+
+hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
+                               const uint32_t *keep_mask, const BlockTable &bt, float *partials, void *out, float *lse,
+                               const Shape &sh, hipStream_t s)
+{
+    return launch_prefill_kernels<false>(q, Kf, Vf, Ku, Vu, keep_mask, bt.runs, bt.rows, bt.info, out, lse, partials, sh, s);
 }
 
 hipError_t launch_expand_ranges(DecodePlan plan, int32_t *idx, int rows, int L, hipStream_t s)

@@ -1,270 +1,459 @@
-// Centroid lookup for prefill (Section 4.1): grid over (sequence, head) x query blocks; a workgroup makes two
-// passes over the head's centroids.  Pass 1 accumulates, per query token, the maximum and the size-weighted
-// normaliser of Eq. 1; pass 2 recomputes the same logits and turns them into scores, so no [queries x clusters]
-// intermediate is ever written to memory (the centroids are read twice instead, from L2).
+// Centroid lookup for prefill (Section 4.1) without a [queries x clusters] intermediate in memory, in two launches that each
+// stream the centroids once; both are spread over (sequence, head) x blocks of query tokens x slices of the clusters, so that
+// a few tokens or heads still fill the chip.
 //
-// Scores run on the matrix cores as S^T = C Q^T (16x16x32 fp16 tiles: A = 16 centroids, B = a wave's 16 query
-// tokens, kept in registers), so a lane owns ONE query token (column) and four centroids per tile: maximum,
-// normaliser and threshold test are per-lane scalars, combined over the four lane groups once per pass.  The
-// four waves of a workgroup (64 tokens) share the centroid stream: groups of 64 centroids travel global memory ->
-// registers (issued two groups ahead) -> one of two LDS stages -> A operands, one barrier per group.
-//
-//   MEAN == false  per-query selection: keep cluster i for token t iff N_i > 0 and exp(x_i - m) > T * D; the
-//                  keep bits of two tiles are gathered into one mask word per token.
-//   MEAN == true   selection on averaged scores (Appendix D, "Prefill Stage"), first half: the scores
-//                  S_i(t) = exp(x_i - m) / D of a wave's 16 tokens are summed per cluster and written as one
-//                  part of part_sum [B*H, ceil(Lq/16), C]; the row-wise selection kernel adds the parts.
-//   CANDS == true  (with MEAN) second level of a hierarchical lookup (Section 3.3, Eq. 3): the clusters scored are the
+//   lookup_pass_kernel<DECIDE = false>  per (token, slice): a reference r and sum_i N_i exp(x_i - r) over the slice's clusters
+//                  (Eq. 1's normaliser), 8 bytes each.
+//   then, with the slices' pairs merged per token:
+//   lookup_pass_kernel<DECIDE = true>   per-query selection: keep cluster i for token t iff N_i > 0 and
+//                  exp(x_i - m) > T * D, compared as x_i >= (log(T D) + m): one comparison per (token, cluster), its bit
+//                  shifted into the token's mask word.
+//   mean_scores_kernel                  selection on averaged scores (Appendix D, "Prefill Stage"), first half: the scores
+//                  S_i(t) = exp(x_i - m) / D are summed over the tokens per cluster and written as part_sum
+//                  [B*H, lookup_parts_for(...), C]; the row-wise selection kernel adds the parts.
+//   CANDS == true  (averaged scores) second level of a hierarchical lookup (Section 3.3, Eq. 3): the clusters scored are the
 //                  n candidates cand_id[bh, 0..n) of the (sequence, head) -- the children of the coarse clusters kept
-//                  one level up -- so maximum and normaliser run over the candidates only; part_sum is written in
-//                  candidate order.
+//                  one level up -- so the normaliser runs over the candidates only; part_sum is written in candidate order.
 //   PARENTS == true (per-query selection) second level of a hierarchical lookup with per-token candidates: fine
 //                  cluster i counts for token t only if t kept its parent coarse cluster (bit parent[i] of the
-//                  token's level-1 mask); the others are treated like clusters without keys, so maximum,
-//                  normaliser and threshold test of Eq. 3 run over the token's candidates only.
+//                  token's level-1 mask); the others are treated like clusters without keys.
+//
+// Scores run on the matrix cores in 32x32x16 fp16 tiles.  In the passes a wave owns 32 tokens (S^T = C Q^T: a lane owns one
+// token column and 16 clusters per tile, so normaliser and threshold test are per-lane scalars) and the four waves of a
+// workgroup share the centroid stream, groups of 64 that travel straight from global memory into one of two LDS buffers.  The
+// averaged form is turned round (S = Q C^T: a lane owns one cluster column and sums over the tokens in its registers; the
+// waves share the staged queries).  Bound by vector instructions: 5 per (token, cluster) in the first pass, 3 in the second.
+// 32 heads x 1024 tokens x 1024 clusters: 20 + 20 us (one launch of two passes over 16x16x32 tiles, a workgroup per 64 tokens: 55 us;
+// averaged 20 + 21 against 61 us); 20 heads x 150 tokens x 613 clusters 6 + 7 against 26.
+#include <algorithm>
+#include <type_traits>
+
 #include "sq_common.hpp"
 #include "sq_internal.hpp"
 
 namespace sq {
 
-constexpr int LK_TU = 4;                     // centroid tiles per group
-constexpr int LK_G = LK_TU * 16;             // centroids per group
-constexpr int LK_STRIDE = D + 8;             // halves per centroid row in LDS (272 B: conflict-free 16-B reads)
-
-struct LkStage {
-    _Float16 Ct[LK_G * LK_STRIDE];
-    float Wt[LK_G];                          // cluster sizes as floats (exact: a head has fewer than 2^24 keys)
-    float bias[LK_G];                        // 0 for a cluster with keys, -inf for one without (or past the end): the
-                                             // score products start from it, so such a cluster's logit is -inf and
-                                             // it drops out of maximum, normaliser and scores without a test
-    int P[LK_G];                             // parent coarse cluster (PARENTS only)
-};
-
+constexpr int LK_G = 64;                     // centroids per staged group
+constexpr int LK_BT = 128;                   // tokens per workgroup (four waves x 32)
+// Rows of at most so many clusters are decided in one launch.  Whole steps, two launches / one: 75 clusters (16 x 28 tokens)
+// 28.0 / 24.4 us, 250 clusters (4 heads x 333 tokens) 45.4 / 46.1, 500 clusters (the same) 46.4 / 55.0.
+constexpr int LK_ONE_C = 256;
 constexpr int LK_MAX_W1 = 32;                // level-1 mask words per token held in LDS: at most 1024 coarse clusters
 
-template <bool MEAN, bool CANDS = false, bool PARENTS = false>
-__global__ __launch_bounds__(256) void prefill_lookup_kernel(
-    const _Float16 *__restrict__ q, const _Float16 *__restrict__ cent, const int32_t *__restrict__ sizes,
-    const float *__restrict__ thresh, uint32_t *__restrict__ keep_mask, int32_t *__restrict__ n_ranges,
-    int32_t *__restrict__ n_keys, float *__restrict__ part_sum, const int32_t *__restrict__ cand_id,
-    const int2 *__restrict__ cand_hdr, const uint32_t *__restrict__ mask1, int W1, int H, int Lq, int C_all,
-    float sm_scale)
+// Rows of 256 B staged unpadded by the load-to-LDS instruction (a wave writes four whole rows); 16-byte chunk c of row r sits
+// at slot c ^ (r % 16), applied on the global side, so the operand reads (32 rows at one chunk index) are free of conflicts.
+typedef __attribute__((address_space(3))) void *lk_lptr_t;
+__device__ __forceinline__ void lk_stage(const char *base, uint32_t off, uint32_t lds)   // base, lds: uniform
 {
-    __shared__ __align__(16) LkStage stage[2];
-    __shared__ uint32_t s_m1[PARENTS ? 64 * LK_MAX_W1 : 1];   // level-1 masks of the workgroup's 64 tokens
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int col = lane & 15, kg = lane >> 4;
-    const int bh = blockIdx.y, h = bh % H;
-    // C: the clusters this workgroup scores (all of the head's, or its candidates); C_all: row length of the arrays.
-    const int C = CANDS ? min(cand_hdr[bh].y, C_all) : C_all;
-    if (CANDS && C <= 0) return;                            // no candidate: nothing to score (workgroup-uniform)
-    const int32_t *cid = CANDS ? cand_id + (size_t)bh * C_all : nullptr;
-    const int32_t *par = PARENTS ? cand_id + (size_t)h * C_all : nullptr;     // (PARENTS: cand_id is parent [H, C])
-    if (PARENTS) {
-        for (int idx = threadIdx.x; idx < 64 * W1; idx += 256) {
-            const int t = idx / W1, w = idx - t * W1;
-            const int token = min((int)blockIdx.x * 64 + t, Lq - 1);
-            s_m1[t * W1 + w] = mask1[((size_t)bh * Lq + token) * W1 + w];
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "m0");
+}
+
+// A token's pairs (r, sum) of the slices first, first + STEP, ... (at most LK_MAX_SLICES / STEP of them): the loads are issued
+// together and merged later, so that their latency lies under the work in between.
+template <int STEP>
+struct SlicePairs {
+    float2 v[LK_MAX_SLICES / STEP];
+    __device__ __forceinline__ void load(const float2 *st, int first, int n_slice)
+    {
+#pragma unroll
+        for (int k = 0; k < LK_MAX_SLICES / STEP; ++k) {
+            v[k] = float2{SQ_NEG_INF, 0.0f};
+            if (k * STEP < n_slice) {                       // (uniform: one jump past the slices there are not)
+                const int s = first + k * STEP;
+                if (s < n_slice) v[k] = st[s];
+            }
         }
     }
-    const int q0 = (blockIdx.x * 4 + wave) * LOOKUP_ROWS;   // first token of this wave (may lie past the end)
-    const int nq = q0 + col;
-    const bool valid = nq < Lq;
-    const size_t row = (size_t)bh * Lq + min(nq, Lq - 1);
-    const int W = (C + 31) >> 5;
-    const int nt = (C + 15) >> 4, ng = (C + LK_G - 1) / LK_G;
+    __device__ __forceinline__ float largest() const
+    {
+        float m = SQ_NEG_INF;
+#pragma unroll
+        for (int k = 0; k < LK_MAX_SLICES / STEP; ++k) m = fmaxf(m, v[k].x);
+        return m;
+    }
+    __device__ __forceinline__ float sum(float m) const     // relative to m >= largest(); 0 if nothing was scored
+    {
+        float d = 0.0f;
+#pragma unroll
+        for (int k = 0; k < LK_MAX_SLICES / STEP; ++k)
+            if (v[k].y > 0.0f) d = fmaf(v[k].y, __builtin_amdgcn_exp2f(v[k].x - m), d);
+        return d;
+    }
+};
 
-    h8 bq[4];
+// Which passes a launch makes.  BOTH: one launch for rows of few clusters, where a second launch costs more than slices give.
+enum LkMode { LK_STATS, LK_DECIDE, LK_BOTH };
+
+template <LkMode MODE, bool CANDS, bool PARENTS, bool KEYS>
+__global__ __launch_bounds__(256) void lookup_pass_kernel(
+    const _Float16 *__restrict__ q, const _Float16 *__restrict__ cent, const int32_t *__restrict__ sizes,
+    const float *__restrict__ thresh, float2 *__restrict__ stats, uint32_t *__restrict__ keep_mask,
+    int32_t *__restrict__ n_keys, const int32_t *__restrict__ cand_id, const int2 *__restrict__ cand_hdr,
+    const uint32_t *__restrict__ mask1, int W1, int n_slice, int H, int Lq, int C_all, float sm_scale, BlockTable table)
+{
+    if (MODE != LK_DECIDE && !CANDS) {                      // extra workgroups: the attention's block table
+        const int extra = (int)blockIdx.x - (Lq + LK_BT - 1) / LK_BT * n_slice;
+        if (extra >= 0) {
+            if ((int)blockIdx.y < H) block_table_part(table, blockIdx.y, extra);
+            return;
+        }
+    }
+    __shared__ __align__(16) unsigned char stage[2 * LK_G * D * 2];
+    __shared__ __align__(16) float s_N[2][LK_G];            // cluster sizes as floats (exact: a head has fewer than 2^24 keys)
+    __shared__ __align__(16) float s_start[2][LK_G];        // where a cluster's score products start: 0, or for a cluster
+                                                            // without keys (or past the end) -inf -- it adds nothing -- or,
+                                                            // when deciding, NaN: it passes no comparison
+    __shared__ __align__(16) int s_par[2][PARENTS ? LK_G : 1];
+    __shared__ uint32_t s_m1[PARENTS ? LK_BT * LK_MAX_W1 : 1];   // level-1 masks of the workgroup's tokens
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, g = lane >> 5, l16 = lane & 15;
+    const int bh = blockIdx.y, h = bh % H, slice = blockIdx.x % n_slice;
+    const int t0 = (int)(blockIdx.x / n_slice) * LK_BT;
+    // C: the clusters scored (all of the head's, or the candidates); C_all: row length of the arrays.
+    const int C = CANDS ? min(cand_hdr[bh].y, C_all) : C_all;
+    const int ng = (C + LK_G - 1) / LK_G, per = (ng + n_slice - 1) / n_slice;
+    const int g0 = min(slice * per, ng), g1 = min(g0 + per, ng);
+    const int t = t0 + wave * 32 + col;                     // this lane's token (past the end: the last one, not stored)
+    const bool valid = t < Lq;
+    const size_t row = (size_t)bh * Lq + min(t, Lq - 1);
+    const int W = (C + 31) >> 5;
+    const float c2 = sm_scale * 1.44269504088896341f;       // base-2 exponents: one instruction per exponential
+    const int32_t *cid = CANDS ? cand_id + (size_t)bh * C_all : nullptr;
+    const int32_t *par = PARENTS ? cand_id + (size_t)h * C_all : nullptr;     // (PARENTS: cand_id is parent [H, C])
+    if (KEYS && MODE == LK_STATS && slice == 0 && g == 0 && valid) n_keys[row] = 0;   // (summed over the slices by the second pass)
+    if (MODE == LK_DECIDE && g0 >= g1) return;              // (workgroup-uniform)
+    if (PARENTS)
+        for (int idx = tid; idx < LK_BT * W1; idx += 256) {
+            const int r = idx / W1, w = idx - r * W1;
+            s_m1[r * W1 + w] = mask1[((size_t)bh * Lq + min(t0 + r, Lq - 1)) * W1 + w];
+        }
+    h8 bq[8];
     {
         const h8 *qp = reinterpret_cast<const h8 *>(q + row * D);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) bq[s] = qp[s * 4 + kg];
+        for (int s = 0; s < 8; ++s) bq[s] = qp[s * 2 + g];
     }
+    // The least raw score that is kept, from the row's reference m and normaliser relative to it.  (T D < 0: everything with
+    // keys; T D = 0: everything whose exponential does not vanish; strict otherwise: the least float above the logarithm.)
+    float x_min = 0.0f;
+    auto set_threshold = [&](float m, float Dsum) {
+        const float thr = thresh[h] * Dsum;
+        const float cut = thr < 0.0f ? SQ_NEG_INF : (m + (thr > 0.0f ? log2f(thr) : -126.0f)) / c2;
+        x_min = thr > 0.0f ? nextafterf(cut, __builtin_inff()) : cut;
+    };
+    if (MODE == LK_DECIDE) {
+        SlicePairs<2> sp;                                   // (the two lanes of a token take every other slice)
+        sp.load(stats + row * n_slice, g, n_slice);
+        const float m = cross32_max(sp.largest());
+        set_threshold(m, cross32_sum(m == SQ_NEG_INF ? 0.0f : sp.sum(m)));
+    }
+
     const char *ch = reinterpret_cast<const char *>(cent + (size_t)h * C_all * D);
     const int32_t *Nh = sizes + (size_t)h * C_all;
-
-    // This thread's share of a group: rows i*16 + tid/16 (i = 0..3), 16-byte chunk tid%16; size of cluster tid.
-    h8 pk[4];
-    int pn = 0, pp = 0;
-    auto fetch = [&](int g) {
+    const int trow = tid >> 4;
+    const uint32_t chunk = (uint32_t)((tid & 15) ^ (trow & 15)) * 16u;
+    const uint32_t lds_w = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lk_lptr_t)stage) + (uint32_t)wave * 1024u;
+    int id_n[4] = {}, id_s = 0;                             // CANDS: rows of the group after next, and this thread's cluster of it
+    auto fetch_ids = [&](int gr) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            int c_row = min(g * LK_G + i * 16 + (tid >> 4), C - 1);          // rows past the end repeat the last one
-            if (CANDS) c_row = min(max(cid[c_row], 0), C_all - 1);
-            pk[i] = *reinterpret_cast<const h8 *>(ch + (size_t)c_row * 256 + (tid & 15) * 16);
+            const int c = min(gr * LK_G + i * 16 + trow, C - 1);
+            id_n[i] = CANDS ? min(max(cid[c], 0), C_all - 1) : c;
         }
-        if (tid < LK_G) {                                                    // 0 past the last cluster
-            const int c = g * LK_G + tid;
-            pn = c < C ? Nh[CANDS ? min(max(cid[c], 0), C_all - 1) : c] : 0;
+        const int c = min(gr * LK_G + (tid & (LK_G - 1)), C - 1);
+        id_s = CANDS ? min(max(cid[c], 0), C_all - 1) : c;
+    };
+    int pn = 0, pp = 0;
+    auto fetch = [&](int gr, int buf) {                     // group gr -> buffer buf (its rows' ids are in id_n)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lk_stage(ch, (uint32_t)id_n[i] * 256u + chunk, lds_w + (uint32_t)(buf * (LK_G * 256) + i * 4096));
+        if (tid < LK_G) {                                   // 0 past the last cluster
+            const int c = gr * LK_G + tid;
+            pn = c < C ? Nh[id_s] : 0;
             if (PARENTS) pp = c < C ? min(max(par[c], 0), W1 * 32 - 1) : 0;
         }
     };
-    auto commit = [&](LkStage &st) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            *reinterpret_cast<h8 *>(st.Ct + (i * 16 + (tid >> 4)) * LK_STRIDE + (tid & 15) * 8) = pk[i];
+    auto commit = [&](int buf, bool decide) {
         if (tid < LK_G) {
-            st.Wt[tid] = (float)pn;
-            st.bias[tid] = pn > 0 ? 0.0f : SQ_NEG_INF;
-            if (PARENTS) st.P[tid] = pp;
+            s_N[buf][tid] = (float)pn;
+            s_start[buf][tid] = pn > 0 ? 0.0f : decide ? __builtin_nanf("") : SQ_NEG_INF;
+            if (PARENTS) s_par[buf][tid] = pp;
         }
-    };
-    const float c2 = sm_scale * 1.44269504088896341f;
-    // Logits of the staged group in units of log 2 (the exponentials below are base-2: one instruction each):
-    // x[u][v] = sm_scale * log2(e) * q . C_c, c = g*64 + u*16 + kg*4 + v, and the cluster sizes.
-    auto scores = [&](const LkStage &st, float (&x)[LK_TU][4], float (&nv)[LK_TU][4]) {
-#pragma unroll
-        for (int u = 0; u < LK_TU; ++u) {
-            f4 acc = *reinterpret_cast<const f4 *>(st.bias + u * 16 + kg * 4);
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const h8 a = *reinterpret_cast<const h8 *>(st.Ct + (u * 16 + col) * LK_STRIDE + s * 32 + kg * 8);
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bq[s], acc, 0, 0, 0);
-            }
-            const f4 n4 = *reinterpret_cast<const f4 *>(st.Wt + u * 16 + kg * 4);
-            nv[u][0] = n4.x;
-            nv[u][1] = n4.y;
-            nv[u][2] = n4.z;
-            nv[u][3] = n4.w;
-            if (PARENTS) {                                  // not a candidate of this lane's token: as if it had no keys
-                const int4 p4 = *reinterpret_cast<const int4 *>(st.P + u * 16 + kg * 4);
-                const uint32_t *mrow = s_m1 + (wave * 16 + col) * W1;
-                const int pv[4] = {p4.x, p4.y, p4.z, p4.w};
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    if (!((mrow[pv[v] >> 5] >> (pv[v] & 31)) & 1u)) {
-                        nv[u][v] = 0.0f;
-                        acc[v] = SQ_NEG_INF;
-                    }
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) x[u][v] = acc[v] * c2;   // (-inf stays -inf: sm_scale > 0)
-        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);                 // this wave's loads to LDS have landed
     };
 
-    float m = SQ_NEG_INF, Dsum = 0.0f, thr = 0.0f, inv_D = 0.0f, m_ref = 0.0f;
-    uint32_t word = 0u;
-    int cnt = 0;
-    float keys = 0.0f;                                       // (exact in fp32, like the sizes)
-    const int part = q0 / LOOKUP_ROWS, n_part = lookup_parts_for(Lq);
-
-    // One loop over both passes: iteration it handles group it % ng; the stream of groups never drains in between.
-    fetch(0);
-    commit(stage[0]);
-    if (2 * ng > 1) fetch(1 % ng);
-    __syncthreads();
-    for (int it = 0; it < 2 * ng; ++it) {
-        const int g = it % ng;
-        if (it + 1 < 2 * ng) {
-            commit(stage[(it + 1) & 1]);                    // group it+1 (in registers since the last iteration)
-            if (it + 2 < 2 * ng) fetch((it + 2) % ng);
+    float ref = SQ_NEG_INF, lim = SQ_NEG_INF, refn = 0.0f, Dsum = 0.0f, keys = 0.0f;
+    auto sweep = [&](auto pass2) {
+        constexpr bool DECIDE = decltype(pass2)::value;
+        if (g0 < g1) {
+            fetch_ids(g0);
+            fetch(g0, 0);
+            fetch_ids(g0 + 1);
+            commit(0, DECIDE);
         }
-        float x[LK_TU][4];
-        float nv[LK_TU][4];
-        scores(stage[it & 1], x, nv);
-        if (it < ng) {
-            // ---- pass 1: m = max over clusters with keys, D = sum N_i exp(x_i - m), per token ---------------------
-            // (a cluster without keys has x = -inf: it does not move the maximum and adds 0 * exp(-inf) = +0)
-            float mt = m;
-#pragma unroll
-            for (int u = 0; u < LK_TU; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) mt = fmaxf(mt, x[u][v]);
-            if (mt != SQ_NEG_INF) {
-                Dsum *= __builtin_amdgcn_exp2f(m - mt);      // m = -inf: Dsum is 0 and stays 0
-#pragma unroll
-                for (int u = 0; u < LK_TU; ++u)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) Dsum += nv[u][v] * __builtin_amdgcn_exp2f(x[u][v] - mt);
-                m = mt;
+        __syncthreads();
+        for (int gr = g0; gr < g1; ++gr) {
+            const int buf = (gr - g0) & 1;
+            if (gr + 1 < g1) {
+                fetch(gr + 1, buf ^ 1);
+                fetch_ids(gr + 2);
             }
-            if (it == ng - 1) {                              // the four lane groups hold the other clusters of the token
+            const _Float16 *tile = reinterpret_cast<const _Float16 *>(stage + buf * (LK_G * 256));
+            uint32_t words[2];
 #pragma unroll
-                for (int off = 16; off <= 32; off <<= 1) {
-                    const float mo = __shfl_xor(m, off), Do = __shfl_xor(Dsum, off);
-                    const float M = fmaxf(m, mo);
-                    const float wa = m == SQ_NEG_INF ? 0.0f : __builtin_amdgcn_exp2f(m - M);
-                    const float wb = mo == SQ_NEG_INF ? 0.0f : __builtin_amdgcn_exp2f(mo - M);
-                    Dsum = Dsum * wa + Do * wb;
-                    m = M;
+            for (int u = 0; u < 2; ++u) {
+                f16v acc;
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    const f4 v = *reinterpret_cast<const f4 *>(&s_start[buf][u * 32 + a * 8 + g * 4]);
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) acc[4 * a + k] = v[k];
                 }
-                thr = thresh[h] * Dsum;
-                inv_D = valid && Dsum > 0.0f ? 1.0f / Dsum : 0.0f;   // scores of pass 2: e * (1 / D), one division per token
-                m_ref = m == SQ_NEG_INF ? 0.0f : m;          // (no cluster with keys at all: exp(-inf - 0) = 0, not NaN)
-            }
-        } else {
-            // ---- pass 2: the same logits again, now as scores ---------------------------------------------------------
 #pragma unroll
-            for (int u = 0; u < LK_TU; ++u) {
-                const int t = g * LK_TU + u;
-                if (t >= nt) break;                          // workgroup-uniform
-                float e[4];
+                for (int s = 0; s < 8; ++s) {
+                    const h8 a = *reinterpret_cast<const h8 *>(tile + (u * 32 + col) * D + ((2 * s + g) ^ l16) * 8);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bq[s], acc, 0, 0, 0);
+                }
+                float nv[16];
+                if (!DECIDE || KEYS) {
 #pragma unroll
-                for (int v = 0; v < 4; ++v) e[v] = __builtin_amdgcn_exp2f(x[u][v] - m_ref);   // 0 for a cluster without keys
-                if (!MEAN) {
+                    for (int a = 0; a < 4; ++a) {
+                        const f4 v = *reinterpret_cast<const f4 *>(&s_N[buf][u * 32 + a * 8 + g * 4]);
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const bool keep = nv[u][v] > 0.0f && e[v] > thr;
-                        word |= (uint32_t)keep << ((t & 1) * 16 + kg * 4 + v);
-                        cnt += keep;
-                        keys += keep ? nv[u][v] : 0.0f;
+                        for (int k = 0; k < 4; ++k) nv[4 * a + k] = v[k];
                     }
-                    if ((t & 1) || t == nt - 1) {            // a mask word is complete
-                        word = cross16_or(word);
-                        if (kg == 0 && valid) keep_mask[row * W + (t >> 1)] = word;
-                        word = 0u;
+                }
+                if (PARENTS) {                                  // not a candidate of this lane's token: as if it had no keys
+                    const uint32_t *mrow = s_m1 + (wave * 32 + col) * W1;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        const int p = s_par[buf][u * 32 + (r >> 2) * 8 + g * 4 + (r & 3)];
+                        if (!((mrow[p >> 5] >> (p & 31)) & 1u)) {
+                            if (!DECIDE || KEYS) nv[r] = 0.0f;
+                            acc[r] = DECIDE ? __builtin_nanf("") : SQ_NEG_INF;
+                        }
                     }
+                }
+                if (!DECIDE) {
+                    float mx = SQ_NEG_INF;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[r]);
+                    mx *= c2;
+                    // (the reference moves when a score passes it by 2^8: the sum stays far inside fp32's range)
+                    if (__ballot(mx > lim) != 0ull && mx > ref) {
+                        Dsum *= __builtin_amdgcn_exp2f(ref - mx);   // ref = -inf: Dsum is 0 and stays 0
+                        ref = mx;
+                        lim = mx + 8.0f;
+                        refn = -mx;
+                    }
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) Dsum = fmaf(nv[r], __builtin_amdgcn_exp2f(fmaf(acc[r], c2, refn)), Dsum);
                 } else {
-                    float sums[4];
+                    uint32_t bits = 0u;
 #pragma unroll
-                    for (int v = 0; v < 4; ++v)             // over the wave's tokens
-                        sums[v] = row16_sum(e[v] * inv_D);
-                    if (col == 0 && part < n_part) {
-                        float *dst = part_sum + ((size_t)bh * n_part + part) * C_all + t * 16 + kg * 4;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v)
-                            if (t * 16 + kg * 4 + v < C) dst[v] = sums[v];
+                    for (int r = 15; r >= 0; --r) {
+                        uint32_t carry;
+                        const uint32_t keep = acc[r] >= x_min;
+                        bits = __builtin_addc(bits, bits, keep, &carry);
+                        if (KEYS) keys += keep ? nv[r] : 0.0f;
                     }
+                    // bit 4 a + i -> bit 8 a + 4 g + i of the word; the other half of the wave holds the other bits
+                    bits = (bits | (bits << 8)) & 0x00ff00ffu;
+                    bits = (bits | (bits << 4)) & 0x0f0f0f0fu;
+                    words[u] = cross32_or(bits << (4 * g));
                 }
             }
+            if (DECIDE && g == 0 && valid) {
+                keep_mask[row * W + 2 * gr] = words[0];
+                if (2 * gr + 1 < W) keep_mask[row * W + 2 * gr + 1] = words[1];
+            }
+            if (gr + 1 < g1) commit(buf ^ 1, DECIDE);
+            __syncthreads();
         }
-        __syncthreads();                                     // stage it & 1 may be overwritten; stage (it+1) & 1 is complete
+    };
+    if (MODE != LK_DECIDE) {
+        sweep(std::false_type{});                           // the two halves of the wave hold the other clusters of the token
+        const float mo = __shfl_xor(ref, 32), Do = __shfl_xor(Dsum, 32), M = fmaxf(ref, mo);
+        const float wa = ref == SQ_NEG_INF ? 0.0f : __builtin_amdgcn_exp2f(ref - M);
+        const float wb = mo == SQ_NEG_INF ? 0.0f : __builtin_amdgcn_exp2f(mo - M);
+        Dsum = Dsum * wa + Do * wb;
+        if (MODE == LK_BOTH) set_threshold(M, Dsum);
+        else if (g == 0 && valid) stats[row * n_slice + slice] = float2{M, Dsum};
     }
-    if (!MEAN) {
-        cnt = cross16_sum_i(cnt);
-        const int keys_i = cross16_sum_i((int)keys);
-        if (kg == 0 && valid) {
-            n_ranges[row] = cnt;
-            n_keys[row] = keys_i;
+    if (MODE != LK_STATS) {
+        sweep(std::true_type{});
+        const int k = KEYS ? (int)cross32_sum(keys) : 0;    // (exact in fp32, like the sizes)
+        if (KEYS && g == 0 && valid) {
+            if (MODE == LK_BOTH) n_keys[row] = k;
+            else if (k) atomicAdd(&n_keys[row], k);
         }
     }
 }
 
-hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int32_t *sizes, const float *thresh,
-                                 uint32_t *keep_mask, int32_t *n_ranges, int32_t *n_keys, float *part_sum, bool mean,
-                                 int B, int H, int Lq, int C, float sm_scale, hipStream_t s, const int32_t *cand_id,
-                                 const int2 *cand_hdr, const int32_t *parent, const uint32_t *mask1, int C1)
+constexpr int LK_MC = 128;                   // clusters per workgroup of the averaging kernel (four waves x 32)
+constexpr int LK_MT = 64;                    // tokens per staged tile
+
+template <bool CANDS>
+__global__ __launch_bounds__(256) void mean_scores_kernel(
+    const _Float16 *__restrict__ q, const _Float16 *__restrict__ cent, const int32_t *__restrict__ sizes,
+    const float2 *__restrict__ stats, float *__restrict__ part_sum, const int32_t *__restrict__ cand_id,
+    const int2 *__restrict__ cand_hdr, int n_slice, int H, int Lq, int C_all, float sm_scale)
 {
-    const dim3 grid((Lq + 4 * LOOKUP_ROWS - 1) / (4 * LOOKUP_ROWS), B * H);
-    const uint32_t *no_mask = nullptr;
-    if (parent) {
-        if (mean || cand_id || !mask1 || C1 <= 0 || (C1 + 31) / 32 > LK_MAX_W1) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((prefill_lookup_kernel<false, false, true>), grid, dim3(256), 0, s, (const _Float16 *)q,
-                           (const _Float16 *)centroids, sizes, thresh, keep_mask, n_ranges, n_keys, part_sum, parent,
-                           (const int2 *)nullptr, mask1, (C1 + 31) / 32, H, Lq, C, sm_scale);
-    } else if (cand_id) {
-        if (!mean || !cand_hdr) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((prefill_lookup_kernel<true, true>), grid, dim3(256), 0, s, (const _Float16 *)q,
-                           (const _Float16 *)centroids, sizes, thresh, keep_mask, n_ranges, n_keys, part_sum, cand_id,
-                           cand_hdr, no_mask, 0, H, Lq, C, sm_scale);
-    } else if (mean)
-        hipLaunchKernelGGL((prefill_lookup_kernel<true, false>), grid, dim3(256), 0, s, (const _Float16 *)q,
-                           (const _Float16 *)centroids, sizes, thresh, keep_mask, n_ranges, n_keys, part_sum,
-                           (const int32_t *)nullptr, (const int2 *)nullptr, no_mask, 0, H, Lq, C, sm_scale);
-    else
-        hipLaunchKernelGGL((prefill_lookup_kernel<false, false>), grid, dim3(256), 0, s, (const _Float16 *)q,
-                           (const _Float16 *)centroids, sizes, thresh, keep_mask, n_ranges, n_keys, part_sum,
-                           (const int32_t *)nullptr, (const int2 *)nullptr, no_mask, 0, H, Lq, C, sm_scale);
+    __shared__ __align__(16) unsigned char stage[2 * LK_MT * D * 2];
+    __shared__ __align__(16) float s_m[2][LK_MT], s_inv[2][LK_MT];   // per token: minus the reference, 1 / D
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 31, g = lane >> 5, l16 = lane & 15;
+    const int bh = blockIdx.z, h = bh % H, part = blockIdx.y, n_part = gridDim.y;
+    const int C = CANDS ? min(cand_hdr[bh].y, C_all) : C_all;
+    if ((int)blockIdx.x * LK_MC >= C) return;               // (workgroup-uniform)
+    const float c2 = sm_scale * 1.44269504088896341f;
+    const int c = (int)blockIdx.x * LK_MC + wave * 32 + col, cc = min(c, C - 1);
+    const int id = CANDS ? min(max(cand_id[(size_t)bh * C_all + cc], 0), C_all - 1) : cc;
+    h8 bc[8];                                               // this lane's centroid, B operand of S = Q C^T
+    {
+        const h8 *cp = reinterpret_cast<const h8 *>(cent + ((size_t)h * C_all + id) * D);
+#pragma unroll
+        for (int s = 0; s < 8; ++s) bc[s] = cp[s * 2 + g];
+    }
+    const bool keys = sizes[(size_t)h * C_all + id] > 0;
+    const int nt = (Lq + LK_MT - 1) / LK_MT;
+    const char *qh = reinterpret_cast<const char *>(q + (size_t)bh * Lq * D);
+    const int trow = tid >> 4;
+    const uint32_t chunk = (uint32_t)((tid & 15) ^ (trow & 15)) * 16u;
+    const uint32_t lds_w = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lk_lptr_t)stage) + (uint32_t)wave * 1024u;
+    SlicePairs<4> sp;
+    int st_t = 0;
+    auto fetch = [&](int tile, int buf) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            lk_stage(qh + (size_t)tile * (LK_MT * 256), (uint32_t)min(i * 16 + trow, Lq - 1 - tile * LK_MT) * 256u + chunk,
+                     lds_w + (uint32_t)(buf * (LK_MT * 256) + i * 4096));
+        st_t = tile * LK_MT + (tid >> 2);
+        sp.load(stats + ((size_t)bh * Lq + min(st_t, Lq - 1)) * n_slice, tid & 3, n_slice);
+    };
+    auto commit = [&](int buf) {
+        float m = sp.largest();                             // the four lanes of a token take every fourth slice
+        m = fmaxf(m, dpp_f<0xb1>(m));
+        m = fmaxf(m, dpp_f<0x4e>(m));
+        float Dsum = m == SQ_NEG_INF ? 0.0f : sp.sum(m);
+        Dsum += dpp_f<0xb1>(Dsum);
+        Dsum += dpp_f<0x4e>(Dsum);
+        if ((tid & 3) == 0) {
+            s_m[buf][tid >> 2] = m == SQ_NEG_INF ? 0.0f : -m;
+            s_inv[buf][tid >> 2] = st_t < Lq && Dsum > 0.0f ? 1.0f / Dsum : 0.0f;
+        }
+        __builtin_amdgcn_s_waitcnt(0x0f70);                 // this wave's loads to LDS have landed
+    };
+    float sum = 0.0f;
+    if (part < nt) {
+        fetch(part, 0);
+        commit(0);
+    }
+    __syncthreads();
+    int buf = 0;
+    for (int tile = part; tile < nt; tile += n_part, buf ^= 1) {
+        if (tile + n_part < nt) fetch(tile + n_part, buf ^ 1);
+        const _Float16 *qt = reinterpret_cast<const _Float16 *>(stage + buf * (LK_MT * 256));
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            f16v acc;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                const h8 a = *reinterpret_cast<const h8 *>(qt + (u * 32 + col) * D + ((2 * s + g) ^ l16) * 8);
+                acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bc[s], acc, 0, 0, 0);
+            }
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                const f4 mv = *reinterpret_cast<const f4 *>(&s_m[buf][u * 32 + a * 8 + g * 4]);
+                const f4 iv = *reinterpret_cast<const f4 *>(&s_inv[buf][u * 32 + a * 8 + g * 4]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) sum = fmaf(__builtin_amdgcn_exp2f(fmaf(acc[4 * a + k], c2, mv[k])), iv[k], sum);
+            }
+        }
+        if (tile + n_part < nt) commit(buf ^ 1);
+        __syncthreads();
+    }
+    sum = cross32_sum(sum);
+    if (g == 0 && c < C) part_sum[((size_t)bh * n_part + part) * C_all + c] = keys ? sum : 0.0f;
+}
+
+// Slices of the clusters: about two workgroups per compute unit (32 heads x 1024 tokens x 1024 clusters, whole averaged step
+// with 256 / 512 / 1024 / 2048 workgroups: 162 / 155 / 160 / 161 us; shapes that cannot fill the chip do not care).  Before
+// there were slices the 8 heads x 512 tokens over 2000 of 16384 clusters ran on 64 workgroups: 144 us against 13 + 18.
+int lookup_slices(int BH, int Lq, int C)
+{
+    const long long units = (long long)BH * ((Lq + LK_BT - 1) / LK_BT);
+    const long long want = (512 + units - 1) / units, groups = (C + LK_G - 1) / LK_G;
+    return (int)std::min({want, groups, (long long)LK_MAX_SLICES});
+}
+
+// Parts the tokens are dealt to where (sequence, head) x blocks of clusters alone are few.
+int lookup_parts(int BH, int Lq, int C)
+{
+    const long long blocks = (long long)BH * ((C + LK_MC - 1) / LK_MC), tiles = (Lq + LK_MT - 1) / LK_MT;
+    return (int)std::max(1ll, std::min(512 / blocks, tiles));
+}
+
+size_t lookup_part_floats(int BH, int Lq, int C)
+{
+    (void)Lq;
+    return (size_t)BH * C + 512 * LK_MC;                    // parts * C * BH for this C and any smaller one (see lookup_parts)
+}
+
+hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int32_t *sizes, const float *thresh,
+                                 float *stats, uint32_t *keep_mask, int32_t *n_keys, float *part_sum, bool mean,
+                                 int B, int H, int Lq, int C, float sm_scale, hipStream_t s, const int32_t *cand_id,
+                                 const int2 *cand_hdr, const int32_t *parent, const uint32_t *mask1, int C1,
+                                 const BlockTable *table)
+{
+    const bool one = !mean && C <= LK_ONE_C;
+    const int BH = B * H, n_slice = one ? 1 : lookup_slices(BH, Lq, C);
+    const dim3 grid((Lq + LK_BT - 1) / LK_BT * n_slice, BH);
+    const _Float16 *qh = (const _Float16 *)q, *ch = (const _Float16 *)centroids;
+    float2 *st = reinterpret_cast<float2 *>(stats);
+    if (parent && (mean || cand_id || !mask1 || C1 <= 0 || (C1 + 31) / 32 > LK_MAX_W1)) return hipErrorInvalidValue;
+    if ((cand_id && (!mean || !cand_hdr)) || (table && cand_id)) return hipErrorInvalidValue;
+    const int32_t *ids = parent ? parent : cand_id;
+    const int W1 = (C1 + 31) / 32;
+    auto pass = [&](auto mode, auto cands, auto parents, auto keys) {
+        const dim3 all(grid.x + (mode != LK_DECIDE && table ? block_table_groups(table->nblk) : 0), grid.y);
+        hipLaunchKernelGGL((lookup_pass_kernel<mode, cands, parents, keys>), all, dim3(256), 0, s, qh, ch, sizes, thresh, st,
+                           keep_mask, n_keys, ids, cand_hdr, mask1, W1, n_slice, H, Lq, C, sm_scale,
+                           table ? *table : BlockTable{});
+    };
+    constexpr std::true_type yes{};
+    constexpr std::false_type no{};
+    constexpr std::integral_constant<LkMode, LK_STATS> first{};
+    constexpr std::integral_constant<LkMode, LK_DECIDE> second{};
+    constexpr std::integral_constant<LkMode, LK_BOTH> both{};
+    if (mean) {
+        const int n_part = lookup_parts(BH, Lq, C);
+        const dim3 mgrid((C + LK_MC - 1) / LK_MC, n_part, BH);
+        if (cand_id) {
+            pass(first, yes, no, no);
+            hipLaunchKernelGGL(mean_scores_kernel<true>, mgrid, dim3(256), 0, s, qh, ch, sizes, st, part_sum, ids, cand_hdr,
+                               n_slice, H, Lq, C, sm_scale);
+        } else {
+            pass(first, no, no, no);
+            hipLaunchKernelGGL(mean_scores_kernel<false>, mgrid, dim3(256), 0, s, qh, ch, sizes, st, part_sum, ids, cand_hdr,
+                               n_slice, H, Lq, C, sm_scale);
+        }
+    } else {
+        auto select = [&](auto parents, auto keys) {
+            if (one) {
+                pass(both, no, parents, keys);
+            } else {
+                pass(first, no, parents, keys);
+                pass(second, no, parents, keys);
+            }
+        };
+        if (parent && n_keys) select(yes, yes);
+        else if (parent) select(yes, no);
+        else if (n_keys) select(no, yes);
+        else select(no, no);
+    }
     return hipGetLastError();
 }
 

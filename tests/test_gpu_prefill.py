@@ -422,6 +422,35 @@ def test_prefill_split_shares(sq, oracle, case):
     compare_prefill_mean(oracle, w, P, run_prefill_mean_step(sq, w, P), stats, f"prefill-mean-split{case}")
 
 
+@pytest.mark.parametrize("case", [
+    dict(B=1, H=1, L=3000, C=256, Lq=129, U=0),       # the most clusters decided in one launch, a second block of tokens
+    dict(B=2, H=1, L=3000, C=257, Lq=31, U=3),        # one more: two launches, slices of one group
+    dict(B=1, H=1, L=9000, C=2113, Lq=1, U=0),        # as many slices as there are, a ragged last one
+    dict(B=1, H=2, L=500, C=1100, Lq=65, U=7),        # empty clusters
+])
+def test_prefill_lookup_slices(sq, oracle, case):
+    """The lookup's slices of the clusters against the oracle, per token and averaged, with and without the key counts; a
+    threshold of zero keeps every cluster whose exponential does not vanish, a negative one everything with keys."""
+    w = wl.calibrate(wl.make_workload("prefill_slices", seed=35, threads=2, keep_frac=0.2, causal_user=False, **case),
+                     oracle.scores)
+    P = sq.upload(w)
+    run_prefill_step(sq, w, P)
+    compare_prefill(oracle, w, P, f"prefill-slices{case}", logits=False)
+    mask = P.keep_mask.clone()
+    sq.sq_prefill_step(P.shape, P.q, P.centroids, P.sizes, P.offsets, P.thresh, P.K_fixed, P.V_fixed, P.K_user,
+                       P.V_user, P.out, P.lse, P.keep_mask.zero_(), None,
+                       sq.workspace(P.shape, sq.SQ_CALL_PREFILL_STEP, P.q.device))
+    torch.cuda.synchronize()
+    assert torch.equal(P.keep_mask, mask)
+    for T in (0.0, -1.0):
+        P.thresh.fill_(T)
+        run_prefill_step(sq, w, P)
+        assert (P.n_keys.cpu().numpy() == w.L).all()
+    w.thresh, stats = mean_thresholds(oracle, w)
+    P = sq.upload(w)
+    compare_prefill_mean(oracle, w, P, run_prefill_mean_step(sq, w, P), stats, f"prefill-mean-slices{case}")
+
+
 def test_prefill_step_queries_alike_within_a_block(sq, oracle):
     """The whole step on queries that resemble their neighbours (each block of 64 tokens shares a direction, as
     consecutive tokens of a prompt do): the selections of a block overlap, most key blocks are kept by no token of it,
