@@ -1,5 +1,7 @@
 // C ABI of the library: argument validation, workspace carving and kernel sequencing.  Nothing here
 // computes; every step of the path runs in the kernels of the other files.
+#include <algorithm>
+
 #include <stdarg.h>
 #include <stdio.h>
 #include <string.h>
@@ -204,6 +206,21 @@ IndexStepWs carve_step_index(Carver &cv, const sq_shape_t *sh, int G = 1)
 bool step_is_indexed(const sq_shape_t *sh, int G = 1)
 {
     return sh->C <= sq::KI_MAX_C && (long long)sh->B * sh->H * G <= sq::KI_MAX_ROWS;
+}
+
+// Partial results of a decode step of small rows (sq_decode_small.hip), nothing else: 0 splits, the call is not small.
+struct SmallStepWs {
+    int splits;
+    float *partials;
+};
+
+SmallStepWs carve_step_small(Carver &cv, const sq_shape_t *sh, int G = 1)
+{
+    const int rows = sh->B * sh->H * G;
+    SmallStepWs w{};
+    w.splits = sq::decode_small_splits(rows, sh->L, sh->C, sh->U);
+    w.partials = cv.take<float>(sq::decode_small_slots(rows, w.splits) * sq::PART_STRIDE);
+    return w;
 }
 
 // Workspace of a decode step over a shared context (B >= 2): per-sequence selection outputs, then the union
@@ -519,8 +536,12 @@ size_t sq_workspace_bytes(const sq_shape_t *sh, int which)
         return cv.off;
     case SQ_CALL_DECODE_STEP:
         if (step_is_shared(sh)) carve_step_shared(cv, sh);
-        else if (step_is_indexed(sh)) carve_step_index(cv, sh);
-        else carve_step(cv, sh);
+        else if (step_is_indexed(sh)) {
+            Carver cv2(nullptr);
+            carve_step_small(cv2, sh);
+            carve_step_index(cv, sh);
+            return std::max(cv.off, cv2.off);
+        } else carve_step(cv, sh);
         return cv.off;
     case SQ_CALL_ATTN_PREFILL:
         carve_prefill_attn(cv, sh);
@@ -539,8 +560,9 @@ size_t sq_workspace_bytes(const sq_shape_t *sh, int which)
         Carver cv2(nullptr), cv3(nullptr);              // ... on any of the kernel families
         carve_step(cv2, sh, sq::SG);
         carve_step_index(cv3, sh, sq::SG);
-        size_t n = cv.off > cv2.off ? cv.off : cv2.off;
-        return n > cv3.off ? n : cv3.off;
+        Carver cv4(nullptr);                            // (small rows: DS_GRID partials at most, whatever the group)
+        cv4.take<float>((size_t)sq::DS_GRID * sq::PART_STRIDE);
+        return std::max(std::max(cv.off, cv2.off), std::max(cv3.off, cv4.off));
     }
     case SQ_CALL_MULTILEVEL_SELECT:
         carve_hier(cv, sh);
@@ -673,7 +695,8 @@ int decode_step_shared(const sq_shape_t *sh, int G, const void *q, const void *c
 }  // namespace
 
 namespace {
-// Decode step of rows that are handled one by one (few query rows per K/V head), through the key-index list:
+// Decode step of rows that are handled one by one (few query rows per K/V head): small rows in two launches
+// (sq_decode_small.hip), the others through the key-index list:
 // score -> selection + key-index lists -> partial results over equal shares of the kept keys (the user keys in extra
 // workgroups of the same launch) -> merge.  rows = B * H * G query rows [B, H, G]; K/V head of a row = (row / G) % H.
 int decode_step_indexed(const sq_shape_t *sh, int G, const void *q, const void *centroids, const int32_t *sizes,
@@ -681,8 +704,15 @@ int decode_step_indexed(const sq_shape_t *sh, int G, const void *q, const void *
                         const void *K_user, const void *V_user, void *out, float *lse, uint32_t *keep_mask,
                         int32_t *n_keys, Carver &cv, hipStream_t s)
 {
-    IndexStepWs w = carve_step_index(cv, sh, G);
     const int rows = sh->B * sh->H * G;
+    if (sq::decode_small_splits(rows, sh->L, sh->C, sh->U)) {
+        const SmallStepWs w = carve_step_small(cv, sh, G);
+        SQ_HIP(sq::launch_decode_small(q, centroids, sizes, offsets, thresh, K_fixed, V_fixed, K_user, V_user, keep_mask,
+                                       n_keys, w.partials, out, lse, rows, sh->H, G, sh->L, sh->C, sh->U, w.splits,
+                                       sh->sm_scale, s));
+        return SQ_OK;
+    }
+    IndexStepWs w = carve_step_index(cv, sh, G);
     const sq::UserAttn ua = make_user_pieces(sh, G, q, K_user, V_user, w.partials, w.user_slot_base, w.nuq);
     SQ_HIP(sq::launch_score(q, centroids, w.logits, nullptr, sh->B, sh->H, G, sh->C, sh->sm_scale, s));
     SQ_HIP(sq::launch_select_index(w.logits, thresh, sizes, offsets, keep_mask, w.n_ranges, n_keys ? n_keys : w.n_keys,

@@ -231,6 +231,20 @@ inline size_t keyidx_partial_slots(int rows, int nuq) { return (size_t)KI_ATTN_G
 hipError_t launch_select_index(const float *logits, const float *thresh, const int32_t *sizes, const int32_t *offsets,
                                uint32_t *keep_mask, int32_t *n_ranges, int32_t *n_keys, KeyIndexPlan plan, int rows,
                                int H, int G, int C, hipStream_t s);
+// Decode step of small rows in two launches (sq_decode_small.hip): the workgroups of a query row each repeat the row's
+// lookup and attend to an equal share of its keys.  decode_small_splits() workgroups per row, 0: the call is not small.
+constexpr int DS_MAX_C = 256;          // clusters a workgroup scores by itself
+constexpr int DS_GRID = 512;           // workgroups of a call, about: two per compute unit
+constexpr int DS_MAX_SPLITS = 64;
+constexpr int DS_MAX_ROWS = 512;
+constexpr int DS_MIN_SHARE = 16;       // keys per workgroup, at least: one round of loads
+constexpr int DS_MAX_SHARE = 320;      // ... at most, where a row keeps everything
+int decode_small_splits(int rows, int L, int C, int U);
+inline size_t decode_small_slots(int rows, int splits) { return (size_t)rows * splits; }
+hipError_t launch_decode_small(const void *q, const void *centroids, const int32_t *sizes, const int32_t *offsets,
+                               const float *thresh, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
+                               uint32_t *keep_mask, int32_t *n_keys, float *partials, void *out, float *lse, int rows,
+                               int H, int G, int L, int C, int U, int splits, float sm_scale, hipStream_t s);
 // Last level of a hierarchical lookup, selected in slices of 256 candidates per workgroup (two launches: count, then
 // write).  rec / hdr / stats / row_items: the candidates' records, per-row candidate counts (hdr[row].y), per-item
 // statistics and per-row (first item, items), as launch_gather_score leaves them; slice_cnt [rows, cand_slices_for(C)]

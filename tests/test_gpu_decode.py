@@ -243,6 +243,46 @@ def test_step_at_key_index_limits(sq, oracle, case):
     step_against_oracle(sq, oracle, w, f"limits{case}")
 
 
+@pytest.mark.parametrize("case", [
+    dict(B=1, H=1, L=3, C=1, U=1, keep_frac=0.9),                 # smallest: 64 workgroups for a handful of keys
+    dict(B=1, H=3, L=1000, C=16, U=0, keep_frac=0.3),             # one whole score tile
+    dict(B=1, H=2, L=2000, C=65, U=63, keep_frac=0.5),            # a tile past a round of four
+    dict(B=2, H=5, L=5000, C=255, U=129, keep_frac=0.4),          # one cluster short of the limit
+    dict(B=1, H=2, L=5000, C=256, U=64, keep_frac=0.98),          # the most clusters
+    dict(B=1, H=2, L=5000, C=257, U=64, keep_frac=0.98),          # one past it: the key-index launches
+    dict(B=4, H=128, L=300, C=20, U=20, keep_frac=0.97),          # the most rows, one workgroup each; the largest share
+    dict(B=4, H=128, L=300, C=20, U=21, keep_frac=0.97),          # one key past it: the key-index launches
+    dict(B=3, H=7, L=700, C=40, U=0, keep_frac=0.02),             # rows that keep (almost) nothing: empty shares
+])
+def test_small_step_limits(sq, oracle, case):
+    w = wl.calibrate(wl.make_workload("small", Lq=1, seed=23, threads=4, **case), oracle.scores)
+    step_against_oracle(sq, oracle, w, f"small{case}")
+
+
+@pytest.mark.parametrize("C", [1, 47, 256])
+def test_small_step_selects_like_the_general_one(sq, oracle, C):
+    """The two-launch step repeats the arithmetic of the general step's lookup: the same masks and counts, bit for bit.
+    More than 512 query rows take the general step, so the same heads are run as they are and repeated."""
+    w = wl.calibrate(wl.make_workload("small_vs", B=1, H=2, L=600, C=C, Lq=1, U=5, keep_frac=0.4, seed=24, threads=2),
+                     oracle.scores)
+    got = []
+    for rep in (1, 257):
+        P = sq.upload(w)
+        t = lambda a, dim: a.repeat(*[rep if d == dim else 1 for d in range(a.dim())])  # noqa: E731
+        sh = sq.make_shape(w.B, w.H * rep, w.L, w.C, 1, w.U, w.sm_scale)
+        q, Ku, Vu = t(P.q, 1), t(P.K_user, 1), t(P.V_user, 1)
+        out, lse, mask, nk = t(P.out, 1), t(P.lse, 1), t(P.keep_mask, 1), t(P.n_keys, 1)
+        sq.sq_decode_step(sh, q, t(P.centroids, 0), t(P.sizes, 0), t(P.offsets, 0), t(P.thresh, 0), t(P.K_fixed, 0),
+                          t(P.V_fixed, 0), Ku, Vu, out, lse, mask, nk, sq.workspace(sh, sq.SQ_CALL_DECODE_STEP, q.device))
+        torch.cuda.synchronize()
+        got.append([a[:, :w.H].cpu() for a in (out, lse, mask, nk)])
+    (o1, l1, m1, n1), (o2, l2, m2, n2) = got
+    assert torch.equal(m1, m2) and torch.equal(n1, n2)
+    # the keys are split differently: fp32 partial sums, rounded to fp16 once (half a unit at |out| < 4 each)
+    assert (o1.float() - o2.float()).abs().max().item() <= 2 * 2 ** -10
+    torch.testing.assert_close(l1, l2, atol=1e-5, rtol=1e-6)
+
+
 def test_shared_context_step_extremes(sq, oracle):
     base = dict(B=10, H=2, L=1024, C=32, Lq=1, U=33, keep_frac=0.5, seed=12, threads=2)
     # every sequence keeps everything: each key is owned by all sequences of the group
