@@ -31,6 +31,21 @@ def test_every_declared_symbol_is_exported(sq):
     assert L.sq_version() >= 100
 
 
+def test_every_entry_point_declares_its_parameters(sq):
+    """The binding passes device pointers as integers: without argtypes ctypes would cut them to 32 bits."""
+    hdr = open(os.path.join(ROOT, "include", "squeezed_attention.h")).read()
+    hdr = re.sub(r"/\*.*?\*/", "", hdr, flags=re.S)
+    L = sq.lib()
+    for name, params in re.findall(r"\b(sq_[a-z_0-9]+)\s*\(([^)]*)\)\s*;", hdr):
+        kinds = [p.strip() for p in params.split(",") if p.strip() != "void"]
+        if not kinds:
+            continue
+        types = getattr(L, name).argtypes
+        assert types is not None and len(types) == len(kinds), name
+        for p, t in zip(kinds, types):
+            assert C.sizeof(t) == (4 if "*" not in p and p.split()[0] in ("int", "int32_t", "float") else 8), (name, p)
+
+
 def test_workspace_sizes(sq):
     sh = sq.make_shape(1, 32, 32768, 1024, 1, 512, 0.0884)
     assert sq.workspace_bytes(sh, sq.SQ_CALL_CENTROID_SCORE) == 0
