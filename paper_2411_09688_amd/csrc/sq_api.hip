@@ -714,9 +714,15 @@ int decode_step_indexed(const sq_shape_t *sh, int G, const void *q, const void *
     }
     IndexStepWs w = carve_step_index(cv, sh, G);
     const sq::UserAttn ua = make_user_pieces(sh, G, q, K_user, V_user, w.partials, w.user_slot_base, w.nuq);
-    SQ_HIP(sq::launch_score(q, centroids, w.logits, nullptr, sh->B, sh->H, G, sh->C, sh->sm_scale, s));
-    SQ_HIP(sq::launch_select_index(w.logits, thresh, sizes, offsets, keep_mask, w.n_ranges, n_keys ? n_keys : w.n_keys,
-                                   w.plan, rows, sh->H, G, sh->C, s));
+    int32_t *nk = n_keys ? n_keys : w.n_keys;
+    if (sq::score_select_is_fused(rows, sh->C)) {
+        SQ_HIP(sq::launch_score_select_index(q, centroids, thresh, sizes, offsets, keep_mask, w.n_ranges, nk, w.plan, rows,
+                                             sh->H, G, sh->C, sh->sm_scale, s));
+    } else {
+        SQ_HIP(sq::launch_score(q, centroids, w.logits, nullptr, sh->B, sh->H, G, sh->C, sh->sm_scale, s));
+        SQ_HIP(sq::launch_select_index(w.logits, thresh, sizes, offsets, keep_mask, w.n_ranges, nk, w.plan, rows, sh->H, G,
+                                       sh->C, s));
+    }
     SQ_HIP(sq::launch_decode_attn_index(q, K_fixed, V_fixed, w.plan, w.partials, out, lse, rows, sh->H, G, sh->sm_scale,
                                         &ua, s));
     return SQ_OK;

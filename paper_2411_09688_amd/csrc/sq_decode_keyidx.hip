@@ -3,6 +3,8 @@
 // The sparse attention kernel of Section 4.2 is driven by a list of the indices of the keys to load; this file
 // builds that list and lets every launch of the step run across the whole chip:
 //
+//   (score_kernel            centroid scores, sq_score.hip; short rows take score_select_index_kernel instead, which does
+//                            both: see score_select_is_fused)
 //   select_index_kernel      one workgroup per (query row, slice of 128 clusters).  Every workgroup of a row
 //                            recomputes the row's statistics (m, D) of Eq. 1 and all of its keep decisions -- a row is
 //                            a few KB of logits, so the redundancy is cheaper than one workgroup per row walking a
@@ -207,6 +209,57 @@ __global__ __launch_bounds__(KI_THREADS) void select_index_kernel(
     const bool mine = wave == wv_s || wave == wv_s + 1;
     const int start_s = (mine && i_s < C) ? off[i_s] : 0;    // fetched with the logits: no second round trip
     select_row_slice<KI_STEPS>(xv, nv, start_s, thresh[h], C, row, sl, keep_mask, n_ranges, n_keys, plan, S);
+}
+
+// Scores and selection in one launch, for rows of at most KI_FUSED_MAX_C clusters: every workgroup of a row scores all of
+// the row's clusters itself (score_kernel's tiles and order of k-steps: bit-identical logits) instead of reading them from
+// a launch in front of it.  Bound by the round trips of one workgroup -- centroids, then the slice's keys.
+constexpr int KI_FUSED_TILES = (KI_FUSED_MAX_C / 16 + KI_WAVES - 1) / KI_WAVES;   // 16-cluster tiles per wave
+__global__ __launch_bounds__(KI_THREADS) void score_select_index_kernel(
+    const _Float16 *__restrict__ q, const _Float16 *__restrict__ cent, const float *__restrict__ thresh,
+    const int32_t *__restrict__ sizes, const int32_t *__restrict__ offsets, uint32_t *__restrict__ keep_mask,
+    int32_t *__restrict__ n_ranges, int32_t *__restrict__ n_keys, KeyIndexPlan plan, int H, int G, int C, int nsl,
+    float sm_scale)
+{
+    static_assert(KI_FUSED_MAX_C <= KI_THREADS && KI_FUSED_MAX_C % 16 == 0, "one cluster per thread");
+    __shared__ SelectLds S;
+    __shared__ float s_x[KI_FUSED_MAX_C];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, p = lane & 15, g = lane >> 4;
+    const int row = (int)blockIdx.x / nsl, sl = (int)blockIdx.x - row * nsl;
+    const int h = (row / G) % H;
+    const h8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+    const h8 *qp = reinterpret_cast<const h8 *>(q + (size_t)row * D);
+    h8 bq[4], a[KI_FUSED_TILES][4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) bq[s] = qp[s * 4 + g];
+#pragma unroll
+    for (int t = 0; t < KI_FUSED_TILES; ++t) {
+        const int i0 = (t * KI_WAVES + wave) * 16;
+        if (i0 < C) {                                        // wave-uniform
+            const h8 *cp = reinterpret_cast<const h8 *>(cent + ((size_t)h * C + min(i0 + p, C - 1)) * D);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) a[t][s] = cp[s * 4 + g];
+        }
+    }
+    const bool mine = (wave >> 1) == sl;                     // the slice's two waves
+    int nv[1] = {tid < C ? sizes[(size_t)h * C + tid] : 0};
+    const int start_s = (mine && tid < C) ? offsets[(size_t)h * (C + 1) + tid] : 0;
+    const float T = thresh[h];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) bq[s] = p == 0 ? bq[s] : zero8;   // the query is column 0 of the tile
+#pragma unroll
+    for (int t = 0; t < KI_FUSED_TILES; ++t) {
+        const int i0 = (t * KI_WAVES + wave) * 16;
+        if (i0 < C) {
+            f4 acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < 4; ++s) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[t][s], bq[s], acc, 0, 0, 0);
+            if (p == 0) *reinterpret_cast<f4 *>(&s_x[i0 + g * 4]) = acc * sm_scale;
+        }
+    }
+    __syncthreads();
+    float xv[1] = {tid < C ? s_x[tid] : 0.0f};
+    select_row_slice<1>(xv, nv, start_s, T, C, row, sl, keep_mask, n_ranges, n_keys, plan, S);
 }
 
 // How the partial kernel's workgroups divide the selected keys (the merge kernel derives the same numbers): the kept
@@ -692,6 +745,29 @@ hipError_t launch_select_index(const float *logits, const float *thresh, const i
     const int nsl = (C + KI_SLICE - 1) / KI_SLICE;
     hipLaunchKernelGGL(select_index_kernel, dim3(rows * nsl), dim3(KI_THREADS), 0, s, logits, thresh, sizes, offsets,
                        keep_mask, n_ranges, n_keys, plan, H, G, C, nsl);
+    return hipGetLastError();
+}
+
+// One launch less (1.5 to 2.7 us of GPU time, 2.5 us of the calling thread) against the centroids read once per workgroup
+// instead of once per head: it pays while a workgroup reads at most ~100 KB of them and the workgroups fit the chip about
+// twice.  GPU time of the whole step, two launches / one, us:
+//   160 rows, 128 clusters  31.6 / 28.9      224 rows, 100 clusters  32.1 / 29.5     224 rows, 256 clusters  35.3 / 34.5
+//    32 rows, 256 clusters  20.0 / 18.5       64 rows, 384 clusters  38.6 / 37.7      16 rows, 384 clusters  23.2 / 22.6
+//    16 rows, 512 clusters  22.7 / 23.4      128 rows, 512 clusters  35.3 / 38.2      32 rows, 1024 clusters 27.7 / 33.4
+bool score_select_is_fused(int rows, int C)
+{
+    return C <= KI_FUSED_MAX_C && (long long)rows * ((C + KI_SLICE - 1) / KI_SLICE) <= KI_FUSED_MAX_WGS;
+}
+
+hipError_t launch_score_select_index(const void *q, const void *centroids, const float *thresh, const int32_t *sizes,
+                                     const int32_t *offsets, uint32_t *keep_mask, int32_t *n_ranges, int32_t *n_keys,
+                                     KeyIndexPlan plan, int rows, int H, int G, int C, float sm_scale, hipStream_t s)
+{
+    if (!score_select_is_fused(rows, C)) return hipErrorInvalidValue;
+    const int nsl = (C + KI_SLICE - 1) / KI_SLICE;
+    hipLaunchKernelGGL(score_select_index_kernel, dim3(rows * nsl), dim3(KI_THREADS), 0, s, (const _Float16 *)q,
+                       (const _Float16 *)centroids, thresh, sizes, offsets, keep_mask, n_ranges, n_keys, plan, H, G, C, nsl,
+                       sm_scale);
     return hipGetLastError();
 }
 

@@ -231,6 +231,13 @@ inline size_t keyidx_partial_slots(int rows, int nuq) { return (size_t)KI_ATTN_G
 hipError_t launch_select_index(const float *logits, const float *thresh, const int32_t *sizes, const int32_t *offsets,
                                uint32_t *keep_mask, int32_t *n_ranges, int32_t *n_keys, KeyIndexPlan plan, int rows,
                                int H, int G, int C, hipStream_t s);
+// Scores and selection of short rows in one launch: where score_select_is_fused().
+constexpr int KI_FUSED_MAX_C = 384;
+constexpr int KI_FUSED_MAX_WGS = 512;
+bool score_select_is_fused(int rows, int C);
+hipError_t launch_score_select_index(const void *q, const void *centroids, const float *thresh, const int32_t *sizes,
+                                     const int32_t *offsets, uint32_t *keep_mask, int32_t *n_ranges, int32_t *n_keys,
+                                     KeyIndexPlan plan, int rows, int H, int G, int C, float sm_scale, hipStream_t s);
 // Decode step of small rows in two launches (sq_decode_small.hip): the workgroups of a query row each repeat the row's
 // lookup and attend to an equal share of its keys.  decode_small_splits() workgroups per row, 0: the call is not small.
 constexpr int DS_MAX_C = 256;          // clusters a workgroup scores by itself

@@ -259,10 +259,22 @@ def test_small_step_limits(sq, oracle, case):
     step_against_oracle(sq, oracle, w, f"small{case}")
 
 
-@pytest.mark.parametrize("C", [1, 47, 256])
-def test_small_step_selects_like_the_general_one(sq, oracle, C):
-    """The two-launch step repeats the arithmetic of the general step's lookup: the same masks and counts, bit for bit.
-    More than 512 query rows take the general step, so the same heads are run as they are and repeated."""
+@pytest.mark.parametrize("case", [
+    dict(B=1, H=3, L=21000, C=37, U=9, keep_frac=0.1),            # scores and selection in one launch: one slice
+    dict(B=1, H=2, L=6000, C=384, U=70, keep_frac=0.3),           # the most clusters
+    dict(B=1, H=2, L=6000, C=385, U=70, keep_frac=0.3),           # one past it: two launches
+    dict(B=2, H=85, L=1500, C=300, U=0, keep_frac=0.3),           # 510 workgroups
+    dict(B=3, H=57, L=1500, C=300, U=0, keep_frac=0.3),           # 513: two launches
+])
+def test_fused_selection_limits(sq, oracle, case):
+    w = wl.calibrate(wl.make_workload("fused", Lq=1, seed=25, threads=4, **case), oracle.scores)
+    step_against_oracle(sq, oracle, w, f"fused{case}")
+
+
+@pytest.mark.parametrize("C", [1, 47, 256, 300, 384])
+def test_short_rows_select_like_the_general_step(sq, oracle, C):
+    """Steps with fewer launches repeat the arithmetic of the general step's lookup: the same masks and counts, bit for
+    bit.  More than 512 query rows take the general step, so the same heads are run as they are and repeated."""
     w = wl.calibrate(wl.make_workload("small_vs", B=1, H=2, L=600, C=C, Lq=1, U=5, keep_frac=0.4, seed=24, threads=2),
                      oracle.scores)
     got = []
