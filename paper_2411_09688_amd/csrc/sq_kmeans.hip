@@ -243,6 +243,9 @@ __global__ __launch_bounds__(1024) void kmeans_scan_kernel(int32_t *__restrict__
 // same centre id are found in registers (a ballot per bit of the id); a lane's slot is the cluster's cursor plus the number of matching lanes below it, so members appear in
 // ascending key order inside every cluster (a stable sort).  The cursors live in LDS and are touched by this one
 // wave only, in program order (all lanes of a group read the cursor, then its last lane advances it): no atomics.
+// The launch is one wave's chain of reads: with the ids of the next 512 keys fetched together instead of 64 at a time, 32
+// heads x 32K keys x 1024 centres take 15.8 us instead of 20.3.
+constexpr int KM_SCATTER_AHEAD = 8;
 __global__ __launch_bounds__(64) void kmeans_scatter_kernel(const int32_t *__restrict__ assign,
                                                             const int32_t *__restrict__ hist,
                                                             const int32_t *__restrict__ offsets,
@@ -252,28 +255,39 @@ __global__ __launch_bounds__(64) void kmeans_scatter_kernel(const int32_t *__res
     const int p = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
     const int32_t *hp = hist + ((size_t)h * P + p) * C;
     const int32_t *op = offsets + (size_t)h * (C + 1);
+#pragma unroll 8
     for (int c = lane; c < C; c += 64) s_cur[c] = op[c] + hp[c];
     __syncthreads();
     const int k_end = min(L, (p + 1) * PL);
     const int nbits = 32 - __clz(max(C - 1, 1));           // bits of a centre id
-    for (int k0 = p * PL; k0 < k_end; k0 += 64) {
-        const int k = k0 + lane;
-        const bool valid = k < k_end;
-        const int c = valid ? min(max(assign[(size_t)h * L + k], 0), C - 1) : -1;   // clamped like the counts
-        // Lanes with the same centre id, found bit by bit: a lane keeps the lanes that agree with it on every bit of
-        // the id (one ballot per bit, no data-dependent loop).
-        uint64_t m = __ballot(valid);
-        for (int b = 0; b < nbits; ++b) {                  // uniform trip count
-            const bool bit = (c >> b) & 1;
-            const uint64_t bal = __ballot(valid && bit);
-            m &= bit ? bal : ~bal;
+    for (int k0 = p * PL; k0 < k_end; k0 += 64 * KM_SCATTER_AHEAD) {
+        int ids[KM_SCATTER_AHEAD];                         // all loads of a stretch in flight before the first is used
+#pragma unroll
+        for (int u = 0; u < KM_SCATTER_AHEAD; ++u) {
+            const int k = k0 + u * 64 + lane;
+            ids[u] = k < k_end ? assign[(size_t)h * L + k] : 0;
         }
-        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-        const int cnt = __popcll(m);
-        if (valid) {
-            const int cur = s_cur[c];
-            if (rank == cnt - 1) s_cur[c] = cur + cnt;
-            perm[(size_t)h * L + cur + rank] = k;
+#pragma unroll
+        for (int u = 0; u < KM_SCATTER_AHEAD; ++u) {
+            if (k0 + u * 64 >= k_end) break;               // uniform
+            const int k = k0 + u * 64 + lane;
+            const bool valid = k < k_end;
+            const int c = valid ? min(max(ids[u], 0), C - 1) : -1;   // clamped like the counts
+            // Lanes with the same centre id, found bit by bit: a lane keeps the lanes that agree with it on every bit of
+            // the id (one ballot per bit, no data-dependent loop).
+            uint64_t m = __ballot(valid);
+            for (int b = 0; b < nbits; ++b) {              // uniform trip count
+                const bool bit = (c >> b) & 1;
+                const uint64_t bal = __ballot(valid && bit);
+                m &= bit ? bal : ~bal;
+            }
+            const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+            const int cnt = __popcll(m);
+            if (valid) {
+                const int cur = s_cur[c];
+                if (rank == cnt - 1) s_cur[c] = cur + cnt;
+                perm[(size_t)h * L + cur + rank] = k;
+            }
         }
     }
 }
