@@ -150,10 +150,9 @@ int sq_sparse_attn_decode(const sq_shape_t *shape, const void *q, const void *K_
  * In:  keep_mask u32 [B,H,Lq,ceil(C/32)], offsets i32 [H,C+1].
  * Out: out f16 [B,H,Lq,d]; lse f32 [B,H,Lq] or NULL.
  * Workspace: sq_workspace_bytes(shape, SQ_CALL_ATTN_PREFILL).
- * Cost: the keys are walked in blocks of 64 by groups of 64 consecutive query tokens.  A block in which no token of
- * the group kept a cluster is not read at all, provided at least an eighth of all (group, block) pairs are of that
- * kind (counted on the device from keep_mask, no host synchronisation) and L <= 262144; otherwise every group walks
- * every block and only the matrix products of such a block are skipped.  The result does not depend on which.
+ * Cost: the keys are walked in blocks of 64 by groups of 256 consecutive query tokens (128 where that pads less); a
+ * block in which no token of the group kept a cluster is not read at all.  Where sequences x heads x groups do not fill
+ * the chip, the blocks of a group are split over several workgroups and their partial results merged.
  */
 int sq_sparse_attn_prefill(const sq_shape_t *shape, const void *q, const void *K_fixed, const void *V_fixed,
                            const int32_t *offsets, const uint32_t *keep_mask,
@@ -294,7 +293,7 @@ int sq_gqa_mean_decode_step(const sq_shape_t *shape, int32_t G, const void *q, c
 /*
  * One whole prefill step with PER-QUERY selection: the lookup of sq_centroid_score + sq_select for every
  * query token, then sq_sparse_attn_prefill.  The lookup makes two passes over the centroids (normaliser,
- * then scores; Section 4.1) and writes no [queries x clusters] intermediate.  Its normaliser is summed in
+ * then scores; Section 4.1), both spread over slices of the clusters, and writes no [queries x clusters] intermediate.  Its normaliser is summed in
  * a different order than sq_centroid_score's, so a cluster whose score is within rounding of the threshold
  * may be decided differently from the separate calls; everything else is identical.
  * Out: out f16 [B,H,Lq,d]; optional (NULL to skip): lse f32 [B,H,Lq], keep_mask u32 [B,H,Lq,ceil(C/32)],

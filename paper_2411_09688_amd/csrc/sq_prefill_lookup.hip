@@ -10,7 +10,7 @@
 //                  shifted into the token's mask word.
 //   mean_scores_kernel                  selection on averaged scores (Appendix D, "Prefill Stage"), first half: the scores
 //                  S_i(t) = exp(x_i - m) / D are summed over the tokens per cluster and written as part_sum
-//                  [B*H, lookup_parts_for(...), C]; the row-wise selection kernel adds the parts.
+//                  [B*H, lookup_parts(), C]; the row-wise selection kernel adds the parts.
 //   CANDS == true  (averaged scores) second level of a hierarchical lookup (Section 3.3, Eq. 3): the clusters scored are the
 //                  n candidates cand_id[bh, 0..n) of the (sequence, head) -- the children of the coarse clusters kept
 //                  one level up -- so the normaliser runs over the candidates only; part_sum is written in candidate order.
