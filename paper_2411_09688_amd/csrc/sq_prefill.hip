@@ -32,6 +32,7 @@
 // Section 4.2); the kernel walks that list 64 keys at a time, gathering K and V rows by index (the indices travel in
 // registers ahead of the rows), with no per-query masks: only the tail of the last block and the causal user keys are
 // hidden, so every executed tile is useful work.
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -60,7 +61,6 @@ __global__ __launch_bounds__(256) void block_table_kernel(BlockTable bt)
 // Kept ranges of every (sequence, head) row -> list of key rows: record (first key, count, keys before) writes
 // key_idx[row, before + j] = first + j, clamped into the tensor.  One wave per record at a time, the records of a row
 // dealt over the gridDim.y workgroups of the row.
-constexpr int EXPAND_SLICES = 16;         // workgroups per row
 __global__ __launch_bounds__(256) void expand_ranges_kernel(DecodePlan plan, int32_t *__restrict__ key_idx, int L)
 {
     const size_t row = blockIdx.x;
@@ -783,7 +783,10 @@ hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, co
 
 hipError_t launch_expand_ranges(DecodePlan plan, int32_t *idx, int rows, int L, hipStream_t s)
 {
-    hipLaunchKernelGGL(expand_ranges_kernel, dim3(rows, EXPAND_SLICES), dim3(256), 0, s, plan, idx, L);
+    // A wave's chain of records is what a launch over few rows waits for: 8 rows x 262144 keys, two launches of a step, 14.2 us
+    // with 16 workgroups per row, 9 with 64 (the step 126.5 -> 121.4); from 32 rows on 16 fill the chip.
+    const int slices = std::clamp(512 / rows, 16, 64);
+    hipLaunchKernelGGL(expand_ranges_kernel, dim3(rows, slices), dim3(256), 0, s, plan, idx, L);
     return hipGetLastError();
 }
 
@@ -791,8 +794,7 @@ hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void 
                                       DecodePlan plan, int32_t *key_idx, float *partials, void *out, float *lse,
                                       const Shape &sh, hipStream_t s)
 {
-    hipLaunchKernelGGL(expand_ranges_kernel, dim3(sh.B * sh.H, EXPAND_SLICES), dim3(256), 0, s, plan, key_idx, sh.L);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_expand_ranges(plan, key_idx, sh.B * sh.H, sh.L, s);
     if (e != hipSuccess) return e;
     return launch_prefill_kernels<true>(q, Kf, Vf, Ku, Vu, nullptr, reinterpret_cast<const uint32_t *>(key_idx), nullptr,
                                         reinterpret_cast<const int32_t *>(plan.hdr), out, lse, partials, sh, s);
