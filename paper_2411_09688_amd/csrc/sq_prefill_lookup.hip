@@ -76,7 +76,7 @@ struct SlicePairs {
         float d = 0.0f;
 #pragma unroll
         for (int k = 0; k < LK_MAX_SLICES / STEP; ++k)
-            if (v[k].y > 0.0f) d = fmaf(v[k].y, __builtin_amdgcn_exp2f(v[k].x - m), d);
+            if (v[k].y != 0.0f) d = fmaf(v[k].y, __builtin_amdgcn_exp2f(v[k].x - m), d);
         return d;
     }
 };
@@ -134,12 +134,12 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
         for (int s = 0; s < 8; ++s) bq[s] = qp[s * 2 + g];
     }
     // The least raw score that is kept, from the row's reference m and normaliser relative to it.  (T D < 0: everything with
-    // keys; T D = 0: everything whose exponential does not vanish; strict otherwise: the least float above the logarithm.)
+    // keys; T D = 0: everything whose exponential does not vanish; T D not a number: nothing, no score is above it.)
     float x_min = 0.0f;
     auto set_threshold = [&](float m, float Dsum) {
         const float thr = thresh[h] * Dsum;
         const float cut = thr < 0.0f ? SQ_NEG_INF : (m + (thr > 0.0f ? log2f(thr) : -126.0f)) / c2;
-        x_min = thr > 0.0f ? nextafterf(cut, __builtin_inff()) : cut;
+        x_min = thr > 0.0f ? nextafterf(cut, __builtin_inff()) : thr <= 0.0f ? cut : __builtin_nanf("");
     };
     if (MODE == LK_DECIDE) {
         SlicePairs<2> sp;                                   // (the two lanes of a token take every other slice)

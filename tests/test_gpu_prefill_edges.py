@@ -1,0 +1,70 @@
+"""GPU parity at the edges of the prefill lookup: thresholds and centroids that are not numbers, exact ties."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import unpack_mask
+from paper_2411_09688_amd import workload as wl
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def sq():
+    from paper_2411_09688_amd import binding
+    binding.lib()
+    return binding
+
+
+def t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def per_query(sq, w, thresh, centroids=None):
+    """Keep mask [B, H, Lq, C], key counts and output of the one-level step."""
+    P = sq.upload(w)
+    sq.sq_prefill_step(P.shape, P.q, P.centroids if centroids is None else t(centroids), P.sizes, P.offsets, t(thresh),
+                       P.K_fixed, P.V_fixed, P.K_user, P.V_user, P.out, P.lse, P.keep_mask, P.n_keys,
+                       sq.workspace(P.shape, sq.SQ_CALL_PREFILL_STEP, DEV))
+    torch.cuda.synchronize()
+    return unpack_mask(P.keep_mask.cpu().numpy(), w.C), P.n_keys.cpu().numpy(), P.out.cpu().numpy()
+
+
+def averaged(sq, w, thresh, centroids=None):
+    P = sq.upload(w)
+    mask = torch.zeros(w.B, w.H, (w.C + 31) // 32, dtype=torch.int32, device=DEV)
+    nk = torch.zeros(w.B, w.H, dtype=torch.int32, device=DEV)
+    sq.sq_prefill_mean_step(P.shape, P.q, P.centroids if centroids is None else t(centroids), P.sizes, P.offsets, t(thresh),
+                            P.K_fixed, P.V_fixed, P.K_user, P.V_user, P.out, P.lse, mask, nk,
+                            sq.workspace(P.shape, sq.SQ_CALL_PREFILL_MEAN_STEP, DEV))
+    torch.cuda.synchronize()
+    return unpack_mask(mask.cpu().numpy(), w.C), nk.cpu().numpy(), P.out.cpu().numpy()
+
+
+ONE_AND_TWO_LAUNCHES = [dict(L=900, C=60, Lq=40), dict(L=3000, C=600, Lq=150)]
+
+
+@pytest.mark.parametrize("case", ONE_AND_TWO_LAUNCHES)
+def test_a_threshold_that_is_not_a_number_keeps_nothing(sq, case):
+    """score > NaN is false: no cluster is kept, in the per-query form as in the averaged form and in decode."""
+    w = wl.make_workload("edges", seed=41, threads=1, B=1, H=3, U=20, keep_frac=0.3, causal_user=False, **case)
+    T = np.array([1e-3, np.nan, 1e-3], np.float32)
+    for fn in (per_query, averaged):
+        keep, nk, _ = fn(sq, w, T)
+        assert not keep[:, 1].any() and (nk[:, 1] == 0).all() and keep[:, 0].any()
+
+
+@pytest.mark.parametrize("case", ONE_AND_TWO_LAUNCHES)
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_a_score_that_is_not_a_number_keeps_nothing_of_its_row(sq, case, bad):
+    """A centroid with keys that holds a NaN or an infinity makes the normaliser of every token NaN: nothing is kept, as in
+    decode, where exp(x - m) > T * NaN is false."""
+    w = wl.make_workload("edges", seed=42, threads=1, B=1, H=2, U=20, keep_frac=0.3, causal_user=False, **case)
+    cent = w.centroids.copy()
+    c = int(np.flatnonzero(w.sizes[1] > 0)[7])
+    cent[1, c, 5] = bad
+    w.q[:, 1, :, 5] = np.abs(w.q[:, 1, :, 5]) + np.float16(0.1)    # (an infinite logit, not a NaN one, for bad = inf)
+    T = np.full(w.H, 1e-4, np.float32)
+    keep, nk, _ = per_query(sq, w, T, cent)
+    assert not keep[:, 1].any() and (nk[:, 1] == 0).all() and keep[:, 0].any()
