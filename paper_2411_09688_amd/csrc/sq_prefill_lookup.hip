@@ -235,16 +235,27 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
                     }
                 }
                 if (!DECIDE) {
-                    float mx = SQ_NEG_INF;
+                    float mx = SQ_NEG_INF;                  // (NaN if a score is)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) mx = fmaxf(mx, acc[r]);
-                    mx *= c2;
+                    for (int r = 0; r < 16; ++r) mx = __builtin_elementwise_maximum(mx, acc[r]);
                     // (the reference moves when a score passes it by 2^8: the sum stays far inside fp32's range)
-                    if (__ballot(mx > lim) != 0ull && mx > ref) {
-                        Dsum *= __builtin_amdgcn_exp2f(ref - mx);   // ref = -inf: Dsum is 0 and stays 0
-                        ref = mx;
-                        lim = mx + 8.0f;
-                        refn = -mx;
+                    if (__ballot(!(mx * c2 <= lim)) != 0ull) {
+                        if (__ballot(mx != mx) != 0ull) {
+                            // a cluster without keys whose centroid is not finite has -inf + inf or NaN here: -inf again
+                            mx = SQ_NEG_INF;
+#pragma unroll
+                            for (int r = 0; r < 16; ++r) {
+                                acc[r] = nv[r] > 0.0f ? acc[r] : SQ_NEG_INF;
+                                mx = fmaxf(mx, acc[r]);
+                            }
+                        }
+                        mx *= c2;
+                        if (mx > ref) {
+                            Dsum *= __builtin_amdgcn_exp2f(ref - mx);   // ref = -inf: Dsum is 0 and stays 0
+                            ref = mx;
+                            lim = mx + 8.0f;
+                            refn = -mx;
+                        }
                     }
 #pragma unroll
                     for (int r = 0; r < 16; ++r) Dsum = fmaf(nv[r], __builtin_amdgcn_exp2f(fmaf(acc[r], c2, refn)), Dsum);

@@ -42,7 +42,20 @@ def averaged(sq, w, thresh, centroids=None):
     return unpack_mask(mask.cpu().numpy(), w.C), nk.cpu().numpy(), P.out.cpu().numpy()
 
 
+def hier_per_query(sq, w, T1, T2, centroids):
+    sh = sq.make_shape(w.B, w.H, w.L, w.C, w.Lq, w.U, w.sm_scale, causal_user=w.causal_user)
+    out = torch.zeros(w.B, w.H, w.Lq, w.d, dtype=torch.float16, device=DEV)
+    mask = torch.zeros(w.B, w.H, w.Lq, (w.C + 31) // 32, dtype=torch.int32, device=DEV)
+    nk = torch.zeros(w.B, w.H, w.Lq, dtype=torch.int32, device=DEV)
+    sq.sq_hier_prefill_step(sh, w.C1, t(w.q), t(w.centroids1), t(w.sizes1), t(w.child_offsets), t(T1), t(centroids), t(w.sizes),
+                            t(w.offsets), t(T2), t(w.K_fixed), t(w.V_fixed), t(w.K_user), t(w.V_user), out, None, mask, nk,
+                            sq.workspace(sh, sq.SQ_CALL_HIER_PREFILL_STEP, DEV))
+    torch.cuda.synchronize()
+    return unpack_mask(mask.cpu().numpy(), w.C), nk.cpu().numpy(), out.cpu().numpy()
+
+
 ONE_AND_TWO_LAUNCHES = [dict(L=900, C=60, Lq=40), dict(L=3000, C=600, Lq=150)]
+EMPTY = [dict(L=150, C=60, Lq=40), dict(L=800, C=600, Lq=150)]                   # some clusters have no keys
 
 
 @pytest.mark.parametrize("case", ONE_AND_TWO_LAUNCHES)
@@ -68,3 +81,35 @@ def test_a_score_that_is_not_a_number_keeps_nothing_of_its_row(sq, case, bad):
     T = np.full(w.H, 1e-4, np.float32)
     keep, nk, _ = per_query(sq, w, T, cent)
     assert not keep[:, 1].any() and (nk[:, 1] == 0).all() and keep[:, 0].any()
+
+
+@pytest.mark.parametrize("case", EMPTY)
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+def test_the_centroid_of_a_cluster_without_keys_may_hold_anything(sq, case, bad):
+    """A cluster without keys adds nothing to the normaliser and is never kept, whatever its centroid is (the mean of no keys
+    is NaN)."""
+    w = wl.make_workload("edges", seed=43, threads=1, B=1, H=2, U=20, keep_frac=0.3, causal_user=False, **case)
+    assert (w.sizes == 0).any(1).all()
+    cent = w.centroids.copy()
+    cent[w.sizes == 0] = bad
+    T = np.full(w.H, 1e-3, np.float32)
+    for fn in (per_query, averaged):
+        ref, got = fn(sq, w, T), fn(sq, w, T, cent)
+        assert ref[0].any()
+        for a, b in zip(ref, got):
+            np.testing.assert_array_equal(a, b)
+
+
+def test_the_same_below_a_coarse_level(sq):
+    w = wl.make_workload("edges_hier", seed=44, threads=1, B=1, H=2, L=500, C=320, C1=8, Lq=70, U=20, keep_frac=0.3,
+                         coarse_keep_frac=0.5, causal_user=False)
+    assert (w.sizes == 0).any(1).all()
+    cent = w.centroids.copy()
+    cent[w.sizes == 0] = np.nan
+    T1, T2 = np.full(w.H, 1e-4, np.float32), np.full(w.H, 1e-3, np.float32)
+    ref, got = hier_per_query(sq, w, T1, T2, w.centroids), hier_per_query(sq, w, T1, T2, cent)
+    assert ref[0].any()
+    for a, b in zip(ref, got):
+        np.testing.assert_array_equal(a, b)
+    keep, nk, _ = hier_per_query(sq, w, T1, np.array([1e-3, np.nan], np.float32), cent)
+    assert keep[:, 0].any() and not keep[:, 1].any() and (nk[:, 1] == 0).all()
