@@ -71,15 +71,44 @@ struct SlicePairs {
         for (int k = 0; k < LK_MAX_SLICES / STEP; ++k) m = fmaxf(m, v[k].x);
         return m;
     }
-    __device__ __forceinline__ float sum(float m) const     // relative to m >= largest(); 0 if nothing was scored
+    __device__ __forceinline__ float sum(float m, float c2) const   // relative to m >= largest(); 0 if nothing was scored
     {
         float d = 0.0f;
 #pragma unroll
         for (int k = 0; k < LK_MAX_SLICES / STEP; ++k)
-            if (v[k].y != 0.0f) d = fmaf(v[k].y, __builtin_amdgcn_exp2f(v[k].x - m), d);
+            if (v[k].y != 0.0f) d = fmaf(v[k].y, __builtin_amdgcn_exp2f((v[k].x - m) * c2), d);
         return d;
     }
 };
+
+// The least raw score x that passes exp2((x - m) c2) > thr, the test of Eq. 1's scores against T * D with m the row's largest
+// score: exactly the boundary of that float expression, so that a score which equals the threshold is dropped.  (thr < 0:
+// everything; thr >= 1 or not a number: nothing -- NaN, which no comparison passes.)  The differences that pass are an interval
+// [d, 0]; d is bisected from a bracket around the logarithm, wide enough for the rounding of the exponential (relative to d that
+// grows as 1 / |d c2|), or from all floats where the bracket does not hold it.  7 to 10 steps, once per token and workgroup.
+__device__ __forceinline__ float lk_least_kept(float m, float thr, float c2)
+{
+    if (thr < 0.0f) return SQ_NEG_INF;
+    if (!(thr < 1.0f)) return __builtin_nanf("");
+    auto passes = [&](uint32_t u) { return __builtin_amdgcn_exp2f(-__builtin_bit_cast(float, u) * c2) > thr; };
+    const float l = thr > 0.0f ? -log2f(thr) : 126.0f;
+    const uint32_t at = __builtin_bit_cast(uint32_t, fminf(l / c2, 3e38f)), w = (uint32_t)fminf(16.0f + 16.0f / l, 4e6f);
+    uint32_t lo = at > w ? at - w : 0u, hi = min(at + w, 0x7f800000u);   // (bit patterns of -d; -0 passes, -inf does not)
+    if (!passes(lo)) lo = 0u;
+    if (passes(hi)) hi = 0x7f800000u;
+    while (hi - lo > 1u) {
+        const uint32_t mid = lo + ((hi - lo) >> 1);
+        if (passes(mid)) lo = mid;
+        else hi = mid;
+    }
+    // x passes iff fl(x - m) >= d: the least one lies next to m + (d + the float below it) / 2
+    const float d = -__builtin_bit_cast(float, lo);
+    const double at_x = (double)m + 0.5 * ((double)d - (double)__builtin_bit_cast(float, hi));
+    float x = nextafterf((float)at_x, SQ_NEG_INF);
+    for (int i = 0; i < 2; ++i)
+        if (!(x - m >= d)) x = nextafterf(x, __builtin_inff());
+    return x;
+}
 
 // Which passes a launch makes.  BOTH: one launch for rows of few clusters, where a second launch costs more than slices give.
 enum LkMode { LK_STATS, LK_DECIDE, LK_BOTH };
@@ -133,20 +162,9 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
 #pragma unroll
         for (int s = 0; s < 8; ++s) bq[s] = qp[s * 2 + g];
     }
-    // The least raw score that is kept, from the row's reference m and normaliser relative to it.  (T D < 0: everything with
-    // keys; T D = 0: everything whose exponential does not vanish; T D not a number: nothing, no score is above it.)
-    float x_min = 0.0f;
-    auto set_threshold = [&](float m, float Dsum) {
-        const float thr = thresh[h] * Dsum;
-        const float cut = thr < 0.0f ? SQ_NEG_INF : (m + (thr > 0.0f ? log2f(thr) : -126.0f)) / c2;
-        x_min = thr > 0.0f ? nextafterf(cut, __builtin_inff()) : thr <= 0.0f ? cut : __builtin_nanf("");
-    };
-    if (MODE == LK_DECIDE) {
-        SlicePairs<2> sp;                                   // (the two lanes of a token take every other slice)
-        sp.load(stats + row * n_slice, g, n_slice);
-        const float m = cross32_max(sp.largest());
-        set_threshold(m, cross32_sum(m == SQ_NEG_INF ? 0.0f : sp.sum(m)));
-    }
+    float x_min = 0.0f;                                     // the least raw score that is kept
+    SlicePairs<MODE == LK_DECIDE ? 2 : LK_MAX_SLICES> sp;   // (the two lanes of a token take every other slice)
+    if (MODE == LK_DECIDE) sp.load(stats + row * n_slice, g, n_slice);
 
     const char *ch = reinterpret_cast<const char *>(cent + (size_t)h * C_all * D);
     const int32_t *Nh = sizes + (size_t)h * C_all;
@@ -182,13 +200,17 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
         __builtin_amdgcn_s_waitcnt(0x0f70);                 // this wave's loads to LDS have landed
     };
 
-    float ref = SQ_NEG_INF, lim = SQ_NEG_INF, refn = 0.0f, Dsum = 0.0f, keys = 0.0f;
+    float ref = SQ_NEG_INF, ref_f = 0.0f, Dsum = 0.0f, keys = 0.0f;   // largest score seen; the same, 0 before there is one
     auto sweep = [&](auto pass2) {
         constexpr bool DECIDE = decltype(pass2)::value;
         if (g0 < g1) {
             fetch_ids(g0);
             fetch(g0, 0);
             fetch_ids(g0 + 1);
+            if (MODE == LK_DECIDE) {                        // (under the loads of the first group)
+                const float m = cross32_max(sp.largest());
+                x_min = lk_least_kept(m, thresh[h] * cross32_sum(m == SQ_NEG_INF ? 0.0f : sp.sum(m, c2)), c2);
+            }
             commit(0, DECIDE);
         }
         __syncthreads();
@@ -238,8 +260,7 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
                     float mx = SQ_NEG_INF;                  // (NaN if a score is)
 #pragma unroll
                     for (int r = 0; r < 16; ++r) mx = __builtin_elementwise_maximum(mx, acc[r]);
-                    // (the reference moves when a score passes it by 2^8: the sum stays far inside fp32's range)
-                    if (__ballot(!(mx * c2 <= lim)) != 0ull) {
+                    if (__ballot(!(mx <= ref)) != 0ull) {
                         if (__ballot(mx != mx) != 0ull) {
                             // a cluster without keys whose centroid is not finite has -inf + inf or NaN here: -inf again
                             mx = SQ_NEG_INF;
@@ -249,16 +270,14 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
                                 mx = fmaxf(mx, acc[r]);
                             }
                         }
-                        mx *= c2;
                         if (mx > ref) {
-                            Dsum *= __builtin_amdgcn_exp2f(ref - mx);   // ref = -inf: Dsum is 0 and stays 0
-                            ref = mx;
-                            lim = mx + 8.0f;
-                            refn = -mx;
+                            Dsum *= __builtin_amdgcn_exp2f((ref - mx) * c2);   // ref = -inf: Dsum is 0 and stays 0
+                            ref = ref_f = mx;
                         }
                     }
+                    // (the difference first: it is exactly 0 for the largest score, so equal scores have equal, exact terms)
 #pragma unroll
-                    for (int r = 0; r < 16; ++r) Dsum = fmaf(nv[r], __builtin_amdgcn_exp2f(fmaf(acc[r], c2, refn)), Dsum);
+                    for (int r = 0; r < 16; ++r) Dsum = fmaf(nv[r], __builtin_amdgcn_exp2f((acc[r] - ref_f) * c2), Dsum);
                 } else {
                     uint32_t bits = 0u;
 #pragma unroll
@@ -285,10 +304,10 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
     if (MODE != LK_DECIDE) {
         sweep(std::false_type{});                           // the two halves of the wave hold the other clusters of the token
         const float mo = __shfl_xor(ref, 32), Do = __shfl_xor(Dsum, 32), M = fmaxf(ref, mo);
-        const float wa = ref == SQ_NEG_INF ? 0.0f : __builtin_amdgcn_exp2f(ref - M);
-        const float wb = mo == SQ_NEG_INF ? 0.0f : __builtin_amdgcn_exp2f(mo - M);
+        const float wa = ref == SQ_NEG_INF ? 0.0f : __builtin_amdgcn_exp2f((ref - M) * c2);
+        const float wb = mo == SQ_NEG_INF ? 0.0f : __builtin_amdgcn_exp2f((mo - M) * c2);
         Dsum = Dsum * wa + Do * wb;
-        if (MODE == LK_BOTH) set_threshold(M, Dsum);
+        if (MODE == LK_BOTH) x_min = lk_least_kept(M, thresh[h] * Dsum, c2);
         else if (g == 0 && valid) stats[row * n_slice + slice] = float2{M, Dsum};
     }
     if (MODE != LK_STATS) {
@@ -311,7 +330,7 @@ __global__ __launch_bounds__(256) void mean_scores_kernel(
     const int2 *__restrict__ cand_hdr, int n_slice, int H, int Lq, int C_all, float sm_scale)
 {
     __shared__ __align__(16) unsigned char stage[2 * LK_MT * D * 2];
-    __shared__ __align__(16) float s_m[2][LK_MT], s_inv[2][LK_MT];   // per token: minus the reference, 1 / D
+    __shared__ __align__(16) float s_m[2][LK_MT], s_inv[2][LK_MT];   // per token: the largest score, 1 / D
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 31, g = lane >> 5, l16 = lane & 15;
     const int bh = blockIdx.z, h = bh % H, part = blockIdx.y, n_part = gridDim.y;
@@ -346,11 +365,11 @@ __global__ __launch_bounds__(256) void mean_scores_kernel(
         float m = sp.largest();                             // the four lanes of a token take every fourth slice
         m = fmaxf(m, dpp_f<0xb1>(m));
         m = fmaxf(m, dpp_f<0x4e>(m));
-        float Dsum = m == SQ_NEG_INF ? 0.0f : sp.sum(m);
+        float Dsum = m == SQ_NEG_INF ? 0.0f : sp.sum(m, c2);
         Dsum += dpp_f<0xb1>(Dsum);
         Dsum += dpp_f<0x4e>(Dsum);
         if ((tid & 3) == 0) {
-            s_m[buf][tid >> 2] = m == SQ_NEG_INF ? 0.0f : -m;
+            s_m[buf][tid >> 2] = m == SQ_NEG_INF ? 0.0f : m;
             s_inv[buf][tid >> 2] = st_t < Lq && Dsum > 0.0f ? 1.0f / Dsum : 0.0f;
         }
         __builtin_amdgcn_s_waitcnt(0x0f70);                 // this wave's loads to LDS have landed
@@ -380,7 +399,7 @@ __global__ __launch_bounds__(256) void mean_scores_kernel(
                 const f4 mv = *reinterpret_cast<const f4 *>(&s_m[buf][u * 32 + a * 8 + g * 4]);
                 const f4 iv = *reinterpret_cast<const f4 *>(&s_inv[buf][u * 32 + a * 8 + g * 4]);
 #pragma unroll
-                for (int k = 0; k < 4; ++k) sum = fmaf(__builtin_amdgcn_exp2f(fmaf(acc[4 * a + k], c2, mv[k])), iv[k], sum);
+                for (int k = 0; k < 4; ++k) sum = fmaf(__builtin_amdgcn_exp2f((acc[4 * a + k] - mv[k]) * c2), iv[k], sum);
             }
         }
         if (tile + n_part < nt) commit(buf ^ 1);

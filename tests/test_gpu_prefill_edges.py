@@ -113,3 +113,31 @@ def test_the_same_below_a_coarse_level(sq):
         np.testing.assert_array_equal(a, b)
     keep, nk, _ = hier_per_query(sq, w, T1, np.array([1e-3, np.nan], np.float32), cent)
     assert keep[:, 0].any() and not keep[:, 1].any() and (nk[:, 1] == 0).all()
+
+
+def tied(C, live, keys, Lq, sm_scale):
+    """`live` of the C clusters hold `keys` keys each and share one centroid; the others hold none.  Every score is then
+    exactly 1 / (live * keys): exp(0) over a sum of exact terms."""
+    w = wl.make_workload("edges_tied", seed=45, threads=1, B=1, H=2, L=live * keys, C=C, Lq=Lq, U=4, keep_frac=0.3,
+                         causal_user=False)
+    rng = np.random.default_rng(2)
+    for h in range(w.H):
+        w.sizes[h] = 0
+        w.sizes[h, rng.choice(C, live, replace=False)] = keys
+        w.offsets[h, 1:] = np.cumsum(w.sizes[h])
+        w.centroids[h] = w.centroids[h, 0]
+    w.sm_scale = float(np.float32(sm_scale))
+    return w
+
+
+@pytest.mark.parametrize("case", [dict(C=8, live=8, keys=64), dict(C=1, live=1, keys=128), dict(C=700, live=16, keys=32)])
+@pytest.mark.parametrize("sm_scale", [128 ** -0.5, 1.0, 0.3])
+def test_a_score_that_equals_the_threshold_is_dropped(sq, case, sm_scale):
+    """The rule is score > T.  With the threshold at the tied score nothing is kept, one float below it everything is."""
+    w = tied(Lq=333, sm_scale=sm_scale, **case)
+    T = np.float32(1.0 / (case["live"] * case["keys"]))
+    for fn in (per_query, averaged):
+        keep, nk, _ = fn(sq, w, np.full(w.H, T, np.float32))
+        assert not keep.any() and (nk == 0).all(), (fn.__name__, keep.mean())
+        keep, nk, _ = fn(sq, w, np.full(w.H, np.nextafter(T, np.float32(0)), np.float32))
+        assert (nk == w.L).all(), (fn.__name__, (nk == w.L).mean())
