@@ -146,7 +146,8 @@ int sq_sparse_attn_decode(const sq_shape_t *shape, const void *q, const void *K_
 /*
  * Prefill-time sparse attention (Section 4.2) with PER-QUERY selection: query t of sequence b
  * attends to the keys of the clusters set in its own keep_mask row, plus user keys 0..t
- * (causal_user != 0) or all U user keys (causal_user == 0).
+ * (causal_user != 0) or all U user keys (causal_user == 0).  A key that a query does not see has no influence on it,
+ * whatever its key and value rows hold (infinities and NaN cost time: the outputs they reach are taken again, key by key).
  * In:  keep_mask u32 [B,H,Lq,ceil(C/32)], offsets i32 [H,C+1].
  * Out: out f16 [B,H,Lq,d]; lse f32 [B,H,Lq] or NULL.
  * Workspace: sq_workspace_bytes(shape, SQ_CALL_ATTN_PREFILL).

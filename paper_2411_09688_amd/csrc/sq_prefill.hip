@@ -315,51 +315,52 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
             mw_hi = w0 + 1 < W ? mrow[w0 + 1] : 0u;
         }
     };
-    // Keys of the block at walk position pos (entry e, table entry info) that this lane's query sees, as the accumulators
+    // Keys of the block with entry e (table entry info; pos: its walk position) that this lane's query sees, as the accumulators
     // hold them: bit 8 a + i of w[t] = key 32 t + 8 a + 4 g + i (i < 4).
-    auto visible = [&](int pos, int e, int info, uint32_t wl, uint32_t wh, uint32_t (&w)[2]) PF_INLINE {
-        if (SHARED || e < 0) {
-            // user keys: those at or before the query (causal); one kept set: all but the slots past the kept keys
-            const int n = (e >= 0 ? n_fixed : causal_user ? min(U, nqc + 1) : U) - (e & 0x7fffffff) * PF_BN;
-            const unsigned long long m = n >= 64 ? ~0ull : (1ull << max(n, 0)) - 1ull;
-            w[0] = (uint32_t)(m >> (4 * g)) & 0x0f0f0f0fu;
-            w[1] = (uint32_t)(m >> 32 >> (4 * g)) & 0x0f0f0f0fu;
-            return;
-        }
+    auto visible_edge = [&](int e, uint32_t (&w)[2]) PF_INLINE {
+        // user keys: those at or before the query (causal); one kept set: all but the slots past the kept keys
+        const int n = (e >= 0 ? n_fixed : causal_user ? min(U, nqc + 1) : U) - (e & 0x7fffffff) * PF_BN;
+        const unsigned long long m = n >= 64 ? ~0ull : (1ull << max(n, 0)) - 1ull;
+        w[0] = (uint32_t)(m >> (4 * g)) & 0x0f0f0f0fu;
+        w[1] = (uint32_t)(m >> 32 >> (4 * g)) & 0x0f0f0f0fu;
+    };
+    auto visible_runs = [&](int e, int info, uint32_t (&w)[2]) PF_INLINE {       // every run's bit from the mask itself
+        const uint32_t *rp = table + ((size_t)h * nblk_all + e) * PF_BN;
         w[0] = w[1] = 0u;
+        for (int i = 0; i < ((info >> 21) & 127); ++i) {
+            const uint32_t r = __builtin_amdgcn_readfirstlane(rp[i]), c = r & 0xffffu;
+            const unsigned long long ks = (~0ull >> (63 - (int)((r >> 22) & 63u))) << ((r >> 16) & 63u);
+            const uint32_t on = 0u - ((mrow[c >> 5] >> (c & 31u)) & 1u);
+            w[0] |= on & (uint32_t)(ks >> (4 * g)) & 0x0f0f0f0fu;
+            w[1] |= on & (uint32_t)(ks >> 32 >> (4 * g)) & 0x0f0f0f0fu;
+        }
+    };
+    auto visible = [&](int pos, int e, int info, uint32_t wl, uint32_t wh, uint32_t (&w)[2]) PF_INLINE {
+        if (SHARED || e < 0) return visible_edge(e, w);
         const int n = (info >> 21) & 127, first = info & 0xffff;
-        if (info >= 0 && n <= PF_ROW_RUNS) {
-            // bit (cluster - first cluster of the block) of the query's window, spread over the keys of its run
-            const uint32_t qb = __builtin_amdgcn_alignbit(wh, wl, (uint32_t)first & 31u) & 0x7fffffffu;
-            const uint32_t *row = s_tab + (pos & (PF_TABS - 1)) * PF_ROW_WORDS;
-            auto group = [&](int k) PF_INLINE {
-                const uint4 rel = *reinterpret_cast<const uint4 *>(row + k * PF_ROW_GROUP);
-                const uint4 k0 = *reinterpret_cast<const uint4 *>(row + k * PF_ROW_GROUP + 4 + 8 * g);
-                const uint4 k1 = *reinterpret_cast<const uint4 *>(row + k * PF_ROW_GROUP + 8 + 8 * g);
-                auto add = [&](uint32_t r, uint32_t a, uint32_t b) PF_INLINE {
-                    const uint32_t on = (uint32_t)__builtin_amdgcn_sbfe((int)qb, r, 1u);
-                    w[0] |= on & a;
-                    w[1] |= on & b;
-                };
-                add(rel.x, k0.x, k1.x);
-                add(rel.y, k0.y, k1.y);
-                add(rel.z, k0.z, k1.z);
-                add(rel.w, k0.w, k1.w);
+        if (info < 0 || n > PF_ROW_RUNS) return visible_runs(e, info, w);   // more than 31 cluster ids, or many runs
+        // bit (cluster - first cluster of the block) of the query's window, spread over the keys of its run
+        const uint32_t qb = __builtin_amdgcn_alignbit(wh, wl, (uint32_t)first & 31u) & 0x7fffffffu;
+        const uint32_t *row = s_tab + (pos & (PF_TABS - 1)) * PF_ROW_WORDS;
+        w[0] = w[1] = 0u;
+        auto group = [&](int k) PF_INLINE {
+            const uint4 rel = *reinterpret_cast<const uint4 *>(row + k * PF_ROW_GROUP);
+            const uint4 k0 = *reinterpret_cast<const uint4 *>(row + k * PF_ROW_GROUP + 4 + 8 * g);
+            const uint4 k1 = *reinterpret_cast<const uint4 *>(row + k * PF_ROW_GROUP + 8 + 8 * g);
+            auto add = [&](uint32_t r, uint32_t a, uint32_t b) PF_INLINE {
+                const uint32_t on = (uint32_t)__builtin_amdgcn_sbfe((int)qb, r, 1u);
+                w[0] |= on & a;
+                w[1] |= on & b;
             };
-            group(0);
-            if (n > 4) {
-                group(1);
-                group(2);
-            }
-        } else {                                            // many runs, or more than 31 cluster ids: every run's bit from the mask itself
-            const uint32_t *rp = table + ((size_t)h * nblk_all + e) * PF_BN;
-            for (int i = 0; i < n; ++i) {
-                const uint32_t r = __builtin_amdgcn_readfirstlane(rp[i]), c = r & 0xffffu;
-                const unsigned long long ks = (~0ull >> (63 - (int)((r >> 22) & 63u))) << ((r >> 16) & 63u);
-                const uint32_t on = 0u - ((mrow[c >> 5] >> (c & 31u)) & 1u);
-                w[0] |= on & (uint32_t)(ks >> (4 * g)) & 0x0f0f0f0fu;
-                w[1] |= on & (uint32_t)(ks >> 32 >> (4 * g)) & 0x0f0f0f0fu;
-            }
+            add(rel.x, k0.x, k1.x);
+            add(rel.y, k0.y, k1.y);
+            add(rel.z, k0.z, k1.z);
+            add(rel.w, k0.w, k1.w);
+        };
+        group(0);
+        if (n > 4) {
+            group(1);
+            group(2);
         }
     };
 
@@ -615,6 +616,56 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
             if (it > 0 && wave_on) any_nxt = start_scores(s_nxt, it + 1, uint2{0u, 0u});
         }
         for (; it < n_mine; it += NB) walks(std::true_type{});
+    }
+
+    // ---- values that are not finite ------------------------------------------------------------------------------------------
+    // The products of a block multiply the values of keys that a query does not see (and of rows past the end of a tensor) by 0,
+    // which is NaN where the value is infinite or NaN.  A query whose output is not finite (finite values cannot cause that) takes
+    // it again from the keys it sees alone, key by key: some thirty times the time of the wave's walk.
+    float unfit[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int r = 0; r < 16; ++r)
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt) unfit[dt] = fmaf(o[dt][r], 0.0f, unfit[dt]);
+    const float bad = cross32_sum((unfit[0] + unfit[1]) + (unfit[2] + unfit[3]));   // (a query's two lanes hold half of its dimensions each)
+    if (__ballot(bad != bad) != 0ull) {
+        const bool again = bad != bad;
+#pragma unroll
+        for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) o[dt][r] = again ? 0.0f : o[dt][r];
+#pragma unroll 1
+        for (int i = 0; i < n_mine; ++i) {
+            const bool user = i >= n_list;
+            const int blk = __builtin_amdgcn_readfirstlane(user ? u_first + (i - n_list) * n_split : SHARED ? split + i * n_split : (int)s_list[i]);
+            uint32_t w[2];
+            if (SHARED || user) visible_edge(user ? blk | (int)0x80000000 : blk, w);
+            else visible_runs(blk, binfo[blk], w);
+            const uint32_t seen[2] = {cross32_or(w[0] << (4 * g)), cross32_or(w[1] << (4 * g))};   // bit j: key j of the block
+#pragma unroll 1
+            for (int j = 0; j < PF_BN; ++j) {
+                const bool mine = again && ((seen[j >> 5] >> (j & 31)) & 1u);
+                if (__ballot(mine) == 0ull) continue;
+                const int r = blk * PF_BN + j;
+                const size_t row = (size_t)(SHARED && !user ? idx_bh[r] : r) * 256;   // (a key that is seen: within the tensor)
+                const h8 *kp = reinterpret_cast<const h8 *>((user ? Kuh : Kfh) + row);
+                float x = 0.0f;
+#pragma unroll
+                for (int s = 0; s < 8; ++s) x = dot8(kp[2 * s + g], bq[s], x);
+                const float p = (float)(_Float16)__builtin_amdgcn_exp2f(fmaf(cross32_sum(x), c2, mneg));
+                const h4 *vp = reinterpret_cast<const h4 *>((user ? Vuh : Vfh) + row);
+                if (mine) {
+#pragma unroll
+                    for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                        for (int a = 0; a < 4; ++a) {
+                            const h4 v = vp[dt * 8 + 2 * a + g];
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) o[dt][4 * a + k] = fmaf(p, (float)v[k], o[dt][4 * a + k]);
+                        }
+                }
+            }
+        }
     }
 
     // ---- normalise and store: lane holds query column nq, dims dt*32 + 8*a + 4*g + (0..3) --------------------------------

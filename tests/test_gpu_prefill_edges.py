@@ -1,9 +1,10 @@
-"""GPU parity at the edges of the prefill lookup: thresholds and centroids that are not numbers, exact ties."""
+"""GPU tests of the prefill calls at the edges of their inputs: thresholds, centroids and values that are not numbers, exact
+ties."""
 import numpy as np
 import pytest
 import torch
 
-from gpu_util import unpack_mask
+from gpu_util import ranges_from_keep, unpack_mask
 from paper_2411_09688_amd import workload as wl
 
 pytestmark = pytest.mark.gpu
@@ -141,3 +142,96 @@ def test_a_score_that_equals_the_threshold_is_dropped(sq, case, sm_scale):
         assert not keep.any() and (nk == 0).all(), (fn.__name__, keep.mean())
         keep, nk, _ = fn(sq, w, np.full(w.H, np.nextafter(T, np.float32(0)), np.float32))
         assert (nk == w.L).all(), (fn.__name__, (nk == w.L).mean())
+
+
+# ---- values of keys a query does not see ---------------------------------------------------------------------------------
+
+def masked_problem(sq, w, share, rng):
+    gk = rng.random((w.B, w.H, w.Lq, w.C)) < share
+    W = (w.C + 31) // 32
+    bits = np.zeros((w.B, w.H, w.Lq, W * 32), bool)
+    bits[..., :w.C] = gk
+    words = (bits.reshape(w.B, w.H, w.Lq, W, 32) * (1 << np.arange(32, dtype=np.uint64))).sum(-1).astype(np.uint32)
+    P = sq.upload(w)
+    P.keep_mask.copy_(torch.from_numpy(words.view(np.int32)))
+    return gk, P
+
+
+def run_masked(sq, P):
+    P.out.fill_(7.0)
+    sq.sq_sparse_attn_prefill(P.shape, P.q, P.K_fixed, P.V_fixed, P.offsets, P.keep_mask, P.K_user, P.V_user, P.out,
+                              P.lse, sq.workspace(P.shape, sq.SQ_CALL_ATTN_PREFILL, P.q.device))
+    torch.cuda.synchronize()
+    return P.out.cpu().numpy().astype(np.float64), P.lse.cpu().numpy()
+
+
+VALUE_CASES = [
+    dict(B=1, H=2, L=900, C=30, Lq=200, U=300),        # 4 keys in the last block of the context, user keys past the prompt
+    dict(B=2, H=12, L=3001, C=99, Lq=333, U=333),
+    dict(B=1, H=40, L=700, C=20, Lq=1024, U=1030),
+]
+
+
+@pytest.mark.parametrize("case", VALUE_CASES)
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+def test_hidden_values_may_hold_anything(sq, case, bad):
+    """A key that a query does not see has no influence on it, whatever its value row holds: clusters the query did not keep,
+    user keys after it.  A query that sees such a key gets it in the dimensions that hold it, and there alone."""
+    w = wl.make_workload("edges_values", seed=46, threads=2, keep_frac=0.3, causal_user=True, **case)
+    gk, P = masked_problem(sq, w, 0.3, np.random.default_rng(6))
+    ref, ref_lse = run_masked(sq, P)
+    c, late = 11, 150
+    for h in range(w.H):
+        P.V_fixed[h, w.offsets[h, c]:w.offsets[h, c + 1], 5] = bad
+        P.V_fixed[h, w.L - 1, 126] = bad
+    P.V_user[:, :, late, 77] = bad
+    P.V_user[:, :, w.Lq:] = bad
+    got, lse = run_masked(sq, P)
+    np.testing.assert_array_equal(lse, ref_lse)
+    last = [int(np.searchsorted(w.offsets[h], w.L, side="left")) - 1 for h in range(w.H)]
+    hit = np.zeros(got.shape, bool)
+    hit[..., 5] = gk[..., c]
+    for h in range(w.H):
+        hit[:, h, :, 126] = gk[:, h, :, last[h]]
+    hit[:, :, late:, 77] = True
+    assert hit.any() and np.abs(got - ref)[~hit].max() <= 1e-3
+    assert not np.isfinite(got[hit]).any()
+
+
+@pytest.mark.parametrize("case", VALUE_CASES)
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+def test_hidden_values_may_hold_anything_one_kept_set(sq, case, bad):
+    """The same where all tokens of a (sequence, head) share one kept set: what is not kept, and user keys after the query."""
+    w = wl.make_workload("edges_values", seed=47, threads=2, keep_frac=0.3, causal_user=True, **case)
+    P = sq.upload(w)
+    rng = np.random.default_rng(8)
+    kept = rng.random((w.B, w.H, w.C)) < 0.4
+    c = 11
+    kept[:, 0, c], kept[:, 1, c] = True, False
+    ranges = np.zeros((w.B, w.H, w.C, 2), np.int32)
+    nr = np.zeros((w.B, w.H), np.int32)
+    for b in range(w.B):
+        for h in range(w.H):
+            ranges[b, h], nr[b, h] = ranges_from_keep(kept[b, h], w.offsets[h], w.sizes[h], w.C)
+    nk = (kept * w.sizes[None]).sum(-1).astype(np.int32)
+
+    def attend():
+        P.out.fill_(7.0)
+        sq.sq_sparse_attn_prefill_shared(P.shape, P.q, P.K_fixed, P.V_fixed, t(ranges), t(nr), t(nk), P.K_user, P.V_user, P.out,
+                                         P.lse, sq.workspace(P.shape, sq.SQ_CALL_ATTN_PREFILL_SHARED, DEV))
+        torch.cuda.synchronize()
+        return P.out.cpu().numpy().astype(np.float64), P.lse.cpu().numpy()
+
+    ref, ref_lse = attend()
+    late = 150
+    for h in range(w.H):
+        P.V_fixed[h, w.offsets[h, c]:w.offsets[h, c + 1], 5] = bad
+    P.V_user[:, :, late, 77] = bad
+    P.V_user[:, :, w.Lq:] = bad
+    got, lse = attend()
+    np.testing.assert_array_equal(lse, ref_lse)
+    hit = np.zeros(got.shape, bool)
+    hit[..., 5] = kept[:, :, None, c]
+    hit[:, :, late:, 77] = True
+    assert np.abs(got - ref)[~hit].max() <= 1e-3
+    assert not np.isfinite(got[hit]).any()
