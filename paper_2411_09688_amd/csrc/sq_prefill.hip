@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256) void expand_ranges_kernel(DecodePlan plan, int
     }
 }
 
-constexpr int PF_LIST_CAP = 4096;         // fixed blocks per workgroup (the split keeps a share within it)
+constexpr int PF_LIST_CAP = 4096;         // fixed blocks per workgroup that are listed; a longer share is walked whole
 constexpr int PF_UMASK_WORDS = SELECT_MAX_C / 32;
 
 // s_um[0..W) |= keep masks of queries q0 .. q0+bm-1 (those below Lq) of query rows row0...; s_um zeroed by the caller,
@@ -209,7 +209,8 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     // ---- the blocks of this share, in order: fixed blocks (masked form: those in which a query of the workgroup kept a
     // cluster; nobody's blocks are neither fetched nor staged), then user blocks ------------------------------------------
     int n_list = (max(nblk_fixed - split, 0) + n_split - 1) / n_split;
-    if constexpr (!SHARED) {
+    const bool listed = !SHARED && n_list <= PF_LIST_CAP;
+    if (listed) {
         for (int w = tid; w < W; w += PF_THREADS) s_um[w] = 0u;
         __syncthreads();
         pf_union_mask(s_um, keep_mask, row0, q0, PF_BM, Lq, W, tid, PF_THREADS);
@@ -244,7 +245,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
         t_base = base;
         const int i = min(base + lane, n_mine - 1);
         const bool user = i >= n_list;
-        const int blk = user ? u_first + (i - n_list) * n_split : SHARED ? split + i * n_split : (int)s_list[i];
+        const int blk = user ? u_first + (i - n_list) * n_split : listed ? (int)s_list[i] : split + i * n_split;
         t_ent = user ? blk | (int)0x80000000 : blk;
         if (!SHARED) t_info = binfo[user ? 0 : blk];
     };
@@ -637,7 +638,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
 #pragma unroll 1
         for (int i = 0; i < n_mine; ++i) {
             const bool user = i >= n_list;
-            const int blk = __builtin_amdgcn_readfirstlane(user ? u_first + (i - n_list) * n_split : SHARED ? split + i * n_split : (int)s_list[i]);
+            const int blk = __builtin_amdgcn_readfirstlane(user ? u_first + (i - n_list) * n_split : listed ? (int)s_list[i] : split + i * n_split);
             uint32_t w[2];
             if (SHARED || user) visible_edge(user ? blk | (int)0x80000000 : blk, w);
             else visible_runs(blk, binfo[blk], w);
@@ -745,14 +746,12 @@ PfPlan prefill_plan(bool shared, const Shape &sh)
     const long long rows = (long long)sh.B * sh.H * sh.Lq;
     const long long fixed = ((long long)(shared ? (sh.L + 7) / 8 : sh.L) + PF_BN - 1) / PF_BN;
     const long long nblk = fixed + (sh.U + PF_BN - 1) / PF_BN;
-    // (the masked form lists the blocks of a share in LDS)
-    const int least = shared ? 1 : (int)((fixed + PF_LIST_CAP - 1) / PF_LIST_CAP);
-    PfPlan best{8, least};
+    PfPlan best{8, 1};
     double best_cost = 0.0;
     for (int waves = 8; waves >= 4; waves -= 4) {
         const long long slots = 256 * 8 / waves, bm = pf_bm(waves);
         const long long units = (long long)sh.B * sh.H * ((sh.Lq + bm - 1) / bm);
-        for (int s = least; s <= least || (s <= PF_MAX_SPLIT && s <= nblk && units * s <= 2 * slots); ++s) {
+        for (int s = 1; s == 1 || (s <= PF_MAX_SPLIT && s <= nblk && units * s <= 2 * slots); ++s) {
             const double rounds = (double)((units * s + slots - 1) / slots);
             const double cost = rounds * ((double)((nblk + s - 1) / s) + 6.0) + (s > 1 ? 3.0 + 1.5e-4 * (double)rows * s : 0.0);
             if (best_cost == 0.0 || cost < (waves < best.waves ? 0.9 * best_cost : best_cost)) {

@@ -59,6 +59,16 @@ def test_workspace_sizes(sq):
     assert sq.workspace_bytes(bad, sq.SQ_CALL_ATTN_DECODE) == 0
 
 
+@pytest.mark.parametrize("H,L,Lq", [(32, 524288, 32768), (8, 2097152, 4096), (32, 262144, 131072), (1, 300000, 200), (32, 32768, 1024),
+                                    (4, 100, 1)])
+def test_prefill_workspace_is_bounded(sq, H, L, Lq):
+    """Besides the block table (129 words per 64 keys and head) the masked prefill attention asks for partial results of at most
+    two rounds of workgroups (512 of 256 tokens or 1024 of 128, 528 bytes a token), whatever the context's length is."""
+    sh = sq.make_shape(1, H, L, 1024, Lq, Lq, 0.0884, causal_user=True)
+    table = H * ((L + 63) // 64) * 129 * 4
+    assert table <= sq.workspace_bytes(sh, sq.SQ_CALL_ATTN_PREFILL) <= table + 131072 * 528 + 1024
+
+
 def test_host_side_validation(sq):
     L = sq.lib()
     buf = (C.c_char * 4096)()

@@ -4,7 +4,7 @@ import numpy as np
 import pytest
 import torch
 
-from gpu_util import ranges_from_keep, unpack_mask
+from gpu_util import ATTN_ATOL, ranges_from_keep, unpack_mask
 from paper_2411_09688_amd import workload as wl
 
 pytestmark = pytest.mark.gpu
@@ -235,3 +235,28 @@ def test_hidden_values_may_hold_anything_one_kept_set(sq, case, bad):
     hit[:, :, late:, 77] = True
     assert np.abs(got - ref)[~hit].max() <= 1e-3
     assert not np.isfinite(got[hit]).any()
+
+
+@pytest.mark.parametrize("case", [
+    dict(B=520, H=1, L=64 * 4100 + 5, C=60, Lq=3, U=2),            # workgroups of four waves
+    dict(B=3, H=1, L=64 * 4100 + 5, C=60, Lq=64 * 700, U=2),       # of eight
+])
+def test_shares_longer_than_a_list(sq, oracle, case):
+    """Contexts of more blocks than a workgroup lists, with too many (head, query block) units to split: walked whole."""
+    w = wl.make_workload("edges_long", seed=48, threads=4, keep_frac=0.3, causal_user=False, **case)
+    gk, P = masked_problem(sq, w, 0.05, np.random.default_rng(9))
+    table = ((w.L + 63) // 64) * 129 * 4
+    assert sq.workspace_bytes(P.shape, sq.SQ_CALL_ATTN_PREFILL) < table + 1024          # no partial results: one share
+    got, lse = run_masked(sq, P)
+    R = (w.B, w.H, w.Lq)
+    sel = np.zeros(R, bool)
+    sel.ravel()[np.random.default_rng(10).choice(sel.size, size=200, replace=False)] = True
+    cap = int(gk.sum(-1)[sel].max()) + 1
+    ranges = np.zeros((*R, cap, 2), np.int32)
+    nr = np.zeros(R, np.int32)
+    for b, h, i in np.argwhere(sel):
+        ranges[b, h, i], nr[b, h, i] = ranges_from_keep(gk[b, h, i], w.offsets[h], w.sizes[h], cap)
+    out, ref = oracle.sparse_attn(w.q, w.K_fixed, w.V_fixed, ranges, nr, w.K_user, w.V_user, w.sm_scale, causal_user=False,
+                                  row_sel=sel)
+    assert np.abs(got[sel] - out[sel]).max() <= ATTN_ATOL
+    np.testing.assert_allclose(lse[sel], ref[sel], atol=2e-4, rtol=1e-5)
