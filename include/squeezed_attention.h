@@ -161,6 +161,14 @@ int sq_sparse_attn_prefill(const sq_shape_t *shape, const void *q, const void *K
                            void *out, float *lse, void *ws, size_t ws_bytes, void *stream);
 
 /*
+ * How the prefill attention of a shape is divided: every workgroup has *waves (8 or 4) waves of 32 query tokens, and the key
+ * blocks of its (sequence, head, group of tokens) are shared by *splits workgroups.  one_set != 0: the calls with one kept set
+ * per (sequence, head) (sq_sparse_attn_prefill_shared and the steps on averaged scores); 0: per-query selection.  Host only;
+ * results do not depend on it beyond the order of summation.
+ */
+int sq_prefill_plan(const sq_shape_t *shape, int one_set, int32_t *waves, int32_t *splits);
+
+/*
  * Prefill selection as the paper does it (Appendix D, "Prefill Stage"): the cluster scores of Eq. 1,
  * S_i(t) = exp(x_i(t) - m(t)) / D(t), are averaged over the Lq query tokens of a (sequence, head) and
  * cluster i is kept iff N_i > 0 and the average is > thresh[h] (strict): ONE kept set for all query

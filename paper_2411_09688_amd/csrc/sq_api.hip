@@ -881,6 +881,17 @@ int sq_decode_step(const sq_shape_t *sh, const void *q, const void *centroids, c
     return SQ_OK;
 }
 
+int sq_prefill_plan(const sq_shape_t *sh, int one_set, int32_t *waves, int32_t *splits)
+{
+    if (int rc = check_shape(sh, __func__, false)) return rc;
+    if (!waves || !splits) return fail(SQ_ERR_INVALID_ARG, "%s: waves or splits is NULL", __func__);
+    const sq::PfPlan plan = sq::prefill_plan(one_set != 0, to_shape(sh));
+    *waves = plan.waves;
+    *splits = plan.n_split;
+    g_err[0] = 0;
+    return SQ_OK;
+}
+
 int sq_sparse_attn_prefill(const sq_shape_t *sh, const void *q, const void *K_fixed, const void *V_fixed,
                            const int32_t *offsets, const uint32_t *keep_mask, const void *K_user, const void *V_user,
                            void *out, float *lse, void *ws, size_t ws_bytes, void *stream)

@@ -186,11 +186,14 @@ hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void 
                                       DecodePlan plan, int32_t *key_idx, float *partials, void *out, float *lse,
                                       const Shape &sh, hipStream_t s);
 
-// Both forms deal a unit's key blocks to prefill_splits() workgroups where (heads x query blocks) alone do not fill the
+// Both forms deal a unit's key blocks to n_split workgroups (of `waves` waves, 32 queries each) where (heads x query blocks) alone do not fill the
 // chip; their partial results (m, l, -, -, o[128]) per (query row, share) go through `partials`
 // (prefill_partial_floats() floats, 0 without a split) to a merge launch.
 constexpr int PF_MAX_SPLIT = 64;
-int prefill_splits(bool shared, const Shape &sh);
+struct PfPlan {
+    int waves, n_split;
+};
+PfPlan prefill_plan(bool shared, const Shape &sh);
 size_t prefill_partial_floats(bool shared, const Shape &sh);
 
 // Offline clustering (sq_kmeans.hip).  hn: [heads * C] floats; hist: [heads * parts * C] ints with

@@ -737,10 +737,6 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
 //   eight / four waves  32 heads x 1024 tokens x 32K keys 582 / 605 us, 2 x 12 heads x 333 tokens x 9001 keys 84 / 76 us;
 //   one / several shares  20 heads x 17 tokens x 22682 keys (20 units) 491 / 82 us, averaged selection 20 heads x 150 tokens x
 //   20011 keys (40 units) 92 / 56 us, two-level step of 8 heads x 512 tokens x 262144 keys 664 / 270 us.
-namespace {
-struct PfPlan {
-    int waves, n_split;
-};
 PfPlan prefill_plan(bool shared, const Shape &sh)
 {
     const long long rows = (long long)sh.B * sh.H * sh.Lq;
@@ -762,13 +758,10 @@ PfPlan prefill_plan(bool shared, const Shape &sh)
     }
     return best;
 }
-}  // namespace
-
-int prefill_splits(bool shared, const Shape &sh) { return prefill_plan(shared, sh).n_split; }
 
 size_t prefill_partial_floats(bool shared, const Shape &sh)
 {
-    const int s = prefill_splits(shared, sh);
+    const int s = prefill_plan(shared, sh).n_split;
     return s > 1 ? (size_t)sh.B * sh.H * sh.Lq * s * PART_STRIDE : 0;
 }
 

@@ -1,0 +1,128 @@
+"""GPU parity of every form of the prefill attention kernels: workgroups of eight and of four waves, one and several shares of
+the key blocks, block lists built in several rounds, walks longer than the entries held in registers.  Each case states the
+division that sq_prefill_plan reports for it, so that a changed rule cannot leave a form untested unnoticed."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import ATTN_ATOL, ranges_from_keep
+from paper_2411_09688_amd import workload as wl
+from test_gpu_prefill import banded_keep
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+@pytest.fixture(scope="module")
+def sq():
+    from paper_2411_09688_amd import binding
+    binding.lib()
+    return binding
+
+
+def t(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def sample_rows(w, n, seed):
+    sel = np.zeros((w.B, w.H, w.Lq), bool)
+    sel.ravel()[np.random.default_rng(seed).choice(sel.size, size=min(n, sel.size), replace=False)] = True
+    sel[0, 0, 0] = sel[-1, -1, -1] = True
+    return sel
+
+
+def compare(oracle, w, P, ranges, nr, sel):
+    out, lse = oracle.sparse_attn(w.q, w.K_fixed, w.V_fixed, ranges, nr, w.K_user, w.V_user, w.sm_scale,
+                                  causal_user=w.causal_user, row_sel=sel)
+    got, glse = P.out.cpu().numpy().astype(np.float64), P.lse.cpu().numpy()
+    assert np.abs(got[sel] - out[sel]).max() <= ATTN_ATOL
+    fin = np.isfinite(lse[sel])
+    assert (np.isneginf(glse[sel]) == ~fin).all()
+    np.testing.assert_allclose(glse[sel][fin], lse[sel][fin], atol=2e-4, rtol=1e-5)
+
+
+def needed_share(w, gk, queries):
+    """Share of the (wave, listed block) pairs with a kept key: a wave owns 32 queries, a workgroup lists what its waves need."""
+    nblk, need, listed = (w.L + 63) // 64, 0, 0
+    for h in range(w.H):
+        cid = np.repeat(np.arange(w.C), w.sizes[h])
+        for b in range(0, w.B, max(1, w.B // 8)):
+            for g in range(0, w.Lq, queries):
+                waves = [np.add.reduceat(gk[b, h, a:min(a + 32, g + queries)].any(0)[cid], np.arange(0, w.L, 64)) > 0
+                         for a in range(g, min(g + queries, w.Lq), 32)]
+                need += sum(int(v.sum()) for v in waves)
+                listed += int(np.any(waves, axis=0).sum()) * len(waves)
+    return need / listed
+
+
+MASKED = [
+    (8, 1, dict(B=200, H=1, L=64 * 600 + 9, C=300, Lq=150, U=5)),       # 601 blocks a share: the list is built in two rounds
+    (4, 1, dict(B=500, H=1, L=64 * 300 + 7, C=150, Lq=3, U=70)),        # 301: two rounds of 256 threads
+    (8, 5, dict(B=2, H=12, L=3001, C=99, Lq=333, U=333)),
+    (4, 6, dict(B=2, H=40, L=4096, C=100, Lq=120, U=120)),
+    (8, 2, dict(B=1, H=32, L=64 * 150, C=300, Lq=1000, U=64)),           # 75 listed blocks
+]
+
+
+@pytest.mark.parametrize("waves,splits,case", MASKED)
+@pytest.mark.parametrize("masks", ["random", "positions"])
+def test_per_query_selection(sq, oracle, waves, splits, case, masks):
+    """Explicit masks, drawn for every query by itself (every wave needs nearly every block) or in bands that 32 queries share."""
+    w = wl.make_workload("prefill_forms", seed=51, threads=4, keep_frac=0.3, causal_user=True, **case)
+    rng = np.random.default_rng(12)
+    if masks == "random":
+        gk = rng.random((w.B, w.H, w.Lq, w.C)) < 0.4
+    else:
+        gk = banded_keep(w, rng, max(4, w.C // 8), 1, qb=32)
+    W = (w.C + 31) // 32
+    bits = np.zeros((w.B, w.H, w.Lq, W * 32), bool)
+    bits[..., :w.C] = gk
+    words = (bits.reshape(w.B, w.H, w.Lq, W, 32) * (1 << np.arange(32, dtype=np.uint64))).sum(-1).astype(np.uint32)
+    P = sq.upload(w)
+    assert sq.sq_prefill_plan(P.shape) == (waves, splits)
+    share = needed_share(w, gk, 32 * waves)
+    assert share > 0.9 if masks == "random" else share < 0.7 or w.Lq <= 32
+    P.keep_mask.copy_(torch.from_numpy(words.view(np.int32)))
+    P.out.fill_(7.0)
+    sq.sq_sparse_attn_prefill(P.shape, P.q, P.K_fixed, P.V_fixed, P.offsets, P.keep_mask, P.K_user, P.V_user, P.out, P.lse,
+                              sq.workspace(P.shape, sq.SQ_CALL_ATTN_PREFILL, DEV))
+    torch.cuda.synchronize()
+    sel = sample_rows(w, 400, 13)
+    cap = int(gk.sum(-1)[sel].max()) + 1
+    ranges = np.zeros((w.B, w.H, w.Lq, cap, 2), np.int32)
+    nr = np.zeros((w.B, w.H, w.Lq), np.int32)
+    for b, h, i in np.argwhere(sel):
+        ranges[b, h, i], nr[b, h, i] = ranges_from_keep(gk[b, h, i], w.offsets[h], w.sizes[h], cap)
+    compare(oracle, w, P, ranges, nr, sel)
+
+
+ONE_SET = [
+    (8, 1, dict(B=200, H=1, L=64 * 300 + 9, C=300, Lq=150, U=5)),
+    (4, 1, dict(B=500, H=1, L=64 * 200 + 7, C=150, Lq=3, U=70)),
+    (8, 3, dict(B=2, H=12, L=3001, C=99, Lq=333, U=333)),
+    (4, 11, dict(B=1, H=40, L=20000, C=600, Lq=33, U=33)),
+]
+
+
+@pytest.mark.parametrize("waves,splits,case", ONE_SET)
+@pytest.mark.parametrize("share", [0.02, 0.6])
+def test_one_kept_set(sq, oracle, waves, splits, case, share):
+    w = wl.make_workload("prefill_forms_one", seed=52, threads=4, keep_frac=0.3, causal_user=True, **case)
+    kept = np.random.default_rng(14).random((w.B, w.H, w.C)) < share
+    P = sq.upload(w)
+    assert sq.sq_prefill_plan(P.shape, one_set=True) == (waves, splits)
+    ranges = np.zeros((w.B, w.H, w.C, 2), np.int32)
+    nr = np.zeros((w.B, w.H), np.int32)
+    for b in range(w.B):
+        for h in range(w.H):
+            ranges[b, h], nr[b, h] = ranges_from_keep(kept[b, h], w.offsets[h], w.sizes[h], w.C)
+    nk = (kept * w.sizes[None]).sum(-1).astype(np.int32)
+    P.out.fill_(7.0)
+    sq.sq_sparse_attn_prefill_shared(P.shape, P.q, P.K_fixed, P.V_fixed, t(ranges), t(nr), t(nk), P.K_user, P.V_user, P.out,
+                                     P.lse, sq.workspace(P.shape, sq.SQ_CALL_ATTN_PREFILL_SHARED, DEV))
+    torch.cuda.synchronize()
+    sel = sample_rows(w, 400, 15)
+    cap = max(1, int(nr.max()))
+    rr = np.ascontiguousarray(np.broadcast_to(ranges[:, :, None, :cap], (w.B, w.H, w.Lq, cap, 2)))
+    nn = np.ascontiguousarray(np.broadcast_to(nr[:, :, None], (w.B, w.H, w.Lq)))
+    compare(oracle, w, P, rr, nn, sel)
