@@ -133,6 +133,71 @@ __device__ __forceinline__ void static_for(F &&f)
 }
 #define PF_INLINE __attribute__((always_inline))          // (a lambda left as a call would put what it captures in memory)
 
+// The outputs of queries (the active lanes; lane = query column + 32 g, as in prefill_attn_kernel) from the keys they see alone,
+// key by key, some thirty times the time of the kernel's walk: for queries whose output is not finite.  A function of its own, not
+// inlined: as part of the kernel its code lengthened the walk of workgroups with idle waves (32 heads x 150 tokens x 32K keys 175
+// -> 184 us).  seen_user: user keys the query sees; dst: the query's output, to be multiplied by scale, or, with several shares,
+// its 128 partial sums.  The other arguments: see the kernel (uniform ones arrive in vector registers).
+template <bool SHARED>
+__device__ __attribute__((noinline)) void prefill_again(const _Float16 *q_row, const char *Kf, const char *Vf, const char *Ku,
+                                                        const char *Vu, const uint32_t *mrow, const void *table,
+                                                        const int32_t *binfo, void *dst, int split, int n_split, int n_fixed, int U,
+                                                        int seen_user, float c2, float mneg, float scale)
+{
+    const int lane = threadIdx.x & 63, g = lane >> 5;
+    h8 bq[8];
+#pragma unroll
+    for (int s = 0; s < 8; ++s) bq[s] = reinterpret_cast<const h8 *>(q_row)[s * 2 + g];
+    f4 o[16];                                               // dimensions 8 i + 4 g + (0..3)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[i] = f4{0.f, 0.f, 0.f, 0.f};
+    n_split = __builtin_amdgcn_readfirstlane(n_split);
+    n_fixed = __builtin_amdgcn_readfirstlane(n_fixed);
+    const int nblk_fixed = (n_fixed + PF_BN - 1) / PF_BN, nblk = nblk_fixed + (__builtin_amdgcn_readfirstlane(U) + PF_BN - 1) / PF_BN;
+    for (int i = __builtin_amdgcn_readfirstlane(split); i < nblk; i += n_split) {   // (fixed blocks, then user blocks: dealt as in the kernel)
+        const bool user = i >= nblk_fixed;
+        const int blk = user ? i - nblk_fixed : i;
+        unsigned long long seen = 0ull;                     // bit j: the query sees key j of the block
+        if (SHARED || user) {
+            const int n = (user ? seen_user : n_fixed) - blk * PF_BN;
+            seen = n >= 64 ? ~0ull : (1ull << max(n, 0)) - 1ull;
+        } else {
+            const uint32_t *rp = static_cast<const uint32_t *>(table) + (size_t)blk * PF_BN;
+            for (int k = 0; k < ((binfo[blk] >> 21) & 127); ++k) {
+                const uint32_t c = rp[k] & 0xffffu;
+                if ((mrow[c >> 5] >> (c & 31u)) & 1u) seen |= (~0ull >> (63 - (int)((rp[k] >> 22) & 63u))) << ((rp[k] >> 16) & 63u);
+            }
+        }
+        for (int j = 0; j < PF_BN; ++j) {
+            const bool mine = (seen >> j) & 1u;
+            if (__ballot(mine) == 0ull) continue;
+            const int r = blk * PF_BN + j;                  // (a key that is seen: within the tensor)
+            const size_t row = (size_t)(SHARED && !user ? static_cast<const int32_t *>(table)[r] : r) * 256;
+            const h8 *kp = reinterpret_cast<const h8 *>((user ? Ku : Kf) + row);
+            float x = 0.0f;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) x = dot8(kp[2 * s + g], bq[s], x);
+            const float p = (float)(_Float16)__builtin_amdgcn_exp2f(fmaf(cross32_sum(x), c2, mneg));
+            const h4 *vp = reinterpret_cast<const h4 *>((user ? Vu : Vf) + row);
+            if (mine) {
+#pragma unroll
+                for (int i8 = 0; i8 < 16; ++i8) {
+                    const h4 v = vp[2 * i8 + g];
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) o[i8][k] = fmaf(p, (float)v[k], o[i8][k]);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+        if (n_split > 1)
+            *reinterpret_cast<f4 *>(static_cast<float *>(dst) + 8 * i + 4 * g) = o[i];
+        else
+            *reinterpret_cast<h4 *>(static_cast<_Float16 *>(dst) + 8 * i + 4 * g) = h4{(_Float16)(o[i][0] * scale), (_Float16)(o[i][1] * scale),
+                                                                                      (_Float16)(o[i][2] * scale), (_Float16)(o[i][3] * scale)};
+}
+
 // SHARED: table is the key-row list [B*H, L] and blk_info the per-row (records, kept keys) headers; keep_mask is not
 // used.  Otherwise table / rows / blk_info are the block table (block_table_kernel).
 template <bool SHARED, int PF_WAVES>
@@ -622,82 +687,51 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     // ---- values that are not finite ------------------------------------------------------------------------------------------
     // The products of a block multiply the values of keys that a query does not see (and of rows past the end of a tensor) by 0,
     // which is NaN where the value is infinite or NaN.  A query whose output is not finite (finite values cannot cause that) takes
-    // it again from the keys it sees alone, key by key: some thirty times the time of the wave's walk.
+    // it again from the keys it sees alone.
     float unfit[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int r = 0; r < 16; ++r)
 #pragma unroll
         for (int dt = 0; dt < 4; ++dt) unfit[dt] = fmaf(o[dt][r], 0.0f, unfit[dt]);
     const float bad = cross32_sum((unfit[0] + unfit[1]) + (unfit[2] + unfit[3]));   // (a query's two lanes hold half of its dimensions each)
-    if (__ballot(bad != bad) != 0ull) {
-        const bool again = bad != bad;
-#pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) o[dt][r] = again ? 0.0f : o[dt][r];
-#pragma unroll 1
-        for (int i = 0; i < n_mine; ++i) {
-            const bool user = i >= n_list;
-            const int blk = __builtin_amdgcn_readfirstlane(user ? u_first + (i - n_list) * n_split : listed ? (int)s_list[i] : split + i * n_split);
-            uint32_t w[2];
-            if (SHARED || user) visible_edge(user ? blk | (int)0x80000000 : blk, w);
-            else visible_runs(blk, binfo[blk], w);
-            const uint32_t seen[2] = {cross32_or(w[0] << (4 * g)), cross32_or(w[1] << (4 * g))};   // bit j: key j of the block
-#pragma unroll 1
-            for (int j = 0; j < PF_BN; ++j) {
-                const bool mine = again && ((seen[j >> 5] >> (j & 31)) & 1u);
-                if (__ballot(mine) == 0ull) continue;
-                const int r = blk * PF_BN + j;
-                const size_t row = (size_t)(SHARED && !user ? idx_bh[r] : r) * 256;   // (a key that is seen: within the tensor)
-                const h8 *kp = reinterpret_cast<const h8 *>((user ? Kuh : Kfh) + row);
-                float x = 0.0f;
-#pragma unroll
-                for (int s = 0; s < 8; ++s) x = dot8(kp[2 * s + g], bq[s], x);
-                const float p = (float)(_Float16)__builtin_amdgcn_exp2f(fmaf(cross32_sum(x), c2, mneg));
-                const h4 *vp = reinterpret_cast<const h4 *>((user ? Vuh : Vfh) + row);
-                if (mine) {
-#pragma unroll
-                    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-                        for (int a = 0; a < 4; ++a) {
-                            const h4 v = vp[dt * 8 + 2 * a + g];
-#pragma unroll
-                            for (int k = 0; k < 4; ++k) o[dt][4 * a + k] = fmaf(p, (float)v[k], o[dt][4 * a + k]);
-                        }
-                }
-            }
-        }
-    }
+    const bool again = bad != bad;
 
     // ---- normalise and store: lane holds query column nq, dims dt*32 + 8*a + 4*g + (0..3) --------------------------------
     const float lt = cross32_sum(l_run);
     if (nq >= Lq) return;
+    const bool empty = !(lt > 0.0f);
+    const float inv = empty ? 0.0f : 1.0f / lt;
+    _Float16 *orow = out + (row0 + nq) * D;
+    float *pr = partials + ((row0 + nq) * (size_t)n_split + split) * PART_STRIDE;
     if (n_split > 1) {                                      // this share's (m, l, o) for the merge launch; m in natural units
-        float *pr = partials + ((row0 + nq) * (size_t)n_split + split) * PART_STRIDE;
+        if (!again)
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt)
+            for (int dt = 0; dt < 4; ++dt)
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
-                *reinterpret_cast<f4 *>(pr + 4 + dt * 32 + 8 * a + 4 * g) = f4{o[dt][4 * a], o[dt][4 * a + 1], o[dt][4 * a + 2], o[dt][4 * a + 3]};
+                for (int a = 0; a < 4; ++a)
+                    *reinterpret_cast<f4 *>(pr + 4 + dt * 32 + 8 * a + 4 * g) = f4{o[dt][4 * a], o[dt][4 * a + 1], o[dt][4 * a + 2], o[dt][4 * a + 3]};
         if (g == 0) {
             pr[0] = m_ref * sm_scale;
             pr[1] = lt;
         }
-        return;
+    } else {
+        if (!again)
+#pragma unroll
+            for (int dt = 0; dt < 4; ++dt)
+#pragma unroll
+                for (int a = 0; a < 4; ++a) {
+                    h4 hv;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) hv[v] = (_Float16)(o[dt][4 * a + v] * inv);
+                    *reinterpret_cast<h4 *>(orow + dt * 32 + 8 * a + 4 * g) = hv;
+                }
+        if (lse && g == 0) lse[row0 + nq] = empty ? SQ_NEG_INF : m_ref * sm_scale + logf(lt);
     }
-    const bool empty = !(lt > 0.0f);
-    const float inv = empty ? 0.0f : 1.0f / lt;
-    _Float16 *orow = out + (row0 + nq) * D;
-#pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
-#pragma unroll
-        for (int a = 0; a < 4; ++a) {
-            h4 hv;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) hv[v] = (_Float16)(o[dt][4 * a + v] * inv);
-            *reinterpret_cast<h4 *>(orow + dt * 32 + 8 * a + 4 * g) = hv;
-        }
-    if (lse && g == 0) lse[row0 + nq] = empty ? SQ_NEG_INF : m_ref * sm_scale + logf(lt);
+    if (again)
+        prefill_again<SHARED>(q + (row0 + nq) * D, Kfh, Vfh, Kuh, Vuh, mrow,
+                              SHARED ? (const void *)idx_bh : (const void *)(table + (size_t)h * nblk_all * PF_BN), binfo,
+                              n_split > 1 ? (void *)(pr + 4) : (void *)orow, split, n_split, n_fixed, U,
+                              causal_user ? min(U, nq + 1) : U, c2, mneg, inv);
 }
 
 // Merges the n_split partial results of a query row: one wave per row, two dimensions per lane.  Bound by the partials'
