@@ -76,22 +76,21 @@ __global__ __launch_bounds__(256) void expand_ranges_kernel(DecodePlan plan, int
 constexpr int PF_LIST_CAP = 4096;         // fixed blocks per workgroup that are listed; a longer share is walked whole
 constexpr int PF_UMASK_WORDS = SELECT_MAX_C / 32;
 
-// s_um[0..W) |= keep masks of queries q0 .. q0+bm-1 (those below Lq) of query rows row0...; s_um zeroed by the caller,
-// barrier after it by the caller.  A mask word of eight queries per item: eight independent loads, one LDS atomic.
-__device__ __forceinline__ void pf_union_mask(uint32_t *s_um, const uint32_t *__restrict__ keep_mask, size_t row0, int q0,
-                                              int bm, int Lq, int W, int tid, int threads)
+// s_um[v * W + 0..W) |= keep masks of the 32 queries of wave v, v = 0..waves-1, those below Lq, of query rows row0...; s_um zeroed
+// by the caller, barrier after it by the caller.  A mask word of eight queries per item: eight independent loads, one LDS atomic.
+__device__ __forceinline__ void pf_union_masks(uint32_t *s_um, const uint32_t *__restrict__ keep_mask, size_t row0, int q0,
+                                               int waves, int Lq, int W, int tid, int threads)
 {
-    for (int idx = tid; idx < (bm / 8) * W; idx += threads) {
+    for (int idx = tid; idx < 4 * waves * W; idx += threads) {
         const int g = idx / W, w = idx - g * W;
         uint32_t acc = 0u;
 #pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (q0 + g * 8 + k < Lq) acc |= keep_mask[(row0 + q0 + g * 8 + k) * W + w];
-        if (acc) atomicOr(&s_um[w], acc);
+        for (int k = 0; k < 8; ++k) acc |= keep_mask[(row0 + min(q0 + g * 8 + k, Lq - 1)) * W + w];   // (past the end: the last row again)
+        if (q0 + g * 8 < Lq && acc) atomicOr(&s_um[(g >> 2) * W + w], acc);
     }
 }
 
-// Does a workgroup whose queries' masks OR to s_um need the block with table entry bi?  (A block that spans more
+// Does a wave whose queries' masks OR to s_um need the block with table entry bi?  (A block that spans more
 // cluster ids than the window is not decided here: needed.)
 __device__ __forceinline__ bool pf_block_needed(int bi, const uint32_t *s_um, int W)
 {
@@ -103,6 +102,16 @@ __device__ __forceinline__ bool pf_block_needed(int bi, const uint32_t *s_um, in
     return ((uint32_t)(two >> (first & 31)) & present) != 0u;
 }
 
+// The masked form walks its blocks in one of two ways, chosen by every workgroup from the keep masks when it lists its blocks.
+// Where most waves need most of the listed blocks, the pipelined walk (see the head of the file).  Where a wave needs fewer than
+// 3/4 of them -- selections that follow the position or that neighbouring queries share -- the sparse walk: a wave does a block
+// it needs from scores to output product in one go and leaves the others out, and with four tiles the blocks of a barrier's
+// pair come from the two halves of the list, so that waves of different positions work side by side.  Attention call, us,
+// 32 heads x 1024 tokens x 32K keys (256 queries a workgroup), pipelined walk / sparse walk, share of (wave, block) pairs needed:
+//   kept clusters in a band of 1/8 per 64 queries 226 / 209 (1/4), per 32 queries 312 / 276 (1/5), per 128 149 / 146 (1/2);
+//   1/8 of the clusters anywhere, shared by 64 queries 402 / 335 (0.4), by 16 queries 540 / 460 (0.55); 0.16 554 / 529 (0.65),
+//   0.2 568 / 573 (0.75), 0.25 571 / 611 (0.8); by nobody 542 / 636 (1).
+constexpr int PF_SPARSE_NUM = 3, PF_SPARSE_DEN = 4;
 constexpr int PF_AHEAD = 4;                                 // operands requested from LDS ahead of their product
 constexpr int pf_bm(int waves) { return 32 * waves; }       // queries per workgroup
 
@@ -215,9 +224,10 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     constexpr int NB = pf_bufs(SHARED, PF_WAVES), LV = NB / 2, LK = LV + 1;   // iteration it fetches V of block it + LV, K of block it + LK
     __shared__ __align__(16) unsigned char stage[2 * NB * PF_TILE];   // NB tiles of K, then NB tiles of V
     __shared__ __align__(16) uint32_t s_tab[SHARED ? 1 : PF_TABS * PF_ROW_WORDS];
-    __shared__ uint32_t s_um[SHARED ? 1 : PF_UMASK_WORDS];  // OR of the keep masks of the workgroup's queries
     __shared__ uint16_t s_list[SHARED ? 1 : PF_LIST_CAP];   // the fixed blocks this workgroup walks
-    __shared__ int s_wc[PF_WAVES];
+    __shared__ int s_wc[PF_WAVES], s_act[PF_WAVES];
+    __shared__ uint8_t s_need[SHARED ? 1 : PF_LIST_CAP];    // bit v: wave v has a query that kept a key of the listed block
+    __shared__ __align__(16) uint32_t s_mw[SHARED ? 1 : PF_WAVES][NB][64];   // mask words of a wave's queries for the blocks at hand (sparse walk)
     __shared__ __align__(16) float s_hide[16 * 4];          // entry n: the start values of four scores whose visibility bits are n
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -271,19 +281,28 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     const int32_t *binfo = blk_info + (size_t)h * nblk_all;
     const uint32_t *mrow = keep_mask + (row0 + nqc) * W;    // mask row of this lane's query
 
-    // ---- the blocks of this share, in order: fixed blocks (masked form: those in which a query of the workgroup kept a
-    // cluster; nobody's blocks are neither fetched nor staged), then user blocks ------------------------------------------
+    // ---- the blocks of this share: fixed blocks (masked form: those in which a query of the workgroup kept a cluster, with the
+    // waves that need them; nobody's blocks are neither fetched nor staged), then user blocks -------------------------------
     int n_list = (max(nblk_fixed - split, 0) + n_split - 1) / n_split;
     const bool listed = !SHARED && n_list <= PF_LIST_CAP;
+    bool sparse = false;
     if (listed) {
-        for (int w = tid; w < W; w += PF_THREADS) s_um[w] = 0u;
+        uint32_t *s_um = reinterpret_cast<uint32_t *>(stage);             // per wave: OR of the keep masks of its queries
+        static_assert(sizeof(stage) >= PF_WAVES * PF_UMASK_WORDS * 4, "the unions lie where the tiles will be");
+        for (int w = tid; w < PF_WAVES * W; w += PF_THREADS) s_um[w] = 0u;
         __syncthreads();
-        pf_union_mask(s_um, keep_mask, row0, q0, PF_BM, Lq, W, tid, PF_THREADS);
+        pf_union_masks(s_um, keep_mask, row0, q0, PF_WAVES, Lq, W, tid, PF_THREADS);
         __syncthreads();
-        int base = 0;
+        int base = 0, active = 0;                           // blocks listed; (wave, block) pairs with a kept key, of this thread's blocks
         for (int i0 = 0; i0 < n_list; i0 += PF_THREADS) {   // in order: a ballot per wave, the waves' counts in LDS
             const int bb = split + (i0 + tid) * n_split;
-            const bool need = i0 + tid < n_list && pf_block_needed(binfo[bb], s_um, W);
+            int waves = 0;
+            if (i0 + tid < n_list) {
+                const int bi = binfo[bb];
+                for (int v = 0; v < PF_WAVES; ++v) waves |= (int)pf_block_needed(bi, s_um + v * W, W) << v;
+            }
+            const bool need = waves != 0;
+            active += __popc(waves);
             const unsigned long long bal = __ballot(need);
             if (lane == 0) s_wc[wave] = __popcll(bal);
             __syncthreads();
@@ -293,26 +312,44 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
                 if (w < wave) before += s_wc[w];
                 total += s_wc[w];
             }
-            if (need)
-                s_list[base + before + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0))] = (uint16_t)bb;
+            if (need) {
+                const int at = base + before + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
+                s_list[at] = (uint16_t)bb;
+                s_need[at] = (uint8_t)waves;
+            }
             base += total;
             __syncthreads();
         }
         n_list = __builtin_amdgcn_readfirstlane(base);
+        const int act = (int)wave_sum((float)active);
+        if (lane == 0) s_act[wave] = act;
+        __syncthreads();
+        int all = 0;
+#pragma unroll
+        for (int w = 0; w < PF_WAVES; ++w) all += s_act[w];
+        all = __builtin_amdgcn_readfirstlane(all);
+        sparse = all * PF_SPARSE_DEN < n_list * min(PF_WAVES, (Lq - q0 + 31) >> 5) * PF_SPARSE_NUM;   // (of the waves with queries)
     }
+    const int half = NB == 4 && sparse ? (n_list + 1) >> 1 : 0;   // (position 2 i + 1 is listed half a list behind position 2 i)
     const int u_first = (split + n_split - nblk_fixed % n_split) % n_split;   // first user block of the share
     const int n_mine = n_list + (max(nblk_user - u_first, 0) + n_split - 1) / n_split;
     // The walk's next entries, one per lane: lane i holds position t_base + i (past the end: the last one again) as block | user
     // flag << 31, and a fixed block's table entry.  Read with v_readlane, refilled every few dozen blocks: scalar values that
     // cost one instruction each.
-    int t_base = 0, t_ent = 0, t_info = 0;
+    int t_base = 0, t_ent = 0, t_info = 0, t_need = 0;
     auto fill_entries = [&](int base) PF_INLINE {
         t_base = base;
         const int i = min(base + lane, n_mine - 1);
         const bool user = i >= n_list;
-        const int blk = user ? u_first + (i - n_list) * n_split : listed ? (int)s_list[i] : split + i * n_split;
+        const int li = half ? (i >> 1) + (i & 1) * half : i;
+        const int blk = user ? u_first + (i - n_list) * n_split : listed ? (int)s_list[li] : split + i * n_split;
         t_ent = user ? blk | (int)0x80000000 : blk;
-        if (!SHARED) t_info = binfo[user ? 0 : blk];
+        if (!SHARED) {
+            t_info = binfo[user ? 0 : blk];
+            // (waited for here: left pending, it makes the compiler wait in every block, for the tiles on their way as well)
+            asm volatile("" : "+v"(t_info));
+            t_need = user || !listed ? 0xff : s_need[li];
+        }
     };
     constexpr int T_KEEP = 56;                              // entries used of a fill: the loop looks up to seven ahead
 
@@ -370,7 +407,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_at(s_tab) + (uint32_t)(pos & (PF_TABS - 1)) * (PF_ROW_WORDS * 4)),
                      "v"(lane * 4), "s"(p) : "m0");
     };
-    uint32_t mw_lo = 0u, mw_hi = 0u;
+    uint32_t mw_lo = 0u, mw_hi = 0u;                        // (pipelined walk)
     int mw_at = -1;
     auto fetch_words = [&](int info) PF_INLINE {
         if (SHARED) return;
@@ -494,10 +531,88 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
         }
     };
 
-    if (n_mine > 0) {                                       // (no kept key and no user key: nothing to do)
+    auto ent = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_ent, i - t_base); };
+    auto inf = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_info, i - t_base); };
+    if (!SHARED && sparse && n_mine > 0) {                  // the sparse walk
         fill_entries(0);
-        auto ent = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_ent, i - t_base); };
-        auto inf = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_info, i - t_base); };
+        // What the block at position pos needs, behind the barrier that ends the pair before it (NB = 2: the block before it): its
+        // tiles, its table row and, for a wave that needs the block, the two words of its queries' masks that hold the block's window
+        // of clusters (lane = query + 32 word).
+        const uint32_t *mw_base = keep_mask + (row0 + min(q0w, Lq - 1)) * W;
+        const uint32_t mw_row = (uint32_t)(nqc - min(q0w, Lq - 1)) * (uint32_t)W;
+        auto needed = [&](int pos) PF_INLINE { return wave_on && ((__builtin_amdgcn_readlane(t_need, pos - t_base) >> wave_u) & 1); };
+        auto fetch_window = [&](int pos, int slot) PF_INLINE {
+            const int w0 = (inf(pos) & 0xffff) >> 5;        // (a window that begins in the last word needs no second one)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds_at(&s_mw[wave_u][slot][0])),
+                         "v"((mw_row + (uint32_t)min(w0 + g, W - 1)) * 4u), "s"(mw_base) : "m0");
+        };
+        auto fetch_at = [&](int pos, auto tile) PF_INLINE {
+            const int e = ent(pos);
+            const Aim aim = aim_at(e);
+#pragma unroll
+            for (int i = 0; i < PF_NP; ++i) {
+                fetch_piece(i, aim.k, aim.end, false, Rows{}, k_at, k_ch, tile * PF_TILE);
+                fetch_piece(i, aim.v, aim.end, false, Rows{}, v_at, v_ch, V_AT + tile * PF_TILE);
+            }
+            fetch_tab(pos, e);
+            if (needed(pos)) fetch_window(pos, tile);
+        };
+        fetch_at(0, std::integral_constant<int, 0>{});
+        if (NB == 4) fetch_at(1, std::integral_constant<int, 1>{});
+        loads_landed();
+        __syncthreads();
+        auto step = [&](int it, auto par) PF_INLINE {
+            constexpr uint32_t at = par * PF_TILE;
+            if (NB == 2) fetch_at(it + 1, std::integral_constant<int, (par + 1) % NB>{});
+            else if (par % 2 == 0) {                        // both of the next pair: its loads have this pair's time to land
+                fetch_at(it + 2, std::integral_constant<int, (par + 2) % NB>{});
+                fetch_at(it + 3, std::integral_constant<int, (par + 3) % NB>{});
+            }
+            uint32_t w[2] = {0u, 0u};
+            if (needed(it)) visible(it, ent(it), inf(it), s_mw[wave_u][par][col], s_mw[wave_u][par][32 + col], w);
+            if (__ballot((w[0] | w[1]) != 0u) != 0ull) {
+                f16v sc[2];
+#pragma unroll
+                for (int gi = 0; gi < 8; ++gi) start_group(sc, w, gi);
+#pragma unroll
+                for (int m = 0; m < 16; ++m)
+                    sc[m & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(k_operand(at, m), bq[m >> 1], sc[m & 1], 0, 0, 0);
+                float mx = SQ_NEG_INF, ps0 = 0.0f, ps1 = 0.0f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) mx = max_pair(mx, sc, i);
+                new_max(mx, sc, w[0], w[1]);
+                h8 bp[4];
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int t = i >> 3, r = 2 * (i & 7);
+                    const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[t][r], c2, mneg));
+                    const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[t][r + 1], c2, mneg));
+                    ps0 += p0;
+                    ps1 += p1;
+                    bp[2 * t + (r >> 3)][r & 7] = (_Float16)p0;
+                    bp[2 * t + (r >> 3)][(r & 7) + 1] = (_Float16)p1;
+                }
+                l_run += ps0 + ps1;
+#pragma unroll
+                for (int m = 0; m < 16; ++m)
+                    o[m & 3] = __builtin_amdgcn_mfma_f32_32x32x16_f16(v_operand(at, m), bp[m >> 2], o[m & 3], 0, 0, 0);
+            }
+            if (it + 1 - t_base >= T_KEEP) fill_entries(it + 1);
+            if (NB == 2 || (par & 1)) {
+                loads_landed();
+                __syncthreads();
+            }
+        };
+        for (int it = 0; it < n_mine; it += NB) {
+            step(it, std::integral_constant<int, 0>{});
+            if (it + 1 < n_mine) step(it + 1, std::integral_constant<int, 1>{});
+            if constexpr (NB == 4) {
+                if (it + 2 < n_mine) step(it + 2, std::integral_constant<int, 2>{});
+                if (it + 3 < n_mine) step(it + 3, std::integral_constant<int, 3>{});
+            }
+        }
+    } else if (n_mine > 0) {                                // (no kept key and no user key: nothing to do)
+        fill_entries(0);
         f16v s_cur[2], s_nxt[2];
         uint32_t vis0 = 0u, vis1 = 0u;                      // visible keys of the block whose start values were made last
         uint2 w2{}, w3{};                                   // mask words of blocks it + 2, it + 3
@@ -580,9 +695,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
                 else fetch_piece(x >> 1, aim_k.k, aim_k.end, gk, rk, k_at, k_ch, to_k);
             };
             // A wave that sees no key of the three blocks at hand has nothing to do: hidden scores stay -inf, whatever block they
-            // belong to.  (Where selections follow the position, most waves skip most of the workgroup's blocks.  32 heads x 1024 tokens x
-            // 32K keys, every 256 / 64 tokens sharing a band of 1/8 of the clusters: 123 / 317 us without this, 126 / 248 with it;
-            // the form before, which listed blocks per 64 queries, 168 / 197.)
+            // belong to.  (User keys after the wave's queries; runs of blocks that only other waves need.)
             bool any_new = true, on = wave_on;
             if (MASKED && on && !any_cur && !any_nxt) {
                 uint32_t w[2] = {0u, 0u};
