@@ -35,9 +35,13 @@ namespace sq {
 
 constexpr int LK_G = 64;                     // centroids per staged group
 constexpr int LK_BT = 128;                   // tokens per workgroup (four waves x 32)
-// Rows of at most so many clusters are decided in one launch.  Whole steps, two launches / one: 75 clusters (16 x 28 tokens)
-// 28.0 / 24.4 us, 250 clusters (4 heads x 333 tokens) 45.4 / 46.1, 500 clusters (the same) 46.4 / 55.0.
-constexpr int LK_ONE_C = 256;
+// Rows of at most so many clusters are decided in one launch.  Whole steps, two launches / one, us, 32 keys per cluster:
+//   clusters                     75            128            192            250            320
+//    1 head  x   16 tokens   25.2 / 22.1    25.6 / 22.3    27.8 / 26.1    28.9 / 29.7    29.9 / 32.3
+//   16 heads x   28 tokens   28.9 / 25.5    31.6 / 28.4    31.8 / 30.6    34.7 / 35.8    36.7 / 39.8
+//    4 heads x  333 tokens   36.8 / 33.7    39.8 / 36.9    41.9 / 41.3    44.5 / 46.1    46.0 / 49.7
+//   32 heads x 1024 tokens   87.7 / 82.6   112.3 / 107.9  151.9 / 146.7  179.6 / 179.0  218.7 / 212.6
+constexpr int LK_ONE_C = 192;
 constexpr int LK_MAX_W1 = 32;                // level-1 mask words per token held in LDS: at most 1024 coarse clusters
 
 // Rows of 256 B staged unpadded by the load-to-LDS instruction (a wave writes four whole rows); 16-byte chunk c of row r sits

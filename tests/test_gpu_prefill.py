@@ -423,8 +423,10 @@ def test_prefill_split_shares(sq, oracle, case):
 
 
 @pytest.mark.parametrize("case", [
-    dict(B=1, H=1, L=3000, C=256, Lq=129, U=0),       # the most clusters decided in one launch, a second block of tokens
-    dict(B=2, H=1, L=3000, C=257, Lq=31, U=3),        # one more: two launches, slices of one group
+    dict(B=1, H=1, L=3000, C=192, Lq=129, U=0),       # the most clusters decided in one launch, a second block of tokens
+    dict(B=2, H=1, L=3000, C=193, Lq=31, U=3),        # one more: two launches, slices of one group
+    dict(B=1, H=1, L=3000, C=256, Lq=129, U=0),       # whole groups of clusters
+    dict(B=2, H=1, L=3000, C=257, Lq=31, U=3),        # a last group of one
     dict(B=1, H=1, L=9000, C=2113, Lq=1, U=0),        # as many slices as there are, a ragged last one
     dict(B=1, H=2, L=500, C=1100, Lq=65, U=7),        # empty clusters
 ])
