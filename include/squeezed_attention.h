@@ -152,8 +152,9 @@ int sq_sparse_attn_decode(const sq_shape_t *shape, const void *q, const void *K_
  * Out: out f16 [B,H,Lq,d]; lse f32 [B,H,Lq] or NULL.
  * Workspace: sq_workspace_bytes(shape, SQ_CALL_ATTN_PREFILL).
  * Cost: the keys are walked in blocks of 64 by groups of 256 consecutive query tokens (128 where that pads less); a
- * block in which no token of the group kept a cluster is not read at all.  Where sequences x heads x groups do not fill
- * the chip, the blocks of a group are split over several workgroups and their partial results merged.
+ * block in which no token of the group kept a cluster is not read, unless it spans more than 31 cluster ids or a
+ * workgroup's share is longer than 4096 blocks.  Where sequences x heads x groups do not fill the chip, the blocks of a
+ * group are split over several workgroups and their partial results merged.
  */
 int sq_sparse_attn_prefill(const sq_shape_t *shape, const void *q, const void *K_fixed, const void *V_fixed,
                            const int32_t *offsets, const uint32_t *keep_mask,
@@ -302,9 +303,9 @@ int sq_gqa_mean_decode_step(const sq_shape_t *shape, int32_t G, const void *q, c
 /*
  * One whole prefill step with PER-QUERY selection: the lookup of sq_centroid_score + sq_select for every
  * query token, then sq_sparse_attn_prefill.  The lookup makes two passes over the centroids (normaliser,
- * then scores; Section 4.1), both spread over slices of the clusters, and writes no [queries x clusters] intermediate.  Its normaliser is summed in
- * a different order than sq_centroid_score's, so a cluster whose score is within rounding of the threshold
- * may be decided differently from the separate calls; everything else is identical.
+ * then scores; Section 4.1), both spread over slices of the clusters, and writes no [queries x clusters] intermediate.
+ * Its normaliser is summed in a different order than sq_centroid_score's, so a cluster whose score is within rounding of
+ * the threshold may be decided differently from the separate calls; everything else is identical.
  * Out: out f16 [B,H,Lq,d]; optional (NULL to skip): lse f32 [B,H,Lq], keep_mask u32 [B,H,Lq,ceil(C/32)],
  *      n_keys i32 [B,H,Lq].
  * Workspace: sq_workspace_bytes(shape, SQ_CALL_PREFILL_STEP).

@@ -460,7 +460,7 @@ PrefillMeanStepWs carve_prefill_mean_step(Carver &cv, const sq_shape_t *sh)
     const size_t rows = (size_t)sh->B * sh->H;
     PrefillMeanStepWs w{};
     w.stats = cv.take<float>(sq::lookup_stat_floats((int)rows, sh->Lq, sh->C));
-    w.part_sum = cv.take<float>(sq::lookup_part_floats((int)rows, sh->Lq, sh->C));
+    w.part_sum = cv.take<float>(sq::lookup_part_floats((int)rows, sh->C));
     w.n_ranges = cv.take<int32_t>(rows);
     w.n_keys = cv.take<int32_t>(rows);
     w.att = carve_prefill_shared(cv, sh);

@@ -24,8 +24,11 @@ struct BlockTable {
     int C, L, nblk;
 };
 
-// It depends on the offsets alone, so a whole step makes it in extra workgroups of the lookup's first launch (a launch of its
-// own: 9 us at 32 heads x 512 blocks, 5 us at 12 x 141).  A workgroup of 256 threads makes PF_TAB_BLOCKS blocks' entries.
+// It depends on the offsets alone, so a whole step makes it in extra workgroups of the lookup's first launch.  That lengthens
+// that launch by about what a launch of its own takes (12 us at 32 heads x 512 blocks), but saves the launch: whole steps, with a
+// launch of its own / in the lookup's, us: 2 x 12 heads x 333 tokens x 9001 keys 80.2 / 77.2, 8 heads x 60 tokens x 32K keys
+// 56.7 / 53.6, 16 heads x 28 tokens x 2400 keys 31.6 / 25.5, 32 heads x 1024 tokens x 32K keys the same (603 / 604).
+// A workgroup of 256 threads makes PF_TAB_BLOCKS blocks' entries.
 constexpr int PF_TAB_BLOCKS = 16;
 inline int block_table_groups(int nblk) { return (nblk + PF_TAB_BLOCKS - 1) / PF_TAB_BLOCKS; }
 

@@ -68,7 +68,7 @@ hipError_t launch_mean_score(const float *logits, const float *row_max, const fl
 constexpr int LK_MAX_SLICES = 32;
 int lookup_slices(int BH, int Lq, int C);
 int lookup_parts(int BH, int Lq, int C);
-size_t lookup_part_floats(int BH, int Lq, int C);
+size_t lookup_part_floats(int BH, int C);
 inline size_t lookup_stat_floats(int BH, int Lq, int C) { return (size_t)BH * Lq * lookup_slices(BH, Lq, C) * 2; }
 hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int32_t *sizes, const float *thresh,
                                  float *stats, uint32_t *keep_mask, int32_t *n_keys, float *part_sum, bool mean,

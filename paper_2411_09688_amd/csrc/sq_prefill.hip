@@ -18,12 +18,15 @@
 //   * masks cost no vector arithmetic per score: a lane's visible keys of a block are two words (one AND/OR pair per run of
 //     keys of one cluster, prepared by a table launch), and the score products start from 0 (visible) or -inf (hidden),
 //     four start values per LDS read from a 16-entry table.
-// What it is bound by at 32 heads x 1024 tokens x 32K keys (549 GFLOP executed): about 3600 cycles per block and pair of waves
-// against 2050 of matrix work, at the 1.9 GHz the chip holds under this load -- 1.06 PFLOP/s in the kernel, where the
-// library's large fp16 product reaches 1.18 on the same card.  The form before it (16 queries per wave, masks and maxima on
-// every score, phases one after the other): 755 us; 32 queries per wave in that order 595; this order 515.  Timing-only builds
-// of it: without loads -9 %, without LDS operand reads -11 %, without exponentials -12 %, without products -25 %
-// (sum of nothing dominates).
+//   * a workgroup whose waves need only part of the blocks it lists (neighbouring queries that keep the same clusters) takes the
+//     sparse walk instead, in which a wave does a block from scores to output product in one go (see PF_SPARSE_NUM);
+//   * outputs that infinite or NaN values made NaN are taken again at the end (prefill_again).
+// What it is bound by at 32 heads x 1024 tokens x 32K keys (560 GFLOP executed, padding included): about 3600 cycles per block and
+// pair of waves against 2050 of matrix work.  The traced kernel takes 527 to 706 us, 576 on average (the clock follows the load):
+// 0.97 PFLOP/s, 1.06 at best, where the library's large fp16 product reaches 1.18 on the same card.  Whole step: 819 us with the
+// form before it (16 queries per wave, masks and maxima on every score, phases one after the other), 660 with 32 queries per wave
+// in that order, 580 in this one.  Timing-only builds of it: without loads -9 %, without LDS operand reads -11 %, without
+// exponentials -12 %, without products -25 % (sum of nothing dominates).
 // The user block is causal when causal_user is set (query t sees user keys 0..t); the fixed context is
 // always fully visible.
 //
@@ -122,12 +125,6 @@ constexpr int pf_bm(int waves) { return 32 * waves; }       // queries per workg
 constexpr int pf_bufs(bool shared, int waves) { return waves == 8 && !shared ? 4 : 2; }
 constexpr uint32_t PF_TILE = PF_BN * D * 2;                 // bytes of a K or V tile
 constexpr int PF_TABS = 4;                // block table rows in LDS: the block's whose start values are made and the next ones
-
-// (mask & a) | (~mask & b) on the bit patterns of floats: one v_bfi_b32.
-__device__ __forceinline__ float select_bits(uint32_t mask, float a, float b)
-{
-    return __builtin_bit_cast(float, (mask & __builtin_bit_cast(uint32_t, a)) | (~mask & __builtin_bit_cast(uint32_t, b)));
-}
 
 // f(0), f(1), ... f(N - 1) with the index a compile-time constant.
 template <int N, typename F, int... I>
@@ -880,10 +877,16 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
 // query blocks).  With u units and s shares the launch takes ceil(u s / slots) rounds of ceil(blocks / s) blocks each plus
 // a fixed part (prologue, first loads, partial results: about six blocks' time), and the merge launch costs its own start
 // and the partials' bytes.  In the shared-set form the number of kept keys is not known on the host: an eighth of the context
-// is assumed (the rule only moves time, not results).  Eight waves unless four promise a tenth less.  Measured, whole steps:
-//   eight / four waves  32 heads x 1024 tokens x 32K keys 582 / 605 us, 2 x 12 heads x 333 tokens x 9001 keys 84 / 76 us;
-//   one / several shares  20 heads x 17 tokens x 22682 keys (20 units) 491 / 82 us, averaged selection 20 heads x 150 tokens x
-//   20011 keys (40 units) 92 / 56 us, two-level step of 8 heads x 512 tokens x 262144 keys 664 / 270 us.
+// is assumed (the rule only moves time, not results).  Eight waves unless four promise a tenth less.  Whole steps, us, the
+// rule's shares / one share / half as many / twice as many, and all with eight / with four waves:
+//   per query  32 heads x 1024 tokens x 32768 keys (8 waves, 2 shares)    608 /  950 / 948 / 652    605 / 623
+//              32 heads x  150 tokens x 32768 keys (8, 8)                 184 /  902 / 275 / 205    184 / 186
+//              2 x 12 heads x 333 tokens x 9001 keys (4, 7)              78.5 /  204 /  97 /  93     87 /  78
+//              20 heads x   17 tokens x 22682 keys (4, 24)               68.5 /  413 /  69 /  77     79 /  69
+//               5 heads x  600 tokens x 12000 keys (8, 17)               58.4 /  333 /  76 /  79     59 /  55
+//   one set    32 heads x 1024 tokens x 32768 keys (8, 2)                 160 /  199 / 196 / 173    160 / 163
+//              20 heads x  150 tokens x 20011 keys (8, 11)               42.1 /   83 /  44 /  51     42 /  43
+//               8 heads x  512 tokens x 262144 keys, two-level (8, 16)    128 /  535 / 148 / 146    128 / 130
 PfPlan prefill_plan(bool shared, const Shape &sh)
 {
     const long long rows = (long long)sh.B * sh.H * sh.Lq;

@@ -2,12 +2,13 @@
 // stream the centroids once; both are spread over (sequence, head) x blocks of query tokens x slices of the clusters, so that
 // a few tokens or heads still fill the chip.
 //
-//   lookup_pass_kernel<DECIDE = false>  per (token, slice): a reference r and sum_i N_i exp(x_i - r) over the slice's clusters
-//                  (Eq. 1's normaliser), 8 bytes each.
+//   lookup_pass_kernel<LK_STATS>        per (token, slice): the largest score r and sum_i N_i exp(x_i - r) over the slice's
+//                  clusters (Eq. 1's normaliser), 8 bytes each.
 //   then, with the slices' pairs merged per token:
-//   lookup_pass_kernel<DECIDE = true>   per-query selection: keep cluster i for token t iff N_i > 0 and
-//                  exp(x_i - m) > T * D, compared as x_i >= (log(T D) + m): one comparison per (token, cluster), its bit
-//                  shifted into the token's mask word.
+//   lookup_pass_kernel<LK_DECIDE>       per-query selection: keep cluster i for token t iff N_i > 0 and
+//                  exp(x_i - m) > T * D, compared as x_i >= the least score that passes (lk_least_kept): one comparison per
+//                  (token, cluster), its bit shifted into the token's mask word.
+//   (lookup_pass_kernel<LK_BOTH>        both in one launch, for rows of few clusters)
 //   mean_scores_kernel                  selection on averaged scores (Appendix D, "Prefill Stage"), first half: the scores
 //                  S_i(t) = exp(x_i - m) / D are summed over the tokens per cluster and written as part_sum
 //                  [B*H, lookup_parts(), C]; the row-wise selection kernel adds the parts.
@@ -22,9 +23,10 @@
 // token column and 16 clusters per tile, so normaliser and threshold test are per-lane scalars) and the four waves of a
 // workgroup share the centroid stream, groups of 64 that travel straight from global memory into one of two LDS buffers.  The
 // averaged form is turned round (S = Q C^T: a lane owns one cluster column and sums over the tokens in its registers; the
-// waves share the staged queries).  Bound by vector instructions: 5 per (token, cluster) in the first pass, 3 in the second.
-// 32 heads x 1024 tokens x 1024 clusters: 20 + 20 us (one launch of two passes over 16x16x32 tiles, a workgroup per 64 tokens: 55 us;
-// averaged 20 + 21 against 61 us); 20 heads x 150 tokens x 613 clusters 6 + 7 against 26.
+// waves share the staged queries).  Bound by vector instructions: 6 per (token, cluster) in the first pass, 3 in the second.
+// 32 heads x 1024 tokens x 1024 clusters, traced: sums 20.9 us by themselves and 32.7 with the block table of the attention in the
+// same launch, decisions 22, averages 22 (one launch of two passes over 16x16x32 tiles, a workgroup per 64 tokens and no block
+// table in it: 55 us, averaged 61); 20 heads x 150 tokens x 613 clusters 6.8 + 6.1 against 26.
 #include <algorithm>
 #include <type_traits>
 
@@ -430,9 +432,8 @@ int lookup_parts(int BH, int Lq, int C)
     return (int)std::max(1ll, std::min(512 / blocks, tiles));
 }
 
-size_t lookup_part_floats(int BH, int Lq, int C)
+size_t lookup_part_floats(int BH, int C)
 {
-    (void)Lq;
     return (size_t)BH * C + 512 * LK_MC;                    // parts * C * BH for this C and any smaller one (see lookup_parts)
 }
 
