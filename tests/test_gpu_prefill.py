@@ -92,9 +92,8 @@ def test_prefill_empty_and_keep_all(sq, oracle):
 
 
 def banded_keep(w, rng, band, extra, qb=64):
-    """Keep sets that follow the query's position: the 64 queries of a query block share a band of clusters (plus
-    `extra` stray clusters per block, and a few queries that keep nothing), so most key blocks are kept by no
-    query of the block."""
+    """Keep sets that follow the query's position: `qb` consecutive queries share a band of clusters (plus `extra` stray
+    clusters per group, and a few queries that keep nothing), so most key blocks are kept by no query of the group."""
     gk = np.zeros((w.B, w.H, w.Lq, w.C), bool)
     for b in range(w.B):
         for h in range(w.H):
@@ -114,20 +113,21 @@ def banded_keep(w, rng, band, extra, qb=64):
 @pytest.mark.parametrize("case", [
     dict(B=1, H=2, L=8192, C=512, Lq=200, U=64, band=48, extra=2, causal_user=True),
     dict(B=2, H=2, L=5000, C=300, Lq=130, U=0, band=30, extra=0, causal_user=False),      # ragged, no user keys
-    dict(B=1, H=2, L=5000, C=300, Lq=200, U=0, band=30, extra=0, causal_user=False, blank=(64, 128)),   # a query block with nothing to attend to
+    dict(B=1, H=2, L=5000, C=300, Lq=200, U=0, band=30, extra=0, causal_user=False, blank=(64, 128)),   # waves with nothing to attend to
+    dict(B=1, H=2, L=5000, C=300, Lq=300, U=0, band=30, extra=0, causal_user=False, blank=(0, 256)),    # a whole workgroup with nothing to attend to
     dict(B=1, H=1, L=4096, C=4096, Lq=64, U=40, band=400, extra=3, causal_user=True),     # empty clusters: wide blocks
-    dict(B=1, H=2, L=40000, C=2000, Lq=100, U=30, band=150, extra=4, causal_user=True),   # 625 key blocks: the list is built in rounds
+    dict(B=1, H=2, L=40000, C=2000, Lq=100, U=30, band=150, extra=4, causal_user=True),   # 625 key blocks over many shares
 ])
 def test_prefill_masks_that_follow_position(sq, oracle, case):
-    """Explicit keep masks under which most (query block, key block) pairs hold no kept key: the kernel that walks only
-    the listed blocks does the work (its rule: an eighth of the pairs or more can be skipped)."""
+    """Explicit keep masks under which most (64 queries, key block) pairs hold no kept key: a workgroup lists the blocks that
+    its queries kept, and its waves leave out those that their 32 queries do not need."""
     case = dict(case); band = case.pop("band"); extra = case.pop("extra"); blank = case.pop("blank", None)
     w = wl.make_workload("prefill_banded", seed=23, threads=2, keep_frac=0.1, **case)
     rng = np.random.default_rng(5)
     gk = banded_keep(w, rng, band, extra)
     if blank:
         gk[:, :, blank[0]:blank[1]] = False
-    # share of (query block, key block) pairs without a kept key
+    # share of (64 queries, key block) pairs without a kept key
     nblk = (w.L + 63) // 64
     skip = tot = 0
     for h in range(w.H):
@@ -204,7 +204,8 @@ def test_prefill_block_tables(sq, oracle, case, gap):
 
 
 def test_prefill_hidden_keys_may_be_infinite(sq):
-    """A key a query does not keep has no influence on it, whatever its components are; a query that keeps it sees it."""
+    """A key a query does not keep has no influence on it, whatever its key row holds; a query that keeps it sees it.  (Value
+    rows: test_gpu_prefill_edges.py.)"""
     w = wl.make_workload("prefill_inf", seed=34, threads=1, B=1, H=2, L=900, C=30, Lq=200, U=70, keep_frac=0.3,
                          causal_user=True)
     gk, words = random_masks(w, np.random.default_rng(4), 0.4)
@@ -455,8 +456,8 @@ def test_prefill_lookup_slices(sq, oracle, case):
 
 def test_prefill_step_queries_alike_within_a_block(sq, oracle):
     """The whole step on queries that resemble their neighbours (each block of 64 tokens shares a direction, as
-    consecutive tokens of a prompt do): the selections of a block overlap, most key blocks are kept by no token of it,
-    and the step's attention runs through the kernel that walks only the listed blocks."""
+    consecutive tokens of a prompt do): the selections of a group overlap and most key blocks are kept by no token of it, so
+    that the attention lists few blocks and its waves need only part of them."""
     w = wl.make_workload("prefill_alike", seed=29, threads=2, B=1, H=2, L=8192, C=512, Lq=192, U=64, keep_frac=0.05,
                          causal_user=True)
     rng = np.random.default_rng(9)
@@ -468,7 +469,7 @@ def test_prefill_step_queries_alike_within_a_block(sq, oracle):
             q[0, h, g:g + n] = base[None, :] + 0.05 * np.abs(base).mean() * rng.standard_normal((n, w.d))
     w.q = q.astype(np.float16)
     w = wl.calibrate(w, oracle.scores)
-    # the scenario itself, from the oracle's selection: at least an eighth of the (query block, key block) pairs are empty
+    # the scenario itself, from the oracle's selection: at least an eighth of the (64 queries, key block) pairs are empty
     x, m, D = oracle.centroid_score(w.q, w.centroids, w.sizes, w.sm_scale)
     mask, _, _, _ = oracle.select(x, m, D, w.thresh, w.sizes, w.offsets)
     keep = unpack_mask(mask, w.C)
