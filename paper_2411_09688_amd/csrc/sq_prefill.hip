@@ -140,7 +140,7 @@ __device__ __forceinline__ void static_for(F &&f)
 #define PF_INLINE __attribute__((always_inline))          // (a lambda left as a call would put what it captures in memory)
 
 // The outputs of queries (the active lanes; lane = query column + 32 g, as in prefill_attn_kernel) from the keys they see alone,
-// key by key, some thirty times the time of the kernel's walk: for queries whose output is not finite.  A function of its own, not
+// key by key, some thirty times the time of the kernel's walk: for queries with a NaN in their output.  A function of its own, not
 // inlined: as part of the kernel its code lengthened the walk of workgroups with idle waves (32 heads x 150 tokens x 32K keys 175
 // -> 184 us).  seen_user: user keys the query sees; dst: the query's output, to be multiplied by scale, or, with several shares,
 // its 128 partial sums.  The other arguments: see the kernel (uniform ones arrive in vector registers).
@@ -796,14 +796,17 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
 
     // ---- values that are not finite ------------------------------------------------------------------------------------------
     // The products of a block multiply the values of keys that a query does not see (and of rows past the end of a tensor) by 0,
-    // which is NaN where the value is infinite or NaN.  A query whose output is not finite (finite values cannot cause that) takes
-    // it again from the keys it sees alone.
-    float unfit[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    // which is NaN where the value is infinite or NaN.  A query with a NaN in its output (finite inputs cannot cause that) takes it
+    // again from the keys it sees alone.
+    float top[4];                                           // (the maximum propagates NaN)
 #pragma unroll
-    for (int r = 0; r < 16; ++r)
+    for (int dt = 0; dt < 4; ++dt) {
+        top[dt] = o[dt][0];
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) unfit[dt] = fmaf(o[dt][r], 0.0f, unfit[dt]);
-    const float bad = cross32_sum((unfit[0] + unfit[1]) + (unfit[2] + unfit[3]));   // (a query's two lanes hold half of its dimensions each)
+        for (int r = 1; r < 15; r += 2) top[dt] = __builtin_elementwise_maximum(__builtin_elementwise_maximum(top[dt], o[dt][r]), o[dt][r + 1]);
+        top[dt] = __builtin_elementwise_maximum(top[dt], o[dt][15]);
+    }
+    const float bad = cross32_sum(__builtin_elementwise_maximum(__builtin_elementwise_maximum(top[0], top[1]), __builtin_elementwise_maximum(top[2], top[3])));   // (a query's two lanes hold half of its dimensions each)
     const bool again = bad != bad;
 
     // ---- normalise and store: lane holds query column nq, dims dt*32 + 8*a + 4*g + (0..3) --------------------------------
