@@ -97,7 +97,7 @@ __device__ __forceinline__ float lk_least_kept(float m, float thr, float c2)
     if (thr < 0.0f) return SQ_NEG_INF;
     if (!(thr < 1.0f)) return __builtin_nanf("");
     auto passes = [&](uint32_t u) { return __builtin_amdgcn_exp2f(-__builtin_bit_cast(float, u) * c2) > thr; };
-    const float l = thr > 0.0f ? -log2f(thr) : 126.0f;
+    const float l = thr > 0.0f ? fmaxf(-log2f(thr), 0x1p-26f) : 126.0f;   // (positive, also for the float below 1)
     const uint32_t at = __builtin_bit_cast(uint32_t, fminf(l / c2, 3e38f)), w = (uint32_t)fminf(16.0f + 16.0f / l, 4e6f);
     uint32_t lo = at > w ? at - w : 0u, hi = min(at + w, 0x7f800000u);   // (bit patterns of -d; -0 passes, -inf does not)
     if (!passes(lo)) lo = 0u;

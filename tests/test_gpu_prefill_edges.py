@@ -142,6 +142,8 @@ def test_a_score_that_equals_the_threshold_is_dropped(sq, case, sm_scale):
         assert not keep.any() and (nk == 0).all(), (fn.__name__, keep.mean())
         keep, nk, _ = fn(sq, w, np.full(w.H, np.nextafter(T, np.float32(0)), np.float32))
         assert (nk == w.L).all(), (fn.__name__, (nk == w.L).mean())
+        keep, nk, _ = fn(sq, w, np.full(w.H, 0.0, np.float32))
+        assert (nk == w.L).all(), (fn.__name__, (nk == w.L).mean())
 
 
 # ---- values of keys a query does not see ---------------------------------------------------------------------------------
