@@ -139,11 +139,12 @@ __device__ __forceinline__ void static_for(F &&f)
 }
 #define PF_INLINE __attribute__((always_inline))          // (a lambda left as a call would put what it captures in memory)
 
-// The outputs of queries (the active lanes; lane = query column + 32 g, as in prefill_attn_kernel) from the keys they see alone,
-// key by key, some thirty times the time of the kernel's walk: for queries with a NaN in their output.  A function of its own, not
-// inlined: as part of the kernel its code lengthened the walk of workgroups with idle waves (32 heads x 150 tokens x 32K keys 175
-// -> 184 us).  seen_user: user keys the query sees; dst: the query's output, to be multiplied by scale, or, with several shares,
-// its 128 partial sums.  The other arguments: see the kernel (uniform ones arrive in vector registers).
+// The outputs of queries (the active lanes; lane = query column + 32 g, as in prefill_attn_kernel) from the keys they see alone, key
+// by key, for queries with a NaN in their output.  Bound by vector instructions, about 200 per key and wave: 32 heads x 1024 tokens
+// x 32K keys with a NaN in every query's reach take 26 ms instead of 0.58 (two keys' loads at a time: 24, four: 68, for spills).
+// A function of its own, not inlined: as part of the kernel its code lengthened the walk of workgroups with idle waves (32 heads x
+// 150 tokens x 32K keys 175 -> 184 us).  seen_user: user keys the query sees; dst: the query's output, to be multiplied by scale,
+// or, with several shares, its 128 partial sums.  The other arguments: see the kernel (uniform ones arrive in vector registers).
 template <bool SHARED>
 __device__ __attribute__((noinline)) void prefill_again(const _Float16 *q_row, const char *Kf, const char *Vf, const char *Ku,
                                                         const char *Vu, const uint32_t *mrow, const void *table,
