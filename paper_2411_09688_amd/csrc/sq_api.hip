@@ -263,7 +263,23 @@ SharedStepWs carve_step_shared(Carver &cv, const sq_shape_t *sh, int G = 1)
 // (measured at 32K context, keep 1/8: 2 sequences 65 us against 50 us per step, 6 sequences 94 against 87,
 // even from 8 on; one sequence with 4 query heads per K/V head 43 us against 31 us).
 constexpr int SHARED_MIN_ROWS = 8;
-bool step_is_shared(const sq_shape_t *sh, int G = 1) { return sh->B * G >= SHARED_MIN_ROWS; }
+// ... and only where the rows have this many keys to select from between them (query rows x keys, fixed context and user
+// keys).  Below it the five launches of the union kernels, 24 us with nothing to read, cost more than the keys that several
+// rows kept are worth: they come from the caches again.  Union / per-row kernels, us per step, by the share of the keys kept:
+//                                                 0.06          1/8         1/4         1/2          all
+//    8 sequences x  1 head  x  8000 keys ( 64 K)  23.9 / 13.9  24.8 / 14.1  24.9 / 14.6  24.9 / 15.4  24.8 / 16.3
+//   16           x  4 heads x  4000      (256 K)  25.8 / 14.7  25.9 / 15.8  26.0 / 18.0  26.1 / 22.6  26.1 / 27.0
+//   12           x  8       x  4000      (384 K)  26.5 / 18.5  28.1 / 19.6  28.4 / 23.5  28.2 / 29.3  28.5 / 36.7
+//    8           x  8       x  8000      (512 K)  26.9 / 18.3  28.3 / 19.9  29.9 / 24.7  31.1 / 33.5  31.4 / 41.1
+//   16           x  8       x  4000      (512 K)  28.2 / 18.1  28.7 / 20.7  28.9 / 25.2  28.8 / 34.1  28.9 / 41.3
+//   16           x  8       x  8000      (1 M)    29.6 / 21.5  32.0 / 26.3  32.3 / 35.6  32.8 / 53.7  33.7 / 67.9
+// The line lies where the per-row kernels still lead at a quarter kept, the upper end of the budgets the method is run at.
+constexpr long long SHARED_MIN_KEYS = 400 * 1024;
+bool step_is_shared(const sq_shape_t *sh, int G = 1)
+{
+    if (sh->B * G < SHARED_MIN_ROWS) return false;
+    return !step_is_indexed(sh, G) || (long long)sh->B * sh->H * G * ((long long)sh->L + sh->U) > SHARED_MIN_KEYS;
+}
 
 // Workspace of the two-level lookup.  C1 <= C2 is not known to sq_workspace_bytes, so level-1 buffers
 // are sized for C2.
@@ -535,7 +551,7 @@ size_t sq_workspace_bytes(const sq_shape_t *sh, int which)
         carve_decode(cv, sh);
         return cv.off;
     case SQ_CALL_DECODE_STEP:
-        if (step_is_shared(sh)) carve_step_shared(cv, sh);
+        if (sh->B >= SHARED_MIN_ROWS) carve_step_shared(cv, sh);   // (the per-row kernels below the line need less)
         else if (step_is_indexed(sh)) {
             Carver cv2(nullptr);
             carve_step_small(cv2, sh);

@@ -295,6 +295,29 @@ def test_short_rows_select_like_the_general_step(sq, oracle, C):
     torch.testing.assert_close(l1, l2, atol=1e-5, rtol=1e-6)
 
 
+
+# Either side of the line from which query rows that share their K/V are taken together: query rows x keys, 400 K.
+@pytest.mark.parametrize("case", [
+    dict(B=8, H=2, L=25000, C=700, U=600, keep_frac=0.2),          # the last size row by row, and one key more
+    dict(B=8, H=2, L=25000, C=700, U=601, keep_frac=0.2),
+    dict(B=17, H=3, L=8100, C=250, U=5, keep_frac=0.25),           # together: two groups, the second of one sequence
+    dict(B=11, H=3, L=12500, C=333, U=300, keep_frac=0.5),         # a part of a group, user keys with a ragged tail
+    dict(B=16, H=2, L=13000, C=50, U=0, keep_frac=0.2),            # clusters of several blocks, no user keys
+    dict(B=9, H=2, L=23000, C=2048, U=17, keep_frac=0.2),          # more clusters than one selection step holds
+    dict(B=8, H=1, L=2000, C=4097, U=33, keep_frac=0.3),           # more clusters than the per-row kernels take
+], ids=lambda c: "B{B}H{H}L{L}C{C}U{U}".format(**c))
+def test_shared_context_line(sq, oracle, case):
+    w = wl.calibrate(wl.make_workload("shared_line", Lq=1, seed=17, threads=4, **case), oracle.scores)
+    step_against_oracle(sq, oracle, w, f"shared_line{case}")
+
+
+@pytest.mark.parametrize("thresh,U", [(-1.0, 33), (2.0, 33), (2.0, 0)], ids=["all", "none", "nothing_at_all"])
+def test_shared_context_line_extremes(sq, oracle, thresh, U):
+    w = wl.make_workload("shared_line_x", B=10, H=3, L=14001, C=90, Lq=1, U=U, keep_frac=0.5, seed=18, threads=4)
+    w.thresh = np.full(w.H, thresh, np.float32)
+    step_against_oracle(sq, oracle, w, f"shared_line extremes {thresh} {U}")
+
+
 def test_shared_context_step_extremes(sq, oracle):
     base = dict(B=10, H=2, L=1024, C=32, Lq=1, U=33, keep_frac=0.5, seed=12, threads=2)
     # every sequence keeps everything: each key is owned by all sequences of the group
