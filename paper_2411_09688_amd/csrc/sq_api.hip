@@ -407,9 +407,9 @@ sq::UserAttn make_user_pieces(const sq_shape_t *sh, int G, const void *q, const 
     return ua;
 }
 
-// Workspace of the shared-set prefill attention: records of the kept ranges and the list of kept key rows.
+// Workspace of the shared-set prefill attention: the rows' lists of kept keys and their lengths.
 struct PrefillSharedWs {
-    sq::DecodePlan plan;
+    int2 *hdr;
     int32_t *key_idx;
     float *partials;
 };
@@ -418,12 +418,26 @@ PrefillSharedWs carve_prefill_shared(Carver &cv, const sq_shape_t *sh)
 {
     const size_t rows = (size_t)sh->B * sh->H;
     PrefillSharedWs w{};
-    w.plan.rec_cap = sh->C;
-    w.plan.L = sh->L;
-    w.plan.rec = cv.take<int4>(rows * sh->C);
-    w.plan.hdr = cv.take<int2>(rows);
+    w.hdr = cv.take<int2>(rows);
     w.key_idx = cv.take<int32_t>(rows * sh->L);
     w.partials = cv.take<float>(sq::prefill_partial_floats(true, to_shape(sh)));
+    return w;
+}
+
+// The same for a caller's ranges, which become records first.
+struct PrefillRangesWs {
+    PrefillSharedWs att;
+    sq::DecodePlan plan;
+};
+
+PrefillRangesWs carve_prefill_ranges(Carver &cv, const sq_shape_t *sh)
+{
+    PrefillRangesWs w{};
+    w.att = carve_prefill_shared(cv, sh);
+    w.plan.hdr = w.att.hdr;
+    w.plan.rec_cap = sh->C;
+    w.plan.L = sh->L;
+    w.plan.rec = cv.take<int4>((size_t)sh->B * sh->H * sh->C);
     return w;
 }
 
@@ -467,7 +481,6 @@ PrefillStepWs carve_prefill_step(Carver &cv, const sq_shape_t *sh)
 
 struct PrefillMeanStepWs {
     float *stats, *part_sum;
-    int32_t *n_ranges, *n_keys;
     PrefillSharedWs att;
 };
 
@@ -477,8 +490,6 @@ PrefillMeanStepWs carve_prefill_mean_step(Carver &cv, const sq_shape_t *sh)
     PrefillMeanStepWs w{};
     w.stats = cv.take<float>(sq::lookup_stat_floats((int)rows, sh->Lq, sh->C));
     w.part_sum = cv.take<float>(sq::lookup_part_floats((int)rows, sh->C));
-    w.n_ranges = cv.take<int32_t>(rows);
-    w.n_keys = cv.take<int32_t>(rows);
     w.att = carve_prefill_shared(cv, sh);
     return w;
 }
@@ -501,12 +512,12 @@ HierPrefillWs carve_hier_prefill(Carver &cv, const sq_shape_t *sh)
     return w;
 }
 
-// Workspace of the hierarchical prefill step on averaged scores: the one-level step's, plus the records of the kept
-// coarse clusters' child ranges and the candidate list they expand to.
+// Workspace of the hierarchical prefill step on averaged scores: the one-level step's, plus the list of the
+// kept coarse clusters' children.
 struct HierPrefillMeanWs {
     PrefillMeanStepWs step;
-    sq::DecodePlan cand;
-    int32_t *cand_id, *nr1, *nk1;
+    int2 *cand_hdr;
+    int32_t *cand_id;
 };
 
 HierPrefillMeanWs carve_hier_prefill_mean(Carver &cv, const sq_shape_t *sh)
@@ -514,13 +525,8 @@ HierPrefillMeanWs carve_hier_prefill_mean(Carver &cv, const sq_shape_t *sh)
     const size_t rows = (size_t)sh->B * sh->H;
     HierPrefillMeanWs w{};
     w.step = carve_prefill_mean_step(cv, sh);
-    w.cand.rec_cap = sh->C;
-    w.cand.L = sh->C;
-    w.cand.rec = cv.take<int4>(rows * sh->C);
-    w.cand.hdr = cv.take<int2>(rows);
+    w.cand_hdr = cv.take<int2>(rows);
     w.cand_id = cv.take<int32_t>(rows * sh->C);
-    w.nr1 = cv.take<int32_t>(rows);
-    w.nk1 = cv.take<int32_t>(rows);
     return w;
 }
 
@@ -566,7 +572,7 @@ size_t sq_workspace_bytes(const sq_shape_t *sh, int which)
         cv.take<float>((size_t)sh->B * sh->H * sq::mean_parts_for(sh->Lq) * sh->C);
         return cv.off;
     case SQ_CALL_ATTN_PREFILL_SHARED:
-        carve_prefill_shared(cv, sh);
+        carve_prefill_ranges(cv, sh);
         return cv.off;
     case SQ_CALL_PREFILL_STEP:
         carve_prefill_step(cv, sh);
@@ -989,10 +995,11 @@ int sq_sparse_attn_prefill_shared(const sq_shape_t *sh, const void *q, const voi
     if (int rc = check_device(__func__)) return rc;
     hipStream_t s = static_cast<hipStream_t>(stream);
     Carver cv(ws);
-    PrefillSharedWs w = carve_prefill_shared(cv, sh);
+    PrefillRangesWs w = carve_prefill_ranges(cv, sh);
     SQ_HIP(sq::launch_ranges_to_rec(ranges, n_ranges, w.plan, sh->B * sh->H, sh->C, s));
-    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.plan, w.key_idx, w.partials, out, lse,
-                                          to_shape(sh), s));
+    SQ_HIP(sq::launch_expand_ranges(w.plan, w.att.key_idx, sh->B * sh->H, sh->L, s));
+    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.att.hdr, w.att.key_idx, w.att.partials, out,
+                                          lse, to_shape(sh), s));
     g_err[0] = 0;
     return SQ_OK;
 }
@@ -1051,14 +1058,11 @@ int sq_prefill_mean_step(const sq_shape_t *sh, const void *q, const void *centro
     const int rows = sh->B * sh->H;
     SQ_HIP(sq::launch_prefill_lookup(q, centroids, sizes, thresh, w.stats, nullptr, nullptr, w.part_sum, true, sh->B,
                                      sh->H, sh->Lq, sh->C, sh->sm_scale, s));
-    sq::SelectOpts opt{};
-    opt.mean_parts = sq::lookup_parts(rows, sh->Lq, sh->C);
-    opt.mean_div = (float)sh->Lq;
-    // the selection writes the kept ranges' records straight into the attention's plan
-    SQ_HIP(sq::launch_select(w.part_sum, nullptr, nullptr, true, thresh, sizes, offsets, keep_mask, nullptr, w.n_ranges,
-                             n_keys ? n_keys : w.n_keys, w.att.plan, false, 0, opt, rows, sh->H, 1, sh->C, s));
-    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.att.plan, w.att.key_idx, w.att.partials, out, lse,
-                                          to_shape(sh), s));
+    SQ_HIP(sq::launch_mean_select(w.part_sum, sq::lookup_parts(rows, sh->Lq, sh->C), (float)sh->Lq, thresh, sizes, offsets,
+                                  nullptr, nullptr, false, keep_mask, n_keys, w.att.hdr, w.att.key_idx, sh->L, rows, sh->H,
+                                  sh->C, s));
+    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.att.hdr, w.att.key_idx, w.att.partials, out,
+                                          lse, to_shape(sh), s));
     g_err[0] = 0;
     return SQ_OK;
 }
@@ -1365,30 +1369,21 @@ int sq_hier_prefill_mean_step(const sq_shape_t *sh, int32_t C1, const void *q, c
     Carver cv(ws);
     HierPrefillMeanWs w = carve_hier_prefill_mean(cv, sh);
     const int rows = sh->B * sh->H;
-    sq::SelectOpts opt{};
-    opt.mean_parts = sq::lookup_parts(rows, sh->Lq, sh->C);
-    opt.mean_div = (float)sh->Lq;
-    // Level 1 (Eq. 2 averaged over the tokens): the kept coarse clusters' child ranges become records ...
+    // Level 1 (Eq. 2 averaged over the tokens): the children of the kept coarse clusters are listed as candidates ...
     SQ_HIP(sq::launch_prefill_lookup(q, centroids1, sizes1, thresh1, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
                                      sh->B, sh->H, sh->Lq, C1, sh->sm_scale, s));
-    sq::SelectOpts opt1 = opt;
-    opt1.len_from_offsets = 1;
-    opt1.mean_parts = sq::lookup_parts(rows, sh->Lq, C1);
-    SQ_HIP(sq::launch_select(w.step.part_sum, nullptr, nullptr, true, thresh1, sizes1, child_offsets, nullptr, nullptr,
-                             w.nr1, w.nk1, w.cand, false, 0, opt1, rows, sh->H, 1, C1, s));
-    // ... which expand to the list of candidate fine clusters of each (sequence, head).
-    SQ_HIP(sq::launch_expand_ranges(w.cand, w.cand_id, rows, sh->C, s));
-    // Level 2 (Eq. 3 per token over the candidates, averaged over the tokens): scores and selection in candidate order.
+    SQ_HIP(sq::launch_mean_select(w.step.part_sum, sq::lookup_parts(rows, sh->Lq, C1), (float)sh->Lq, thresh1, sizes1,
+                                  child_offsets, nullptr, nullptr, true, nullptr, nullptr, w.cand_hdr, w.cand_id, sh->C, rows,
+                                  sh->H, C1, s));
+    // ... level 2 (Eq. 3 per token over the candidates, averaged over the tokens): scores and selection in candidate order.
     SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
-                                     sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s, w.cand_id, w.cand.hdr));
-    sq::SelectOpts opt2 = opt;
-    opt2.cand_id = w.cand_id;
-    opt2.cand_hdr = w.cand.hdr;
-    SQ_HIP(sq::launch_select(w.step.part_sum, nullptr, nullptr, true, thresh2, sizes2, offsets2, keep_mask2, nullptr,
-                             w.step.n_ranges, n_keys ? n_keys : w.step.n_keys, w.step.att.plan, false, 0, opt2, rows,
-                             sh->H, 1, sh->C, s));
-    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.step.att.plan, w.step.att.key_idx, w.step.att.partials, out,
-                                          lse, to_shape(sh), s));
+                                     sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s, w.cand_id, w.cand_hdr));
+    SQ_HIP(sq::launch_mean_select(w.step.part_sum, sq::lookup_parts(rows, sh->Lq, sh->C), (float)sh->Lq, thresh2, sizes2,
+                                  offsets2, w.cand_id, w.cand_hdr, false, keep_mask2, n_keys, w.step.att.hdr,
+                                  w.step.att.key_idx, sh->L, rows, sh->H, sh->C, s));
+    const PrefillSharedWs &att = w.step.att;
+    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, att.hdr, att.key_idx, att.partials, out, lse,
+                                          to_shape(sh), s));
     g_err[0] = 0;
     return SQ_OK;
 }

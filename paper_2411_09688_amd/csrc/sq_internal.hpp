@@ -82,9 +82,16 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
 hipError_t launch_child_parent(const int32_t *child_offsets, int32_t *parent, int H, int C1, int C2, hipStream_t s);
 // (cand_id [B*H, C] / cand_hdr [B*H] given, with mean: only the hdr.y candidates listed for a (sequence, head) are
 // scored, statistics over them alone, part_sum in candidate order: level 2 of a hierarchical lookup.)
-// Kept ranges (records of a plan) -> flat index lists idx [rows, L]: the key rows of the attention, or the candidate
-// clusters of the next level.
+// Kept ranges (records of a plan) -> the rows' lists of kept keys idx [rows, L].
 hipError_t launch_expand_ranges(DecodePlan plan, int32_t *idx, int rows, int L, hipStream_t s);
+// Averaged selection (sq_mean_select.hip): part_sum [rows, parts, C], keep iff N > 0 and sum of the parts / div > T, into the
+// mask (optional), the rows' lists of kept keys, or with `children` of the kept clusters' child clusters, list [rows, list_len],
+// and hdr[row] = (clusters, list entries); n_keys (optional) = list entries.  cand_id / cand_hdr given: the row's entries are its
+// candidates.
+hipError_t launch_mean_select(const float *part_sum, int parts, float div, const float *thresh, const int32_t *sizes,
+                              const int32_t *offsets, const int32_t *cand_id, const int2 *cand_hdr, bool children,
+                              uint32_t *keep_mask, int32_t *n_keys, int2 *hdr, int32_t *list, int list_len, int rows, int H,
+                              int C, hipStream_t s);
 // Options of the row-wise selection for the two-level lookup (all zero for the one-level path).
 struct SelectOpts {
     const int32_t *cand_id;          // level 2: `logits` is [rows, C] in candidate order, cand_id [rows, C] the
@@ -180,10 +187,9 @@ hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, co
                                const uint32_t *keep_mask, const BlockTable &bt, float *partials, void *out, float *lse,
                                const Shape &sh, hipStream_t s);
 
-// Prefill attention with ONE kept set per (sequence, head): plan.rec / plan.hdr hold the kept ranges' records
-// (from launch_ranges_to_rec); key_idx [B*H, L] is workspace for the list of kept key rows.
+// Prefill attention with ONE kept set per (sequence, head): key_idx [B*H, L] holds a row's kept keys, hdr[row].y of them.
 hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
-                                      DecodePlan plan, int32_t *key_idx, float *partials, void *out, float *lse,
+                                      const int2 *hdr, const int32_t *key_idx, float *partials, void *out, float *lse,
                                       const Shape &sh, hipStream_t s);
 
 // Both forms deal a unit's key blocks to n_split workgroups (of `waves` waves, 32 queries each) where (heads x query blocks) alone do not fill the

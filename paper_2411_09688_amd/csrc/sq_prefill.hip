@@ -980,21 +980,19 @@ hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, co
 
 hipError_t launch_expand_ranges(DecodePlan plan, int32_t *idx, int rows, int L, hipStream_t s)
 {
-    // A wave's chain of records is what a launch over few rows waits for: 8 rows x 262144 keys, two launches of a step, 14.2 us
-    // with 16 workgroups per row, 9 with 64 (the step 126.5 -> 121.4); from 32 rows on 16 fill the chip.
+    // A wave's chain of records is what a launch over few rows waits for: 8 rows, 262144 keys and 16384 clusters, two launches,
+    // 14.2 us with 16 workgroups per row, 9 with 64; from 32 rows on 16 fill the chip.
     const int slices = std::clamp(512 / rows, 16, 64);
     hipLaunchKernelGGL(expand_ranges_kernel, dim3(rows, slices), dim3(256), 0, s, plan, idx, L);
     return hipGetLastError();
 }
 
 hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
-                                      DecodePlan plan, int32_t *key_idx, float *partials, void *out, float *lse,
+                                      const int2 *hdr, const int32_t *key_idx, float *partials, void *out, float *lse,
                                       const Shape &sh, hipStream_t s)
 {
-    hipError_t e = launch_expand_ranges(plan, key_idx, sh.B * sh.H, sh.L, s);
-    if (e != hipSuccess) return e;
     return launch_prefill_kernels<true>(q, Kf, Vf, Ku, Vu, nullptr, reinterpret_cast<const uint32_t *>(key_idx), nullptr,
-                                        reinterpret_cast<const int32_t *>(plan.hdr), out, lse, partials, sh, s);
+                                        reinterpret_cast<const int32_t *>(hdr), out, lse, partials, sh, s);
 }
 
 }  // namespace sq
