@@ -1378,7 +1378,7 @@ int sq_hier_prefill_mean_step(const sq_shape_t *sh, int32_t C1, const void *q, c
     // ... level 2 (Eq. 3 per token over the candidates, averaged over the tokens): scores and selection in candidate order.
     SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
                                      sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s, w.cand_id, w.cand_hdr));
-    SQ_HIP(sq::launch_mean_select(w.step.part_sum, sq::lookup_parts(rows, sh->Lq, sh->C), (float)sh->Lq, thresh2, sizes2,
+    SQ_HIP(sq::launch_mean_select(w.step.part_sum, sq::lookup_parts(rows, sh->Lq, sh->C, true), (float)sh->Lq, thresh2, sizes2,
                                   offsets2, w.cand_id, w.cand_hdr, false, keep_mask2, n_keys, w.step.att.hdr,
                                   w.step.att.key_idx, sh->L, rows, sh->H, sh->C, s));
     const PrefillSharedWs &att = w.step.att;

@@ -67,7 +67,7 @@ hipError_t launch_mean_score(const float *logits, const float *row_max, const fl
 // (lookup_part_floats() floats).
 constexpr int LK_MAX_SLICES = 32;
 int lookup_slices(int BH, int Lq, int C);
-int lookup_parts(int BH, int Lq, int C);
+int lookup_parts(int BH, int Lq, int C, bool cands = false);
 size_t lookup_part_floats(int BH, int C);
 inline size_t lookup_stat_floats(int BH, int Lq, int C) { return (size_t)BH * Lq * lookup_slices(BH, Lq, C) * 2; }
 hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int32_t *sizes, const float *thresh,
@@ -79,6 +79,14 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
 // (table given, per-query mode: the first launch also makes the attention's block table.)
 // (parent [H, C] / mask1 [B*H*Lq, ceil(C1/32)] given, per-query mode: a cluster counts for a token only if the token's
 // level-1 mask holds its parent: level 2 of a hierarchical lookup with per-token candidates; C1 <= 1024.)
+// The same in one launch (sq_lookup_rows.hip) where lookup_in_rows(), without parents or candidates: the scores stay in
+// registers.  mean: part_sum [B*H, lookup_rows_parts(), C].
+constexpr int LR_MAX_C = 1024;
+bool lookup_in_rows(int BH, int Lq, int C);
+int lookup_rows_parts(int BH, int Lq);
+hipError_t launch_lookup_rows(const void *q, const void *centroids, const int32_t *sizes, const float *thresh,
+                              uint32_t *keep_mask, int32_t *n_keys, float *part_sum, bool mean, int B, int H, int Lq, int C,
+                              float sm_scale, hipStream_t s, const BlockTable *table);
 hipError_t launch_child_parent(const int32_t *child_offsets, int32_t *parent, int H, int C1, int C2, hipStream_t s);
 // (cand_id [B*H, C] / cand_hdr [B*H] given, with mean: only the hdr.y candidates listed for a (sequence, head) are
 // scored, statistics over them alone, part_sum in candidate order: level 2 of a hierarchical lookup.)

@@ -58,7 +58,7 @@ __device__ __forceinline__ int pf_v_swz(int row) { return (row & 3) << 2; }
 // The block table of a call that has no lookup launch to make it in (sq_sparse_attn_prefill): see sq_block_table.hpp.
 __global__ __launch_bounds__(256) void block_table_kernel(BlockTable bt)
 {
-    block_table_part(bt, blockIdx.y, blockIdx.x);
+    block_table_part(bt, blockIdx.y, blockIdx.x, 4);
 }
 
 // Kept ranges of every (sequence, head) row -> list of key rows: record (first key, count, keys before) writes
@@ -967,7 +967,7 @@ hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf,
 
 hipError_t launch_block_table(const BlockTable &bt, int H, hipStream_t s)
 {
-    hipLaunchKernelGGL(block_table_kernel, dim3(block_table_groups(bt.nblk), H), dim3(256), 0, s, bt);
+    hipLaunchKernelGGL(block_table_kernel, dim3(block_table_groups(bt.nblk, 4), H), dim3(256), 0, s, bt);
     return hipGetLastError();
 }
 

@@ -1,6 +1,6 @@
 // Centroid lookup for prefill (Section 4.1) without a [queries x clusters] intermediate in memory, in two launches that each
 // stream the centroids once; both are spread over (sequence, head) x blocks of query tokens x slices of the clusters, so that
-// a few tokens or heads still fill the chip.
+// a few tokens or heads still fill the chip.  (Rows whose scores fit the registers of a workgroup: sq_lookup_rows.hip.)
 //
 //   lookup_pass_kernel<LK_STATS>        per (token, slice): the largest score r and sum_i N_i exp(x_i - r) over the slice's
 //                  clusters (Eq. 1's normaliser), 8 bytes each.
@@ -8,7 +8,7 @@
 //   lookup_pass_kernel<LK_DECIDE>       per-query selection: keep cluster i for token t iff N_i > 0 and
 //                  exp(x_i - m) > T * D, compared as x_i >= the least score that passes (lk_least_kept): one comparison per
 //                  (token, cluster), its bit shifted into the token's mask word.
-//   (lookup_pass_kernel<LK_BOTH>        both in one launch, for rows of few clusters)
+//   (lookup_pass_kernel<LK_BOTH>        both in one launch, for rows of few clusters with per-token candidates)
 //   mean_scores_kernel                  selection on averaged scores (Appendix D, "Prefill Stage"), first half: the scores
 //                  S_i(t) = exp(x_i - m) / D are summed over the tokens per cluster and written as part_sum
 //                  [B*H, lookup_parts(), C]; the row-wise selection kernel adds the parts.
@@ -32,12 +32,14 @@
 
 #include "sq_common.hpp"
 #include "sq_internal.hpp"
+#include "sq_lookup.hpp"
 
 namespace sq {
 
 constexpr int LK_G = 64;                     // centroids per staged group
 constexpr int LK_BT = 128;                   // tokens per workgroup (four waves x 32)
-// Rows of at most so many clusters are decided in one launch.  Whole steps, two launches / one, us, 32 keys per cluster:
+// With per-token candidates, rows of at most so many clusters are decided in one launch.  Whole steps (measured without
+// candidates, whose rows of up to 1024 clusters have a kernel of their own now), two launches / one, us, 32 keys per cluster:
 //   clusters                     75            128            192            250            320
 //    1 head  x   16 tokens   25.2 / 22.1    25.6 / 22.3    27.8 / 26.1    28.9 / 29.7    29.9 / 32.3
 //   16 heads x   28 tokens   28.9 / 25.5    31.6 / 28.4    31.8 / 30.6    34.7 / 35.8    36.7 / 39.8
@@ -45,14 +47,6 @@ constexpr int LK_BT = 128;                   // tokens per workgroup (four waves
 //   32 heads x 1024 tokens   87.7 / 82.6   112.3 / 107.9  151.9 / 146.7  179.6 / 179.0  218.7 / 212.6
 constexpr int LK_ONE_C = 192;
 constexpr int LK_MAX_W1 = 32;                // level-1 mask words per token held in LDS: at most 1024 coarse clusters
-
-// Rows of 256 B staged unpadded by the load-to-LDS instruction (a wave writes four whole rows); 16-byte chunk c of row r sits
-// at slot c ^ (r % 16), applied on the global side, so the operand reads (32 rows at one chunk index) are free of conflicts.
-typedef __attribute__((address_space(3))) void *lk_lptr_t;
-__device__ __forceinline__ void lk_stage(const char *base, uint32_t off, uint32_t lds)   // base, lds: uniform
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "m0");
-}
 
 // A token's pairs (r, sum) of the slices first, first + STEP, ... (at most LK_MAX_SLICES / STEP of them): the loads are issued
 // together and merged later, so that their latency lies under the work in between.
@@ -87,35 +81,6 @@ struct SlicePairs {
     }
 };
 
-// The least raw score x that passes exp2((x - m) c2) > thr, the test of Eq. 1's scores against T * D with m the row's largest
-// score: exactly the boundary of that float expression, so that a score which equals the threshold is dropped.  (thr < 0:
-// everything; thr >= 1 or not a number: nothing -- NaN, which no comparison passes.)  The differences that pass are an interval
-// [d, 0]; d is bisected from a bracket around the logarithm, wide enough for the rounding of the exponential (relative to d that
-// grows as 1 / |d c2|), or from all floats where the bracket does not hold it.  7 to 10 steps, once per token and workgroup.
-__device__ __forceinline__ float lk_least_kept(float m, float thr, float c2)
-{
-    if (thr < 0.0f) return SQ_NEG_INF;
-    if (!(thr < 1.0f)) return __builtin_nanf("");
-    auto passes = [&](uint32_t u) { return __builtin_amdgcn_exp2f(-__builtin_bit_cast(float, u) * c2) > thr; };
-    const float l = thr > 0.0f ? fmaxf(-log2f(thr), 0x1p-26f) : 126.0f;   // (positive, also for the float below 1)
-    const uint32_t at = __builtin_bit_cast(uint32_t, fminf(l / c2, 3e38f)), w = (uint32_t)fminf(16.0f + 16.0f / l, 4e6f);
-    uint32_t lo = at > w ? at - w : 0u, hi = min(at + w, 0x7f800000u);   // (bit patterns of -d; -0 passes, -inf does not)
-    if (!passes(lo)) lo = 0u;
-    if (passes(hi)) hi = 0x7f800000u;
-    while (hi - lo > 1u) {
-        const uint32_t mid = lo + ((hi - lo) >> 1);
-        if (passes(mid)) lo = mid;
-        else hi = mid;
-    }
-    // x passes iff fl(x - m) >= d: the least one lies next to m + (d + the float below it) / 2
-    const float d = -__builtin_bit_cast(float, lo);
-    const double at_x = (double)m + 0.5 * ((double)d - (double)__builtin_bit_cast(float, hi));
-    float x = nextafterf((float)at_x, SQ_NEG_INF);
-    for (int i = 0; i < 2; ++i)
-        if (!(x - m >= d)) x = nextafterf(x, __builtin_inff());
-    return x;
-}
-
 // Which passes a launch makes.  BOTH: one launch for rows of few clusters, where a second launch costs more than slices give.
 enum LkMode { LK_STATS, LK_DECIDE, LK_BOTH };
 
@@ -129,7 +94,7 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
     if (MODE != LK_DECIDE && !CANDS) {                      // extra workgroups: the attention's block table
         const int extra = (int)blockIdx.x - (Lq + LK_BT - 1) / LK_BT * n_slice;
         if (extra >= 0) {
-            if ((int)blockIdx.y < H) block_table_part(table, blockIdx.y, extra);
+            if ((int)blockIdx.y < H) block_table_part(table, blockIdx.y, extra, 4);
             return;
         }
     }
@@ -426,15 +391,16 @@ int lookup_slices(int BH, int Lq, int C)
 }
 
 // Parts the tokens are dealt to where (sequence, head) x blocks of clusters alone are few.
-int lookup_parts(int BH, int Lq, int C)
+int lookup_parts(int BH, int Lq, int C, bool cands)
 {
+    if (!cands && lookup_in_rows(BH, Lq, C)) return lookup_rows_parts(BH, Lq);
     const long long blocks = (long long)BH * ((C + LK_MC - 1) / LK_MC), tiles = (Lq + LK_MT - 1) / LK_MT;
     return (int)std::max(1ll, std::min(512 / blocks, tiles));
 }
 
-size_t lookup_part_floats(int BH, int C)
+size_t lookup_part_floats(int BH, int C)                    // parts * C * BH for this C and any smaller one (see lookup_parts)
 {
-    return (size_t)BH * C + 512 * LK_MC;                    // parts * C * BH for this C and any smaller one (see lookup_parts)
+    return std::max((size_t)BH * C + 512 * LK_MC, (size_t)std::max(BH, 512) * std::min(C, LR_MAX_C));
 }
 
 hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int32_t *sizes, const float *thresh,
@@ -443,7 +409,9 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
                                  const int2 *cand_hdr, const int32_t *parent, const uint32_t *mask1, int C1,
                                  const BlockTable *table)
 {
-    const bool one = !mean && C <= LK_ONE_C;
+    if (!parent && !cand_id && lookup_in_rows(B * H, Lq, C))
+        return launch_lookup_rows(q, centroids, sizes, thresh, keep_mask, n_keys, part_sum, mean, B, H, Lq, C, sm_scale, s, table);
+    const bool one = parent && C <= LK_ONE_C;
     const int BH = B * H, n_slice = one ? 1 : lookup_slices(BH, Lq, C);
     const dim3 grid((Lq + LK_BT - 1) / LK_BT * n_slice, BH);
     const _Float16 *qh = (const _Float16 *)q, *ch = (const _Float16 *)centroids;
@@ -453,7 +421,7 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
     const int32_t *ids = parent ? parent : cand_id;
     const int W1 = (C1 + 31) / 32;
     auto pass = [&](auto mode, auto cands, auto parents, auto keys) {
-        const dim3 all(grid.x + (mode != LK_DECIDE && table ? block_table_groups(table->nblk) : 0), grid.y);
+        const dim3 all(grid.x + (mode != LK_DECIDE && table ? block_table_groups(table->nblk, 4) : 0), grid.y);
         hipLaunchKernelGGL((lookup_pass_kernel<mode, cands, parents, keys>), all, dim3(256), 0, s, qh, ch, sizes, thresh, st,
                            keep_mask, n_keys, ids, cand_hdr, mask1, W1, n_slice, H, Lq, C, sm_scale,
                            table ? *table : BlockTable{});
@@ -464,7 +432,7 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
     constexpr std::integral_constant<LkMode, LK_DECIDE> second{};
     constexpr std::integral_constant<LkMode, LK_BOTH> both{};
     if (mean) {
-        const int n_part = lookup_parts(BH, Lq, C);
+        const int n_part = lookup_parts(BH, Lq, C, cand_id != nullptr);
         const dim3 mgrid((C + LK_MC - 1) / LK_MC, n_part, BH);
         if (cand_id) {
             pass(first, yes, no, no);
@@ -477,12 +445,10 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
         }
     } else {
         auto select = [&](auto parents, auto keys) {
-            if (one) {
-                pass(both, no, parents, keys);
-            } else {
-                pass(first, no, parents, keys);
-                pass(second, no, parents, keys);
-            }
+            if constexpr (parents)
+                if (one) return pass(both, no, parents, keys);
+            pass(first, no, parents, keys);
+            pass(second, no, parents, keys);
         };
         if (parent && n_keys) select(yes, yes);
         else if (parent) select(yes, no);
