@@ -12,25 +12,35 @@
 //
 // The assignment is the only dense contraction: S^T = C X^T on 16x16x32 fp16 MFMA tiles, A = 16 centres read
 // from LDS, B = 16 key vectors held in registers.  A wave holds four B sets (64 keys), so every A operand read
-// feeds four MFMAs; the four waves of a workgroup (256 keys) share the centre stream, which travels global
-// memory -> registers (two groups ahead) -> one of two LDS stages, one barrier per group of 64 centres.  A lane
-// owns one key per B set and four centres per tile, so the running (best score, best centre) is a per-lane
-// scalar pair; the four lane groups are combined once at the end.  Ties go to the lowest centre index: a lane
+// feeds four MFMAs; the four waves of a workgroup (256 keys) share the centre stream, which travels from global memory
+// straight into one of three LDS stages, two groups of 64 centres ahead, one barrier per group.  A lane
+// owns one key per B set and four consecutive centres per tile; it keeps the best four it has seen, and which of them it was is
+// settled at the end.  The four lane groups are combined last.  Ties go to the lowest centre index: a lane
 // visits its centres in ascending order and replaces only on a strictly larger score, and the final combination
 // prefers the lower index on equal scores.
+// Bound by issue: a workgroup's 16 groups of 1024 matrix cycles each take 36 us at 1.84 GHz, three waves per SIMD 4150 cycles of
+// which 3072 are products (74 %); 16x16x32 products draw less power than 32x32x16 (1.95 against 1.68 PFLOP/s in a loop of nothing
+// else).  32 heads x 32768 keys x 1024 centres: 281 -> 242 us traced on the same card, where compares and selects were three per
+// centre and key instead of 1.75, went through padded rows written from registers, and waited for every group at its barrier; with
+// products and compares left in the compiler's order 252.
+#include <algorithm>
+#include <cstddef>
+
 #include "sq_common.hpp"
 #include "sq_internal.hpp"
 
 namespace sq {
 
 constexpr int KM_G = 64;                     // centres per staged group
-constexpr int KM_STRIDE = D + 8;             // halves per centre row in LDS (272 B: conflict-free 16-B reads)
 constexpr int KM_RW = 4;                     // B sets (16 keys each) per wave
 constexpr int KM_ROWS_PER_WG = 4 * 16 * KM_RW;
+constexpr int KM_STAGES = 3;                 // groups in LDS: one read, two on their way
 
+// Rows of 256 B without padding, filled by the load-to-LDS instruction; the 16-byte chunk c of row r lies at slot c ^ (r % 16), so
+// that 16 rows read at one chunk index fall into all banks.
 struct KmStage {
-    _Float16 Ct[KM_G * KM_STRIDE];
-    float nhn[KM_G];                         // minus the half norm: the accumulator's starting value
+    _Float16 Ct[KM_G * D];
+    float nhn[KM_G];                         // minus the half norms: the accumulators' starting values
 };
 
 // x / |x| per row (fp32 arithmetic), one wave per row; a zero row stays zero.
@@ -50,30 +60,59 @@ __global__ __launch_bounds__(256) void normalize_rows_kernel(const _Float16 *__r
     reinterpret_cast<h2 *>(X + row * D)[lane] = o;
 }
 
-__global__ __launch_bounds__(256) void half_norm_kernel(const _Float16 *__restrict__ cent, float *__restrict__ hn,
+// Minus half the squared norm of every row: 16 lanes per row.  (The sum runs in wave_sum's order, a lane standing for four.)
+__global__ __launch_bounds__(256) void half_norm_kernel(const _Float16 *__restrict__ cent, float *__restrict__ nhn,
                                                         int rows)
 {
-    const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= rows) return;
-    const h2 v = reinterpret_cast<const h2 *>(cent + (size_t)row * D)[lane];
-    const float a = (float)v[0], b = (float)v[1];
-    const float ss = wave_sum(a * a + b * b);
-    if (lane == 0) hn[row] = 0.5f * ss;
+    const int row = blockIdx.x * 16 + (threadIdx.x >> 4), l16 = threadIdx.x & 15;
+    const h8 v = reinterpret_cast<const h8 *>(cent + (size_t)min(row, rows - 1) * D)[l16];
+    float t[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const float a = (float)v[2 * j], b = (float)v[2 * j + 1];
+        t[j] = a * a + b * b;
+    }
+    float ss = (t[0] + t[1]) + (t[2] + t[3]);
+    ss += dpp_f<0xb1>(ss);
+    ss += dpp_f<0x4e>(ss);
+    ss += dpp_f<0x141>(ss);
+    ss += dpp_f<0x140>(ss);
+    if (l16 == 0 && row < rows) nhn[row] = -(0.5f * ss);
 }
 
-__global__ __launch_bounds__(256) void kmeans_assign_kernel(const _Float16 *__restrict__ X,
-                                                            const _Float16 *__restrict__ cent,
-                                                            const float *__restrict__ hn,
-                                                            int32_t *__restrict__ assign, int L, int C)
+__global__ __launch_bounds__(256, 3) void kmeans_assign_kernel(const _Float16 *__restrict__ X,
+                                                               const _Float16 *__restrict__ cent,
+                                                               const float *__restrict__ nhn,
+                                                               int32_t *__restrict__ assign, int L, int C)
 {
-    __shared__ __align__(16) KmStage stage[2];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ __align__(16) KmStage stage[KM_STAGES];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int col = lane & 15, kg = lane >> 4;
     const int h = blockIdx.y;
     const int r0 = (blockIdx.x * 4 + wave) * 16 * KM_RW;      // first key of this wave (may lie past the end)
     const int ng = (C + KM_G - 1) / KM_G;
 
+    // A group: 16 pieces of four rows, four per wave; the half norms by wave 0.  Centres past the end repeat the last one, whose
+    // index is lower, so they are never best.
+    const char *ch = reinterpret_cast<const char *>(cent + (size_t)h * C * D);
+    const float *hh = nhn + (size_t)h * C;
+    typedef __attribute__((address_space(3))) void *lptr_t;
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t)stage);
+    auto fetch = [&](int g, int st) {
+        const uint32_t lds = lds0 + (uint32_t)(st * sizeof(KmStage));
+        if (wave == 0)
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(lds + (uint32_t)offsetof(KmStage, nhn)),
+                         "v"((uint32_t)min(g * KM_G + lane, C - 1) * 4u), "s"(hh) : "m0", "memory");
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int r = (wave * 4 + i) * 4 + kg;            // row of the group; r % 16 = 4 i + kg
+            const uint32_t at = (uint32_t)min(g * KM_G + r, C - 1) * 256u + (uint32_t)((lane & 15) ^ (4 * i + kg)) * 16u;
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds + (uint32_t)((wave * 4 + i) * 1024)),
+                         "v"(at), "s"(ch) : "m0", "memory");
+        }
+    };
+    fetch(0, 0);
+    if (ng > 1) fetch(1, 1);
     h8 bx[KM_RW][4];
 #pragma unroll
     for (int r = 0; r < KM_RW; ++r) {
@@ -82,86 +121,83 @@ __global__ __launch_bounds__(256) void kmeans_assign_kernel(const _Float16 *__re
 #pragma unroll
         for (int s = 0; s < 4; ++s) bx[r][s] = xp[s * 4 + kg];
     }
-    const char *ch = reinterpret_cast<const char *>(cent + (size_t)h * C * D);
-    const float *hh = hn + (size_t)h * C;
 
-    // This thread's share of a group: rows i*16 + tid/16 (i = 0..3), 16-byte chunk tid%16; half norm of centre tid.
-    h8 pk[4];
-    float pn = 0.0f;
-    auto fetch = [&](int g) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int c_row = min(g * KM_G + i * 16 + (tid >> 4), C - 1);
-            pk[i] = *reinterpret_cast<const h8 *>(ch + (size_t)c_row * 256 + (tid & 15) * 16);
-        }
-        if (tid < KM_G) pn = g * KM_G + tid < C ? -hh[g * KM_G + tid] : SQ_NEG_INF;   // past the end: never best
-    };
-    auto commit = [&](KmStage &st) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            *reinterpret_cast<h8 *>(st.Ct + (i * 16 + (tid >> 4)) * KM_STRIDE + (tid & 15) * 8) = pk[i];
-        if (tid < KM_G) st.nhn[tid] = pn;
-    };
-
-    float best[KM_RW];
+    // The running best of a lane's centres, four consecutive ones (a tile's rows kg * 4 ..) at a time: the largest score, the first
+    // of the four that reached it first, and their scores but the last one's, which tell at the end which of the four it was.
+    // Seven instructions per four centres and key, where a compare and two selects per centre were twelve.
+    float best[KM_RW], sv[KM_RW][3];
     int bi[KM_RW];
 #pragma unroll
     for (int r = 0; r < KM_RW; ++r) {
         best[r] = SQ_NEG_INF;
         bi[r] = 0;
+#pragma unroll
+        for (int v = 0; v < 3; ++v) sv[r][v] = SQ_NEG_INF;
     }
+    uint32_t rd[4];                                           // operand of step s: row col of a tile, chunk 4 s + kg
+#pragma unroll
+    for (int s = 0; s < 4; ++s) rd[s] = (uint32_t)(col * 256 + ((s * 4 + kg) ^ col) * 16);
     // Scores of tile u of a staged group: acc[r][v] = x_r . c - hn_c for c = u*16 + kg*4 + v (the accumulator starts
     // at -hn_c).
     auto tile = [&](const KmStage &st, int u, f4 (&acc)[KM_RW]) {
         const f4 nh = *reinterpret_cast<const f4 *>(st.nhn + u * 16 + kg * 4);
+        const char *rows = reinterpret_cast<const char *>(st.Ct) + u * 4096;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
-            const h8 a = *reinterpret_cast<const h8 *>(st.Ct + (u * 16 + col) * KM_STRIDE + s * 32 + kg * 8);
+            const h8 a = *reinterpret_cast<const h8 *>(rows + rd[s]);
 #pragma unroll
             for (int r = 0; r < KM_RW; ++r)
                 acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, bx[r][s], s == 0 ? nh : acc[r], 0, 0, 0);
         }
     };
     auto take = [&](const f4 (&acc)[KM_RW], int c0) {
+        float m[KM_RW];
+        bool win[KM_RW];
 #pragma unroll
-        for (int v = 0; v < 4; ++v)
+        for (int r = 0; r < KM_RW; ++r) m[r] = fmaxf(fmaxf(fmaxf(fmaxf(best[r], acc[r][0]), acc[r][1]), acc[r][2]), acc[r][3]);
 #pragma unroll
-            for (int r = 0; r < KM_RW; ++r)
-                if (acc[r][v] > best[r]) {
-                    best[r] = acc[r][v];
-                    bi[r] = c0 + v;
-                }
+        for (int r = 0; r < KM_RW; ++r) win[r] = m[r] > best[r];
+#pragma unroll
+        for (int r = 0; r < KM_RW; ++r) {
+            bi[r] = win[r] ? c0 : bi[r];
+#pragma unroll
+            for (int v = 0; v < 3; ++v) sv[r][v] = win[r] ? acc[r][v] : sv[r][v];
+            best[r] = m[r];
+        }
     };
     // The running best is updated one tile behind the matrix cores: the compares of a tile come after the MFMAs of
     // the next one in program order, which lets the compiler interleave the two kinds of work.
     f4 cur[KM_RW];
 #pragma unroll
     for (int r = 0; r < KM_RW; ++r) cur[r] = f4{SQ_NEG_INF, SQ_NEG_INF, SQ_NEG_INF, SQ_NEG_INF};
-    int cur_c0 = 0;
-    fetch(0);
-    commit(stage[0]);
-    if (ng > 1) fetch(1);
-    __syncthreads();
+    int cur_c0 = 0, st = 0;
     for (int g = 0; g < ng; ++g) {
-        if (g + 1 < ng) {
-            commit(stage[(g + 1) & 1]);
-            if (g + 2 < ng) fetch(g + 2);
-        }
-        const KmStage &st = stage[g & 1];
+        // Group g has landed when the loads of group g + 1 alone (four rows' pieces; none behind the last group) are under way;
+        // behind the barrier that holds for all waves, and group g - 1 has been read by all of them.
+        if (g + 1 < ng) asm volatile("s_waitcnt vmcnt(4) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (g + 2 < ng) fetch(g + 2, st == 0 ? 2 : st - 1);
+        const KmStage &cs = stage[st];
 #pragma unroll
         for (int u = 0; u < KM_G / 16; ++u) {
             f4 nxt[KM_RW];
-            tile(st, u, nxt);
+            tile(cs, u, nxt);
             take(cur, cur_c0);
 #pragma unroll
             for (int r = 0; r < KM_RW; ++r) cur[r] = nxt[r];
             cur_c0 = g * KM_G + u * 16 + kg * 4;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {                    // (products and compares alternate)
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+            }
         }
-        __syncthreads();                                      // stage g & 1 may be overwritten; the other is complete
+        st = st == 2 ? 0 : st + 1;
     }
     take(cur, cur_c0);
 #pragma unroll
     for (int r = 0; r < KM_RW; ++r) {
+        bi[r] += sv[r][0] == best[r] ? 0 : sv[r][1] == best[r] ? 1 : sv[r][2] == best[r] ? 2 : 3;
 #pragma unroll
         for (int off = 16; off <= 32; off <<= 1) {
             const float so = __shfl_xor(best[r], off);
@@ -192,51 +228,38 @@ __global__ __launch_bounds__(256) void kmeans_hist_kernel(const int32_t *__restr
     for (int c = threadIdx.x; c < C; c += 256) dst[c] = s_cnt[c];
 }
 
-// Grouping, step 2 (one workgroup of 1024 threads per head): per centre, the part counts become exclusive prefixes
-// over the parts and their total the cluster size; the sizes are scanned over the centres into offsets.
-__global__ __launch_bounds__(1024) void kmeans_scan_kernel(int32_t *__restrict__ hist, int32_t *__restrict__ sizes,
-                                                           int32_t *__restrict__ offsets, int L, int C, int P)
+// Grouping, step 2: per centre, the part counts become exclusive prefixes over the parts and their total the cluster size.  A
+// workgroup takes 64 centres, each of its four waves a quarter of the parts (at most 64, see kmeans_part_len).  5.8 us at 32 heads x
+// 1024 centres x 64 parts, where one workgroup per head, which also scanned the sizes into offsets, took 9.4.
+constexpr int KM_SCAN_PARTS = 16;
+__global__ __launch_bounds__(256) void kmeans_scan_kernel(int32_t *__restrict__ hist, int32_t *__restrict__ sizes, int C, int P)
 {
-    __shared__ int s_wave[16];
-    __shared__ int s_carry;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int h = blockIdx.x;
-    if (tid == 0) s_carry = 0;
+    __shared__ int s_tot[4][64];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c = blockIdx.x * 64 + lane, h = blockIdx.y;
+    const int per = (P + 3) >> 2, p0 = wave * per, n = max(0, min(per, P - p0));
+    int32_t *col = hist + ((size_t)h * P + p0) * C + min(c, C - 1);
+    int t[KM_SCAN_PARTS], sum = 0;
+#pragma unroll
+    for (int u = 0; u < KM_SCAN_PARTS; ++u) t[u] = u < n ? col[(size_t)u * C] : 0;
+#pragma unroll
+    for (int u = 0; u < KM_SCAN_PARTS; ++u) sum += t[u];
+    s_tot[wave][lane] = sum;
     __syncthreads();
-    for (int base = 0; base < C; base += 1024) {
-        const int c = base + tid;
-        int total = 0;
-        if (c < C) {
-            int32_t *col = hist + (size_t)h * P * C + c;
-            int p = 0;
-            for (; p + 8 <= P; p += 8) {                        // eight loads in flight
-                int t8[8];
+    int before = 0, total = 0;
 #pragma unroll
-                for (int u = 0; u < 8; ++u) t8[u] = col[(size_t)(p + u) * C];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    col[(size_t)(p + u) * C] = total;
-                    total += t8[u];
-                }
-            }
-            for (; p < P; ++p) {
-                const int t = col[(size_t)p * C];
-                col[(size_t)p * C] = total;
-                total += t;
-            }
-            sizes[(size_t)h * C + c] = total;
-        }
-        const int inc = wave_inclusive_scan(total, lane);
-        if (lane == 63) s_wave[wave] = inc;
-        __syncthreads();
-        int before = s_carry;
-        for (int w = 0; w < wave; ++w) before += s_wave[w];
-        if (c < C) offsets[(size_t)h * (C + 1) + c] = before + inc - total;
-        __syncthreads();
-        if (tid == 1023) s_carry = before + inc;
-        __syncthreads();
+    for (int w = 0; w < 4; ++w) {
+        const int v = s_tot[w][lane];
+        if (w < wave) before += v;
+        total += v;
     }
-    if (tid == 0) offsets[(size_t)h * (C + 1) + C] = L;
+    if (c >= C) return;
+#pragma unroll
+    for (int u = 0; u < KM_SCAN_PARTS; ++u) {
+        if (u < n) col[(size_t)u * C] = before;
+        before += t[u];
+    }
+    if (wave == 0) sizes[(size_t)h * C + c] = total;
 }
 
 // Grouping, step 3: one WAVE per part walks the part's keys in index order, 64 at a time.  The lanes that hold the
@@ -248,15 +271,35 @@ __global__ __launch_bounds__(1024) void kmeans_scan_kernel(int32_t *__restrict__
 constexpr int KM_SCATTER_AHEAD = 8;
 __global__ __launch_bounds__(64) void kmeans_scatter_kernel(const int32_t *__restrict__ assign,
                                                             const int32_t *__restrict__ hist,
-                                                            const int32_t *__restrict__ offsets,
+                                                            const int32_t *__restrict__ sizes, int32_t *__restrict__ offsets,
                                                             int32_t *__restrict__ perm, int L, int C, int PL, int P)
 {
     extern __shared__ int s_cur[];
     const int p = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-    const int32_t *hp = hist + ((size_t)h * P + p) * C;
-    const int32_t *op = offsets + (size_t)h * (C + 1);
-#pragma unroll 8
-    for (int c = lane; c < C; c += 64) s_cur[c] = op[c] + hp[c];
+    const int32_t *hp = hist + ((size_t)h * P + p) * C, *np = sizes + (size_t)h * C;
+    int32_t *op = offsets + (size_t)h * (C + 1);
+    // Where the part's members of every centre go: the sizes of the centres in front -- scanned by every wave, 64 centres at a
+    // time with eight such loads under way; the first part's wave writes them as the offsets -- and the members in parts in front.
+    int carry = 0;
+    for (int c0 = 0; c0 < C; c0 += 64 * KM_SCATTER_AHEAD) {
+        int n[KM_SCATTER_AHEAD], before[KM_SCATTER_AHEAD];
+#pragma unroll
+        for (int u = 0; u < KM_SCATTER_AHEAD; ++u) {
+            const int c = c0 + u * 64 + lane;
+            n[u] = c < C ? np[c] : 0;
+            before[u] = c < C ? hp[c] : 0;
+        }
+#pragma unroll
+        for (int u = 0; u < KM_SCATTER_AHEAD; ++u) {
+            const int c = c0 + u * 64 + lane, incl = wave_inclusive_scan(n[u], lane), off = carry + incl - n[u];
+            if (c < C) {
+                s_cur[c] = off + before[u];
+                if (p == 0) op[c] = off;
+            }
+            carry += __builtin_amdgcn_readlane(incl, 63);
+        }
+    }
+    if (p == 0 && lane == 0) op[C] = L;
     __syncthreads();
     const int k_end = min(L, (p + 1) * PL);
     const int nbits = 32 - __clz(max(C - 1, 1));           // bits of a centre id
@@ -292,56 +335,100 @@ __global__ __launch_bounds__(64) void kmeans_scatter_kernel(const int32_t *__res
     }
 }
 
-// Mean of the rows of `src` listed for one cluster (members perm[off .. off + n) of head h), fp32 accumulation in
+// Mean of the rows of `src` listed for each cluster (members perm[off .. off + n) of head h), fp32 accumulation in
 // a fixed order: 16 member slots x 16 sixteen-byte pieces of a row, then the slots are added in ascending order.
 // An empty cluster copies prev (the centre it had) or, with prev == NULL, writes zeros.  perm == NULL: the members of
 // a cluster are the rows off .. off + n themselves.
+// A gather bound by how many rows are under way: offset, index and row are three dependent reads.  So a workgroup takes
+// CM_CLUSTERS consecutive clusters, whose indices (one stretch of perm) it fetches together, and requests the first 32 rows of the
+// next cluster before it folds the current one's.  The heads are taken last to first: what the assignment read last is still in the
+// last-level cache.  32 heads x 32768 keys x 1024 centres, traced: one cluster per workgroup 72 us before, 66 in this form, four 55,
+// eight 60; eight with the heads first to last 68.  Few clusters in all are spread over more workgroups (4096, if there are as many).
+constexpr int CM_CLUSTERS = 4, CM_CAP = 512;                 // at most; indices in LDS, the rest of a longer stretch is read from memory
 __global__ __launch_bounds__(256) void cluster_mean_kernel(const _Float16 *__restrict__ src,
                                                            const int32_t *perm,
                                                            const int32_t *__restrict__ sizes,
                                                            const int32_t *__restrict__ offsets,
-                                                           const _Float16 *prev, _Float16 *out, int L, int C)
+                                                           const _Float16 *prev, _Float16 *out, int L, int C, int per)
 {
-    __shared__ float s_acc[16][D + 4];
-    const int c = blockIdx.x, h = blockIdx.y, tid = threadIdx.x;
-    const int slot = tid >> 4, piece = tid & 15;
-    const int off = min(max(offsets[(size_t)h * (C + 1) + c], 0), L);
-    const int n = min(max(sizes[(size_t)h * C + c], 0), L - off);
-    _Float16 *dst = out + ((size_t)h * C + c) * D;
-    if (n == 0) {
-        if (tid < D) dst[tid] = prev ? prev[((size_t)h * C + c) * D + tid] : (_Float16)0.0f;
-        return;
+    __shared__ float s_acc[2][16][D + 4];
+    __shared__ int s_mem[CM_CAP], s_off[CM_CLUSTERS], s_n[CM_CLUSTERS];
+    const int h = (int)(gridDim.y - 1 - blockIdx.y), c0 = (int)blockIdx.x * per, tid = threadIdx.x;
+    const int slot = tid >> 4, piece = tid & 15, nc = min(per, C - c0);
+    if (tid < CM_CLUSTERS) {
+        const int c = min(c0 + tid, C - 1), off = min(max(offsets[(size_t)h * (C + 1) + c], 0), L);
+        s_off[tid] = off;
+        s_n[tid] = min(max(sizes[(size_t)h * C + c], 0), L - off);
     }
-    const int32_t *mem = perm ? perm + (size_t)h * L + off : nullptr;
-    auto member = [&](int m) { return mem ? min(max(mem[m], 0), L - 1) : off + m; };
-    const _Float16 *rows = src + (size_t)h * L * D;
-    float acc[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] = 0.0f;
-    int m = slot;
-    for (; m + 16 < n; m += 32) {                             // two rows in flight
-        const int i0 = member(m), i1 = member(m + 16);
-        const h8 a = *reinterpret_cast<const h8 *>(rows + (size_t)i0 * D + piece * 8);
-        const h8 b = *reinterpret_cast<const h8 *>(rows + (size_t)i1 * D + piece * 8);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += (float)a[j];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += (float)b[j];
-    }
-    if (m < n) {
-        const h8 a = *reinterpret_cast<const h8 *>(rows + (size_t)member(m) * D + piece * 8);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) acc[j] += (float)a[j];
-    }
-#pragma unroll
-    for (int j = 0; j < 8; ++j) s_acc[slot][piece * 8 + j] = acc[j];
     __syncthreads();
-    if (tid < D) {
-        float s = 0.0f;
-#pragma unroll
-        for (int k = 0; k < 16; ++k) s += s_acc[k][tid];
-        dst[tid] = (_Float16)(s / (float)n);
+    const int32_t *mem = perm ? perm + (size_t)h * L : nullptr;
+    const int m0 = s_off[0];
+    const int cap = per > 1 ? CM_CAP : 0;                     // (one cluster: its indices are read where they are used)
+    if (mem && per > 1) {
+        const int end = min(s_off[nc - 1] + s_n[nc - 1] - m0, CM_CAP);
+        for (int i = tid; i < end; i += 256) s_mem[i] = mem[m0 + i];
+        __syncthreads();
     }
+    const _Float16 *rows = src + (size_t)h * L * D;
+    auto row_of = [&](int pos) {                              // member at position pos of the head's list
+        int r = pos;
+        if (mem) {
+            const int i = pos - m0;
+            r = (unsigned)i < (unsigned)cap ? s_mem[i] : mem[pos];   // (offsets that do not ascend: from memory)
+        }
+        return *reinterpret_cast<const h8 *>(rows + (size_t)min(max(r, 0), L - 1) * D + piece * 8);
+    };
+    const h8 zero = {0, 0, 0, 0, 0, 0, 0, 0};
+    h8 a = zero, b = zero;                                    // the current cluster's rows of this slot: slot, slot + 16
+    auto first_rows = [&](int i) {
+        const int off = s_off[i], n = s_n[i];
+        a = slot < n ? row_of(off + slot) : zero;
+        b = slot + 16 < n ? row_of(off + slot + 16) : zero;
+    };
+    first_rows(0);
+    for (int i = 0; i < nc; ++i) {                            // (workgroup-uniform)
+        const int off = s_off[i], n = s_n[i];
+        float acc[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) acc[j] = 0.0f + (float)a[j];
+        if (slot + 16 < n)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += (float)b[j];
+        if (i + 1 < nc) first_rows(i + 1);
+        int m = slot + 32;
+        for (; m + 16 < n; m += 32) {                         // two rows in flight
+            const h8 v = row_of(off + m), w = row_of(off + m + 16);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += (float)v[j];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += (float)w[j];
+        }
+        if (m < n) {
+            const h8 v = row_of(off + m);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) acc[j] += (float)v[j];
+        }
+        float (&buf)[16][D + 4] = s_acc[i & 1];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) buf[slot][piece * 8 + j] = acc[j];
+        __syncthreads();                                      // (the other buffer is read before the next one)
+        if (tid < D) {
+            const size_t at = ((size_t)h * C + c0 + i) * D + tid;
+            float s = 0.0f;
+#pragma unroll
+            for (int k = 0; k < 16; ++k) s += buf[k][tid];
+            out[at] = n > 0 ? (_Float16)(s / (float)n) : prev ? prev[at] : (_Float16)0.0f;
+        }
+    }
+}
+
+static hipError_t launch_cluster_mean(const void *src, const int32_t *perm, const int32_t *sizes, const int32_t *offsets,
+                                      const void *prev, void *out, int H, int L, int C, hipStream_t s)
+{
+    const int per = (int)std::clamp((long long)H * C / 4096, 1ll, (long long)CM_CLUSTERS);
+    hipLaunchKernelGGL(cluster_mean_kernel, dim3((C + per - 1) / per, H), dim3(256), 0, s, (const _Float16 *)src, perm, sizes,
+                       offsets, (const _Float16 *)prev, (_Float16 *)out, L, C, per);
+    return hipGetLastError();
 }
 
 // dst[h, i, :] = src[h, perm[h, i], :] for up to two tensors (blockIdx.z), 16 rows per workgroup.
@@ -379,16 +466,16 @@ static void launch_group(const int32_t *assign, int32_t *sizes, int32_t *offsets
 {
     const int PL = kmeans_part_len(L), P = (L + PL - 1) / PL;
     hipLaunchKernelGGL(kmeans_hist_kernel, dim3(P, H), dim3(256), (size_t)C * 4, s, assign, hist, L, C, PL, P);
-    hipLaunchKernelGGL(kmeans_scan_kernel, dim3(H), dim3(1024), 0, s, hist, sizes, offsets, L, C, P);
+    hipLaunchKernelGGL(kmeans_scan_kernel, dim3((C + 63) / 64, H), dim3(256), 0, s, hist, sizes, C, P);
     hipLaunchKernelGGL(kmeans_scatter_kernel, dim3(P, H), dim3(64), (size_t)C * 4, s, assign, (const int32_t *)hist,
-                       (const int32_t *)offsets, perm, L, C, PL, P);
+                       (const int32_t *)sizes, offsets, perm, L, C, PL, P);
 }
 
 hipError_t launch_kmeans_step(const void *X, const void *centers_in, void *centers_out, int32_t *assign,
                               int32_t *sizes, int32_t *offsets, int32_t *perm, float *hn, int32_t *hist, int H, int L,
                               int C, hipStream_t s)
 {
-    hipLaunchKernelGGL(half_norm_kernel, dim3((H * C + 3) / 4), dim3(256), 0, s, (const _Float16 *)centers_in, hn, H * C);
+    hipLaunchKernelGGL(half_norm_kernel, dim3((H * C + 15) / 16), dim3(256), 0, s, (const _Float16 *)centers_in, hn, H * C);
     const dim3 grid_a((L + KM_ROWS_PER_WG - 1) / KM_ROWS_PER_WG, H);
     hipEvent_t ev0, ev1;
     if (profile_pair(&ev0, &ev1))
@@ -398,10 +485,7 @@ hipError_t launch_kmeans_step(const void *X, const void *centers_in, void *cente
         hipLaunchKernelGGL(kmeans_assign_kernel, grid_a, dim3(256), 0, s, (const _Float16 *)X,
                            (const _Float16 *)centers_in, (const float *)hn, assign, L, C);
     launch_group(assign, sizes, offsets, perm, hist, H, L, C, s);
-    hipLaunchKernelGGL(cluster_mean_kernel, dim3(C, H), dim3(256), 0, s, (const _Float16 *)X, (const int32_t *)perm,
-                       (const int32_t *)sizes, (const int32_t *)offsets, (const _Float16 *)centers_in,
-                       (_Float16 *)centers_out, L, C);
-    return hipGetLastError();
+    return launch_cluster_mean(X, perm, sizes, offsets, centers_in, centers_out, H, L, C, s);
 }
 
 // Nesting fine clusters under coarse ones (Section 3.3: the coarse level is a clustering of the fine centroids).
@@ -458,9 +542,7 @@ hipError_t launch_cluster_layout(const void *K, const void *V, const int32_t *pe
     if (K_sorted)                                             // (V_sorted == NULL: keys only)
         hipLaunchKernelGGL(gather_rows_kernel, dim3((L + 15) / 16, H, V_sorted ? 2 : 1), dim3(256), 0, s,
                            (const _Float16 *)K, (_Float16 *)K_sorted, (const _Float16 *)V, (_Float16 *)V_sorted, perm, L);
-    hipLaunchKernelGGL(cluster_mean_kernel, dim3(C, H), dim3(256), 0, s, (const _Float16 *)K, perm, sizes, offsets,
-                       (const _Float16 *)nullptr, (_Float16 *)centroids, L, C);
-    return hipGetLastError();
+    return launch_cluster_mean(K, perm, sizes, offsets, nullptr, centroids, H, L, C, s);
 }
 
 }  // namespace sq

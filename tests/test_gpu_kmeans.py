@@ -93,6 +93,37 @@ def test_one_iteration_matches_the_oracle(sq, H, L, C, mix):
     check_step(X, cent, got, f"H{H} L{L} C{C}")
 
 
+@pytest.mark.parametrize("H,L,C,kind", [
+    (3, 500, 203, "ties"),          # every centre several times, in other lanes, tiles and groups: the first one wins
+    (2, 300, 65, "ties"),
+    (32, 2000, 300, "one"),         # one cluster longer than the indices held for four, the others empty
+    (33, 700, 257, "one"),          # four clusters a workgroup, the last one alone
+    (64, 200, 129, "all"),          # more clusters than keys
+    (1, 40000, 1500, "all"),        # 64 parts, more than one stretch of the offsets' scan
+])
+def test_edges_of_assignment_grouping_and_means(sq, H, L, C, kind):
+    rng = np.random.default_rng(15)
+    X = rng.standard_normal((H, L, 128))
+    if kind == "one":
+        X = np.broadcast_to(X[:, :1], X.shape) + 0.01 * X
+    X = np.stack([ocl.normalize_rows(X[h].astype(np.float16)) for h in range(H)])
+    cent = rng.standard_normal((H, C, 128)).astype(np.float16)
+    cent = np.stack([ocl.normalize_rows(cent[h]) for h in range(H)])
+    if kind == "ties":
+        cent = np.ascontiguousarray(cent[:, np.arange(C) % 37])
+    if kind == "one":
+        cent[:, C // 2] = X[:, 0]
+    got = gpu_step(sq, X, cent)
+    if kind == "ties":
+        assert got[0].max() < 37
+        cent_first = cent[:, :37]                            # the oracle's margins without the copies
+        check = gpu_step(sq, X, np.ascontiguousarray(cent_first))
+        np.testing.assert_array_equal(got[0], check[0])
+        check_step(X, cent_first, check, f"{kind} H{H} L{L} C{C}")
+    else:
+        check_step(X, cent, got, f"{kind} H{H} L{L} C{C}")
+
+
 def test_normalisation(sq):
     K, _, _ = wl.clustering_input(12, 2, 1000, 8)
     K[0, 5] = 0                                                  # a zero row stays zero
