@@ -126,3 +126,24 @@ def test_one_kept_set(sq, oracle, waves, splits, case, share):
     rr = np.ascontiguousarray(np.broadcast_to(ranges[:, :, None, :cap], (w.B, w.H, w.Lq, cap, 2)))
     nn = np.ascontiguousarray(np.broadcast_to(nr[:, :, None], (w.B, w.H, w.Lq)))
     compare(oracle, w, P, rr, nn, sel)
+
+
+# Rows x shares on either side of the lines between the merges: one, two and eight half waves per row, one and several rounds.
+MERGED = [
+    (8, 12, dict(B=1, H=20, L=3000, C=99, Lq=60, U=3)),                  # 1200 rows: two half waves
+    (8, 19, dict(B=1, H=4, L=6000, C=99, Lq=369, U=3)),                  # 1476 rows: two half waves, two rounds
+    (4, 16, dict(B=1, H=32, L=9600, C=99, Lq=20, U=3)),                  # 640 rows
+    (8, 24, dict(B=1, H=10, L=6000, C=99, Lq=100, U=3)),                 # 1000 rows: eight half waves
+    (8, 46, dict(B=1, H=1, L=64 * 90, C=99, Lq=9, U=3)),                 # nine rows
+]
+
+
+@pytest.mark.parametrize("waves,splits,case", MERGED)
+def test_merges(sq, oracle, waves, splits, case):
+    test_per_query_selection(sq, oracle, waves, splits, case, "random")
+
+
+@pytest.mark.parametrize("waves,splits,case", [(8, 9, dict(B=1, H=9, L=4000, C=99, Lq=100, U=3)),
+                                               (8, 13, dict(B=1, H=1, L=64 * 90, C=99, Lq=9, U=3))])
+def test_merges_one_kept_set(sq, oracle, waves, splits, case):
+    test_one_kept_set(sq, oracle, waves, splits, case, 0.02)             # (shares without a key among them)
