@@ -1058,7 +1058,7 @@ int sq_prefill_mean_step(const sq_shape_t *sh, const void *q, const void *centro
     const int rows = sh->B * sh->H;
     SQ_HIP(sq::launch_prefill_lookup(q, centroids, sizes, thresh, w.stats, nullptr, nullptr, w.part_sum, true, sh->B,
                                      sh->H, sh->Lq, sh->C, sh->sm_scale, s));
-    SQ_HIP(sq::launch_mean_select(w.part_sum, sq::lookup_parts(rows, sh->Lq, sh->C), (float)sh->Lq, thresh, sizes, offsets,
+    SQ_HIP(sq::launch_mean_select(w.part_sum, sq::lookup_parts(rows, sh->Lq, sh->C), sh->Lq, thresh, sizes, offsets,
                                   nullptr, nullptr, false, keep_mask, n_keys, w.att.hdr, w.att.key_idx, sh->L, rows, sh->H,
                                   sh->C, s));
     SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.att.hdr, w.att.key_idx, w.att.partials, out,
@@ -1372,13 +1372,13 @@ int sq_hier_prefill_mean_step(const sq_shape_t *sh, int32_t C1, const void *q, c
     // Level 1 (Eq. 2 averaged over the tokens): the children of the kept coarse clusters are listed as candidates ...
     SQ_HIP(sq::launch_prefill_lookup(q, centroids1, sizes1, thresh1, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
                                      sh->B, sh->H, sh->Lq, C1, sh->sm_scale, s));
-    SQ_HIP(sq::launch_mean_select(w.step.part_sum, sq::lookup_parts(rows, sh->Lq, C1), (float)sh->Lq, thresh1, sizes1,
+    SQ_HIP(sq::launch_mean_select(w.step.part_sum, sq::lookup_parts(rows, sh->Lq, C1), sh->Lq, thresh1, sizes1,
                                   child_offsets, nullptr, nullptr, true, nullptr, nullptr, w.cand_hdr, w.cand_id, sh->C, rows,
                                   sh->H, C1, s));
     // ... level 2 (Eq. 3 per token over the candidates, averaged over the tokens): scores and selection in candidate order.
     SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
                                      sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s, w.cand_id, w.cand_hdr));
-    SQ_HIP(sq::launch_mean_select(w.step.part_sum, sq::lookup_parts(rows, sh->Lq, sh->C, true), (float)sh->Lq, thresh2, sizes2,
+    SQ_HIP(sq::launch_mean_select(w.step.part_sum, 0, sh->Lq, thresh2, sizes2,
                                   offsets2, w.cand_id, w.cand_hdr, false, keep_mask2, n_keys, w.step.att.hdr,
                                   w.step.att.key_idx, sh->L, rows, sh->H, sh->C, s));
     const PrefillSharedWs &att = w.step.att;

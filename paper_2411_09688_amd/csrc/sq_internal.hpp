@@ -67,7 +67,7 @@ hipError_t launch_mean_score(const float *logits, const float *row_max, const fl
 // (lookup_part_floats() floats).
 constexpr int LK_MAX_SLICES = 32;
 int lookup_slices(int BH, int Lq, int C);
-int lookup_parts(int BH, int Lq, int C, bool cands = false);
+int lookup_parts(int BH, int Lq, int C);
 size_t lookup_part_floats(int BH, int C);
 inline size_t lookup_stat_floats(int BH, int Lq, int C) { return (size_t)BH * Lq * lookup_slices(BH, Lq, C) * 2; }
 hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int32_t *sizes, const float *thresh,
@@ -89,14 +89,14 @@ hipError_t launch_lookup_rows(const void *q, const void *centroids, const int32_
                               float sm_scale, hipStream_t s, const BlockTable *table);
 hipError_t launch_child_parent(const int32_t *child_offsets, int32_t *parent, int H, int C1, int C2, hipStream_t s);
 // (cand_id [B*H, C] / cand_hdr [B*H] given, with mean: only the hdr.y candidates listed for a (sequence, head) are
-// scored, statistics over them alone, part_sum in candidate order: level 2 of a hierarchical lookup.)
+// scored, statistics over them alone, part_sum [B*H, lookup_cand_stride()] in candidate order: level 2 of a hierarchical lookup.)
 // Kept ranges (records of a plan) -> the rows' lists of kept keys idx [rows, L].
 hipError_t launch_expand_ranges(DecodePlan plan, int32_t *idx, int rows, int L, hipStream_t s);
-// Averaged selection (sq_mean_select.hip): part_sum [rows, parts, C], keep iff N > 0 and sum of the parts / div > T, into the
+// Averaged selection (sq_mean_select.hip): part_sum [rows, parts, C], keep iff N > 0 and sum of the parts / Lq > T, into the
 // mask (optional), the rows' lists of kept keys, or with `children` of the kept clusters' child clusters, list [rows, list_len],
 // and hdr[row] = (clusters, list entries); n_keys (optional) = list entries.  cand_id / cand_hdr given: the row's entries are its
-// candidates.
-hipError_t launch_mean_select(const float *part_sum, int parts, float div, const float *thresh, const int32_t *sizes,
+// candidates, with part_sum as launch_prefill_lookup leaves it for them (parts not used).
+hipError_t launch_mean_select(const float *part_sum, int parts, int Lq, const float *thresh, const int32_t *sizes,
                               const int32_t *offsets, const int32_t *cand_id, const int2 *cand_hdr, bool children,
                               uint32_t *keep_mask, int32_t *n_keys, int2 *hdr, int32_t *list, int list_len, int rows, int H,
                               int C, hipStream_t s);

@@ -12,6 +12,21 @@ __device__ __forceinline__ void lk_stage(const char *base, uint32_t off, uint32_
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(lds), "v"(off), "s"(base) : "m0");
 }
 
+constexpr int LK_MC = 128;                   // clusters per workgroup of the averaging kernel (four waves x 32)
+constexpr int LK_MT = 64;                    // tokens per staged tile
+constexpr int LK_MEAN_GROUPS = 512;          // workgroups of it that there should be: two per compute unit
+
+// Parts the tokens of a row with C clusters are dealt to where (sequence, head) x blocks of clusters alone are few; and, for
+// candidates, whose number n the device alone knows, the length of a row's partial sums, [parts of n][n] in front: room for n = C_all
+// in one part and for any n whose parts are more (parts * blocks * BH <= LK_MEAN_GROUPS).
+__host__ __device__ inline int lookup_mean_parts(int BH, int Lq, int C)
+{
+    const int blocks = (C + LK_MC - 1) / LK_MC, tiles = (Lq + LK_MT - 1) / LK_MT, groups = LK_MEAN_GROUPS / BH;
+    const int p = blocks > 0 ? groups / blocks : 1;
+    return p < 1 ? 1 : p < tiles ? p : tiles;
+}
+__host__ __device__ inline size_t lookup_cand_stride(int BH, int C_all) { return (size_t)C_all + LK_MEAN_GROUPS * LK_MC / BH; }
+
 // The least raw score x that passes exp2((x - m) c2) > thr, the test of Eq. 1's scores against T * D with m the row's largest
 // score: exactly the boundary of that float expression, so that a score which equals the threshold is dropped.  (thr < 0:
 // everything; thr >= 1 or not a number: nothing -- NaN, which no comparison passes.)  The differences that pass are an interval

@@ -13,6 +13,7 @@
 #include "sq_common.hpp"
 #include "sq_internal.hpp"
 #include "sq_key_list.hpp"
+#include "sq_lookup.hpp"
 
 namespace sq {
 
@@ -21,12 +22,12 @@ constexpr int MS_STEPS = SELECT_MAX_C / MS_THREADS;          // entries per thre
 constexpr int MS_GROUPS = SELECT_MAX_C / 64;                 // an entry group: one wave in one step
 constexpr int MS_SLICE_GROUPS = 16;                          // of a slice, at most: its kept clusters lie in LDS
 
-// CAND: the row's entries are its candidates cand_id[row, 0 .. cand_hdr[row].y), part_sum is in candidate order and mask bits
-// are set by cluster id.  children: a kept cluster stands for the offsets[i] .. offsets[i + 1] - 1 of the next level (a kept
+// CAND: the row's entries are its candidates cand_id[row, 0 .. cand_hdr[row].y), part_sum is in candidate order (row_parts not
+// used, see lookup_mean_parts) and mask bits are set by cluster id.  children: a kept cluster stands for the offsets[i] .. offsets[i + 1] - 1 of the next level (a kept
 // cluster without children emits nothing) instead of its N_i keys.  list [rows, list_len]; hdr[row] = (entries kept, length).
 template <bool CAND, int MS_AHEAD>                           // MS_AHEAD: steps whose loads are in flight together
 __global__ __launch_bounds__(MS_THREADS) void mean_select_kernel(
-    const float *__restrict__ part_sum, int parts, float div, const float *__restrict__ thresh,
+    const float *__restrict__ part_sum, int row_parts, int Lq, const float *__restrict__ thresh,
     const int32_t *__restrict__ sizes, const int32_t *__restrict__ offsets, const int32_t *__restrict__ cand_id,
     const int2 *__restrict__ cand_hdr, bool children, uint32_t *__restrict__ keep_mask, int32_t *__restrict__ n_keys,
     int2 *__restrict__ hdr, int32_t *__restrict__ list, int list_len, int nsl, int H, int C)
@@ -42,7 +43,10 @@ __global__ __launch_bounds__(MS_THREADS) void mean_select_kernel(
     const int ga = sl * per, gb = min(ga + per, ng);         // this slice's groups
     if (ga >= ng && sl > 0) return;                          // (workgroup-uniform)
     const bool last = gb == ng;
-    const float *ps = part_sum + (size_t)row * parts * C;
+    const int parts = CAND ? lookup_mean_parts((int)gridDim.x / nsl, Lq, n) : row_parts;
+    const int part_len = CAND ? n : C;
+    const float *ps = part_sum + (CAND ? row * lookup_cand_stride((int)gridDim.x / nsl, C) : (size_t)row * parts * C);
+    const float div = (float)Lq;
     const int32_t *N = sizes + (size_t)h * C, *off = offsets + (size_t)h * (C + 1);
     const int32_t *cid = CAND ? cand_id + (size_t)row * C : nullptr;
     const float T = thresh[h];
@@ -74,7 +78,7 @@ __global__ __launch_bounds__(MS_THREADS) void mean_select_kernel(
         for (int p = 0; p < parts; ++p) {                    // parts added in ascending order
 #pragma unroll
             for (int k = 0; k < MS_AHEAD; ++k)
-                sum[k] += at[(size_t)p * C + (MS_AHEAD == 1 ? 0 : min(k * MS_THREADS, max(n_end - 1 - st0 * MS_THREADS - tid, 0)))];
+                sum[k] += at[(size_t)p * part_len + (MS_AHEAD == 1 ? 0 : min(k * MS_THREADS, max(n_end - 1 - st0 * MS_THREADS - tid, 0)))];
         }
 #pragma unroll
         for (int k = 0; k < MS_AHEAD; ++k) {
@@ -134,7 +138,7 @@ __global__ __launch_bounds__(MS_THREADS) void mean_select_kernel(
     write_key_index(s_rec, all_c - first, list + (size_t)row * list_len, list_len, MS_THREADS);
 }
 
-hipError_t launch_mean_select(const float *part_sum, int parts, float div, const float *thresh, const int32_t *sizes,
+hipError_t launch_mean_select(const float *part_sum, int parts, int Lq, const float *thresh, const int32_t *sizes,
                               const int32_t *offsets, const int32_t *cand_id, const int2 *cand_hdr, bool children,
                               uint32_t *keep_mask, int32_t *n_keys, int2 *hdr, int32_t *list, int list_len, int rows, int H,
                               int C, hipStream_t s)
@@ -145,7 +149,7 @@ hipError_t launch_mean_select(const float *part_sum, int parts, float div, const
     const int groups = (C + 63) / 64, least = (groups + MS_SLICE_GROUPS - 1) / MS_SLICE_GROUPS;
     const int nsl = std::clamp(256 / rows, least, groups);
     auto launch = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(rows * nsl), dim3(MS_THREADS), 0, s, part_sum, parts, div, thresh, sizes, offsets,
+        hipLaunchKernelGGL(kernel, dim3(rows * nsl), dim3(MS_THREADS), 0, s, part_sum, parts, Lq, thresh, sizes, offsets,
                            cand_id, cand_hdr, children, keep_mask, n_keys, hdr, list, list_len, nsl, H, C);
     };
     if (cand_id) C <= MS_THREADS ? launch(mean_select_kernel<true, 1>) : launch(mean_select_kernel<true, 4>);

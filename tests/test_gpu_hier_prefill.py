@@ -125,6 +125,29 @@ def test_hier_prefill_mean_step_small(sq, oracle, case):
     assert 0 < gk.sum() < w.B * w.H * w.C
 
 
+# The averages over the candidates: blocks of 128 candidates times parts of the tokens (tiles of 64), the parts by the row's own
+# number of candidates, 512 workgroups over all rows.
+PART_CASES = [
+    dict(B=1, H=2, L=1500, C=128, C1=8, Lq=200),      # one full block, a part per tile, the last tile of 8 tokens
+    dict(B=1, H=2, L=1500, C=129, C1=8, Lq=257),      # a second block of one candidate, five tiles
+    dict(B=2, H=30, L=900, C=300, C1=12, Lq=129),     # two parts for three tiles
+    dict(B=2, H=65, L=700, C=260, C1=10, Lq=65),      # a part a row, three blocks
+    dict(B=3, H=175, L=400, C=130, C1=5, Lq=3),       # more rows than workgroups wanted
+]
+
+
+@pytest.mark.parametrize("first", ["all", "some"])
+@pytest.mark.parametrize("case", PART_CASES, ids=lambda c: "B{B}H{H}C{C}Lq{Lq}".format(**c))
+def test_candidate_parts(sq, oracle, case, first):
+    w = wl.make_workload("hier_prefill_parts", seed=35, threads=4, U=9, keep_frac=0.2, coarse_keep_frac=0.5,
+                         causal_user=False, variable_fanout=True, **case)
+    T1, T2 = thresholds(w)
+    if first == "all":
+        T1 = np.full(w.H, -1.0, np.float32)
+    gk, _ = compare(oracle, w, T1, T2, run(sq, w, T1, T2), f"candidate parts {case} {first}", sample=400)
+    assert 0 < gk.sum() < w.B * w.H * w.C
+
+
 def test_first_level_keeping_everything_is_the_one_level_step(sq, oracle):
     w = wl.make_workload("hier_prefill_mean_all", B=1, H=2, L=4096, C=128, C1=8, Lq=50, U=20, keep_frac=0.2,
                          coarse_keep_frac=0.5, causal_user=True, seed=32, threads=2)
