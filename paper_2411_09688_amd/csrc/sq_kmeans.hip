@@ -266,31 +266,46 @@ __global__ __launch_bounds__(256) void kmeans_scan_kernel(int32_t *__restrict__ 
 // same centre id are found in registers (a ballot per bit of the id); a lane's slot is the cluster's cursor plus the number of matching lanes below it, so members appear in
 // ascending key order inside every cluster (a stable sort).  The cursors live in LDS and are touched by this one
 // wave only, in program order (all lanes of a group read the cursor, then its last lane advances it): no atomics.
-// The launch is one wave's chain of reads: with the ids of the next 512 keys fetched together instead of 64 at a time, 32
-// heads x 32K keys x 1024 centres take 15.8 us instead of 20.3.
-constexpr int KM_SCATTER_AHEAD = 8;
+// The launch is one wave's chain of reads, so the ids of 512 keys are fetched together, the first ones before the sizes are
+// scanned, and the sizes of 1024 centres.  The parts of a head share an XCD: they fill the same lines of the list, which would
+// otherwise lie in eight L2s, a few words in each.  Whole iteration of 32 heads x 32K keys x 1024 centres 299.4 -> 294.2 us (scatter
+// 17.0 -> 12.0 traced; with the XCDs alone 295.8, with the reads alone 298.9), 16 heads x 30000 x 800 139.4 -> 137.1, one head x 20000
+// x 500 35.0 -> 34.6.
+constexpr int KM_SCATTER_AHEAD = 8, KM_CURSOR_AHEAD = 16;
 __global__ __launch_bounds__(64) void kmeans_scatter_kernel(const int32_t *__restrict__ assign,
                                                             const int32_t *__restrict__ hist,
                                                             const int32_t *__restrict__ sizes, int32_t *__restrict__ offsets,
-                                                            int32_t *__restrict__ perm, int L, int C, int PL, int P)
+                                                            int32_t *__restrict__ perm, int H, int L, int C, int PL, int P)
 {
     extern __shared__ int s_cur[];
-    const int p = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
+    const int per_xcd = (H * P + 7) >> 3, unit = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
+    if (unit >= H * P) return;
+    const int h = unit / P, p = unit - h * P, lane = threadIdx.x;
     const int32_t *hp = hist + ((size_t)h * P + p) * C, *np = sizes + (size_t)h * C;
     int32_t *op = offsets + (size_t)h * (C + 1);
     // Where the part's members of every centre go: the sizes of the centres in front -- scanned by every wave, 64 centres at a
-    // time with eight such loads under way; the first part's wave writes them as the offsets -- and the members in parts in front.
-    int carry = 0;
-    for (int c0 = 0; c0 < C; c0 += 64 * KM_SCATTER_AHEAD) {
-        int n[KM_SCATTER_AHEAD], before[KM_SCATTER_AHEAD];
+    // time with sixteen such loads under way; the first part's wave writes them as the offsets -- and the members in parts in front.
+    const int k_end = min(L, (p + 1) * PL);
+    const int32_t *ap = assign + (size_t)h * L;
+    int ids[KM_SCATTER_AHEAD];                             // of a stretch of keys, all of them under way before the first is used
+    auto fetch = [&](int k0) {
 #pragma unroll
-        for (int u = 0; u < KM_SCATTER_AHEAD; ++u) {
-            const int c = c0 + u * 64 + lane;
-            n[u] = c < C ? np[c] : 0;
-            before[u] = c < C ? hp[c] : 0;
+        for (int u = 0; u < KM_SCATTER_AHEAD; ++u) ids[u] = ap[min(k0 + u * 64 + lane, L - 1)];
+    };
+    fetch(p * PL);
+    int carry = 0;
+    for (int c0 = 0; c0 < C; c0 += 64 * KM_CURSOR_AHEAD) {
+        int n[KM_CURSOR_AHEAD], before[KM_CURSOR_AHEAD];
+#pragma unroll
+        for (int u = 0; u < KM_CURSOR_AHEAD; ++u) {
+            const int c = min(c0 + u * 64 + lane, C - 1);
+            n[u] = np[c];
+            before[u] = hp[c];
         }
 #pragma unroll
-        for (int u = 0; u < KM_SCATTER_AHEAD; ++u) {
+        for (int u = 0; u < KM_CURSOR_AHEAD; ++u) {
+            if (c0 + u * 64 >= C) break;                   // uniform
+            n[u] = c0 + u * 64 + lane < C ? n[u] : 0;
             const int c = c0 + u * 64 + lane, incl = wave_inclusive_scan(n[u], lane), off = carry + incl - n[u];
             if (c < C) {
                 s_cur[c] = off + before[u];
@@ -301,15 +316,9 @@ __global__ __launch_bounds__(64) void kmeans_scatter_kernel(const int32_t *__res
     }
     if (p == 0 && lane == 0) op[C] = L;
     __syncthreads();
-    const int k_end = min(L, (p + 1) * PL);
     const int nbits = 32 - __clz(max(C - 1, 1));           // bits of a centre id
     for (int k0 = p * PL; k0 < k_end; k0 += 64 * KM_SCATTER_AHEAD) {
-        int ids[KM_SCATTER_AHEAD];                         // all loads of a stretch in flight before the first is used
-#pragma unroll
-        for (int u = 0; u < KM_SCATTER_AHEAD; ++u) {
-            const int k = k0 + u * 64 + lane;
-            ids[u] = k < k_end ? assign[(size_t)h * L + k] : 0;
-        }
+        if (k0 > p * PL) fetch(k0);
 #pragma unroll
         for (int u = 0; u < KM_SCATTER_AHEAD; ++u) {
             if (k0 + u * 64 >= k_end) break;               // uniform
@@ -467,8 +476,8 @@ static void launch_group(const int32_t *assign, int32_t *sizes, int32_t *offsets
     const int PL = kmeans_part_len(L), P = (L + PL - 1) / PL;
     hipLaunchKernelGGL(kmeans_hist_kernel, dim3(P, H), dim3(256), (size_t)C * 4, s, assign, hist, L, C, PL, P);
     hipLaunchKernelGGL(kmeans_scan_kernel, dim3((C + 63) / 64, H), dim3(256), 0, s, hist, sizes, C, P);
-    hipLaunchKernelGGL(kmeans_scatter_kernel, dim3(P, H), dim3(64), (size_t)C * 4, s, assign, (const int32_t *)hist,
-                       (const int32_t *)sizes, offsets, perm, L, C, PL, P);
+    hipLaunchKernelGGL(kmeans_scatter_kernel, dim3((H * P + 7) / 8 * 8), dim3(64), (size_t)C * 4, s, assign, (const int32_t *)hist,
+                       (const int32_t *)sizes, offsets, perm, H, L, C, PL, P);
 }
 
 hipError_t launch_kmeans_step(const void *X, const void *centers_in, void *centers_out, int32_t *assign,

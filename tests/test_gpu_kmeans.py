@@ -124,6 +124,19 @@ def test_edges_of_assignment_grouping_and_means(sq, H, L, C, kind):
         check_step(X, cent, got, f"{kind} H{H} L{L} C{C}")
 
 
+@pytest.mark.parametrize("H,L,C", [
+    (3, 1537, 1024),           # one round of cursors, full; the last part one key long; parts x heads no multiple of eight
+    (1, 2049, 1025),           # a second round of one centre; fewer workgroups than XCDs
+    (5, 512, 64),              # a part a head, one stretch of ids, full
+    (7, 33000, 2049),          # parts of two stretches, three rounds
+])
+def test_grouping_rounds_and_stretches(sq, H, L, C):
+    rng = np.random.default_rng(16)
+    X = np.stack([ocl.normalize_rows(rng.standard_normal((L, 128)).astype(np.float16)) for _ in range(H)])
+    cent = np.stack([X[h][rng.choice(L, size=C, replace=C > L)] for h in range(H)])
+    check_step(X, cent, gpu_step(sq, X, cent), f"grouping H{H} L{L} C{C}")
+
+
 def test_normalisation(sq):
     K, _, _ = wl.clustering_input(12, 2, 1000, 8)
     K[0, 5] = 0                                                  # a zero row stays zero
