@@ -543,38 +543,56 @@ __global__ __launch_bounds__(MERGE_THREADS) void decode_merge_index_kernel(const
 // bit-identical whichever slice asks.  Two launches: the first counts the kept clusters and keys of every slice and
 // sets the mask bits (by cluster id, into a mask the scoring launch zeroed); the second, knowing the counts of the
 // slices in front of its own, writes the key rows into the row's key-index list and (slice 0) the row's counts.
+// Up to CAND_ONE_C clusters one launch does both: a workgroup decides the candidates in front of its slice itself, which costs 16
+// bytes for each of them per slice.  Whole step, us, two launches / one: one head x 1500 clusters 29.9 / 26.2, 32 heads x 4000
+// 42.3 / 38.7, 8 x 6000 39.6 / 36.1, 16 x 8192 51.7 / 49.6, 32 x 8192 68.8 / 66.4, 20 x 12000 76.6 / 77.3, 32 x 16384 111.2 / 117.7.
 constexpr int CAND_THREADS = 1024;                               // = items of a row, at most
 constexpr int CAND_SLICE = 256;
 constexpr int CAND_WAVES = CAND_SLICE / 64;                      // waves that hold candidates
 constexpr int CAND_ITEM_WAVES = CAND_THREADS / 64;
 static_assert(CAND_SLICE == 256, "cand_slices_for counts slices of 256 candidates");
 
-template <bool EMIT>
+constexpr int CAND_ONE_C = 8192;
+constexpr int CAND_AHEAD = 4;                                    // records in front that a thread has under way
+enum CandPass { CAND_COUNT, CAND_WRITE, CAND_BOTH };
+
+template <CandPass PASS>
 struct CandLds {
     float red[CAND_ITEM_WAVES];
+    int front_cnt[CAND_ITEM_WAVES], front_keys[CAND_ITEM_WAVES];
     int cnt[CAND_WAVES + 1], keys[CAND_WAVES + 1], base[2];
     int wsum[CAND_ITEM_WAVES], unit[3];
-    int4 rec[EMIT ? CAND_SLICE : 1];
+    int4 rec[PASS != CAND_COUNT ? CAND_SLICE : 1];
 };
 
 // Slice `sl` of row `row` (n candidates), by the whole workgroup.  Leaves the LDS free for the next slice.
-template <bool EMIT>
+template <CandPass PASS>
 __device__ __forceinline__ void cand_select_slice(const CandSelect &cs, const float *__restrict__ thresh,
                                                   uint32_t *__restrict__ keep_mask,
                                                   int32_t *__restrict__ n_ranges, int32_t *__restrict__ n_keys,
                                                   const KeyIndexPlan &plan, int H, int C, int nsl, int row, int sl, int n,
-                                                  CandLds<EMIT> &S)
+                                                  CandLds<PASS> &S)
 {
     float (&s_red)[CAND_ITEM_WAVES] = S.red;
     int (&s_cnt)[CAND_WAVES + 1] = S.cnt, (&s_keys)[CAND_WAVES + 1] = S.keys, (&s_base)[2] = S.base;
-    int4 (&s_rec)[EMIT ? CAND_SLICE : 1] = S.rec;
+    int4 (&s_rec)[PASS != CAND_COUNT ? CAND_SLICE : 1] = S.rec;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int j = sl * CAND_SLICE + tid;
     const int4 rv = tid < CAND_SLICE && j < n ? cs.rec[(size_t)row * C + j] : make_int4(0, (int)0x80000000u, 0, 0);
     const int n_sl = (n + CAND_SLICE - 1) / CAND_SLICE;         // slices with candidates: at most 64
+    const int n_front = PASS == CAND_BOTH ? min(sl * CAND_SLICE, n) : 0;
+    int4 front[CAND_AHEAD];
+    auto fetch = [&](int i0) {
+#pragma unroll
+        for (int k = 0; k < CAND_AHEAD; ++k) {
+            const int i = i0 + k * CAND_THREADS + tid;
+            front[k] = i < n_front ? cs.rec[(size_t)row * C + i] : make_int4(0, (int)0x80000000u, 0, 0);
+        }
+    };
+    if (PASS == CAND_BOTH) fetch(0);
     int2 sc = make_int2(0, 0);
     float m, thr;                                               // the row's maximum and T * D
-    if constexpr (EMIT) {
+    if constexpr (PASS == CAND_WRITE) {
         // (the counting launch left them: the same bits, without the round trip to the items' pairs and three barriers)
         if (tid < n_sl) sc = cs.slice_cnt[(size_t)row * nsl + tid];
         const float2 rs = cs.row_stat[row];
@@ -599,9 +617,28 @@ __device__ __forceinline__ void cand_select_slice(const CandSelect &cs, const fl
 #pragma unroll
         for (int w = 0; w < CAND_ITEM_WAVES; ++w) Dsum += s_red[w];
         thr = T * Dsum;
-        if (sl == 0 && tid == 0) cs.row_stat[row] = make_float2(m, thr);   // for the writing launch
+        if (PASS == CAND_COUNT && sl == 0 && tid == 0) cs.row_stat[row] = make_float2(m, thr);   // for the writing launch
     }
-    const bool keep = tid < CAND_SLICE && j < n && rv.y >= 0 && expf(__int_as_float(rv.x) - m) > thr;
+    auto kept = [&](const int4 &r) { return r.y >= 0 && expf(__int_as_float(r.x) - m) > thr; };
+    const bool keep = tid < CAND_SLICE && j < n && kept(rv);
+    if (n_front > 0) {                                          // (workgroup-uniform)
+        int fc = 0, fk = 0;
+        for (int i0 = 0; i0 < n_front; i0 += CAND_AHEAD * CAND_THREADS) {
+            if (i0 > 0) fetch(i0);
+#pragma unroll
+            for (int k = 0; k < CAND_AHEAD; ++k)
+                if (kept(front[k])) {
+                    ++fc;
+                    fk += front[k].w;
+                }
+        }
+        fc = wave_sum_i(fc);
+        fk = wave_sum_i(fk);
+        if (lane == 0) {
+            S.front_cnt[wave] = fc;
+            S.front_keys[wave] = fk;
+        }
+    }
 
     const unsigned long long bal = __ballot(keep);
     const int kv = keep ? rv.w : 0;
@@ -610,10 +647,10 @@ __device__ __forceinline__ void cand_select_slice(const CandSelect &cs, const fl
         s_cnt[wave] = __popcll(bal);
         s_keys[wave] = incl;
     }
-    if (!EMIT && keep_mask && wave < CAND_WAVES)
+    if (PASS != CAND_WRITE && keep_mask && wave < CAND_WAVES)
         wave_mask_or(keep_mask + (size_t)row * ((C + 31) >> 5), rv.y & 0x7fffffff, keep, lane);
     __syncthreads();
-    if (!EMIT) {
+    if (PASS == CAND_COUNT) {
         if (tid == 0) {
             int r = 0, k = 0;
 #pragma unroll
@@ -630,8 +667,18 @@ __device__ __forceinline__ void cand_select_slice(const CandSelect &cs, const fl
         // exclusive prefix of the per-wave counts; records and keys of the slices in front; the row's totals
         const int c = lane < CAND_WAVES ? s_cnt[lane] : 0, kk = lane < CAND_WAVES ? s_keys[lane] : 0;
         const int ci = wave_inclusive_scan(c, lane), ki = wave_inclusive_scan(kk, lane);
-        const int before_r = wave_sum_i(lane < sl ? sc.x : 0), before_k = wave_sum_i(lane < sl ? sc.y : 0);
-        const int tot_r = wave_sum_i(sc.x), tot_k = wave_sum_i(sc.y);
+        int before_r, before_k, tot_r, tot_k;
+        bool counts;                                            // this slice writes the row's counts
+        if constexpr (PASS == CAND_BOTH) {
+            const bool f = n_front > 0 && lane < CAND_ITEM_WAVES;
+            before_r = wave_sum_i(f ? S.front_cnt[lane] : 0), before_k = wave_sum_i(f ? S.front_keys[lane] : 0);
+            tot_r = before_r + ci, tot_k = before_k + ki;       // (in lane 63)
+            counts = (sl + 1) * CAND_SLICE >= n;
+        } else {
+            before_r = wave_sum_i(lane < sl ? sc.x : 0), before_k = wave_sum_i(lane < sl ? sc.y : 0);
+            tot_r = wave_sum_i(sc.x), tot_k = wave_sum_i(sc.y);
+            counts = sl == 0;
+        }
         if (lane < CAND_WAVES) {
             s_cnt[lane] = ci - c;
             s_keys[lane] = ki - kk;
@@ -640,7 +687,7 @@ __device__ __forceinline__ void cand_select_slice(const CandSelect &cs, const fl
             s_cnt[CAND_WAVES] = ci;
             s_base[0] = before_r;
             s_base[1] = before_k;
-            if (sl == 0) {
+            if (counts) {
                 n_ranges[row] = tot_r;
                 n_keys[row] = tot_k;
                 plan.row_keys[row] = min(tot_k, plan.L);
@@ -661,14 +708,14 @@ __device__ __forceinline__ void cand_select_slice(const CandSelect &cs, const fl
 // Workgroups -> slices (rows <= CAND_THREADS): a fixed grid; every workgroup reads all rows' candidate counts and takes
 // the non-empty slices u = workgroup, workgroup + grid, ... of the rows laid end to end (a row without candidates counts
 // as one slice: its counts are still written), so no workgroup is launched only to find that its slice is empty.
-template <bool EMIT>
+template <CandPass PASS>
 __global__ __launch_bounds__(CAND_THREADS) void cand_select_kernel(CandSelect cs, const float *__restrict__ thresh,
                                                                    uint32_t *__restrict__ keep_mask,
                                                                    int32_t *__restrict__ n_ranges,
                                                                    int32_t *__restrict__ n_keys, KeyIndexPlan plan,
                                                                    int rows, int H, int C, int nsl)
 {
-    __shared__ CandLds<EMIT> S;
+    __shared__ CandLds<PASS> S;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n_t = tid < rows ? min(cs.hdr[tid].y, C) : 0;
     const int cnt = tid < rows ? max(1, (n_t + CAND_SLICE - 1) / CAND_SLICE) : 0;
@@ -690,7 +737,7 @@ __global__ __launch_bounds__(CAND_THREADS) void cand_select_kernel(CandSelect cs
         }
         __syncthreads();
         const int row = S.unit[0], sl = S.unit[1], n = S.unit[2];
-        cand_select_slice<EMIT>(cs, thresh, keep_mask, n_ranges, n_keys, plan, H, C, nsl, row, sl, n, S);
+        cand_select_slice<PASS>(cs, thresh, keep_mask, n_ranges, n_keys, plan, H, C, nsl, row, sl, n, S);
     }
 }
 
@@ -701,15 +748,15 @@ hipError_t launch_cand_select(CandSelect cs, const float *thresh, uint32_t *keep
     if (nsl > 64 || chunk_cap_for(C) > CAND_ITEM_WAVES * 64 || rows > CAND_THREADS || !plan.key_idx || !plan.row_keys)
         return hipErrorInvalidValue;
     const int grid = (int)std::min<long long>((long long)rows * nsl, 2 * 256);   // two workgroups per compute unit
-    hipLaunchKernelGGL(cand_select_kernel<false>, dim3(grid), dim3(CAND_THREADS), 0, s, cs, thresh, keep_mask, n_ranges,
-                       n_keys, plan, rows, H, C, nsl);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(cand_select_kernel<true>, dim3(grid), dim3(CAND_THREADS), 0, s, cs, thresh, keep_mask, n_ranges,
-                       n_keys, plan, rows, H, C, nsl);
-    return hipGetLastError();
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(CAND_THREADS), 0, s, cs, thresh, keep_mask, n_ranges, n_keys, plan, rows, H, C,
+                           nsl);
+        return hipGetLastError();
+    };
+    if (C <= CAND_ONE_C) return launch(cand_select_kernel<CAND_BOTH>);
+    const hipError_t e = launch(cand_select_kernel<CAND_COUNT>);
+    return e != hipSuccess ? e : launch(cand_select_kernel<CAND_WRITE>);
 }
-
 
 hipError_t launch_select_index(const float *logits, const float *thresh, const int32_t *sizes, const int32_t *offsets,
                                uint32_t *keep_mask, int32_t *n_ranges, int32_t *n_keys, KeyIndexPlan plan, int rows,

@@ -269,12 +269,12 @@ hipError_t launch_decode_small(const void *q, const void *centroids, const int32
                                const float *thresh, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                uint32_t *keep_mask, int32_t *n_keys, float *partials, void *out, float *lse, int rows,
                                int H, int G, int L, int C, int U, int splits, float sm_scale, hipStream_t s);
-// Last level of a hierarchical lookup, selected in slices of 256 candidates per workgroup (two launches: count, then
-// write).  rec / hdr / stats / row_items: the candidates' records, per-row candidate counts (hdr[row].y), per-item
+// Last level of a hierarchical lookup, selected in slices of 256 candidates per workgroup (one launch, or for many
+// clusters two: count, then write).  rec / hdr / stats / row_items: the candidates' records, per-row candidate counts (hdr[row].y), per-item
 // statistics and per-row (first item, items), as launch_gather_score leaves them; slice_cnt [rows, cand_slices_for(C)]
 // is scratch.  keep_mask (optional) must have been zeroed (launch_gather_score does it).  C <= SELECT_MAX_C, at most
 // 1024 rows.  (The lookup without attention, which returns ranges, keeps the one-workgroup-per-row selection: over all
-// queries of a workload its single launch is faster than these two.)
+// queries of a workload its single launch is faster than these.)
 struct CandSelect {
     const int4 *rec;
     const int2 *hdr;

@@ -156,6 +156,27 @@ def test_hier_decode_medium(sq, oracle):
     hier_decode_and_compare(sq, oracle, w, "hier_medium")
 
 
+@pytest.mark.parametrize("B,H,C,L", [
+    (1, 2, 256, 4000),              # one slice, full
+    (1, 3, 257, 4000),              # a second slice of one candidate
+    (2, 1, 1281, 9000),             # slices with more records in front than threads
+    (1, 1, 4097, 20000),            # ... and (the last one) than a thread has under way
+    (1, 2, 8192, 30000),            # the most clusters of one launch
+    (1, 2, 8193, 30000),            # the fewest of two
+    (300, 2, 300, 1500),            # more slices than workgroups
+])
+@pytest.mark.parametrize("coarse", ["all", "none", "some"])
+def test_selection_in_slices(sq, oracle, B, H, C, L, coarse):
+    w = wl.make_workload("hier_slices", B=B, H=H, L=L, C=C, Lq=1, U=20, keep_frac=1 / 8, C1=9, coarse_keep_frac=1 / 3, seed=17,
+                         threads=4, variable_fanout=True)
+    wl.calibrate(w, oracle.scores)
+    if coarse != "some":
+        w.thresh1 = np.full(H, -1.0 if coarse == "all" else 2.0, np.float32)
+    P = hier_decode_and_compare(sq, oracle, w, f"slices C{C} {coarse}")
+    nk = P.n_keys.cpu().numpy()
+    assert (nk == 0).all() if coarse == "none" else nk.sum() > 0
+
+
 def test_cfg5_hier_decode_512k(sq, oracle):
     print("cfg5: generating (8 GiB of K/V)", flush=True)
     w = wl.make_config("cfg5_hier_decode_512k", threads=16)
