@@ -851,8 +851,11 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
 // Merges the n_split partial results of a query row.  GROUPS half waves per row, four dimensions per lane: half wave i takes shares
 // i, i + GROUPS, ..., AHEAD of them under way together, with a running maximum, and their results meet in LDS.  Bound by the
 // partials' bytes where rows are many (528 per row and share, just written), by one round of loads where they are few.
-// Traced against a wave per row that found the maximum first: 32768 rows x 2 shares 11.7 -> 8.2 us, 7992 x 7 7.2 -> 6.1, 4096 x 16
-// 8.0 -> 6.6 (with two half waves a row 7.3), 176 x 64 6.0 -> 4.1 (with one 7.2); 4 heads x 33 tokens, whole step 24.1 -> 20.3.
+// Only a row's own shares are folded, each once: a share's sums may be infinite or NaN, and even without weight they would reach
+// the result.  Slots past the end hold zeros (a select per value; without the fence behind the loads the compiler puts selects and
+// loads in turn: 7992 rows x 7 shares 7.3 us).
+// Traced, a wave per row that found the maximum first / this kernel: 32768 rows x 2 shares 11.7 / 8.4 us, 7992 x 7 7.2 / 6.6, 4096 x
+// 15 8.0 / 6.9; this kernel 3000 x 11 5.3, 132 x 48 4.0; 4 heads x 33 tokens, whole step 24.1 / 20.3.
 template <int AHEAD, int GROUPS>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restrict__ partials, _Float16 *__restrict__ out,
                                                             float *__restrict__ lse, int n_split, size_t rows)
@@ -862,15 +865,16 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
     const float *pr = partials + min(row, rows - 1) * (size_t)n_split * PART_STRIDE;
     float M = SQ_NEG_INF, l = 0.0f;
     f4 o = {0.f, 0.f, 0.f, 0.f};
-    auto fold = [&](const float (&m)[AHEAD], const float (&n)[AHEAD], const f4 (&v)[AHEAD]) {
+    auto fold = [&](const auto &m, const auto &n, const auto &v) {
+        constexpr int N = (int)std::extent_v<std::remove_reference_t<decltype(m)>>;
         float top = M;
 #pragma unroll
-        for (int k = 0; k < AHEAD; ++k) top = fmaxf(top, m[k]);
+        for (int k = 0; k < N; ++k) top = fmaxf(top, m[k]);
         const float old = M == SQ_NEG_INF ? 0.0f : expf(M - top);
         l *= old;
         o *= old;
 #pragma unroll
-        for (int k = 0; k < AHEAD; ++k) {
+        for (int k = 0; k < N; ++k) {
             const float w = m[k] == SQ_NEG_INF ? 0.0f : expf(m[k] - top);
             l = fmaf(w, n[k], l);
 #pragma unroll
@@ -882,12 +886,21 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
         float m[AHEAD], n[AHEAD];
         f4 v[AHEAD];
 #pragma unroll
-        for (int k = 0; k < AHEAD; ++k) {                   // (past the end: the last share again, without weight)
+        for (int k = 0; k < AHEAD; ++k) {
             const float *p = pr + (size_t)min(s0 + k * GROUPS, n_split - 1) * PART_STRIDE;
             const float2 ml = *reinterpret_cast<const float2 *>(p);
-            m[k] = s0 + k * GROUPS < n_split ? ml.x : SQ_NEG_INF;
+            m[k] = ml.x;
             n[k] = ml.y;
             v[k] = *reinterpret_cast<const f4 *>(p + 4 + 4 * lane);
+        }
+        __builtin_amdgcn_sched_barrier(0);                  // (all of them under way)
+#pragma unroll
+        for (int k = 0; k < AHEAD; ++k) {                   // past the end: zeros, no share's values, which may be infinite or NaN
+            const bool there = s0 + k * GROUPS < n_split;
+            m[k] = there ? m[k] : SQ_NEG_INF;
+            n[k] = there ? n[k] : 0.0f;
+#pragma unroll
+            for (int d = 0; d < 4; ++d) v[k][d] = there ? v[k][d] : 0.0f;
         }
         fold(m, n, v);
     }
@@ -900,13 +913,12 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
         *reinterpret_cast<f4 *>(&s_part[half][4 + 4 * lane]) = o;
         __syncthreads();
         if (group != 0) return;
-        static_assert(AHEAD >= GROUPS - 1, "the other groups' results are folded together");
-        float m[AHEAD], n[AHEAD];
-        f4 v[AHEAD];
+        float m[GROUPS - 1], n[GROUPS - 1];
+        f4 v[GROUPS - 1];
 #pragma unroll
-        for (int k = 0; k < AHEAD; ++k) {
-            const float *p = s_part[min(half + k + 1, 7)];
-            m[k] = k + 1 < GROUPS ? p[0] : SQ_NEG_INF;
+        for (int k = 0; k < GROUPS - 1; ++k) {              // (the row's other half waves)
+            const float *p = s_part[half + 1 + k];
+            m[k] = p[0];
             n[k] = p[1];
             v[k] = *reinterpret_cast<const f4 *>(p + 4 + 4 * lane);
         }
