@@ -372,10 +372,10 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const _Float16 *__res
     __syncthreads();
     const int32_t *mem = perm ? perm + (size_t)h * L : nullptr;
     const int m0 = s_off[0];
-    const int cap = per > 1 ? CM_CAP : 0;                     // (one cluster: its indices are read where they are used)
+    int held = 0;                                             // indices in LDS (one cluster: they are read where they are used)
     if (mem && per > 1) {
-        const int end = min(s_off[nc - 1] + s_n[nc - 1] - m0, CM_CAP);
-        for (int i = tid; i < end; i += 256) s_mem[i] = mem[m0 + i];
+        held = __builtin_amdgcn_readfirstlane(min(s_off[nc - 1] + s_n[nc - 1] - m0, CM_CAP));
+        for (int i = tid; i < held; i += 256) s_mem[i] = mem[m0 + i];
         __syncthreads();
     }
     const _Float16 *rows = src + (size_t)h * L * D;
@@ -383,7 +383,7 @@ __global__ __launch_bounds__(256) void cluster_mean_kernel(const _Float16 *__res
         int r = pos;
         if (mem) {
             const int i = pos - m0;
-            r = (unsigned)i < (unsigned)cap ? s_mem[i] : mem[pos];   // (offsets that do not ascend: from memory)
+            r = i >= 0 && i < held ? s_mem[i] : mem[pos];     // (clusters in another order may lie outside the stretch)
         }
         return *reinterpret_cast<const h8 *>(rows + (size_t)min(max(r, 0), L - 1) * D + piece * 8);
     };

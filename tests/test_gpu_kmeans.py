@@ -137,6 +137,46 @@ def test_grouping_rounds_and_stretches(sq, H, L, C):
     check_step(X, cent, gpu_step(sq, X, cent), f"grouping H{H} L{L} C{C}")
 
 
+@pytest.mark.parametrize("H,L,C", [
+    (64, 1500, 257),           # four clusters a workgroup, the last one alone; one longer than the indices held for four
+    (64, 1500, 259),           # the last three
+    (9, 900, 1001),            # two a workgroup
+    (3, 1000, 100),            # one
+])
+@pytest.mark.parametrize("members", ["listed", "rows"])
+@pytest.mark.parametrize("order", ["ascending", "shuffled"])
+def test_means_of_clusters_in_any_order(sq, H, L, C, members, order):
+    """Centroids of a caller's grouping, whose clusters may lie in any order in the list of members and may share some of it:
+    cluster c is perm[offsets[c] .. offsets[c] + sizes[c]), or with perm NULL those rows themselves."""
+    rng = np.random.default_rng(19)
+    K = (rng.standard_normal((H, L, 128)) + 2.0).astype(np.float16)
+    perm = np.stack([rng.permutation(L) for _ in range(H)]).astype(np.int32)
+    sizes, offsets = np.zeros((H, C), np.int32), np.zeros((H, C + 1), np.int32)
+    for h in range(H):
+        sizes[h] = rng.multinomial(L - 600, np.full(C, 1.0 / C)) if L > 1200 else rng.multinomial(L, np.full(C, 1.0 / C))
+        if L > 1200:
+            sizes[h, rng.integers(C)] += 600
+        place = np.arange(C) if order == "ascending" else rng.permutation(C)
+        offsets[h, place] = np.cumsum(sizes[h, place]) - sizes[h, place]
+        offsets[h, C] = L
+        if order == "shuffled":                                  # ... and some reach into their neighbours
+            wide = rng.choice(C, size=C // 8, replace=False)
+            sizes[h, wide] = np.minimum(sizes[h, wide] + 40, L - offsets[h, wide])
+    sh = sq.make_shape(1, H, L, C, 1, 0, 1.0)
+    cent = torch.full((H, C, 128), 7.0, dtype=torch.float16, device=DEV)
+    sq.sq_cluster_layout(sh, t(K), None, t(perm) if members == "listed" else None, t(sizes), t(offsets), None, None, cent)
+    torch.cuda.synchronize()
+    got = cent.cpu().numpy().astype(np.float64)
+    Kd = K.astype(np.float64)
+    for h in range(H):
+        want = np.zeros((C, 128))
+        for c in np.flatnonzero(sizes[h]):
+            at = np.arange(offsets[h, c], offsets[h, c] + sizes[h, c])
+            want[c] = Kd[h, perm[h, at] if members == "listed" else at].mean(0)
+        # fp32 sums of at most 700 terms below 8, rounded to fp16: half a unit in the last place and a little
+        np.testing.assert_allclose(got[h], want, rtol=6e-4, atol=1e-3)
+
+
 def test_normalisation(sq):
     K, _, _ = wl.clustering_input(12, 2, 1000, 8)
     K[0, 5] = 0                                                  # a zero row stays zero
