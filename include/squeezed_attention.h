@@ -230,10 +230,13 @@ int sq_hier_select(const sq_shape_t *shape, int32_t C1, const void *q,
  * Benchmarking").  The selection is bit-identical to the three separate calls; the attention output
  * agrees up to rounding (the keys are split over workgroups differently).
  * With B >= 2 the sequences share K_fixed/V_fixed (the shared-prefix setting of Section 1) and each
- * sequence still selects on its own.  From B = 8 on, the step streams the union of the selections of every
- * group of 16 sequences, so a key kept by several sequences is read once; the probabilities are then rounded
- * to fp16 before they multiply V (matrix-core product, fp32 accumulation), as in sq_sparse_attn_prefill.
- * Below that the selections overlap too little to pay for the union and every sequence is handled by itself.
+ * sequence still selects on its own.  From B = 8 on, where B * H * (L + U) exceeds 409600, the step streams the
+ * union of the selections of every group of 16 sequences, so a key kept by several sequences is read once; the
+ * probabilities are then rounded to fp16 before they multiply V (matrix-core product, fp32 accumulation), as in
+ * sq_sparse_attn_prefill.  Below that the selections overlap too little, or hold too few keys, to pay for the union and
+ * every sequence is handled by itself.  (B >= 8 just below that line: with half of the keys kept
+ * both ways take the same time, with a quarter or less the one taken is 20 to 35 % shorter, with nearly all of them up to
+ * 40 % longer.  More than 4096 clusters or 1024 (sequence, head) pairs: the union from B = 8 on whatever the size.)
  * Out: out f16 [B,H,1,d]; optional (NULL to skip): lse f32 [B,H,1], keep_mask u32 [B,H,1,ceil(C/32)],
  *      n_keys i32 [B,H,1].
  * Workspace: sq_workspace_bytes(shape, SQ_CALL_DECODE_STEP).
@@ -267,10 +270,10 @@ int sq_decode_step_noalloc(const sq_shape_t *shape, const void *q,
  * selects its clusters independently (the setting of the appendix "Additional Longbench Evaluation": keys and
  * values shared amongst a subset of the heads, each head selecting on its own).  shape->H is the number of K/V
  * heads; query head hq = h * G + g uses K/V head h.  The B * G (sequence, query head) pairs of a K/V head are
- * handled like B * G sequences over a shared context: from B * G = 8 on, the union of the selections of every group
- * of 16 of them is streamed once, so a key kept by several query heads leaves HBM once; below that every pair is a
- * row of the per-sequence kernels, which read the K/V head once per query head (same kernels, arithmetic and
- * rounding as sq_decode_step; G = 1 is that call).  1 <= G <= 16; a group size that does not divide 16 (3 or 6 query
+ * handled like B * G sequences over a shared context: from B * G = 8 on, where B * H * G * (L + U) exceeds
+ * 409600, the union of the selections of every group of 16 of them is streamed once, so a key kept by several query heads
+ * leaves HBM once; below that every pair is a row of the per-sequence kernels, which read the K/V head once per query head
+ * (same kernels, arithmetic and rounding as sq_decode_step; G = 1 is that call).  1 <= G <= 16; a group size that does not divide 16 (3 or 6 query
  * heads per K/V head) takes the per-sequence kernels at any batch size.
  * In:  q f16 [B, H*G, 1, d]; centroids, sizes, offsets, thresh, K_fixed, V_fixed per K/V head as everywhere;
  *      K_user, V_user f16 [B, H, U, d].

@@ -268,12 +268,18 @@ constexpr int SHARED_MIN_ROWS = 8;
 // rows kept are worth: they come from the caches again.  Union / per-row kernels, us per step, by the share of the keys kept:
 //                                                 0.06          1/8         1/4         1/2          all
 //    8 sequences x  1 head  x  8000 keys ( 64 K)  23.9 / 13.9  24.8 / 14.1  24.9 / 14.6  24.9 / 15.4  24.8 / 16.3
-//   16           x  4 heads x  4000      (256 K)  25.8 / 14.7  25.9 / 15.8  26.0 / 18.0  26.1 / 22.6  26.1 / 27.0
+//   10           x  4 heads x  4000      (160 K)  26.4 / 15.6  26.4 / 15.4  26.6 / 16.9  26.4 / 19.2  26.5 / 25.1
+//    9           x  1       x 20000      (180 K)  27.0 / 18.1  27.2 / 19.0  27.5 / 20.2  27.6 / 22.8  27.8 / 30.3
+//    8           x  1       x 32000      (256 K)  28.5 / 19.7  28.6 / 21.3  28.9 / 23.7  29.6 / 26.9  29.5 / 31.2
+//   16           x  4       x  4000      (256 K)  25.8 / 14.7  25.9 / 15.8  26.0 / 18.0  26.1 / 22.6  26.1 / 27.0
 //   12           x  8       x  4000      (384 K)  26.5 / 18.5  28.1 / 19.6  28.4 / 23.5  28.2 / 29.3  28.5 / 36.7
 //    8           x  8       x  8000      (512 K)  26.9 / 18.3  28.3 / 19.9  29.9 / 24.7  31.1 / 33.5  31.4 / 41.1
 //   16           x  8       x  4000      (512 K)  28.2 / 18.1  28.7 / 20.7  28.9 / 25.2  28.8 / 34.1  28.9 / 41.3
 //   16           x  8       x  8000      (1 M)    29.6 / 21.5  32.0 / 26.3  32.3 / 35.6  32.8 / 53.7  33.7 / 67.9
-// The line lies where the per-row kernels still lead at a quarter kept, the upper end of the budgets the method is run at.
+// The budget is the device's to know, so one line serves all.  It lies where the two are about even with half of the keys kept:
+// below it every budget up to a half gains or loses next to nothing, and a threshold that keeps nearly everything costs up to 40 %
+// (384 K); the thresholds the method is run at keep a quarter at most.  Further out, up to 512 K, those would still gain 15 %, but
+// a half loses as much and everything 40 %.
 constexpr long long SHARED_MIN_KEYS = 400 * 1024;
 bool step_is_shared(const sq_shape_t *sh, int G = 1)
 {
