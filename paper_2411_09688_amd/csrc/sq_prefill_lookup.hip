@@ -11,7 +11,7 @@
 //   (lookup_pass_kernel<LK_BOTH>        both in one launch, for rows of few clusters with per-token candidates)
 //   mean_scores_kernel                  selection on averaged scores (Appendix D, "Prefill Stage"), first half: the scores
 //                  S_i(t) = exp(x_i - m) / D are summed over the tokens per cluster and written as part_sum
-//                  [B*H, lookup_parts(), C]; the row-wise selection kernel adds the parts.
+//                  [B*H, lookup_parts(), C]; mean_select_kernel adds the parts.
 //   CANDS == true  (averaged scores) second level of a hierarchical lookup (Section 3.3, Eq. 3): the clusters scored are the
 //                  n candidates cand_id[bh, 0..n) of the (sequence, head) -- the children of the coarse clusters kept
 //                  one level up -- so the normaliser runs over the candidates only; part_sum is written in candidate order.
@@ -38,14 +38,14 @@ namespace sq {
 
 constexpr int LK_G = 64;                     // centroids per staged group
 constexpr int LK_BT = 128;                   // tokens per workgroup (four waves x 32)
-// With per-token candidates, rows of at most so many clusters are decided in one launch.  Whole steps (measured without
-// candidates, whose rows of up to 1024 clusters have a kernel of their own now), two launches / one, us, 32 keys per cluster:
+// With per-token candidates, rows of at most so many clusters are decided in one launch.  Whole steps over two levels (16 coarse
+// clusters, three tenths kept), two launches / one, us, 32 keys per cluster:
 //   clusters                     75            128            192            250            320
-//    1 head  x   16 tokens   25.2 / 22.1    25.6 / 22.3    27.8 / 26.1    28.9 / 29.7    29.9 / 32.3
-//   16 heads x   28 tokens   28.9 / 25.5    31.6 / 28.4    31.8 / 30.6    34.7 / 35.8    36.7 / 39.8
-//    4 heads x  333 tokens   36.8 / 33.7    39.8 / 36.9    41.9 / 41.3    44.5 / 46.1    46.0 / 49.7
-//   32 heads x 1024 tokens   87.7 / 82.6   112.3 / 107.9  151.9 / 146.7  179.6 / 179.0  218.7 / 212.6
-constexpr int LK_ONE_C = 192;
+//    1 head  x   16 tokens   31.3 / 28.8    31.5 / 29.8    32.0 / 33.2    31.8 / 36.2    32.1 / 40.4
+//   16 heads x   28 tokens   35.3 / 34.0    38.5 / 37.4    37.9 / 39.8    38.5 / 44.3    39.5 / 48.6
+//    4 heads x  333 tokens   43.3 / 42.6    46.7 / 45.8    47.5 / 49.5    47.6 / 53.9    50.0 / 58.9
+//   32 heads x 1024 tokens    98.5 / 97.1  117.8 / 114.9  143.3 / 140.1  157.5 / 159.2  179.9 / 177.1
+constexpr int LK_ONE_C = 128;
 constexpr int LK_MAX_W1 = 32;                // level-1 mask words per token held in LDS: at most 1024 coarse clusters
 
 // A token's pairs (r, sum) of the slices first, first + STEP, ... (at most LK_MAX_SLICES / STEP of them): the loads are issued

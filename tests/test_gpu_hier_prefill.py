@@ -277,6 +277,18 @@ def test_hier_prefill_step_small(sq, oracle, case):
     assert 0 < gk.sum() < gk.size
 
 
+@pytest.mark.parametrize("case", [
+    dict(B=1, H=2, L=3000, C=128, C1=8, Lq=129, U=0, keep_frac=0.2, coarse_keep_frac=0.5, causal_user=False),   # the last size of one launch
+    dict(B=2, H=1, L=3000, C=129, C1=9, Lq=31, U=3, keep_frac=0.2, coarse_keep_frac=0.5, causal_user=False),    # two, slices of one group
+    dict(B=1, H=2, L=3000, C=192, C1=16, Lq=129, U=0, keep_frac=0.2, coarse_keep_frac=0.3, causal_user=False),  # whole groups
+], ids=lambda c: "C{C}".format(**c))
+def test_one_launch_and_two(sq, oracle, case):
+    w = wl.make_workload("hier_prefill_line", seed=38, threads=2, variable_fanout=True, **case)
+    T1, T2 = per_query_thresholds(w)
+    gk, _ = compare_per_query(oracle, w, T1, T2, run_per_query(sq, w, T1, T2), f"hier-prefill-line C{w.C}")
+    assert 0 < gk.sum() < gk.size
+
+
 def test_per_query_first_level_keeping_everything_is_the_one_level_step(sq, oracle):
     w = wl.make_workload("hier_prefill_all", B=1, H=2, L=4096, C=128, C1=8, Lq=50, U=20, keep_frac=0.2,
                          coarse_keep_frac=0.5, causal_user=True, seed=37, threads=2)
