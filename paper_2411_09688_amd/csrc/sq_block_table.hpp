@@ -28,12 +28,9 @@ struct BlockTable {
 // that launch by about what a launch of its own takes (12 us at 32 heads x 512 blocks), but saves the launch: whole steps, with a
 // launch of its own / in the lookup's, us: 2 x 12 heads x 333 tokens x 9001 keys 80.2 / 77.2, 8 heads x 60 tokens x 32K keys
 // 56.7 / 53.6, 16 heads x 28 tokens x 2400 keys 31.6 / 25.5, 32 heads x 1024 tokens x 32K keys the same (603 / 604).
-// A workgroup makes the entries of two blocks per wave of a lookup launch, of four in a launch of four waves.
-__host__ __device__ inline int block_table_share(int waves) { return waves == 4 ? 16 : 2 * waves; }
-__host__ __device__ inline int block_table_groups(int nblk, int waves)
-{
-    return (nblk + block_table_share(waves) - 1) / block_table_share(waves);
-}
+// A workgroup makes the entries of PF_TAB_BLOCKS blocks, whatever its number of waves.
+constexpr int PF_TAB_BLOCKS = 16;
+__host__ __device__ inline int block_table_groups(int nblk) { return (nblk + PF_TAB_BLOCKS - 1) / PF_TAB_BLOCKS; }
 
 __device__ __forceinline__ void block_table_entry(const BlockTable &bt, int h, int blk, int lane)
 {
@@ -100,9 +97,8 @@ __device__ __forceinline__ void block_table_entry(const BlockTable &bt, int h, i
 __device__ __forceinline__ void block_table_part(const BlockTable &bt, int h, int group, int waves)
 {
     const int lane = threadIdx.x & 63;
-    const int per = block_table_share(waves);
-    for (int i = threadIdx.x >> 6; i < per; i += waves) {
-        const int blk = group * per + i;
+    for (int i = threadIdx.x >> 6; i < PF_TAB_BLOCKS; i += waves) {
+        const int blk = group * PF_TAB_BLOCKS + i;
         if (blk < bt.nblk) block_table_entry(bt, h, blk, lane);
     }
 }

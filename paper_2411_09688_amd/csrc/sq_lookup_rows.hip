@@ -41,7 +41,7 @@ __global__ __launch_bounds__(LR_THREADS, 4) void lookup_rows_kernel(
     const int nbt = (Lq + LR_BT - 1) / LR_BT, n_blk = MEAN ? n_part : nbt, units = n_blk * BH;
     const int per_xcd = (units + 7) >> 3, extra = (int)blockIdx.x - 8 * per_xcd;
     if (!MEAN && extra >= 0) {                              // extra workgroups: the attention's block table
-        const int groups = block_table_groups(table.nblk, LR_WAVES);
+        const int groups = block_table_groups(table.nblk);
         block_table_part(table, extra / groups, extra % groups, LR_WAVES);
         return;
     }
@@ -336,7 +336,7 @@ hipError_t launch_lookup_rows(const void *q, const void *centroids, const int32_
 {
     if (C > LR_MAX_C || (table && mean)) return hipErrorInvalidValue;
     const int BH = B * H, nbt = (Lq + LR_BT - 1) / LR_BT, n_part = lookup_rows_parts(BH, Lq);
-    const int units = (mean ? n_part : nbt) * BH, extra = table ? block_table_groups(table->nblk, LR_WAVES) * H : 0;
+    const int units = (mean ? n_part : nbt) * BH, extra = table ? block_table_groups(table->nblk) * H : 0;
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((units + 7) / 8 * 8 + extra), dim3(LR_THREADS), 0, s, (const _Float16 *)q,
                            (const _Float16 *)centroids, sizes, thresh, keep_mask, n_keys, part_sum, n_part, BH, H, Lq, C, sm_scale,

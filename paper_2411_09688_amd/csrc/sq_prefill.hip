@@ -1032,7 +1032,7 @@ hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf,
 
 hipError_t launch_block_table(const BlockTable &bt, int H, hipStream_t s)
 {
-    hipLaunchKernelGGL(block_table_kernel, dim3(block_table_groups(bt.nblk, 4), H), dim3(256), 0, s, bt);
+    hipLaunchKernelGGL(block_table_kernel, dim3(block_table_groups(bt.nblk), H), dim3(256), 0, s, bt);
     return hipGetLastError();
 }
 

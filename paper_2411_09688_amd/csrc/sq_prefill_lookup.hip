@@ -424,7 +424,7 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
     const int32_t *ids = parent ? parent : cand_id;
     const int W1 = (C1 + 31) / 32;
     auto pass = [&](auto mode, auto cands, auto parents, auto keys) {
-        const dim3 all(grid.x + (mode != LK_DECIDE && table ? block_table_groups(table->nblk, 4) : 0), grid.y);
+        const dim3 all(grid.x + (mode != LK_DECIDE && table ? block_table_groups(table->nblk) : 0), grid.y);
         hipLaunchKernelGGL((lookup_pass_kernel<mode, cands, parents, keys>), all, dim3(256), 0, s, qh, ch, sizes, thresh, st,
                            keep_mask, n_keys, ids, cand_hdr, mask1, W1, n_slice, H, Lq, C, sm_scale,
                            table ? *table : BlockTable{});
