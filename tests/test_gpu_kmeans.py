@@ -96,10 +96,12 @@ def test_one_iteration_matches_the_oracle(sq, H, L, C, mix):
 @pytest.mark.parametrize("H,L,C,kind", [
     (3, 500, 203, "ties"),          # every centre several times, in other lanes, tiles and groups: the first one wins
     (2, 300, 65, "ties"),
-    (32, 2000, 300, "one"),         # one cluster longer than the indices held for four, the others empty
-    (33, 700, 257, "one"),          # four clusters a workgroup, the last one alone
-    (64, 200, 129, "all"),          # more clusters than keys
-    (1, 40000, 1500, "all"),        # 64 parts, more than one stretch of the offsets' scan
+    (32, 2000, 300, "one"),         # one cluster longer than the indices held for a workgroup's two, the others empty
+    (33, 700, 257, "one"),          # two clusters a workgroup, the last one alone
+    (64, 1200, 259, "one"),         # four, the last three; a stretch longer than the indices held
+    (64, 200, 129, "all"),          # hardly more keys than clusters: many of one key and of none
+    (1, 40000, 1500, "all"),        # 53 parts, more than one stretch of the offsets' scan
+    (2, 32705, 70, "all"),          # 64 parts, the last of 449 keys
 ])
 def test_edges_of_assignment_grouping_and_means(sq, H, L, C, kind):
     rng = np.random.default_rng(15)

@@ -424,12 +424,19 @@ def test_prefill_split_shares(sq, oracle, case):
 
 
 @pytest.mark.parametrize("case", [
-    dict(B=1, H=1, L=3000, C=192, Lq=129, U=0),       # the most clusters decided in one launch, a second block of tokens
-    dict(B=2, H=1, L=3000, C=193, Lq=31, U=3),        # one more: two launches, slices of one group
-    dict(B=1, H=1, L=3000, C=256, Lq=129, U=0),       # whole groups of clusters
-    dict(B=2, H=1, L=3000, C=257, Lq=31, U=3),        # a last group of one
-    dict(B=1, H=1, L=9000, C=2113, Lq=1, U=0),        # as many slices as there are, a ragged last one
+    dict(B=1, H=1, L=3000, C=192, Lq=129, U=0),       # rows that stay in registers: five blocks of 32 tokens, six tiles for eight waves
+    dict(B=2, H=1, L=3000, C=193, Lq=31, U=3),        # a tile of one cluster
+    dict(B=1, H=1, L=3000, C=256, Lq=129, U=0),       # one full tile per wave
+    dict(B=2, H=1, L=3000, C=257, Lq=31, U=3),        # a ninth tile, of one cluster
+    dict(B=1, H=1, L=9000, C=2113, Lq=1, U=0),        # slices: as many as there are, a ragged last one
     dict(B=1, H=2, L=500, C=1100, Lq=65, U=7),        # empty clusters
+    dict(B=1, H=2, L=2000, C=1025, Lq=129, U=0),      # a second block of 128 tokens, of one; a last group of one cluster
+    dict(B=2, H=1, L=2000, C=1088, Lq=257, U=3),      # three blocks, the last of one; whole groups
+    dict(B=1, H=1, L=2000, C=1089, Lq=257, U=0),
+    dict(B=1, H=3, L=2500, C=1152, Lq=129, U=5),      # whole blocks of the averages' clusters; averaged, the tokens in parts
+    dict(B=16, H=8, L=1300, C=1152, Lq=257, U=0),     # two slices, one part of five tiles
+    dict(B=1, H=2, L=2000, C=513, Lq=129, U=2),       # too few tokens for so long a row to stay in registers
+    dict(B=1, H=9, L=2500, C=1024, Lq=200, U=0),      # the longest such row: 63 blocks of 32 tokens
 ])
 def test_prefill_lookup_slices(sq, oracle, case):
     """The lookup's slices of the clusters against the oracle, per token and averaged, with and without the key counts; a

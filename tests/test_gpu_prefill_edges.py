@@ -55,8 +55,9 @@ def hier_per_query(sq, w, T1, T2, centroids):
     return unpack_mask(mask.cpu().numpy(), w.C), nk.cpu().numpy(), out.cpu().numpy()
 
 
-ONE_AND_TWO_LAUNCHES = [dict(L=900, C=60, Lq=40), dict(L=3000, C=600, Lq=150)]
-EMPTY = [dict(L=150, C=60, Lq=40), dict(L=800, C=600, Lq=150)]                   # some clusters have no keys
+# rows in registers, one, two and four tiles a wave, and sliced over two launches
+ONE_AND_TWO_LAUNCHES = [dict(L=900, C=60, Lq=40), dict(L=3000, C=600, Lq=150), dict(L=2500, C=500, Lq=40), dict(L=3000, C=600, Lq=1100)]
+EMPTY = [dict(L=150, C=60, Lq=40), dict(L=800, C=600, Lq=150), dict(L=700, C=500, Lq=40), dict(L=1500, C=1000, Lq=1100)]  # some clusters have no keys
 
 
 @pytest.mark.parametrize("case", ONE_AND_TWO_LAUNCHES)
@@ -131,11 +132,12 @@ def tied(C, live, keys, Lq, sm_scale):
     return w
 
 
-@pytest.mark.parametrize("case", [dict(C=8, live=8, keys=64), dict(C=1, live=1, keys=128), dict(C=700, live=16, keys=32)])
+@pytest.mark.parametrize("case", [dict(C=8, live=8, keys=64), dict(C=1, live=1, keys=128), dict(C=700, live=16, keys=32),
+                                  dict(C=500, live=32, keys=16), dict(C=700, live=16, keys=32, Lq=1100)])
 @pytest.mark.parametrize("sm_scale", [128 ** -0.5, 1.0, 0.3])
 def test_a_score_that_equals_the_threshold_is_dropped(sq, case, sm_scale):
     """The rule is score > T.  With the threshold at the tied score nothing is kept, one float below it everything is."""
-    w = tied(Lq=333, sm_scale=sm_scale, **case)
+    w = tied(**{"Lq": 333, "sm_scale": sm_scale, **case})
     T = np.float32(1.0 / (case["live"] * case["keys"]))
     for fn in (per_query, averaged):
         keep, nk, _ = fn(sq, w, np.full(w.H, T, np.float32))
