@@ -19,9 +19,10 @@
 // visits its centres in ascending order and replaces only on a strictly larger score, and the final combination
 // prefers the lower index on equal scores.
 // Bound by issue: a workgroup's 16 groups of 1024 matrix cycles each take 36 us at 1.84 GHz, three waves per SIMD 4150 cycles of
-// which 3072 are products (74 %); 16x16x32 products draw less power than 32x32x16 (1.95 against 1.68 PFLOP/s in a loop of nothing
+// which 3072 are products (74 %; over the whole launch the counters have the matrix cores busy for 68 %, with 2.3 vector
+// instructions per score beside the products: 1.9 in the loop, the rest addresses of the loads and the start); 16x16x32 products draw less power than 32x32x16 (1.95 against 1.68 PFLOP/s in a loop of nothing
 // else).  32 heads x 32768 keys x 1024 centres: 281 -> 242 us traced on the same card, where compares and selects were three per
-// centre and key instead of 1.75, went through padded rows written from registers, and waited for every group at its barrier; with
+// centre and key instead of 1.75 (seven for four), went through padded rows written from registers, and waited for every group at its barrier; with
 // products and compares left in the compiler's order 252.
 #include <algorithm>
 #include <cstddef>

@@ -16,7 +16,10 @@
 // Bound by its phases one after the other: 20 heads x 150 tokens x 613 clusters, by the workgroups' clocks: operands there 1.3 us,
 // scores 3.5, maxima 1.9, normalisers 1.6; at 32 heads x 1024 tokens x 1024 clusters a workgroup's second block of tokens takes 9
 // us, its first 16 (the centroids come from memory; without one XCD per head every XCD fetched all of them: 20).  Traced there:
-// averaged 31.8 us against 20.5 + 21.6 of the two sliced passes, per query 47 with the attention's block table against 32.8 + 21.2.
+// averaged 31.8 us against 20.5 + 21.6 of the two sliced passes, per query 47 with the attention's block table against 32.8 + 21.2,
+// 59 with the tokens' key counts as well (the step 585 us on either path).  Counters there: matrix cores busy 13 % (averaged), no
+// bank conflicts.  The form of four tiles per wave fills its 128 registers: the compiler puts 7 values (averaged 3) of the
+// addresses and the start in scratch memory, 32 bytes a lane.
 #include <algorithm>
 
 #include "sq_common.hpp"
