@@ -852,14 +852,16 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
 // i, i + GROUPS, ..., AHEAD of them under way together, with a running maximum, and their results meet in LDS.  Bound by the
 // partials' bytes where rows are many (528 per row and share, just written), by one round of loads where they are few.
 // Only a row's own shares are folded, each once: a share's sums may be infinite or NaN, and even without weight they would reach
-// the result.  Slots past the end hold zeros (a select per value; without the fence behind the loads the compiler puts selects and
-// loads in turn: 7992 rows x 7 shares 7.3 us).
-// Traced, a wave per row that found the maximum first / this kernel: 32768 rows x 2 shares 11.7 / 8.4 us, 7992 x 7 7.2 / 6.6, 4096 x
-// 15 8.0 / 6.9; this kernel 3000 x 11 5.3, 132 x 48 4.0; 4 heads x 33 tokens, whole step 24.1 / 20.3.
-template <int AHEAD, int GROUPS>
+// the result.  Up to eight shares have a form each (SHARES), without a slot to spare; the others (SHARES = 0) hold zeros in slots
+// past the end, a select per value, and fence the loads off, between which the compiler puts the selects otherwise.
+// Traced, a wave per row that found the maximum first / this kernel (with selects up to eight shares as well): 32768 rows x 2 shares
+// 11.7 / 7.8 us (8.4), 7992 x 7 7.2 / 5.9 (6.7), 7992 x 5 - / 5.0 (5.6), 4096 x 15 8.0 / 6.9, 3000 x 11 - / 5.4, 132 x 48 - / 4.0; 4
+// heads x 33 tokens, whole step 24.1 / 20.3.
+template <int AHEAD, int GROUPS, int SHARES>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restrict__ partials, _Float16 *__restrict__ out,
-                                                            float *__restrict__ lse, int n_split, size_t rows)
+                                                            float *__restrict__ lse, int n_shares, size_t rows)
 {
+    const int n_split = SHARES ? SHARES : n_shares;
     const int half = threadIdx.x >> 5, lane = threadIdx.x & 31, group = half % GROUPS;
     const size_t row = (size_t)blockIdx.x * (8 / GROUPS) + half / GROUPS;
     const float *pr = partials + min(row, rows - 1) * (size_t)n_split * PART_STRIDE;
@@ -1020,11 +1022,19 @@ hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf,
     };
     // Several half waves per row where the rows are few: one takes eight shares in a round of loads.  (3000 rows x 11 shares: two
     // half waves 38.2 us a step, one 38.9; 1476 x 17: eight of them 6.3 us traced against 5.3 of a wave per row.)
-    if (plan.n_split <= 2) merge(prefill_merge_kernel<2, 1>, 1);
-    else if (plan.n_split <= 4) merge(prefill_merge_kernel<4, 1>, 1);
-    else if (plan.n_split <= 8 || n >= 4096) merge(prefill_merge_kernel<8, 1>, 1);
-    else if (plan.n_split <= 16 || n >= 1024) merge(prefill_merge_kernel<8, 2>, 2);
-    else merge(prefill_merge_kernel<8, 8>, 8);
+    if (plan.n_split <= 8) {
+        switch (plan.n_split) {
+        case 2: merge(prefill_merge_kernel<2, 1, 2>, 1); break;
+        case 3: merge(prefill_merge_kernel<3, 1, 3>, 1); break;
+        case 4: merge(prefill_merge_kernel<4, 1, 4>, 1); break;
+        case 5: merge(prefill_merge_kernel<5, 1, 5>, 1); break;
+        case 6: merge(prefill_merge_kernel<6, 1, 6>, 1); break;
+        case 7: merge(prefill_merge_kernel<7, 1, 7>, 1); break;
+        default: merge(prefill_merge_kernel<8, 1, 8>, 1);
+        }
+    } else if (n >= 4096) merge(prefill_merge_kernel<8, 1, 0>, 1);
+    else if (plan.n_split <= 16 || n >= 1024) merge(prefill_merge_kernel<8, 2, 0>, 2);
+    else merge(prefill_merge_kernel<8, 8, 0>, 8);
     return hipGetLastError();
 }
 
