@@ -268,11 +268,15 @@ def test_shares_longer_than_a_list(sq, oracle, case):
 
 # ---- values that are not finite, where shares of a row are merged ----------------------------------------------------------
 
-# (one kept set, shares, case): three to 20 shares a row, in merges that take 4, 8, 16 and 64 of them in a round.
+# (one kept set, shares, case): two to eight shares a row, a form each; nine to 20, in merges that take 8, 16 and 64 in a round.
 MERGE_CASES = [
+    (False, 2, dict(B=2, H=60, L=1200, C=40, Lq=100, U=100)),
     (True, 3, dict(B=2, H=12, L=3001, C=99, Lq=333, U=333)),
+    (False, 4, dict(B=2, H=60, L=1200, C=40, Lq=33, U=33)),
     (False, 5, dict(B=2, H=12, L=3001, C=99, Lq=333, U=333)),
+    (False, 6, dict(B=1, H=40, L=3000, C=99, Lq=150, U=150)),
     (True, 7, dict(B=1, H=20, L=3000, C=99, Lq=60, U=60)),
+    (True, 8, dict(B=1, H=8, L=20000, C=300, Lq=512, U=512)),
     (False, 10, dict(B=1, H=12, L=12000, C=300, Lq=400, U=400)),
     (True, 11, dict(B=1, H=20, L=20011, C=613, Lq=150, U=150)),
     (True, 11, dict(B=1, H=8, L=4000, C=99, Lq=160, U=160)),
