@@ -128,12 +128,12 @@ constexpr int PF_TABS = 4;                // block table rows in LDS: the block'
 
 // f(0), f(1), ... f(N - 1) with the index a compile-time constant.
 template <int N, typename F, int... I>
-__device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
+__host__ __device__ __forceinline__ void static_for_impl(F &&f, std::integer_sequence<int, I...>)
 {
     (f(std::integral_constant<int, I>{}), ...);
 }
 template <int N, typename F>
-__device__ __forceinline__ void static_for(F &&f)
+__host__ __device__ __forceinline__ void static_for(F &&f)
 {
     static_for_impl<N>(f, std::make_integer_sequence<int, N>{});
 }
@@ -852,16 +852,16 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
 // i, i + GROUPS, ..., AHEAD of them under way together, with a running maximum, and their results meet in LDS.  Bound by the
 // partials' bytes where rows are many (528 per row and share, just written), by one round of loads where they are few.
 // Only a row's own shares are folded, each once: a share's sums may be infinite or NaN, and even without weight they would reach
-// the result.  Up to eight shares have a form each (SHARES), without a slot to spare; the others (SHARES = 0) hold zeros in slots
-// past the end, a select per value, and fence the loads off, between which the compiler puts the selects otherwise.
-// Traced, a wave per row that found the maximum first / this kernel (with selects up to eight shares as well): 32768 rows x 2 shares
-// 11.7 / 7.8 us (8.4), 7992 x 7 7.2 / 5.9 (6.7), 7992 x 5 - / 5.0 (5.6), 4096 x 15 8.0 / 6.9, 3000 x 11 - / 5.4, 132 x 48 - / 4.0; 4
-// heads x 33 tokens, whole step 24.1 / 20.3.
-template <int AHEAD, int GROUPS, int SHARES>
+// the result.  So AHEAD is what the shares divide into (ONE: a single round), and a slot that may lie past the end -- the last one,
+// and with several rounds any -- holds zeros there, a select per value; the loads are fenced off, between which the compiler puts
+// the selects otherwise.
+// Traced, a wave per row that found the maximum first / eight shares a round, the last of them taken again to fill it / this kernel:
+// 32768 rows x 2 shares 11.7 / 8.2 / 7.8 us, 7992 x 7 7.2 / 6.4 / 5.9, 4096 x 16 8.0 / 7.7 / 7.3; 4096 x 10 6.5 / 5.4, 3000 x 11
+// 4.9 / 4.5, 3000 x 17 8.2 / 7.1, 1000 x 24 5.2 / 4.1, 100 x 63 4.0 / 3.9 (the last two of the three).
+template <int AHEAD, int GROUPS, bool ONE>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restrict__ partials, _Float16 *__restrict__ out,
-                                                            float *__restrict__ lse, int n_shares, size_t rows)
+                                                            float *__restrict__ lse, int n_split, size_t rows)
 {
-    const int n_split = SHARES ? SHARES : n_shares;
     const int half = threadIdx.x >> 5, lane = threadIdx.x & 31, group = half % GROUPS;
     const size_t row = (size_t)blockIdx.x * (8 / GROUPS) + half / GROUPS;
     const float *pr = partials + min(row, rows - 1) * (size_t)n_split * PART_STRIDE;
@@ -884,12 +884,13 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
         }
         M = top;
     };
-    for (int s0 = group; s0 < n_split; s0 += AHEAD * GROUPS) {
+    for (int s0 = group; ONE ? s0 == group : s0 < n_split; s0 += AHEAD * GROUPS) {
         float m[AHEAD], n[AHEAD];
         f4 v[AHEAD];
+        constexpr auto full = [](int k) { return ONE && (GROUPS == 1 || k < AHEAD - 1); };
 #pragma unroll
         for (int k = 0; k < AHEAD; ++k) {
-            const float *p = pr + (size_t)min(s0 + k * GROUPS, n_split - 1) * PART_STRIDE;
+            const float *p = pr + (size_t)(full(k) ? s0 + k * GROUPS : min(s0 + k * GROUPS, n_split - 1)) * PART_STRIDE;
             const float2 ml = *reinterpret_cast<const float2 *>(p);
             m[k] = ml.x;
             n[k] = ml.y;
@@ -898,7 +899,7 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
         __builtin_amdgcn_sched_barrier(0);                  // (all of them under way)
 #pragma unroll
         for (int k = 0; k < AHEAD; ++k) {                   // past the end: zeros, no share's values, which may be infinite or NaN
-            const bool there = s0 + k * GROUPS < n_split;
+            const bool there = full(k) || s0 + k * GROUPS < n_split;
             m[k] = there ? m[k] : SQ_NEG_INF;
             n[k] = there ? n[k] : 0.0f;
 #pragma unroll
@@ -1020,21 +1021,24 @@ hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf,
         hipLaunchKernelGGL(kernel, dim3((unsigned)((n * groups + 7) / 8)), dim3(256), 0, s, partials, (_Float16 *)out, lse,
                            plan.n_split, n);
     };
-    // Several half waves per row where the rows are few: one takes eight shares in a round of loads.  (3000 rows x 11 shares: two
-    // half waves 38.2 us a step, one 38.9; 1476 x 17: eight of them 6.3 us traced against 5.3 of a wave per row.)
-    if (plan.n_split <= 8) {
-        switch (plan.n_split) {
-        case 2: merge(prefill_merge_kernel<2, 1, 2>, 1); break;
-        case 3: merge(prefill_merge_kernel<3, 1, 3>, 1); break;
-        case 4: merge(prefill_merge_kernel<4, 1, 4>, 1); break;
-        case 5: merge(prefill_merge_kernel<5, 1, 5>, 1); break;
-        case 6: merge(prefill_merge_kernel<6, 1, 6>, 1); break;
-        case 7: merge(prefill_merge_kernel<7, 1, 7>, 1); break;
-        default: merge(prefill_merge_kernel<8, 1, 8>, 1);
+    // Several half waves per row where the rows are few; a half wave takes its shares in rounds of at most eight, as even as they go.
+    // (3000 rows x 11 shares: two half waves 38.2 us a step, one 38.9; 1476 x 17: eight of them 6.3 us traced against 5.3 of a wave
+    // per row.)
+    const int groups = plan.n_split <= 8 || n >= 4096 ? 1 : plan.n_split <= 16 || n >= 1024 ? 2 : 8;
+    const int each = (plan.n_split + groups - 1) / groups, rounds = (each + 7) / 8, ahead = (each + rounds - 1) / rounds;
+    static_for<9>([&](auto a) {
+        constexpr int A = a;
+        if constexpr (A >= 2) {
+            if (ahead != A) return;
+            if (groups == 1 && rounds == 1) return merge(prefill_merge_kernel<A, 1, true>, 1);
+            if constexpr (A >= 3)                           // (from 17 shares on)
+                if (groups == 8) return merge(prefill_merge_kernel<A, 8, true>, 8);
+            if constexpr (A >= 5) {                         // (from nine shares of a half wave on: at least five in each of its rounds)
+                if (groups == 1) return merge(prefill_merge_kernel<A, 1, false>, 1);
+                return rounds == 1 ? merge(prefill_merge_kernel<A, 2, true>, 2) : merge(prefill_merge_kernel<A, 2, false>, 2);
+            }
         }
-    } else if (n >= 4096) merge(prefill_merge_kernel<8, 1, 0>, 1);
-    else if (plan.n_split <= 16 || n >= 1024) merge(prefill_merge_kernel<8, 2, 0>, 2);
-    else merge(prefill_merge_kernel<8, 8, 0>, 8);
+    });
     return hipGetLastError();
 }
 
