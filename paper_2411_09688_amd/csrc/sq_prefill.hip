@@ -1033,7 +1033,7 @@ hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf,
             if (groups == 1 && rounds == 1) return merge(prefill_merge_kernel<A, 1, true>, 1);
             if constexpr (A >= 3)                           // (from 17 shares on)
                 if (groups == 8) return merge(prefill_merge_kernel<A, 8, true>, 8);
-            if constexpr (A >= 5) {                         // (from nine shares of a half wave on: at least five in each of its rounds)
+            if constexpr (A >= 5) {                         // (from nine shares on: at least five in a round)
                 if (groups == 1) return merge(prefill_merge_kernel<A, 1, false>, 1);
                 return rounds == 1 ? merge(prefill_merge_kernel<A, 2, true>, 2) : merge(prefill_merge_kernel<A, 2, false>, 2);
             }

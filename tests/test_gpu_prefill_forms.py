@@ -135,6 +135,18 @@ MERGED = [
     (4, 16, dict(B=1, H=32, L=9600, C=99, Lq=20, U=3)),                  # 640 rows
     (8, 24, dict(B=1, H=10, L=6000, C=99, Lq=100, U=3)),                 # 1000 rows: eight half waves
     (8, 46, dict(B=1, H=1, L=64 * 90, C=99, Lq=9, U=3)),                 # nine rows
+    (8, 8, dict(B=1, H=5, L=4000, C=99, Lq=1000, U=3)),                  # one round of eight
+    (8, 11, dict(B=1, H=6, L=4000, C=99, Lq=700, U=3)),                  # one half wave, rounds of six and five
+    (8, 14, dict(B=1, H=6, L=8000, C=99, Lq=700, U=3)),                  # of seven
+    (8, 16, dict(B=1, H=8, L=12000, C=99, Lq=512, U=3)),                 # of eight
+    (8, 13, dict(B=1, H=3, L=4000, C=99, Lq=1000, U=3)),                 # two half waves, seven and six
+    (8, 22, dict(B=1, H=2, L=4000, C=99, Lq=512, U=3)),                  # two rounds of six, five in the last
+    (8, 32, dict(B=1, H=2, L=8000, C=99, Lq=512, U=3)),                  # of eight
+    (8, 38, dict(B=1, H=2, L=12000, C=99, Lq=512, U=3)),                 # three rounds of seven, five in the last
+    (8, 32, dict(B=1, H=1, L=4000, C=99, Lq=300, U=3)),                  # eight half waves, four shares each
+    (8, 33, dict(B=1, H=1, L=2000, C=99, Lq=9, U=3)),                    # and one of them five
+    (8, 53, dict(B=1, H=1, L=20000, C=99, Lq=700, U=3)),
+    (8, 64, dict(B=1, H=1, L=4000, C=99, Lq=9, U=3)),                    # the most shares
 ]
 
 
