@@ -1064,11 +1064,16 @@ int sq_prefill_mean_step(const sq_shape_t *sh, const void *q, const void *centro
     const int rows = sh->B * sh->H;
     SQ_HIP(sq::launch_prefill_lookup(q, centroids, sizes, thresh, w.stats, nullptr, nullptr, w.part_sum, true, sh->B,
                                      sh->H, sh->Lq, sh->C, sh->sm_scale, s));
-    SQ_HIP(sq::launch_mean_select(w.part_sum, sq::lookup_parts(rows, sh->Lq, sh->C), sh->Lq, thresh, sizes, offsets,
-                                  nullptr, nullptr, false, keep_mask, n_keys, w.att.hdr, w.att.key_idx, sh->L, rows, sh->H,
-                                  sh->C, s));
-    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.att.hdr, w.att.key_idx, w.att.partials, out,
-                                          lse, to_shape(sh), s));
+    const int parts = sq::lookup_parts(rows, sh->Lq, sh->C);
+    if (sq::prefill_selects(to_shape(sh))) {
+        const sq::PfSelect sel{w.part_sum, parts, thresh, sizes, offsets, keep_mask, n_keys};
+        SQ_HIP(sq::launch_prefill_attn_select(q, K_fixed, V_fixed, K_user, V_user, sel, w.att.partials, out, lse, to_shape(sh), s));
+    } else {
+        SQ_HIP(sq::launch_mean_select(w.part_sum, parts, sh->Lq, thresh, sizes, offsets, nullptr, nullptr, false, keep_mask, n_keys,
+                                      w.att.hdr, w.att.key_idx, sh->L, rows, sh->H, sh->C, s));
+        SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.att.hdr, w.att.key_idx, w.att.partials, out,
+                                              lse, to_shape(sh), s));
+    }
     g_err[0] = 0;
     return SQ_OK;
 }

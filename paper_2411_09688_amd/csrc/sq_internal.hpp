@@ -200,6 +200,22 @@ hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void 
                                       const int2 *hdr, const int32_t *key_idx, float *partials, void *out, float *lse,
                                       const Shape &sh, hipStream_t s);
 
+// The same with the kept set made by the attention launch itself, where prefill_selects(): part_sum [B*H, parts, C] are the parts of
+// the clusters' scores summed over the tokens (see launch_mean_select, which makes the same decisions).
+constexpr int PF_SELECT_MAX_C = 2048;
+constexpr int pf_select_blocks(int waves) { return waves == 8 ? 256 : 48; }   // fixed blocks of a share, at most: their rows lie in LDS
+struct PfSelect {
+    const float *part_sum;
+    int parts;
+    const float *thresh;
+    const int32_t *sizes, *offsets;
+    uint32_t *keep_mask;                   // outputs, either may be null
+    int32_t *n_keys;
+};
+bool prefill_selects(const Shape &sh);
+hipError_t launch_prefill_attn_select(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
+                                      const PfSelect &sel, float *partials, void *out, float *lse, const Shape &sh, hipStream_t s);
+
 // Both forms deal a unit's key blocks to n_split workgroups (of `waves` waves, 32 queries each) where (heads x query blocks) alone do not fill the
 // chip; their partial results (m, l, -, -, o[128]) per (query row, share) go through `partials`
 // (prefill_partial_floats() floats, 0 without a split) to a merge launch.

@@ -1,6 +1,6 @@
 // Selection on averaged scores (Appendix D, "Prefill Stage") straight into the list the next launch walks: from the partial
 // score sums of the lookup to the row's list of kept keys (the key-index tensor of Section 4.2), or of candidate clusters where
-// the kept clusters are coarse ones.
+// the kept clusters are coarse ones.  (One level: where prefill_selects() the attention launch does this by itself.)
 //
 // One workgroup per ((sequence, head) row, slice of the row's clusters).  A workgroup adds up the averages of every cluster up
 // to the end of its slice, so it knows without talking to the others how many keys are kept in front of its own; it writes its

@@ -145,7 +145,8 @@ __host__ __device__ __forceinline__ void static_for(F &&f)
 // A function of its own, not inlined: as part of the kernel its code lengthened the walk of workgroups with idle waves (32 heads x
 // 150 tokens x 32K keys 175 -> 184 us).  seen_user: user keys the query sees; dst: the query's output, to be multiplied by scale,
 // or, with several shares, its 128 partial sums.  The other arguments: see the kernel (uniform ones arrive in vector registers).
-template <bool SHARED>
+// LOCAL: table holds the rows of the share's fixed blocks alone, one after the other.
+template <bool SHARED, bool LOCAL>
 __device__ __attribute__((noinline)) void prefill_again(const _Float16 *q_row, const char *Kf, const char *Vf, const char *Ku,
                                                         const char *Vu, const uint32_t *mrow, const void *table,
                                                         const int32_t *binfo, void *dst, int split, int n_split, int n_fixed, int U,
@@ -161,7 +162,8 @@ __device__ __attribute__((noinline)) void prefill_again(const _Float16 *q_row, c
     n_split = __builtin_amdgcn_readfirstlane(n_split);
     n_fixed = __builtin_amdgcn_readfirstlane(n_fixed);
     const int nblk_fixed = (n_fixed + PF_BN - 1) / PF_BN, nblk = nblk_fixed + (__builtin_amdgcn_readfirstlane(U) + PF_BN - 1) / PF_BN;
-    for (int i = __builtin_amdgcn_readfirstlane(split); i < nblk; i += n_split) {   // (fixed blocks, then user blocks: dealt as in the kernel)
+    int own = 0;                                            // blocks of the share in front of this one
+    for (int i = __builtin_amdgcn_readfirstlane(split); i < nblk; i += n_split, ++own) {   // (fixed blocks, then user blocks: dealt as in the kernel)
         const bool user = i >= nblk_fixed;
         const int blk = user ? i - nblk_fixed : i;
         unsigned long long seen = 0ull;                     // bit j: the query sees key j of the block
@@ -179,7 +181,7 @@ __device__ __attribute__((noinline)) void prefill_again(const _Float16 *q_row, c
             const bool mine = (seen >> j) & 1u;
             if (__ballot(mine) == 0ull) continue;
             const int r = blk * PF_BN + j;                  // (a key that is seen: within the tensor)
-            const size_t row = (size_t)(SHARED && !user ? static_cast<const int32_t *>(table)[r] : r) * 256;
+            const size_t row = (size_t)(SHARED && !user ? static_cast<const int32_t *>(table)[LOCAL ? own * PF_BN + j : r] : r) * 256;
             const h8 *kp = reinterpret_cast<const h8 *>((user ? Ku : Kf) + row);
             float x = 0.0f;
 #pragma unroll
@@ -205,16 +207,121 @@ __device__ __attribute__((noinline)) void prefill_again(const _Float16 *q_row, c
                                                                                       (_Float16)(o[i][2] * scale), (_Float16)(o[i][3] * scale)};
 }
 
+// ---- the kept set made by the attention launch ----------------------------------------------------------------------------
+// Bound by a chain of one round of loads (the clusters' sizes, offsets and up to eight parts of their scores together) and three
+// barriers, about 3 us of the launch's prologue; the rows' searches run in parallel, a few per thread.
+// Kept keys of a (sequence, head), by the whole workgroup: parts of its clusters' averaged scores, added in ascending order,
+// divided by the tokens and compared with the threshold (mean_select_kernel's decision).  Left in LDS: s[0..kept) positions of the
+// kept clusters' first keys in the list of kept keys, s[PF_SELECT_MAX_C ..) those keys; s[2 PF_SELECT_MAX_C] the number of kept clusters.
+// A barrier at the end.  write: the mask and the count, too.
+template <int PF_WAVES>
+__device__ __forceinline__ int pf_select(const PfSelect &sel, size_t bh, int h, int L, int C, int Lq, bool write, int *s)
+{
+    constexpr int THREADS = 64 * PF_WAVES, STEPS = PF_SELECT_MAX_C / THREADS, GROUPS = PF_SELECT_MAX_C / 64;
+    static_assert(GROUPS <= 64, "a group's counts per lane");
+    int *s_pos = s, *s_first = s + PF_SELECT_MAX_C, *s_n = s_first + PF_SELECT_MAX_C, *s_cnt = s_n + 1, *s_len = s_cnt + GROUPS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), W = (C + 31) >> 5;
+    const float *ps = sel.part_sum + bh * sel.parts * C;
+    const int32_t *N = sel.sizes + (size_t)h * C, *off = sel.offsets + (size_t)h * (C + 1);
+    const float T = sel.thresh[h], div = (float)Lq;
+    if (tid < GROUPS) s_cnt[tid] = s_len[tid] = 0;
+    int first[STEPS], len[STEPS];
+    float sum[STEPS];
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+        const int i = min(k * THREADS + tid, C - 1);
+        sum[k] = 0.0f;
+        len[k] = first[k] = 0;
+        if (k * THREADS < C) {                              // (uniform)
+            len[k] = N[i];
+            first[k] = off[i];
+        }
+    }
+    constexpr int AHEAD = 8;                                // parts under way together
+    for (int p0 = 0; p0 < sel.parts; p0 += AHEAD)
+#pragma unroll
+        for (int k = 0; k < STEPS; ++k) {
+            if (k * THREADS >= C) break;                    // (uniform)
+            const float *at = ps + min(k * THREADS + tid, C - 1);
+            float v[AHEAD];
+#pragma unroll
+            for (int p = 0; p < AHEAD; ++p) v[p] = at[(size_t)min(p0 + p, sel.parts - 1) * C];
+#pragma unroll
+            for (int p = 0; p < AHEAD; ++p) sum[k] = p0 + p < sel.parts ? sum[k] + v[p] : sum[k];
+        }
+    __syncthreads();                                        // (the counts are zero)
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+        if (k * THREADS >= C) break;
+        const bool keep = k * THREADS + tid < C && len[k] > 0 && sum[k] / div > T;
+        len[k] = keep ? len[k] : 0;
+        const unsigned long long bal = __ballot(keep);
+        const int total = wave_sum_i(len[k]), g = k * PF_WAVES + wave;
+        if (lane == 0) {
+            s_cnt[g] = __popcll(bal);
+            s_len[g] = total;
+            if (write && sel.keep_mask && 2 * g < W) {
+                sel.keep_mask[bh * W + 2 * g] = (uint32_t)bal;
+                if (2 * g + 1 < W) sel.keep_mask[bh * W + 2 * g + 1] = (uint32_t)(bal >> 32);
+            }
+        }
+    }
+    __syncthreads();
+    const int gc = lane < GROUPS ? s_cnt[lane] : 0, gl = lane < GROUPS ? s_len[lane] : 0;
+    const int ic = wave_inclusive_scan(gc, lane), il = wave_inclusive_scan(gl, lane);
+    const int kept = __builtin_amdgcn_readlane(ic, 63), keys = __builtin_amdgcn_readlane(il, 63);
+#pragma unroll
+    for (int k = 0; k < STEPS; ++k) {
+        if (k * THREADS >= C) break;
+        const int g = k * PF_WAVES + wave;
+        const unsigned long long bal = __ballot(len[k] > 0);
+        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
+        const int c = __builtin_amdgcn_readlane(ic - gc, g) + rank;
+        const int pos = __builtin_amdgcn_readlane(il - gl, g) + wave_inclusive_scan(len[k], lane) - len[k];
+        if (len[k] > 0) {
+            s_pos[c] = pos;
+            s_first[c] = first[k];
+        }
+    }
+    if (tid == 0) {
+        *s_n = kept;
+        if (write && sel.n_keys) sel.n_keys[bh] = keys;
+    }
+    __syncthreads();
+    return keys;
+}
+
+// Rows of the keys of a share's n_list fixed blocks, split, split + n_split, ... of the list of kept keys: every key finds its cluster
+// among the records of pf_select.  (Behind the last key: that key again.)
+template <int PF_WAVES>
+__device__ __forceinline__ void pf_share_rows(const int *s, int32_t *s_idx, int n_list, int split, int n_split, int n_fixed, int L)
+{
+    const int *s_pos = s, *s_first = s + PF_SELECT_MAX_C;
+    const int kept = s[2 * PF_SELECT_MAX_C];
+    for (int i = threadIdx.x; i < n_list * PF_BN; i += 64 * PF_WAVES) {
+        const int j = min((split + (i >> 6) * n_split) * PF_BN + (i & 63), n_fixed - 1);
+        int c = 0;
+#pragma unroll
+        for (int step = PF_SELECT_MAX_C / 2; step > 0; step >>= 1)
+            if (c + step < kept && s_pos[c + step] <= j) c += step;
+        s_idx[i] = min(max(s_first[c] + j - s_pos[c], 0), L - 1);   // (malformed offsets stay in the tensor)
+    }
+}
+
 // SHARED: table is the key-row list [B*H, L] and blk_info the per-row (records, kept keys) headers; keep_mask is not
 // used.  Otherwise table / rows / blk_info are the block table (block_table_kernel).
-template <bool SHARED, int PF_WAVES>
+// SELECT (with SHARED): the kept set is made here, from the parts of the averaged scores (what mean_select_kernel does in a launch of
+// its own otherwise): every workgroup adds up its head's scores and decides all of its clusters, and the rows of its share's keys go to
+// a list in LDS.  The (sequence, head)'s first workgroup writes the mask and the count.
+template <bool SHARED, int PF_WAVES, bool SELECT>
 __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kernel(
     const _Float16 *__restrict__ q, const _Float16 *__restrict__ Kf, const _Float16 *__restrict__ Vf,
     const _Float16 *__restrict__ Ku, const _Float16 *__restrict__ Vu, const uint32_t *__restrict__ keep_mask,
     const uint32_t *__restrict__ table, const uint32_t *__restrict__ rows, const int32_t *__restrict__ blk_info,
     _Float16 *__restrict__ out, float *__restrict__ lse, float *__restrict__ partials, int n_split, int B, int H, int L,
-    int C, int Lq, int U, int causal_user, float sm_scale)
+    int C, int Lq, int U, int causal_user, float sm_scale, PfSelect sel)
 {
+    static_assert(SHARED || !SELECT, "one kept set");
     constexpr int PF_BM = pf_bm(PF_WAVES), PF_THREADS = 64 * PF_WAVES;
     constexpr int PF_RP = PF_THREADS / 16;                  // rows of a key block the workgroup moves per pass (16 lanes per row)
     constexpr int PF_NP = PF_BN / PF_RP;                    // passes per block
@@ -226,6 +333,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     __shared__ int s_wc[PF_WAVES], s_act[PF_WAVES];
     __shared__ uint8_t s_need[SHARED ? 1 : PF_LIST_CAP];    // bit v: wave v has a query that kept a key of the listed block
     __shared__ __align__(16) uint32_t s_mw[SHARED ? 1 : PF_WAVES][NB][64];   // mask words of a wave's queries for the blocks at hand (sparse walk)
+    __shared__ int32_t s_idx[SELECT ? pf_select_blocks(PF_WAVES) * PF_BN : 1];   // rows of the share's fixed blocks
     __shared__ __align__(16) float s_hide[16 * 4];          // entry n: the start values of four scores whose visibility bits are n
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -269,8 +377,12 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     const char *Kuh = reinterpret_cast<const char *>(Ku + ((size_t)b * H + h) * (size_t)U * D);
     const char *Vuh = reinterpret_cast<const char *>(Vu + ((size_t)b * H + h) * (size_t)U * D);
     // keys of the fixed context this (sequence, head) walks: all of them, or the kept ones through the row list
-    const int n_fixed = SHARED ? min(blk_info[2 * ((size_t)b * H + h) + 1], L) : L;
-    const int32_t *idx_bh = reinterpret_cast<const int32_t *>(table) + ((size_t)b * H + h) * (size_t)L;   // SHARED only
+    int n_fixed = L;
+    if constexpr (SELECT)
+        n_fixed = min(pf_select<PF_WAVES>(sel, (size_t)b * H + h, h, L, C, Lq, unit % nqb == 0 && split == 0, reinterpret_cast<int *>(stage)), L);
+    else if constexpr (SHARED)
+        n_fixed = min(blk_info[2 * ((size_t)b * H + h) + 1], L);
+    const int32_t *idx_bh = reinterpret_cast<const int32_t *>(table) + ((size_t)b * H + h) * (size_t)L;   // SHARED without SELECT only
     const int nblk_fixed = (n_fixed + PF_BN - 1) / PF_BN;
     // Causal user block: queries of this workgroup see user keys 0 .. min(U, q0 + BM) - 1 at most.
     const int u_vis = causal_user ? min(U, q0 + PF_BM) : U;
@@ -283,6 +395,10 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     // waves that need them; nobody's blocks are neither fetched nor staged), then user blocks -------------------------------
     int n_list = (max(nblk_fixed - split, 0) + n_split - 1) / n_split;
     const bool listed = !SHARED && n_list <= PF_LIST_CAP;
+    if constexpr (SELECT) {
+        pf_share_rows<PF_WAVES>(reinterpret_cast<const int *>(stage), s_idx, n_list, split, n_split, n_fixed, L);
+        __syncthreads();                                    // (the records lie where the tiles will be)
+    }
     bool sparse = false;
     if (listed) {
         uint32_t *s_um = reinterpret_cast<uint32_t *>(stage);             // per wave: OR of the keep masks of its queries
@@ -349,6 +465,8 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
             t_need = user || !listed ? 0xff : s_need[li];
         }
     };
+    auto ent = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_ent, i - t_base); };
+    auto inf = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_info, i - t_base); };
     constexpr int T_KEEP = 56;                              // entries used of a fill: the loop looks up to seven ahead
 
     // ---- staging -----------------------------------------------------------------------------------------------------------
@@ -380,6 +498,15 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
             for (int k = 0; k < PF_NP; ++k) x.r[k] = idx_bh[min(j0 + k * PF_RP + trow, last)];
         }
         return x;
+    };
+    auto rows_at = [&](int i) PF_INLINE {                   // of the block at position i
+        if constexpr (SELECT) {
+            Rows x{};
+#pragma unroll
+            for (int k = 0; k < PF_NP; ++k) x.r[k] = s_idx[min(i, max(n_list - 1, 0)) * PF_BN + k * PF_RP + trow];
+            return x;
+        } else
+            return rows_of(ent(i));
     };
     typedef __attribute__((address_space(3))) void *lptr_t;
     auto lds_at = [&](const void *p) PF_INLINE { return __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t)p); };
@@ -529,8 +656,6 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
         }
     };
 
-    auto ent = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_ent, i - t_base); };
-    auto inf = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_info, i - t_base); };
     if (!SHARED && sparse && n_mine > 0) {                  // the sparse walk
         fill_entries(0);
         // What the block at position pos needs, behind the barrier that ends the pair before it (NB = 2: the block before it): its
@@ -630,12 +755,12 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
             return uint2{mw_lo, mw_hi};
         };
         Aim aim_v{};                                        // of block it + LV (computed with its K, one iteration before)
-        Rows rv = rows_of(ent(LV)), rk = rows_of(ent(LK)), rk1 = rows_of(ent(LK + 1));   // blocks it + LV, it + LK, it + LK + 1
+        Rows rv = rows_at(LV), rk = rows_at(LK), rk1 = rows_at(LK + 1);   // blocks it + LV, it + LK, it + LK + 1
 #pragma unroll
         for (int b = 0; b < LK; ++b) {
             const int e = ent(b);
             aim_v = aim_at(e);
-            const Rows r = rows_of(e);
+            const Rows r = rows_at(b);
 #pragma unroll
             for (int i = 0; i < PF_NP; ++i) {
                 fetch_piece(i, aim_v.k, aim_v.end, e >= 0, r, k_at, k_ch, b * PF_TILE);
@@ -684,7 +809,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
                 }
             };
             auto look_further = [&]() PF_INLINE {
-                rk2 = rows_of(ent(it + LK + 2));
+                rk2 = rows_at(it + LK + 2);
                 fetch_tab(it + 4, ent(it + 4));
                 w4 = words_of(it + 4);
             };
@@ -842,8 +967,8 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
         if (lse && g == 0) lse[row0 + nq] = empty ? SQ_NEG_INF : m_ref * sm_scale + logf(lt);
     }
     if (again)
-        prefill_again<SHARED>(q + (row0 + nq) * D, Kfh, Vfh, Kuh, Vuh, mrow,
-                              SHARED ? (const void *)idx_bh : (const void *)(table + (size_t)h * nblk_all * PF_BN), binfo,
+        prefill_again<SHARED, SELECT>(q + (row0 + nq) * D, Kfh, Vfh, Kuh, Vuh, mrow,
+                              SELECT ? (const void *)s_idx : SHARED ? (const void *)idx_bh : (const void *)(table + (size_t)h * nblk_all * PF_BN), binfo,
                               n_split > 1 ? (void *)(pr + 4) : (void *)orow, split, n_split, n_fixed, U,
                               causal_user ? min(U, nq + 1) : U, c2, mneg, inv);
 }
@@ -980,41 +1105,41 @@ size_t prefill_partial_floats(bool shared, const Shape &sh)
 
 namespace {
 
-template <bool SHARED, int WAVES>
+template <bool SHARED, int WAVES, bool SELECT>
 hipError_t launch_prefill_kernel(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                  const uint32_t *keep_mask, const uint32_t *table, const uint32_t *rows,
                                  const int32_t *blk_info, void *out, float *lse, float *partials, int n_split,
-                                 const Shape &sh, hipStream_t s)
+                                 const PfSelect &sel, const Shape &sh, hipStream_t s)
 {
     constexpr int BM = pf_bm(WAVES);
     const int units = ((sh.Lq + BM - 1) / BM) * sh.H * sh.B * n_split;
     const dim3 grid((units + 7) / 8 * 8), block(64 * WAVES);
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (profile_pair(&ev0, &ev1))
-        hipExtLaunchKernelGGL((prefill_attn_kernel<SHARED, WAVES>), grid, block, 0, s, ev0, ev1, 0, (const _Float16 *)q,
+        hipExtLaunchKernelGGL((prefill_attn_kernel<SHARED, WAVES, SELECT>), grid, block, 0, s, ev0, ev1, 0, (const _Float16 *)q,
                               (const _Float16 *)Kf, (const _Float16 *)Vf, (const _Float16 *)Ku, (const _Float16 *)Vu,
                               keep_mask, table, rows, blk_info, (_Float16 *)out, lse, partials, n_split, sh.B, sh.H, sh.L,
-                              sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale);
+                              sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale, sel);
     else
-        hipLaunchKernelGGL((prefill_attn_kernel<SHARED, WAVES>), grid, block, 0, s, (const _Float16 *)q,
+        hipLaunchKernelGGL((prefill_attn_kernel<SHARED, WAVES, SELECT>), grid, block, 0, s, (const _Float16 *)q,
                            (const _Float16 *)Kf, (const _Float16 *)Vf, (const _Float16 *)Ku, (const _Float16 *)Vu,
                            keep_mask, table, rows, blk_info, (_Float16 *)out, lse, partials, n_split, sh.B, sh.H, sh.L,
-                           sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale);
+                           sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale, sel);
     return hipGetLastError();
 }
 
 // The attention launch and, where the blocks are split, the merge launch.
-template <bool SHARED>
+template <bool SHARED, bool SELECT>
 hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                   const uint32_t *keep_mask, const uint32_t *table, const uint32_t *rows,
-                                  const int32_t *blk_info, void *out, float *lse, float *partials, const Shape &sh,
-                                  hipStream_t s)
+                                  const int32_t *blk_info, void *out, float *lse, float *partials, const PfSelect &sel,
+                                  const Shape &sh, hipStream_t s)
 {
     const PfPlan plan = prefill_plan(SHARED, sh);
-    const hipError_t e = plan.waves == 8 ? launch_prefill_kernel<SHARED, 8>(q, Kf, Vf, Ku, Vu, keep_mask, table, rows, blk_info,
-                                                                            out, lse, partials, plan.n_split, sh, s)
-                                         : launch_prefill_kernel<SHARED, 4>(q, Kf, Vf, Ku, Vu, keep_mask, table, rows, blk_info,
-                                                                            out, lse, partials, plan.n_split, sh, s);
+    const hipError_t e = plan.waves == 8 ? launch_prefill_kernel<SHARED, 8, SELECT>(q, Kf, Vf, Ku, Vu, keep_mask, table, rows, blk_info,
+                                                                                    out, lse, partials, plan.n_split, sel, sh, s)
+                                         : launch_prefill_kernel<SHARED, 4, SELECT>(q, Kf, Vf, Ku, Vu, keep_mask, table, rows, blk_info,
+                                                                                    out, lse, partials, plan.n_split, sel, sh, s);
     if (e != hipSuccess || plan.n_split == 1) return e;
     const size_t n = (size_t)sh.B * sh.H * sh.Lq;
     auto merge = [&](auto kernel, int groups) {
@@ -1054,7 +1179,7 @@ hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, co
                                const uint32_t *keep_mask, const BlockTable &bt, float *partials, void *out, float *lse,
                                const Shape &sh, hipStream_t s)
 {
-    return launch_prefill_kernels<false>(q, Kf, Vf, Ku, Vu, keep_mask, bt.runs, bt.rows, bt.info, out, lse, partials, sh, s);
+    return launch_prefill_kernels<false, false>(q, Kf, Vf, Ku, Vu, keep_mask, bt.runs, bt.rows, bt.info, out, lse, partials, PfSelect{}, sh, s);
 }
 
 hipError_t launch_expand_ranges(DecodePlan plan, int32_t *idx, int rows, int L, hipStream_t s)
@@ -1070,8 +1195,29 @@ hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void 
                                       const int2 *hdr, const int32_t *key_idx, float *partials, void *out, float *lse,
                                       const Shape &sh, hipStream_t s)
 {
-    return launch_prefill_kernels<true>(q, Kf, Vf, Ku, Vu, nullptr, reinterpret_cast<const uint32_t *>(key_idx), nullptr,
-                                        reinterpret_cast<const int32_t *>(hdr), out, lse, partials, sh, s);
+    return launch_prefill_kernels<true, false>(q, Kf, Vf, Ku, Vu, nullptr, reinterpret_cast<const uint32_t *>(key_idx), nullptr,
+                                               reinterpret_cast<const int32_t *>(hdr), out, lse, partials, PfSelect{}, sh, s);
+}
+
+// Where the attention launch makes the kept set itself: whenever the records and the rows of a share's keys find room in LDS, since a
+// workgroup's few loads of scores (about 3 us, traced) cost less than a launch in front (5 to 7 us) and the two round trips to
+// the list it leaves (2 us) for every shape measured.  Whole steps, us, a launch of its own / here:
+//   32 heads x 1024 tokens x 32768 keys, 1024 clusters 140.3 / 137.4    20 x 150 x 20011, 613 37.7 / 34.8    32 x 16 x 2000, 32 23.8 / 19.1
+//    1 x 1024 x 32768, 1638  41.4 / 37.3     1 x 16 x 2000, 40  19.4 / 15.7     4 x 1024 x 8000, 400  43.4 / 39.5
+//   2 x 32 x 500 x 20000, 500  127.9 / 124.9    32 x 16 x 32768, 1024  75.0 / 71.3    20 x 17 x 30000, 1500  49.8 / 47.9
+// Eight waves: 64 KB of rows beside 66 KB of tiles, one workgroup per compute unit as before; four: 12 KB, still two.
+bool prefill_selects(const Shape &sh)
+{
+    const PfPlan plan = prefill_plan(true, sh);
+    const long long blocks = ((long long)sh.L + PF_BN - 1) / PF_BN;
+    return sh.C <= PF_SELECT_MAX_C && (blocks + plan.n_split - 1) / plan.n_split <= pf_select_blocks(plan.waves);
+}
+
+hipError_t launch_prefill_attn_select(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
+                                      const PfSelect &sel, float *partials, void *out, float *lse, const Shape &sh, hipStream_t s)
+{
+    if (!prefill_selects(sh)) return hipErrorInvalidValue;
+    return launch_prefill_kernels<true, true>(q, Kf, Vf, Ku, Vu, nullptr, nullptr, nullptr, nullptr, out, lse, partials, sel, sh, s);
 }
 
 }  // namespace sq
