@@ -231,6 +231,7 @@ struct SharedStepWs {
     uint32_t *mask;
     sq::DecodePlan plan;
     float *partials;
+    int user_slot_base;
 };
 
 // G: query rows per (sequence, head) that share the head's K/V (1, or the group size of grouped-query attention).
@@ -253,7 +254,8 @@ SharedStepWs carve_step_shared(Carver &cv, const sq_shape_t *sh, int G = 1)
     w.plan.row_rank = cv.take<int>(urows);
     w.plan.total = cv.take<int>(2);
     w.plan.item = cv.take<int2>(items * sq::ITEM_STRIDE);
-    w.partials = cv.take<float>(((size_t)sq::SHARED_ATTN_GRID + urows) * sq::SG * sq::PART_STRIDE);
+    w.user_slot_base = (int)((sq::SHARED_ATTN_GRID + urows) * sq::SG);
+    w.partials = cv.take<float>((w.user_slot_base + rows * (size_t)sq::user_pieces_for(sh->U)) * sq::PART_STRIDE);
     return w;
 }
 
@@ -713,11 +715,14 @@ int decode_step_shared(const sq_shape_t *sh, int G, const void *q, const void *c
     uint32_t *mask = keep_mask ? keep_mask : w.mask;
     // the G query heads of a (sequence, K/V head) are G query rows of that head: logits [B, H, G, C]
     SQ_HIP(sq::launch_score(q, centroids, w.logits, w.plan.total, sh->B, sh->H, G, sh->C, sh->sm_scale, s));
+    const sq::UserAttn ua = G == 1 ? make_user_pieces(sh, G, q, K_user, V_user, w.partials, w.user_slot_base, sq::user_pieces_for(sh->U))
+                                   : sq::UserAttn{};
     SQ_HIP(sq::launch_union_schedule(w.logits, thresh, sizes, offsets, mask, w.n_ranges, n_keys ? n_keys : w.n_keys,
-                                     w.plan, sh->U, sh->B, G, sh->H, sh->C, s));
+                                     w.plan, ua.q ? 0 : sh->U, sh->B, G, sh->H, sh->C, s, &ua));
     sq::Shape shp = to_shape(sh);
     shp.Lq = G;
-    SQ_HIP(sq::launch_decode_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.plan, w.partials, out, lse, shp, s));
+    SQ_HIP(sq::launch_decode_attn_shared(q, K_fixed, V_fixed, K_user, V_user, w.plan, w.partials, out, lse, shp, s,
+                                         w.user_slot_base, ua.nuq));
     return SQ_OK;
 }
 }  // namespace

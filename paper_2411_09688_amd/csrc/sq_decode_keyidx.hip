@@ -280,7 +280,7 @@ __global__ __launch_bounds__(256) void decode_attn_index_kernel(
     // The workgroups past the first `grid` attend to the rows' user keys, one piece each: they stream at once, while
     // the others make their two dependent round trips (key counts, then index entries).
     if ((int)blockIdx.x >= grid) {                           // workgroup-uniform
-        user_piece_partial(ua, (int)blockIdx.x - grid, s_part);
+        user_piece_partial(ua, (int)blockIdx.x - grid, s_part, threadIdx.x);
         return;
     }
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;

@@ -3,7 +3,7 @@
 // several sequences is read from HBM once.  Sequences are handled in groups of SG = 16; the work items of a
 // (group, head) "union row" are chunks of KPC keys drawn from the clusters kept by ANY sequence of the group,
 // every key carrying the set of sequences that kept it.  The user keys of a sequence are chunks owned by that
-// one sequence.
+// one sequence, or, with one query row per K/V head, are attended to beside the selection (see launch_select) and merged here.
 //
 // With 16 sequences per group the scores of a chunk form a 16-column matrix, which is the shape of a CDNA4
 // matrix-core tile, so the arithmetic runs on MFMA and the kernel stays bound by the K/V stream:
@@ -315,11 +315,11 @@ __global__ __launch_bounds__(256, 3) void decode_attn_shared_kernel(
 }
 
 // Phase 2: one workgroup per (sequence, head) row merges the partials its union row's segments wrote for
-// that sequence.
+// that sequence, and its nuq partials of user keys from slot user_slot_base on (in slots of one row).
 __global__ __launch_bounds__(MERGE_THREADS) void decode_merge_shared_kernel(const float *__restrict__ partials,
                                                                             DecodePlan plan, _Float16 *__restrict__ out,
                                                                             float *__restrict__ lse, int H, int G,
-                                                                            int attn_grid)
+                                                                            int attn_grid, int user_slot_base, int nuq)
 {
     __shared__ float s_red[MERGE_GROUPS * 130];
     const size_t bh = blockIdx.x;                    // output row (b, h, g) of the [B, H, G] tensors
@@ -331,13 +331,15 @@ __global__ __launch_bounds__(MERGE_THREADS) void decode_merge_shared_kernel(cons
     const RunSplit rs = run_split(total, attn_grid);
     const int w_lo = rs.owner(it.x);                 // the attention workgroups that hold the row's items
     const int n = it.y == 0 ? 0 : rs.owner(it.x + it.y - 1) - w_lo + 1;
-    auto slot_ptr = [&](int c) { return partials + ((size_t)(w_lo + c + rank) * SG + sq_) * PART_STRIDE; };
-    merge_row<true>(slot_ptr, n, out + bh * D, lse ? lse + bh : nullptr, s_red, threadIdx.x);
+    auto slot_ptr = [&](int c) {
+        return partials + (c < n ? (size_t)(w_lo + c + rank) * SG + sq_ : (size_t)user_slot_base + bh * nuq + (c - n)) * PART_STRIDE;
+    };
+    merge_row<true>(slot_ptr, n + nuq, out + bh * D, lse ? lse + bh : nullptr, s_red, threadIdx.x);
 }
 
 hipError_t launch_decode_attn_shared(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                      DecodePlan plan, float *partials, void *out, float *lse, const Shape &sh,
-                                     hipStream_t s)
+                                     hipStream_t s, int user_slot_base, int nuq)
 {
     const int G = sh.Lq;                             // query rows per (sequence, head): 1, or the GQA group size
     const int rows = sh.B * sh.H * G;
@@ -353,7 +355,7 @@ hipError_t launch_decode_attn_shared(const void *q, const void *Kf, const void *
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(decode_merge_shared_kernel, dim3(rows), dim3(MERGE_THREADS), 0, s, partials, plan,
-                       (_Float16 *)out, lse, sh.H, G, SHARED_ATTN_GRID);
+                       (_Float16 *)out, lse, sh.H, G, SHARED_ATTN_GRID, user_slot_base, nuq);
     return hipGetLastError();
 }
 

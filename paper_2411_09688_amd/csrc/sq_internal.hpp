@@ -124,6 +124,7 @@ struct UserAttn {
     const _Float16 *q, *Ku, *Vu;
     float *partials;
     int rows, U, G, slot_base, nuq;
+    int first_group, first_piece, end_piece;   // rider of a union selection's launches: see launch_select
     float sm_scale;
 };
 
@@ -181,10 +182,11 @@ hipError_t launch_decode_attn(const void *q, const void *Kf, const void *Vf, con
 // rows) * SG slots of PART_STRIDE floats.
 hipError_t launch_union_schedule(const float *logits, const float *thresh, const int32_t *sizes,
                                  const int32_t *offsets, uint32_t *keep_masks, int32_t *n_ranges, int32_t *n_keys,
-                                 DecodePlan plan, int U, int B, int G, int H, int C, hipStream_t s);
+                                 DecodePlan plan, int U, int B, int G, int H, int C, hipStream_t s,
+                                 const UserAttn *user = nullptr);
 hipError_t launch_decode_attn_shared(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                      DecodePlan plan, float *partials, void *out, float *lse, const Shape &sh,
-                                     hipStream_t s);
+                                     hipStream_t s, int user_slot_base = 0, int nuq = 0);   // nuq: user partials per row, see there
 
 // Prefill attention with per-query keep masks.  The block table is workspace (prefill_table_words(H, L) words for runs and
 // rows, prefill_blocks(H, L) for info), made by launch_block_table or by the first launch of the lookup.

@@ -14,6 +14,8 @@
 // schedule_kernel turns the records of all rows into the work items of the split-KV attention
 // kernel: chunks of KPC selected keys (Section 4.2: a fixed number of keys per workgroup, so rows
 // that keep more keys get more workgroups), each carrying its own copy of the records it touches.
+#include <algorithm>
+
 #include "sq_common.hpp"
 #include "sq_internal.hpp"
 #include "sq_user_attn.hpp"
@@ -252,6 +254,13 @@ __global__ __launch_bounds__(SEL_THREADS) void select_kernel(
     UserAttn ua)
 {
     extern __shared__ __align__(16) unsigned char smem[];
+    // Rider of a union selection: the workgroups past the union rows attend to pieces of the rows' user keys, four each.
+    if (UNION && ua.q && (int)blockIdx.x >= ua.first_group) {   // workgroup-uniform
+        const int piece = ua.first_piece + ((int)blockIdx.x - ua.first_group) * 4 + (int)(threadIdx.x >> 8);
+        user_piece_partial(ua, min(piece, ua.end_piece - 1), reinterpret_cast<float (*)[PART_STRIDE]>(smem) + (threadIdx.x >> 8) * 4,
+                           threadIdx.x & 255, piece < ua.end_piece);
+        return;
+    }
     // Rider (plain scheduling rows only): the workgroups past the first ua.rows compute the rows' attention over their
     // user keys, one chunk each, which does not depend on the selection, while the first ua.rows select.
     if (SCHEDULE && !STATS_IN && !UNION && !CAND) {
@@ -739,8 +748,13 @@ __global__ __launch_bounds__(256) void select_mask_kernel(const float *__restric
                                                           const int32_t *__restrict__ sizes,
                                                           uint32_t *__restrict__ keep_mask,
                                                           int32_t *__restrict__ n_ranges, int32_t *__restrict__ n_keys,
-                                                          int rows, int H, int Lq, int C)
+                                                          int rows, int H, int Lq, int C, UserAttn ua)
 {
+    __shared__ float s_part[4][PART_STRIDE];
+    if (ua.q && (int)blockIdx.x >= ua.first_group) {         // rider: a piece of the rows' user keys (workgroup-uniform)
+        user_piece_partial(ua, ua.first_piece + (int)blockIdx.x - ua.first_group, s_part, threadIdx.x);
+        return;
+    }
     const int lane = threadIdx.x & 63;
     const size_t row = (size_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (row >= (size_t)rows) return;
@@ -810,21 +824,23 @@ __global__ __launch_bounds__(256) void schedule_kernel(DecodePlan plan, int rows
                           256, false, 0, make_int4(0, 0, 0, 0));
 }
 
+constexpr int UNION_PIECES = 512;                            // pieces of user keys that ride on a union selection, at most
+
 // schedule == true also emits the row's work items (needs *plan.total == 0 on entry).
 hipError_t launch_select(const float *logits, const float *row_max, const float *denom, bool stats_in,
                          const float *thresh, const int32_t *sizes, const int32_t *offsets, uint32_t *keep_mask,
                          int32_t *ranges, int32_t *n_ranges, int32_t *n_keys, DecodePlan plan, bool schedule, int U,
                          SelectOpts opt, int rows, int H, int Lq, int C, hipStream_t s, const UserAttn *user)
 {
-    if (user && user->q && (!schedule || stats_in || opt.union_rows || opt.cand_id)) return hipErrorInvalidValue;
+    if (user && user->q && (!schedule || stats_in || opt.cand_id)) return hipErrorInvalidValue;
     if (!ranges && !plan.rec && !schedule && !opt.cand_id && !opt.len_from_offsets && !opt.mean_parts && keep_mask) {
         // mask and counts only (prefill): one wave per row
         if (stats_in)
             hipLaunchKernelGGL(select_mask_kernel<true>, dim3((rows + 3) / 4), dim3(256), 0, s, logits, row_max, denom,
-                               thresh, sizes, keep_mask, n_ranges, n_keys, rows, H, Lq, C);
+                               thresh, sizes, keep_mask, n_ranges, n_keys, rows, H, Lq, C, UserAttn{});
         else
             hipLaunchKernelGGL(select_mask_kernel<false>, dim3((rows + 3) / 4), dim3(256), 0, s, logits, row_max, denom,
-                               thresh, sizes, keep_mask, n_ranges, n_keys, rows, H, Lq, C);
+                               thresh, sizes, keep_mask, n_ranges, n_keys, rows, H, Lq, C, UserAttn{});
         return hipGetLastError();
     }
     // LDS: logits + sizes of the row; reused for two ints per chunk when scheduling.
@@ -861,15 +877,34 @@ hipError_t launch_select(const float *logits, const float *row_max, const float 
         // union row and queue for its vector ALUs, so they get a launch of their own, four rows per workgroup
         // across the chip (the same function, the same bits); the union kernel then reads the mask words.
         opt.masks_ready = 0;
+        // The rows' user keys ride along (one query row per K/V head and sequence: with more, every row would read them again, 2 to
+        // 5 % slower): both launches are chains of round trips that leave the memory system idle, while the attention behind them
+        // takes as long as its bytes.  The union launch, one workgroup per compute unit for a few rows, takes what its idle compute
+        // units read in its own time, the mask launch the rest.  Whole steps, us, none / all in the mask launch / in halves / all in
+        // the union launch / this: 16 sequences x 32 heads x 32768 keys, 256 user keys 112.9 / 111.3 / 112.7 / 114.0 / 109.8, 1024
+        // user keys 142.8 / 141.3 / 143.0 / 148.4 / 138.5, 8 x 20 x 10000, 300 43.4 / 41.4 / 39.9 / 39.8 / 40.3, 9 x 5 x 30000, 700
+        // 49.0 / 46.8 / 46.2 / 45.8 / 45.6; 256 pieces instead of 512 110.3, 139.4, 40.8, 45.8; one user key: the same.
+        UserAttn ua{};
+        int pieces = 0;
+        if (user && user->q) {
+            if (U != 0 || user->nuq != user_pieces_for(user->U)) return hipErrorInvalidValue;
+            ua = *user;
+            pieces = user->rows * user->nuq;
+            ua.end_piece = pieces;
+            if (smem < (size_t)16 * PART_STRIDE * sizeof(float)) smem = (size_t)16 * PART_STRIDE * sizeof(float);
+        }
         if (opt.B >= 8) {
-            const int seq_rows = opt.B * H;
-            hipLaunchKernelGGL(select_mask_kernel<false>, dim3((seq_rows + 3) / 4), dim3(256), 0, s, logits, row_max, denom,
-                               thresh, sizes, keep_mask, n_ranges, n_keys, seq_rows, H, opt.G, C);
+            const int seq_rows = opt.B * H, ahead = std::max(0, pieces - UNION_PIECES);
+            ua.first_group = (seq_rows + 3) / 4;
+            hipLaunchKernelGGL(select_mask_kernel<false>, dim3(ua.first_group + ahead), dim3(256), 0, s, logits, row_max, denom,
+                               thresh, sizes, keep_mask, n_ranges, n_keys, seq_rows, H, opt.G, C, ua);
+            ua.first_piece = ahead;
             opt.masks_ready = 1;
         }
-        hipLaunchKernelGGL((select_kernel<false, true, true>), dim3(rows), dim3(SEL_THREADS), smem, s, logits, row_max,
+        ua.first_group = rows;
+        hipLaunchKernelGGL((select_kernel<false, true, true>), dim3(rows + (pieces - ua.first_piece + 3) / 4), dim3(SEL_THREADS), smem, s, logits, row_max,
                            denom, thresh, sizes, offsets, keep_mask, ranges, n_ranges, n_keys, plan, opt, H, Lq, C, U,
-                           nuc, UserAttn{});
+                           nuc, ua);
         return hipGetLastError();
     }
     if (opt.cand_id) {
@@ -903,14 +938,14 @@ hipError_t launch_select(const float *logits, const float *row_max, const float 
 
 hipError_t launch_union_schedule(const float *logits, const float *thresh, const int32_t *sizes,
                                  const int32_t *offsets, uint32_t *keep_masks, int32_t *n_ranges, int32_t *n_keys,
-                                 DecodePlan plan, int U, int B, int G, int H, int C, hipStream_t s)
+                                 DecodePlan plan, int U, int B, int G, int H, int C, hipStream_t s, const UserAttn *user)
 {
     SelectOpts opt{};
     opt.union_rows = 1;
     opt.B = B * G;
     opt.G = G;
     return launch_select(logits, nullptr, nullptr, false, thresh, sizes, offsets, keep_masks, nullptr, n_ranges,
-                         n_keys, plan, true, U, opt, seq_groups_for(B * G) * H, H, 1, C, s);
+                         n_keys, plan, true, U, opt, seq_groups_for(B * G) * H, H, 1, C, s, user);
 }
 
 hipError_t launch_ranges_to_rec(const int32_t *ranges, const int32_t *n_ranges, DecodePlan plan, int rows,

@@ -11,7 +11,7 @@
 // (nuq = chunks per row).
 //
 // user_piece_partial (steps through the key-index list): extra workgroups of the PARTIAL kernel's launch, 256 threads per
-// piece of USER_PIECE keys (see there).
+// piece of USER_PIECE keys (see there); steps over a shared context: of the selection's two launches (see launch_select).
 #pragma once
 #include "sq_common.hpp"
 #include "sq_internal.hpp"
@@ -95,10 +95,11 @@ __device__ __forceinline__ void user_chunk_partial(const UserAttn &ua, int unit,
 // depend on nothing the lookup computes: the decode step through the key-index list reads them in extra workgroups of
 // its partial kernel, whose other workgroups spend their first microseconds on two dependent round trips (key counts,
 // then index entries) and leave the memory system idle.  256 threads: a wave owns 16 of the piece's 64 keys (16 lanes per key row, four wave-wide loads of
-// four whole rows), the four waves' results are folded in LDS.
-__device__ __forceinline__ void user_piece_partial(const UserAttn &ua, int piece, float (*s_part)[PART_STRIDE])
+// four whole rows), the four waves' results are folded in LDS.  tid: thread of the 256; store: false where a larger workgroup's
+// 256 threads have no piece of their own and repeat another's, for the barrier.
+__device__ __forceinline__ void user_piece_partial(const UserAttn &ua, int piece, float (*s_part)[PART_STRIDE], int tid, bool store = true)
 {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, g = lane >> 4, p = lane & 15;
+    const int lane = tid & 63, wave = tid >> 6, g = lane >> 4, p = lane & 15;
     const int row = piece / ua.nuq, c = piece - row * ua.nuq;
     const size_t bkv = (size_t)row / ua.G;                  // (sequence, K/V head): G query rows share its user keys
     const int first = c * USER_PIECE, nvalid = min(USER_PIECE, ua.U - first);
@@ -142,7 +143,7 @@ __device__ __forceinline__ void user_piece_partial(const UserAttn &ua, int piece
         for (int e = 0; e < 8; ++e) s_part[wave][4 + p * 8 + e] = ow[e];
     }
     __syncthreads();
-    if (tid < D) {
+    if (store && tid < D) {
         const float M = fmaxf(fmaxf(s_part[0][0], s_part[1][0]), fmaxf(s_part[2][0], s_part[3][0]));
         float lsum = 0.0f, acc = 0.0f;
 #pragma unroll

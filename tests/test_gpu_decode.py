@@ -318,6 +318,13 @@ def test_shared_context_line_extremes(sq, oracle, thresh, U):
     step_against_oracle(sq, oracle, w, f"shared_line extremes {thresh} {U}")
 
 
+@pytest.mark.parametrize("U", [1, 64, 65, 1024, 2048, 2049])
+def test_shared_context_user_pieces(sq, oracle, U):
+    """User keys beside the two selection launches, in pieces of 64: ragged pieces, 512 in all (U = 2048: one launch), and more."""
+    w = wl.calibrate(wl.make_workload("shared_pieces", B=8, H=2, L=26000, C=120, Lq=1, U=U, keep_frac=0.2, seed=19, threads=4), oracle.scores)
+    step_against_oracle(sq, oracle, w, f"shared_pieces U={U}")
+
+
 def test_shared_context_step_extremes(sq, oracle):
     base = dict(B=10, H=2, L=1024, C=32, Lq=1, U=33, keep_frac=0.5, seed=12, threads=2)
     # every sequence keeps everything: each key is owned by all sequences of the group
