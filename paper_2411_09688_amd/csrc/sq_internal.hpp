@@ -228,6 +228,16 @@ struct PfPlan {
 PfPlan prefill_plan(bool shared, const Shape &sh);
 size_t prefill_partial_floats(bool shared, const Shape &sh);
 
+// The one-set form with given lists, long shares and few units: the launch's shares (n_split a unit on average) are dealt to the units in
+// proportion to their blocks.  units == 0: the same number for all of them.  ws: the partial results' place.
+constexpr int PF_DEAL_MIN_SPLIT = 4, PF_DEAL_MIN_BLOCKS = 16;   // shares a unit and blocks a share (an eighth of the context), at least
+struct PfDeal {
+    int units, shares;
+    int2 *dealt;                           // [units]: first share, shares; behind the partial results [shares, 32 * waves]
+    size_t words;                          // of both
+};
+PfDeal prefill_deal(const Shape &sh, float *ws);
+
 // Offline clustering (sq_kmeans.hip).  hn: [heads * C] floats; hist: [heads * parts * C] ints with
 // parts = ceil(L / kmeans_part_len(L)).
 int kmeans_part_len(int L);

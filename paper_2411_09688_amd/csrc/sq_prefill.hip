@@ -207,6 +207,32 @@ __device__ __attribute__((noinline)) void prefill_again(const _Float16 *q_row, c
                                                                                       (_Float16)(o[i][2] * scale), (_Float16)(o[i][3] * scale)};
 }
 
+// ---- one kept set: shares in proportion ---------------------------------------------------------------------------------
+// Heads keep different numbers of keys: with as many shares for every unit the launch ends with the unit that keeps most (8 heads x 512
+// tokens x 262144 keys, 16384 clusters: 7 to 23 blocks a workgroup).  So the launch's shares are dealt to the units by their numbers of
+// blocks, one each and the rest in proportion, which every wave works out by itself from the counts, a unit per lane.
+struct PfDealt {
+    int unit, first, n;                                     // the unit, its first share and its number of shares
+};
+__device__ __forceinline__ PfDealt pf_deal(const PfDeal &deal, int piece, const int32_t *__restrict__ blk_info, int bm, int B, int H,
+                                           int L, int Lq, int U, int causal_user)
+{
+    const int lane = threadIdx.x & 63, u = min(lane, deal.units - 1), nqb = (Lq + bm - 1) / bm;
+    const int h = u / (nqb * B), b = (u / nqb) % B, q_end = u % nqb * bm + bm;
+    const int kept = max(min(blk_info[2 * ((size_t)b * H + h) + 1], L), 0), seen = causal_user ? min(U, q_end) : U;
+    const int blocks = lane < deal.units ? (kept + PF_BN - 1) / PF_BN + (seen + PF_BN - 1) / PF_BN : 0;
+    const int incl = wave_inclusive_scan(blocks, lane), all = __builtin_amdgcn_readlane(incl, 63);
+    // shares up to and with the lane's unit: one a unit, and the others by the blocks so far (1 of 1 for the last unit)
+    const float spare = (float)(deal.shares - deal.units), part = all > 0 ? (float)incl / (float)all : (float)(u + 1) / (float)deal.units;
+    const int end = lane < deal.units ? u + 1 + (int)(part * spare + 0.5f) : deal.shares;
+    const int before = __builtin_popcountll(__ballot(lane < deal.units && end <= piece));   // units that end in front of this share
+    PfDealt d;
+    d.unit = before;
+    d.first = before > 0 ? __builtin_amdgcn_readlane(end, before - 1) : 0;
+    d.n = __builtin_amdgcn_readlane(end, before) - d.first;
+    return d;
+}
+
 // ---- the kept set made by the attention launch ----------------------------------------------------------------------------
 // Bound by a chain of one round of loads (the clusters' sizes, offsets and up to eight parts of their scores together) and three
 // barriers, about 3 us of the launch's prologue; the rows' searches run in parallel, a few per thread.
@@ -319,7 +345,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     const _Float16 *__restrict__ Ku, const _Float16 *__restrict__ Vu, const uint32_t *__restrict__ keep_mask,
     const uint32_t *__restrict__ table, const uint32_t *__restrict__ rows, const int32_t *__restrict__ blk_info,
     _Float16 *__restrict__ out, float *__restrict__ lse, float *__restrict__ partials, int n_split, int B, int H, int L,
-    int C, int Lq, int U, int causal_user, float sm_scale, PfSelect sel)
+    int C, int Lq, int U, int causal_user, float sm_scale, PfSelect sel, PfDeal deal)
 {
     static_assert(SHARED || !SELECT, "one kept set");
     constexpr int PF_BM = pf_bm(PF_WAVES), PF_THREADS = 64 * PF_WAVES;
@@ -350,7 +376,16 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     // With few (head, query block) units the key blocks of a unit are dealt to n_split workgroups: blocks split,
     // split + n_split, ... (interleaved, so that a run of blocks nobody kept or the causal end of the user keys is shared
     // out evenly).
-    const int unit = piece / n_split, split = piece - unit * n_split;
+    int unit = piece / n_split, split = piece - unit * n_split, share0 = 0;   // share0: shares of the units in front (PfDeal)
+    if constexpr (SHARED && !SELECT)
+        if (deal.units) {                                   // shares in proportion to the units' blocks
+            const PfDealt d = pf_deal(deal, piece, blk_info, PF_BM, B, H, L, Lq, U, causal_user);
+            unit = d.unit;
+            share0 = d.first;
+            split = piece - d.first;
+            n_split = d.n;
+            if (split == 0 && tid == 0) deal.dealt[unit] = int2{d.first, d.n};
+        }
     const int h = unit / (nqb * B), b = (unit / nqb) % B;
     const int q0 = (unit % nqb) * PF_BM;                    // first query of the workgroup
     const int W = (C + 31) >> 5;
@@ -941,7 +976,8 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     const bool empty = !(lt > 0.0f);
     const float inv = empty ? 0.0f : 1.0f / lt;
     _Float16 *orow = out + (row0 + nq) * D;
-    float *pr = partials + ((row0 + nq) * (size_t)n_split + split) * PART_STRIDE;
+    const bool dealt = SHARED && !SELECT && deal.units != 0;   // (uniform)
+    float *pr = partials + ((dealt ? (size_t)share0 * PF_BM + (size_t)(nq - q0) * n_split : (row0 + nq) * (size_t)n_split) + split) * PART_STRIDE;
     if (n_split > 1) {                                      // this share's (m, l, o) for the merge launch; m in natural units
         if (!again)
 #pragma unroll
@@ -983,13 +1019,27 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
 // Traced, a wave per row that found the maximum first / eight shares a round, the last of them taken again to fill it / this kernel:
 // 32768 rows x 2 shares 11.7 / 8.2 / 7.8 us, 7992 x 7 7.2 / 6.4 / 5.9, 4096 x 16 8.0 / 7.7 / 7.3; 4096 x 10 6.5 / 5.4, 3000 x 11
 // 4.9 / 4.5, 3000 x 17 8.2 / 7.1, 1000 x 24 5.2 / 4.1, 100 x 63 4.0 / 3.9 (the last two of the three).
-template <int AHEAD, int GROUPS, bool ONE>
+// DEALT: rows are units times bm positions, and the attention launch named every unit's first share and number of shares.
+struct PfMerge {
+    PfDeal deal;
+    int bm, nqb, B, H, Lq;
+};
+template <int AHEAD, int GROUPS, bool ONE, bool DEALT>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restrict__ partials, _Float16 *__restrict__ out,
-                                                            float *__restrict__ lse, int n_split, size_t rows)
+                                                            float *__restrict__ lse, int n_split, size_t rows, PfMerge mg)
 {
     const int half = threadIdx.x >> 5, lane = threadIdx.x & 31, group = half % GROUPS;
-    const size_t row = (size_t)blockIdx.x * (8 / GROUPS) + half / GROUPS;
+    size_t row = (size_t)blockIdx.x * (8 / GROUPS) + half / GROUPS;
     const float *pr = partials + min(row, rows - 1) * (size_t)n_split * PART_STRIDE;
+    if constexpr (DEALT) {                                  // (a workgroup's rows are of one unit: bm is a multiple of 8)
+        const int unit = (int)(row / mg.bm), r = (int)(row - (size_t)unit * mg.bm), nq = unit % mg.nqb * mg.bm + r;
+        const int2 d = mg.deal.dealt[unit];
+        n_split = d.y;
+        if (n_split == 1) return;                           // (its only share wrote the outputs)
+        pr = partials + ((size_t)d.x * mg.bm + (size_t)r * n_split) * PART_STRIDE;
+        rows = (size_t)mg.B * mg.H * mg.Lq;
+        row = nq < mg.Lq ? ((size_t)(unit / mg.nqb % mg.B) * mg.H + unit / (mg.nqb * mg.B)) * mg.Lq + nq : rows;
+    }
     float M = SQ_NEG_INF, l = 0.0f;
     f4 o = {0.f, 0.f, 0.f, 0.f};
     auto fold = [&](const auto &m, const auto &n, const auto &v) {
@@ -1100,7 +1150,27 @@ PfPlan prefill_plan(bool shared, const Shape &sh)
 size_t prefill_partial_floats(bool shared, const Shape &sh)
 {
     const int s = prefill_plan(shared, sh).n_split;
+    if (shared && prefill_deal(sh, nullptr).units) return prefill_deal(sh, nullptr).words;
     return s > 1 ? (size_t)sh.B * sh.H * sh.Lq * s * PART_STRIDE : 0;
+}
+
+// Dealing costs a workgroup about a microsecond in front of its first load and pays where shares are long; heads differ by a factor of
+// three at the measured thresholds.  Whole two-level steps, us, even / in proportion, by heads x tokens x keys (blocks a share, an eighth
+// of the context): 8 x 512 x 262144, 1/16 kept 104.7 / 98.8, 0.09 kept 123.7 / 114.5 (32); 4 x 300 x 200000 67.8 / 68.4 (12); 8 x 200 x
+// 131072 69.0 / 67.6, 8 x 512 x 65536 73.5 / 74.0, one head x 512 x 262144 57.6 / 58.7 (8; one head's units keep the same keys).
+PfDeal prefill_deal(const Shape &sh, float *ws)
+{
+    const PfPlan plan = prefill_plan(true, sh);
+    const int bm = pf_bm(plan.waves);
+    const long long units = (long long)sh.B * sh.H * ((sh.Lq + bm - 1) / bm);
+    PfDeal d{};
+    if (units > 64 || sh.B * sh.H == 1 || plan.n_split < PF_DEAL_MIN_SPLIT || (long long)sh.L < 8ll * PF_BN * PF_DEAL_MIN_BLOCKS * plan.n_split) return d;
+    d.units = (int)units;
+    d.shares = (int)units * plan.n_split;
+    const size_t floats = (size_t)d.shares * bm * PART_STRIDE;
+    d.dealt = reinterpret_cast<int2 *>(ws + floats);
+    d.words = floats + 2 * (size_t)units;
+    return d;
 }
 
 namespace {
@@ -1109,7 +1179,7 @@ template <bool SHARED, int WAVES, bool SELECT>
 hipError_t launch_prefill_kernel(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                  const uint32_t *keep_mask, const uint32_t *table, const uint32_t *rows,
                                  const int32_t *blk_info, void *out, float *lse, float *partials, int n_split,
-                                 const PfSelect &sel, const Shape &sh, hipStream_t s)
+                                 const PfSelect &sel, const PfDeal &deal, const Shape &sh, hipStream_t s)
 {
     constexpr int BM = pf_bm(WAVES);
     const int units = ((sh.Lq + BM - 1) / BM) * sh.H * sh.B * n_split;
@@ -1119,12 +1189,12 @@ hipError_t launch_prefill_kernel(const void *q, const void *Kf, const void *Vf, 
         hipExtLaunchKernelGGL((prefill_attn_kernel<SHARED, WAVES, SELECT>), grid, block, 0, s, ev0, ev1, 0, (const _Float16 *)q,
                               (const _Float16 *)Kf, (const _Float16 *)Vf, (const _Float16 *)Ku, (const _Float16 *)Vu,
                               keep_mask, table, rows, blk_info, (_Float16 *)out, lse, partials, n_split, sh.B, sh.H, sh.L,
-                              sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale, sel);
+                              sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale, sel, deal);
     else
         hipLaunchKernelGGL((prefill_attn_kernel<SHARED, WAVES, SELECT>), grid, block, 0, s, (const _Float16 *)q,
                            (const _Float16 *)Kf, (const _Float16 *)Vf, (const _Float16 *)Ku, (const _Float16 *)Vu,
                            keep_mask, table, rows, blk_info, (_Float16 *)out, lse, partials, n_split, sh.B, sh.H, sh.L,
-                           sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale, sel);
+                           sh.C, sh.Lq, sh.U, sh.causal_user, sh.sm_scale, sel, deal);
     return hipGetLastError();
 }
 
@@ -1136,16 +1206,23 @@ hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf,
                                   const Shape &sh, hipStream_t s)
 {
     const PfPlan plan = prefill_plan(SHARED, sh);
+    const PfDeal deal = SHARED && !SELECT ? prefill_deal(sh, partials) : PfDeal{};
     const hipError_t e = plan.waves == 8 ? launch_prefill_kernel<SHARED, 8, SELECT>(q, Kf, Vf, Ku, Vu, keep_mask, table, rows, blk_info,
-                                                                                    out, lse, partials, plan.n_split, sel, sh, s)
+                                                                                    out, lse, partials, plan.n_split, sel, deal, sh, s)
                                          : launch_prefill_kernel<SHARED, 4, SELECT>(q, Kf, Vf, Ku, Vu, keep_mask, table, rows, blk_info,
-                                                                                    out, lse, partials, plan.n_split, sel, sh, s);
+                                                                                    out, lse, partials, plan.n_split, sel, deal, sh, s);
     if (e != hipSuccess || plan.n_split == 1) return e;
-    const size_t n = (size_t)sh.B * sh.H * sh.Lq;
+    const int bm = pf_bm(plan.waves);
+    const size_t n = deal.units ? (size_t)deal.units * bm : (size_t)sh.B * sh.H * sh.Lq;
     auto merge = [&](auto kernel, int groups) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)((n * groups + 7) / 8)), dim3(256), 0, s, partials, (_Float16 *)out, lse,
-                           plan.n_split, n);
+                           plan.n_split, n, PfMerge{deal, bm, (sh.Lq + bm - 1) / bm, sh.B, sh.H, sh.Lq});
     };
+    if (deal.units) {                                       // (a unit's shares are known there)
+        n >= 4096 ? merge(prefill_merge_kernel<8, 1, false, true>, 1) : n >= 1024 ? merge(prefill_merge_kernel<8, 2, false, true>, 2)
+                                                                                : merge(prefill_merge_kernel<8, 8, false, true>, 8);
+        return hipGetLastError();
+    }
     // Several half waves per row where the rows are few; a half wave takes its shares in rounds of at most eight, as even as they go.
     // (3000 rows x 11 shares: two half waves 38.2 us a step, one 38.9; 1476 x 17: eight of them 6.3 us traced against 5.3 of a wave
     // per row.)
@@ -1155,12 +1232,12 @@ hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf,
         constexpr int A = a;
         if constexpr (A >= 2) {
             if (ahead != A) return;
-            if (groups == 1 && rounds == 1) return merge(prefill_merge_kernel<A, 1, true>, 1);
+            if (groups == 1 && rounds == 1) return merge(prefill_merge_kernel<A, 1, true, false>, 1);
             if constexpr (A >= 3)                           // (from 17 shares on)
-                if (groups == 8) return merge(prefill_merge_kernel<A, 8, true>, 8);
+                if (groups == 8) return merge(prefill_merge_kernel<A, 8, true, false>, 8);
             if constexpr (A >= 5) {                         // (from nine shares on: at least five in a round)
-                if (groups == 1) return merge(prefill_merge_kernel<A, 1, false>, 1);
-                return rounds == 1 ? merge(prefill_merge_kernel<A, 2, true>, 2) : merge(prefill_merge_kernel<A, 2, false>, 2);
+                if (groups == 1) return merge(prefill_merge_kernel<A, 1, false, false>, 1);
+                return rounds == 1 ? merge(prefill_merge_kernel<A, 2, true, false>, 2) : merge(prefill_merge_kernel<A, 2, false, false>, 2);
             }
         }
     });

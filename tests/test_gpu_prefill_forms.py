@@ -159,3 +159,36 @@ def test_merges(sq, oracle, waves, splits, case):
                                                (8, 13, dict(B=1, H=1, L=64 * 90, C=99, Lq=9, U=3))])
 def test_merges_one_kept_set(sq, oracle, waves, splits, case):
     test_one_kept_set(sq, oracle, waves, splits, case, 0.02)             # (shares without a key among them)
+
+
+DEALT = [
+    dict(B=1, H=32, L=64 * 512, C=300, Lq=300, U=300),       # 64 units, four shares each on average
+    dict(B=2, H=8, L=64 * 1024 + 5, C=400, Lq=257, U=10),    # 32 units, a unit of one query among every two
+    dict(B=3, H=1, L=500000, C=200, Lq=200, U=0),            # three units, 59 shares each, no user keys
+]
+
+
+@pytest.mark.parametrize("case", DEALT, ids=lambda c: "B{B}H{H}L{L}Lq{Lq}".format(**c))
+def test_shares_in_proportion(sq, oracle, case):
+    """Long contexts of few units: the shares follow the rows' numbers of kept keys, which go from none over one cluster to all."""
+    w = wl.make_workload("prefill_dealt", seed=53, threads=4, keep_frac=0.3, causal_user=True, **case)
+    rng = np.random.default_rng(16)
+    share = np.resize([0.0, 0.02, 0.5, 1.0, 0.1], (w.B, w.H))
+    kept = rng.random((w.B, w.H, w.C)) < share[..., None]
+    kept[share == 0.02] = np.arange(w.C) == 7                 # one cluster
+    P = sq.upload(w)
+    assert sq.sq_prefill_plan(P.shape, one_set=True)[1] >= 4
+    ranges, nr = np.zeros((w.B, w.H, w.C, 2), np.int32), np.zeros((w.B, w.H), np.int32)
+    for b in range(w.B):
+        for h in range(w.H):
+            ranges[b, h], nr[b, h] = ranges_from_keep(kept[b, h], w.offsets[h], w.sizes[h], w.C)
+    nk = (kept * w.sizes[None]).sum(-1).astype(np.int32)
+    P.out.fill_(7.0)
+    sq.sq_sparse_attn_prefill_shared(P.shape, P.q, P.K_fixed, P.V_fixed, t(ranges), t(nr), t(nk), P.K_user, P.V_user, P.out,
+                                     P.lse, sq.workspace(P.shape, sq.SQ_CALL_ATTN_PREFILL_SHARED, DEV))
+    torch.cuda.synchronize()
+    sel = sample_rows(w, 300, 17)
+    cap = max(1, int(nr.max()))
+    rr = np.ascontiguousarray(np.broadcast_to(ranges[:, :, None, :cap], (w.B, w.H, w.Lq, cap, 2)))
+    nn = np.ascontiguousarray(np.broadcast_to(nr[:, :, None], (w.B, w.H, w.Lq)))
+    compare(oracle, w, P, rr, nn, sel)
