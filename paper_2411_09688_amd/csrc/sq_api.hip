@@ -355,7 +355,7 @@ KmeansWs carve_kmeans(Carver &cv, const sq_shape_t *sh)
     const size_t parts = (size_t)(sh->L + PL - 1) / PL;
     KmeansWs w{};
     w.hn = cv.take<float>(heads * sh->C);
-    w.hist = cv.take<int32_t>(heads * parts * sh->C);
+    w.hist = cv.take<int32_t>(heads * parts * ((sh->C + 1) & ~1));   // (or two parts' counts of 16 bits in the place of one)
     return w;
 }
 

@@ -3,8 +3,9 @@
 //
 //   half norms  hn_c = |c|^2 / 2 of the current centres                         (one wave per centre)
 //   assignment  a(x) = argmin_c |x - c|^2 = argmax_c (x . c - hn_c)              (matrix cores, below)
-//   grouping    stable counting sort of the key indices by centre id: per-part histograms, a scan over parts
-//               and centres, and a scatter in key order -- sizes, offsets and the member list of every cluster
+//   grouping    stable counting sort of the key indices by centre id: per-part histograms (left by the assignment's workgroups
+//               up to 32768 keys), a scan over parts and centres, and a scatter in key order -- sizes, offsets and the member
+//               list of every cluster
 //   update      centre = mean of its members' vectors (a cluster without members keeps its centre)
 //
 // and a last call turns an assignment into what the online path reads: keys and values reordered so that each
@@ -35,6 +36,7 @@ namespace sq {
 constexpr int KM_G = 64;                     // centres per staged group
 constexpr int KM_RW = 4;                     // B sets (16 keys each) per wave
 constexpr int KM_ROWS_PER_WG = 4 * 16 * KM_RW;
+constexpr int KM_FUSED_PARTS = 128;          // parts (of a workgroup's keys) whose histograms the assignment leaves, at most
 constexpr int KM_STAGES = 3;                 // groups in LDS: one read, two on their way
 
 // Rows of 256 B without padding, filled by the load-to-LDS instruction; the 16-byte chunk c of row r lies at slot c ^ (r % 16), so
@@ -81,10 +83,13 @@ __global__ __launch_bounds__(256) void half_norm_kernel(const _Float16 *__restri
     if (l16 == 0 && row < rows) nhn[row] = -(0.5f * ss);
 }
 
+// HIST: the workgroup's keys are a part of the grouping below, and it leaves their histogram, 16 bits a centre, too.
+template <bool HIST>
 __global__ __launch_bounds__(256, 3) void kmeans_assign_kernel(const _Float16 *__restrict__ X,
                                                                const _Float16 *__restrict__ cent,
                                                                const float *__restrict__ nhn,
-                                                               int32_t *__restrict__ assign, int L, int C)
+                                                               int32_t *__restrict__ assign, uint32_t *__restrict__ hist,
+                                                               int L, int C)
 {
     __shared__ __align__(16) KmStage stage[KM_STAGES];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -196,6 +201,14 @@ __global__ __launch_bounds__(256, 3) void kmeans_assign_kernel(const _Float16 *_
         st = st == 2 ? 0 : st + 1;
     }
     take(cur, cur_c0);
+    uint32_t *s_cnt = reinterpret_cast<uint32_t *>(stage);    // two centres a word, where the groups were
+    const int words = (C + 1) >> 1;
+    if constexpr (HIST) {
+        static_assert(sizeof(stage) >= SELECT_MAX_C * 2, "a count of 16 bits for every centre");
+        __syncthreads();                                      // (the last group is read)
+        for (int w = tid; w < words; w += 256) s_cnt[w] = 0u;
+        __syncthreads();
+    }
 #pragma unroll
     for (int r = 0; r < KM_RW; ++r) {
         bi[r] += sv[r][0] == best[r] ? 0 : sv[r][1] == best[r] ? 1 : sv[r][2] == best[r] ? 2 : 3;
@@ -209,11 +222,20 @@ __global__ __launch_bounds__(256, 3) void kmeans_assign_kernel(const _Float16 *_
             }
         }
         const int row = r0 + r * 16 + col;
-        if (kg == 0 && row < L) assign[(size_t)h * L + row] = bi[r];
+        if (kg == 0 && row < L) {
+            assign[(size_t)h * L + row] = bi[r];
+            const int c = min(bi[r], C - 1);                  // (clamped like an id that is read back)
+            if (HIST) atomicAdd(&s_cnt[c >> 1], 1u << (16 * (c & 1)));   // (at most 256 a centre)
+        }
+    }
+    if constexpr (HIST) {
+        __syncthreads();
+        uint32_t *dst = hist + ((size_t)h * gridDim.x + blockIdx.x) * words;
+        for (int w = tid; w < words; w += 256) dst[w] = s_cnt[w];
     }
 }
 
-// Grouping, step 1: histogram of centre ids over one part of a head's keys.
+// Grouping, step 1: histogram of centre ids over one part of a head's keys.  (Where the assignment did not leave it.)
 __global__ __launch_bounds__(256) void kmeans_hist_kernel(const int32_t *__restrict__ assign, int32_t *__restrict__ hist,
                                                           int L, int C, int PL, int P)
 {
@@ -232,17 +254,19 @@ __global__ __launch_bounds__(256) void kmeans_hist_kernel(const int32_t *__restr
 // Grouping, step 2: per centre, the part counts become exclusive prefixes over the parts and their total the cluster size.  A
 // workgroup takes 64 centres, each of its four waves a quarter of the parts (at most 64, see kmeans_part_len).  5.8 us at 32 heads x
 // 1024 centres x 64 parts, where one workgroup per head, which also scanned the sizes into offsets, took 9.4.
-constexpr int KM_SCAN_PARTS = 16;
-__global__ __launch_bounds__(256) void kmeans_scan_kernel(int32_t *__restrict__ hist, int32_t *__restrict__ sizes, int C, int P)
+// CT: type of the counts, 16 bits where the keys of a head are at most 2^15 in at most 128 parts.  Cs: counts of a part's row.
+template <typename CT>
+__global__ __launch_bounds__(256) void kmeans_scan_kernel(CT *__restrict__ hist, int32_t *__restrict__ sizes, int C, int Cs, int P)
 {
+    constexpr int KM_SCAN_PARTS = sizeof(CT) == 2 ? KM_FUSED_PARTS / 4 : 16;
     __shared__ int s_tot[4][64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int c = blockIdx.x * 64 + lane, h = blockIdx.y;
     const int per = (P + 3) >> 2, p0 = wave * per, n = max(0, min(per, P - p0));
-    int32_t *col = hist + ((size_t)h * P + p0) * C + min(c, C - 1);
+    CT *col = hist + ((size_t)h * P + p0) * Cs + min(c, C - 1);
     int t[KM_SCAN_PARTS], sum = 0;
 #pragma unroll
-    for (int u = 0; u < KM_SCAN_PARTS; ++u) t[u] = u < n ? col[(size_t)u * C] : 0;
+    for (int u = 0; u < KM_SCAN_PARTS; ++u) t[u] = u < n ? (int)col[(size_t)u * Cs] : 0;
 #pragma unroll
     for (int u = 0; u < KM_SCAN_PARTS; ++u) sum += t[u];
     s_tot[wave][lane] = sum;
@@ -257,7 +281,7 @@ __global__ __launch_bounds__(256) void kmeans_scan_kernel(int32_t *__restrict__ 
     if (c >= C) return;
 #pragma unroll
     for (int u = 0; u < KM_SCAN_PARTS; ++u) {
-        if (u < n) col[(size_t)u * C] = before;
+        if (u < n) col[(size_t)u * Cs] = (CT)before;
         before += t[u];
     }
     if (wave == 0) sizes[(size_t)h * C + c] = total;
@@ -273,16 +297,18 @@ __global__ __launch_bounds__(256) void kmeans_scan_kernel(int32_t *__restrict__ 
 // 17.0 -> 12.0 traced; with the XCDs alone 295.8, with the reads alone 298.9), 16 heads x 30000 x 800 139.4 -> 137.1, one head x 20000
 // x 500 35.0 -> 34.6.
 constexpr int KM_SCATTER_AHEAD = 8, KM_CURSOR_AHEAD = 16;
+template <typename CT>
 __global__ __launch_bounds__(64) void kmeans_scatter_kernel(const int32_t *__restrict__ assign,
-                                                            const int32_t *__restrict__ hist,
+                                                            const CT *__restrict__ hist,
                                                             const int32_t *__restrict__ sizes, int32_t *__restrict__ offsets,
-                                                            int32_t *__restrict__ perm, int H, int L, int C, int PL, int P)
+                                                            int32_t *__restrict__ perm, int H, int L, int C, int Cs, int PL, int P)
 {
     extern __shared__ int s_cur[];
     const int per_xcd = (H * P + 7) >> 3, unit = (int)(blockIdx.x & 7) * per_xcd + (int)(blockIdx.x >> 3);
     if (unit >= H * P) return;
     const int h = unit / P, p = unit - h * P, lane = threadIdx.x;
-    const int32_t *hp = hist + ((size_t)h * P + p) * C, *np = sizes + (size_t)h * C;
+    const CT *hp = hist + ((size_t)h * P + p) * Cs;
+    const int32_t *np = sizes + (size_t)h * C;
     int32_t *op = offsets + (size_t)h * (C + 1);
     // Where the part's members of every centre go: the sizes of the centres in front -- scanned by every wave, 64 centres at a
     // time with sixteen such loads under way; the first part's wave writes them as the offsets -- and the members in parts in front.
@@ -301,7 +327,7 @@ __global__ __launch_bounds__(64) void kmeans_scatter_kernel(const int32_t *__res
         for (int u = 0; u < KM_CURSOR_AHEAD; ++u) {
             const int c = min(c0 + u * 64 + lane, C - 1);
             n[u] = np[c];
-            before[u] = hp[c];
+            before[u] = (int)hp[c];
         }
 #pragma unroll
         for (int u = 0; u < KM_CURSOR_AHEAD; ++u) {
@@ -471,14 +497,22 @@ hipError_t launch_normalize_rows(const void *K, void *X, size_t rows, hipStream_
 }
 
 // Stable grouping of the rows by centre id: sizes, offsets and the member list of every centre.
+template <typename CT>
+static void launch_scan_scatter(const int32_t *assign, int32_t *sizes, int32_t *offsets, int32_t *perm, CT *hist, int H, int L, int C,
+                                int Cs, int PL, hipStream_t s)
+{
+    const int P = (L + PL - 1) / PL;
+    hipLaunchKernelGGL(kmeans_scan_kernel<CT>, dim3((C + 63) / 64, H), dim3(256), 0, s, hist, sizes, C, Cs, P);
+    hipLaunchKernelGGL(kmeans_scatter_kernel<CT>, dim3((H * P + 7) / 8 * 8), dim3(64), (size_t)C * 4, s, assign, (const CT *)hist,
+                       (const int32_t *)sizes, offsets, perm, H, L, C, Cs, PL, P);
+}
+
 static void launch_group(const int32_t *assign, int32_t *sizes, int32_t *offsets, int32_t *perm, int32_t *hist, int H,
                          int L, int C, hipStream_t s)
 {
     const int PL = kmeans_part_len(L), P = (L + PL - 1) / PL;
     hipLaunchKernelGGL(kmeans_hist_kernel, dim3(P, H), dim3(256), (size_t)C * 4, s, assign, hist, L, C, PL, P);
-    hipLaunchKernelGGL(kmeans_scan_kernel, dim3((C + 63) / 64, H), dim3(256), 0, s, hist, sizes, C, P);
-    hipLaunchKernelGGL(kmeans_scatter_kernel, dim3((H * P + 7) / 8 * 8), dim3(64), (size_t)C * 4, s, assign, (const int32_t *)hist,
-                       (const int32_t *)sizes, offsets, perm, H, L, C, PL, P);
+    launch_scan_scatter(assign, sizes, offsets, perm, hist, H, L, C, C, PL, s);
 }
 
 hipError_t launch_kmeans_step(const void *X, const void *centers_in, void *centers_out, int32_t *assign,
@@ -487,14 +521,28 @@ hipError_t launch_kmeans_step(const void *X, const void *centers_in, void *cente
 {
     hipLaunchKernelGGL(half_norm_kernel, dim3((H * C + 15) / 16), dim3(256), 0, s, (const _Float16 *)centers_in, hn, H * C);
     const dim3 grid_a((L + KM_ROWS_PER_WG - 1) / KM_ROWS_PER_WG, H);
-    hipEvent_t ev0, ev1;
-    if (profile_pair(&ev0, &ev1))
-        hipExtLaunchKernelGGL(kmeans_assign_kernel, grid_a, dim3(256), 0, s, ev0, ev1, 0, (const _Float16 *)X,
-                              (const _Float16 *)centers_in, (const float *)hn, assign, L, C);
-    else
-        hipLaunchKernelGGL(kmeans_assign_kernel, grid_a, dim3(256), 0, s, (const _Float16 *)X,
-                           (const _Float16 *)centers_in, (const float *)hn, assign, L, C);
-    launch_group(assign, sizes, offsets, perm, hist, H, L, C, s);
+    // The launch that counted the ids again is a launch's time where there is little to count; what it costs the assignment is a
+    // microsecond a workgroup, under the others' products, and the rows of 256 keys in 16 bits are as many bytes as those of 512 in 32.
+    // Whole step, us, with that launch / here: 32 heads x 32768 keys x 1024 centres 287.1 / 283.2, 16 x 30000 x 800 129.9 / 127.0,
+    // 4 x 32768 x 1638 79.0 / 75.7, 1 x 20000 x 500 34.0 / 30.4, 32 x 3000 x 130 35.4 / 32.1, 1 x 2000 x 40 23.1 / 20.0.  The line is
+    // the scan's 128 parts (and every prefix has to fit 16 bits).
+    const bool fused = L <= KM_FUSED_PARTS * KM_ROWS_PER_WG;
+    auto assign_kernel = [&](auto kernel) {
+        hipEvent_t ev0, ev1;
+        if (profile_pair(&ev0, &ev1))
+            hipExtLaunchKernelGGL(kernel, grid_a, dim3(256), 0, s, ev0, ev1, 0, (const _Float16 *)X, (const _Float16 *)centers_in,
+                                  (const float *)hn, assign, reinterpret_cast<uint32_t *>(hist), L, C);
+        else
+            hipLaunchKernelGGL(kernel, grid_a, dim3(256), 0, s, (const _Float16 *)X, (const _Float16 *)centers_in, (const float *)hn,
+                               assign, reinterpret_cast<uint32_t *>(hist), L, C);
+    };
+    if (fused) {
+        assign_kernel(kmeans_assign_kernel<true>);
+        launch_scan_scatter(assign, sizes, offsets, perm, reinterpret_cast<uint16_t *>(hist), H, L, C, (C + 1) & ~1, KM_ROWS_PER_WG, s);
+    } else {
+        assign_kernel(kmeans_assign_kernel<false>);
+        launch_group(assign, sizes, offsets, perm, hist, H, L, C, s);
+    }
     return launch_cluster_mean(X, perm, sizes, offsets, centers_in, centers_out, H, L, C, s);
 }
 
