@@ -1388,12 +1388,16 @@ int sq_hier_prefill_mean_step(const sq_shape_t *sh, int32_t C1, const void *q, c
     // Level 1 (Eq. 2 averaged over the tokens): the children of the kept coarse clusters are listed as candidates ...
     SQ_HIP(sq::launch_prefill_lookup(q, centroids1, sizes1, thresh1, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
                                      sh->B, sh->H, sh->Lq, C1, sh->sm_scale, s));
-    SQ_HIP(sq::launch_mean_select(w.step.part_sum, sq::lookup_parts(rows, sh->Lq, C1), sh->Lq, thresh1, sizes1,
-                                  child_offsets, nullptr, nullptr, true, nullptr, nullptr, w.cand_hdr, w.cand_id, sh->C, rows,
-                                  sh->H, C1, s));
+    const int parts1 = sq::lookup_parts(rows, sh->Lq, C1);
+    const sq::PfSelect coarse{w.step.part_sum, parts1, thresh1, sizes1, child_offsets, nullptr, nullptr};
+    const bool children = sq::lookup_selects_children(rows, sh->Lq, sh->C, C1);
+    if (!children)
+        SQ_HIP(sq::launch_mean_select(w.step.part_sum, parts1, sh->Lq, thresh1, sizes1, child_offsets, nullptr, nullptr, true, nullptr,
+                                      nullptr, w.cand_hdr, w.cand_id, sh->C, rows, sh->H, C1, s));
     // ... level 2 (Eq. 3 per token over the candidates, averaged over the tokens): scores and selection in candidate order.
     SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
-                                     sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s, w.cand_id, w.cand_hdr));
+                                     sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s, w.cand_id, w.cand_hdr, nullptr, nullptr, C1,
+                                     nullptr, children ? &coarse : nullptr));
     SQ_HIP(sq::launch_mean_select(w.step.part_sum, 0, sh->Lq, thresh2, sizes2,
                                   offsets2, w.cand_id, w.cand_hdr, false, keep_mask2, n_keys, w.step.att.hdr,
                                   w.step.att.key_idx, sh->L, rows, sh->H, sh->C, s));

@@ -75,7 +75,10 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
                                  int B, int H, int Lq, int C, float sm_scale, hipStream_t s,
                                  const int32_t *cand_id = nullptr, const int2 *cand_hdr = nullptr,
                                  const int32_t *parent = nullptr, const uint32_t *mask1 = nullptr, int C1 = 0,
-                                 const BlockTable *table = nullptr);
+                                 const BlockTable *table = nullptr, const struct PfSelect *coarse = nullptr);
+// coarse (averaged scores over candidates, C1 coarse clusters): the pass makes the candidates itself, from the coarse level's part_sum,
+// sizes, thresholds and child offsets, and leaves cand_id and cand_hdr (as launch_mean_select with children does).
+bool lookup_selects_children(int BH, int Lq, int C, int C1);
 // (table given, per-query mode: the first launch also makes the attention's block table.)
 // (parent [H, C] / mask1 [B*H*Lq, ceil(C1/32)] given, per-query mode: a cluster counts for a token only if the token's
 // level-1 mask holds its parent: level 2 of a hierarchical lookup with per-token candidates; C1 <= 1024.)

@@ -1,6 +1,7 @@
 // Selection on averaged scores (Appendix D, "Prefill Stage") straight into the list the next launch walks: from the partial
 // score sums of the lookup to the row's list of kept keys (the key-index tensor of Section 4.2), or of candidate clusters where
-// the kept clusters are coarse ones.  (One level: where prefill_selects() the attention launch does this by itself.)
+// the kept clusters are coarse ones.  (Where prefill_selects() the attention launch does this by itself, where
+// lookup_selects_children() the pass over the candidates.)
 //
 // One workgroup per ((sequence, head) row, slice of the row's clusters).  A workgroup adds up the averages of every cluster up
 // to the end of its slice, so it knows without talking to the others how many keys are kept in front of its own; it writes its

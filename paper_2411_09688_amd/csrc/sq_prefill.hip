@@ -42,6 +42,7 @@
 #include "sq_block_table.hpp"
 #include "sq_common.hpp"
 #include "sq_internal.hpp"
+#include "sq_mean_row.hpp"
 
 namespace sq {
 
@@ -234,91 +235,10 @@ __device__ __forceinline__ PfDealt pf_deal(const PfDeal &deal, int piece, const 
 }
 
 // ---- the kept set made by the attention launch ----------------------------------------------------------------------------
-// Bound by a chain of one round of loads (the clusters' sizes, offsets and up to eight parts of their scores together) and three
-// barriers, about 3 us of the launch's prologue; the rows' searches run in parallel, a few per thread.
-// Kept keys of a (sequence, head), by the whole workgroup: parts of its clusters' averaged scores, added in ascending order,
-// divided by the tokens and compared with the threshold (mean_select_kernel's decision).  Left in LDS: s[0..kept) positions of the
-// kept clusters' first keys in the list of kept keys, s[PF_SELECT_MAX_C ..) those keys; s[2 PF_SELECT_MAX_C] the number of kept clusters.
-// A barrier at the end.  write: the mask and the count, too.
-template <int PF_WAVES>
-__device__ __forceinline__ int pf_select(const PfSelect &sel, size_t bh, int h, int L, int C, int Lq, bool write, int *s)
-{
-    constexpr int THREADS = 64 * PF_WAVES, STEPS = PF_SELECT_MAX_C / THREADS, GROUPS = PF_SELECT_MAX_C / 64;
-    static_assert(GROUPS <= 64, "a group's counts per lane");
-    int *s_pos = s, *s_first = s + PF_SELECT_MAX_C, *s_n = s_first + PF_SELECT_MAX_C, *s_cnt = s_n + 1, *s_len = s_cnt + GROUPS;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), W = (C + 31) >> 5;
-    const float *ps = sel.part_sum + bh * sel.parts * C;
-    const int32_t *N = sel.sizes + (size_t)h * C, *off = sel.offsets + (size_t)h * (C + 1);
-    const float T = sel.thresh[h], div = (float)Lq;
-    if (tid < GROUPS) s_cnt[tid] = s_len[tid] = 0;
-    int first[STEPS], len[STEPS];
-    float sum[STEPS];
-#pragma unroll
-    for (int k = 0; k < STEPS; ++k) {
-        const int i = min(k * THREADS + tid, C - 1);
-        sum[k] = 0.0f;
-        len[k] = first[k] = 0;
-        if (k * THREADS < C) {                              // (uniform)
-            len[k] = N[i];
-            first[k] = off[i];
-        }
-    }
-    constexpr int AHEAD = 8;                                // parts under way together
-    for (int p0 = 0; p0 < sel.parts; p0 += AHEAD)
-#pragma unroll
-        for (int k = 0; k < STEPS; ++k) {
-            if (k * THREADS >= C) break;                    // (uniform)
-            const float *at = ps + min(k * THREADS + tid, C - 1);
-            float v[AHEAD];
-#pragma unroll
-            for (int p = 0; p < AHEAD; ++p) v[p] = at[(size_t)min(p0 + p, sel.parts - 1) * C];
-#pragma unroll
-            for (int p = 0; p < AHEAD; ++p) sum[k] = p0 + p < sel.parts ? sum[k] + v[p] : sum[k];
-        }
-    __syncthreads();                                        // (the counts are zero)
-#pragma unroll
-    for (int k = 0; k < STEPS; ++k) {
-        if (k * THREADS >= C) break;
-        const bool keep = k * THREADS + tid < C && len[k] > 0 && sum[k] / div > T;
-        len[k] = keep ? len[k] : 0;
-        const unsigned long long bal = __ballot(keep);
-        const int total = wave_sum_i(len[k]), g = k * PF_WAVES + wave;
-        if (lane == 0) {
-            s_cnt[g] = __popcll(bal);
-            s_len[g] = total;
-            if (write && sel.keep_mask && 2 * g < W) {
-                sel.keep_mask[bh * W + 2 * g] = (uint32_t)bal;
-                if (2 * g + 1 < W) sel.keep_mask[bh * W + 2 * g + 1] = (uint32_t)(bal >> 32);
-            }
-        }
-    }
-    __syncthreads();
-    const int gc = lane < GROUPS ? s_cnt[lane] : 0, gl = lane < GROUPS ? s_len[lane] : 0;
-    const int ic = wave_inclusive_scan(gc, lane), il = wave_inclusive_scan(gl, lane);
-    const int kept = __builtin_amdgcn_readlane(ic, 63), keys = __builtin_amdgcn_readlane(il, 63);
-#pragma unroll
-    for (int k = 0; k < STEPS; ++k) {
-        if (k * THREADS >= C) break;
-        const int g = k * PF_WAVES + wave;
-        const unsigned long long bal = __ballot(len[k] > 0);
-        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
-        const int c = __builtin_amdgcn_readlane(ic - gc, g) + rank;
-        const int pos = __builtin_amdgcn_readlane(il - gl, g) + wave_inclusive_scan(len[k], lane) - len[k];
-        if (len[k] > 0) {
-            s_pos[c] = pos;
-            s_first[c] = first[k];
-        }
-    }
-    if (tid == 0) {
-        *s_n = kept;
-        if (write && sel.n_keys) sel.n_keys[bh] = keys;
-    }
-    __syncthreads();
-    return keys;
-}
-
+// (mean_row_select.)  Bound by a chain of one round of loads (the clusters' sizes, offsets and up to eight parts of their scores
+// together) and three barriers, about 3 us of the launch's prologue; the rows' searches run in parallel, a few per thread.
 // Rows of the keys of a share's n_list fixed blocks, split, split + n_split, ... of the list of kept keys: every key finds its cluster
-// among the records of pf_select.  (Behind the last key: that key again.)
+// among the records of mean_row_select.  (Behind the last key: that key again.)
 template <int PF_WAVES>
 __device__ __forceinline__ void pf_share_rows(const int *s, int32_t *s_idx, int n_list, int split, int n_split, int n_fixed, int L)
 {
@@ -414,7 +334,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     // keys of the fixed context this (sequence, head) walks: all of them, or the kept ones through the row list
     int n_fixed = L;
     if constexpr (SELECT)
-        n_fixed = min(pf_select<PF_WAVES>(sel, (size_t)b * H + h, h, L, C, Lq, unit % nqb == 0 && split == 0, reinterpret_cast<int *>(stage)), L);
+        n_fixed = min(mean_row_select<PF_WAVES, PF_SELECT_MAX_C, false>(sel, (size_t)b * H + h, h, C, Lq, unit % nqb == 0 && split == 0, reinterpret_cast<int *>(stage)), L);
     else if constexpr (SHARED)
         n_fixed = min(blk_info[2 * ((size_t)b * H + h) + 1], L);
     const int32_t *idx_bh = reinterpret_cast<const int32_t *>(table) + ((size_t)b * H + h) * (size_t)L;   // SHARED without SELECT only

@@ -33,6 +33,7 @@
 #include "sq_common.hpp"
 #include "sq_internal.hpp"
 #include "sq_lookup.hpp"
+#include "sq_mean_row.hpp"
 
 namespace sq {
 
@@ -46,6 +47,8 @@ constexpr int LK_BT = 128;                   // tokens per workgroup (four waves
 //    4 heads x  333 tokens   43.3 / 42.6    46.7 / 45.8    47.5 / 49.5    47.6 / 53.9    50.0 / 58.9
 //   32 heads x 1024 tokens    98.5 / 97.1  117.8 / 114.9  143.3 / 140.1  157.5 / 159.2  179.9 / 177.1
 constexpr int LK_ONE_C = 128;
+constexpr int LK_COARSE_MAX = 1024;          // coarse clusters that the pass over the candidates selects from
+constexpr int LK_MAX_GROUPS = 32;            // groups of a slice's candidates that it holds, at most
 constexpr int LK_MAX_W1 = 32;                // level-1 mask words per token held in LDS: at most 1024 coarse clusters
 
 // A token's pairs (r, sum) of the slices first, first + STEP, ... (at most LK_MAX_SLICES / STEP of them): the loads are issued
@@ -84,12 +87,16 @@ struct SlicePairs {
 // Which passes a launch makes.  BOTH: one launch for rows of few clusters, where a second launch costs more than slices give.
 enum LkMode { LK_STATS, LK_DECIDE, LK_BOTH };
 
-template <LkMode MODE, bool CANDS, bool PARENTS, bool KEYS>
+// CHILDREN (with CANDS, sums): the candidates are made here, from the parts of the coarse level's averaged scores (what
+// mean_select_kernel does in a launch of its own otherwise); the first token block's workgroups write cand_id and cand_hdr for the
+// launches behind.
+template <LkMode MODE, bool CANDS, bool PARENTS, bool KEYS, bool CHILDREN>
 __global__ __launch_bounds__(256) void lookup_pass_kernel(
     const _Float16 *__restrict__ q, const _Float16 *__restrict__ cent, const int32_t *__restrict__ sizes,
     const float *__restrict__ thresh, float2 *__restrict__ stats, uint32_t *__restrict__ keep_mask,
-    int32_t *__restrict__ n_keys, const int32_t *__restrict__ cand_id, const int2 *__restrict__ cand_hdr,
-    const uint32_t *__restrict__ mask1, int W1, int n_slice, int H, int Lq, int C_all, float sm_scale, BlockTable table)
+    int32_t *__restrict__ n_keys, const int32_t *cand_id, const int2 *cand_hdr,
+    const uint32_t *__restrict__ mask1, int W1, int n_slice, int H, int Lq, int C_all, float sm_scale, BlockTable table,
+    PfSelect coarse, int C1)
 {
     if (MODE != LK_DECIDE && !CANDS) {                      // extra workgroups: the attention's block table
         const int extra = (int)blockIdx.x - (Lq + LK_BT - 1) / LK_BT * n_slice;
@@ -110,7 +117,14 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
     const int bh = blockIdx.y, h = bh % H, slice = blockIdx.x % n_slice;
     const int t0 = (int)(blockIdx.x / n_slice) * LK_BT;
     // C: the clusters scored (all of the head's, or the candidates); C_all: row length of the arrays.
-    const int C = CANDS ? min(cand_hdr[bh].y, C_all) : C_all;
+    __shared__ int s_ids[CHILDREN ? LK_MAX_GROUPS * LK_G : 1];   // CHILDREN: the slice's candidates
+    int n_cand = 0;
+    if constexpr (CHILDREN) {
+        static_assert(sizeof(stage) >= mean_row_words(LK_COARSE_MAX) * sizeof(int), "the records lie where the centroids will be");
+        n_cand = mean_row_select<4, LK_COARSE_MAX, true>(coarse, bh, h, C1, Lq, false, reinterpret_cast<int *>(stage));
+    } else if constexpr (CANDS)
+        n_cand = cand_hdr[bh].y;
+    const int C = CANDS ? min(n_cand, C_all) : C_all;
     const int ng = (C + LK_G - 1) / LK_G, per = (ng + n_slice - 1) / n_slice;
     const int g0 = min(slice * per, ng), g1 = min(g0 + per, ng);
     const int t = t0 + wave * 32 + col;                     // this lane's token (past the end: the last one, not stored)
@@ -119,6 +133,21 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
     const int W = (C + 31) >> 5;
     const float c2 = sm_scale * 1.44269504088896341f;       // base-2 exponents: one instruction per exponential
     const int32_t *cid = CANDS ? cand_id + (size_t)bh * C_all : nullptr;
+    if constexpr (CHILDREN) {
+        const int *s_pos = reinterpret_cast<const int *>(stage), *s_first = s_pos + LK_COARSE_MAX;
+        const int emit = s_pos[2 * LK_COARSE_MAX], p0 = g0 * LK_G, p1 = min(g1 * LK_G, C);
+        for (int p = p0 + tid; p < p1; p += 256) {
+            int k = 0;                                      // the kept coarse cluster whose children p is one of
+#pragma unroll
+            for (int step = LK_COARSE_MAX / 2; step > 0; step >>= 1)
+                if (k + step < emit && s_pos[k + step] <= p) k += step;
+            const int id = min(max(s_first[k] + p - s_pos[k], 0), C_all - 1);
+            s_ids[p - p0] = id;
+            if (t0 == 0) const_cast<int32_t *>(cand_id)[(size_t)bh * C_all + p] = id;
+        }
+        if (t0 == 0 && slice == 0 && tid == 0) const_cast<int2 *>(cand_hdr)[bh] = int2{emit, n_cand};
+        __syncthreads();                                    // (the records are read)
+    }
     const int32_t *par = PARENTS ? cand_id + (size_t)h * C_all : nullptr;     // (PARENTS: cand_id is parent [H, C])
     if (KEYS && MODE == LK_STATS && slice == 0 && g == 0 && valid) n_keys[row] = 0;   // (summed over the slices by the second pass)
     if (MODE == LK_DECIDE && g0 >= g1) return;              // (workgroup-uniform)
@@ -143,14 +172,17 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
     const uint32_t chunk = (uint32_t)((tid & 15) ^ (trow & 15)) * 16u;
     const uint32_t lds_w = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lk_lptr_t)stage) + (uint32_t)wave * 1024u;
     int id_n[4] = {}, id_s = 0;                             // CANDS: rows of the group after next, and this thread's cluster of it
+    auto cluster_at = [&](int c) {                          // (a group past the slice's last one is never used)
+        if constexpr (CHILDREN) return s_ids[min(c, min(g1 * LK_G, C) - 1) - g0 * LK_G];
+        else return CANDS ? min(max(cid[c], 0), C_all - 1) : c;
+    };
     auto fetch_ids = [&](int gr) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int c = min(gr * LK_G + i * 16 + trow, C - 1);
-            id_n[i] = CANDS ? min(max(cid[c], 0), C_all - 1) : c;
+            id_n[i] = cluster_at(c);
         }
-        const int c = min(gr * LK_G + (tid & (LK_G - 1)), C - 1);
-        id_s = CANDS ? min(max(cid[c], 0), C_all - 1) : c;
+        id_s = cluster_at(min(gr * LK_G + (tid & (LK_G - 1)), C - 1));
     };
     int pn = 0, pp = 0;
     auto fetch = [&](int gr, int buf) {                     // group gr -> buffer buf (its rows' ids are in id_n)
@@ -406,11 +438,22 @@ size_t lookup_part_floats(int BH, int C)
     return std::max((size_t)BH * C + LK_MEAN_GROUPS * LK_MC, (size_t)std::max(BH, 512) * std::min(C, LR_MAX_C));
 }
 
+// The coarse selection inside the pass (about 2 us more of its prologue: a round of loads and three barriers) against a launch of its own
+// (6.5 us, and the round trip to the list it leaves), whole two-level steps, us, own launch / inside, by heads x tokens x keys, fine /
+// coarse clusters: 8 x 512 x 262144, 16384 / 256 99.0 / 94.6, 1 x 512 x 262144, 16384 / 256 57.7 / 52.7, 4 x 300 x 200000, 10000 / 100
+// 68.2 / 63.5, 8 x 200 x 131072, 6000 / 64 69.9 / 64.8, 8 x 300 x 40000, 2000 / 40 56.7 / 52.3, 1 x 64 x 100000, 4000 / 64 38.4 / 32.4.
+// The line is what a slice holds in LDS: 8 KB of candidates beside 32 KB of centroids, three workgroups per compute unit.
+bool lookup_selects_children(int BH, int Lq, int C, int C1)
+{
+    const int groups = (C + LK_G - 1) / LK_G, n_slice = lookup_slices(BH, Lq, C);
+    return C1 <= LK_COARSE_MAX && (groups + n_slice - 1) / n_slice <= LK_MAX_GROUPS;
+}
+
 hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int32_t *sizes, const float *thresh,
                                  float *stats, uint32_t *keep_mask, int32_t *n_keys, float *part_sum, bool mean,
                                  int B, int H, int Lq, int C, float sm_scale, hipStream_t s, const int32_t *cand_id,
                                  const int2 *cand_hdr, const int32_t *parent, const uint32_t *mask1, int C1,
-                                 const BlockTable *table)
+                                 const BlockTable *table, const PfSelect *coarse)
 {
     if (!parent && !cand_id && lookup_in_rows(B * H, Lq, C))
         return launch_lookup_rows(q, centroids, sizes, thresh, keep_mask, n_keys, part_sum, mean, B, H, Lq, C, sm_scale, s, table);
@@ -421,13 +464,14 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
     float2 *st = reinterpret_cast<float2 *>(stats);
     if (parent && (mean || cand_id || !mask1 || C1 <= 0 || (C1 + 31) / 32 > LK_MAX_W1)) return hipErrorInvalidValue;
     if ((cand_id && (!mean || !cand_hdr)) || (table && cand_id)) return hipErrorInvalidValue;
+    if (coarse && (!cand_id || !lookup_selects_children(BH, Lq, C, C1))) return hipErrorInvalidValue;
     const int32_t *ids = parent ? parent : cand_id;
     const int W1 = (C1 + 31) / 32;
-    auto pass = [&](auto mode, auto cands, auto parents, auto keys) {
+    auto pass = [&](auto mode, auto cands, auto parents, auto keys, auto children) {
         const dim3 all(grid.x + (mode != LK_DECIDE && table ? block_table_groups(table->nblk) : 0), grid.y);
-        hipLaunchKernelGGL((lookup_pass_kernel<mode, cands, parents, keys>), all, dim3(256), 0, s, qh, ch, sizes, thresh, st,
+        hipLaunchKernelGGL((lookup_pass_kernel<mode, cands, parents, keys, children>), all, dim3(256), 0, s, qh, ch, sizes, thresh, st,
                            keep_mask, n_keys, ids, cand_hdr, mask1, W1, n_slice, H, Lq, C, sm_scale,
-                           table ? *table : BlockTable{});
+                           table ? *table : BlockTable{}, coarse ? *coarse : PfSelect{}, C1);
     };
     constexpr std::true_type yes{};
     constexpr std::false_type no{};
@@ -437,12 +481,12 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
     if (mean) {
         const int blocks = (C + LK_MC - 1) / LK_MC;
         if (cand_id) {
-            pass(first, yes, no, no);
+            coarse ? pass(first, yes, no, no, yes) : pass(first, yes, no, no, no);
             const dim3 mgrid(std::max(blocks, LK_MEAN_GROUPS / BH), 1, BH);
             hipLaunchKernelGGL(mean_scores_kernel<true>, mgrid, dim3(256), 0, s, qh, ch, sizes, st, part_sum, ids, cand_hdr,
                                n_slice, H, Lq, C, sm_scale);
         } else {
-            pass(first, no, no, no);
+            pass(first, no, no, no, no);
             const dim3 mgrid(blocks, lookup_mean_parts(BH, Lq, C), BH);
             hipLaunchKernelGGL(mean_scores_kernel<false>, mgrid, dim3(256), 0, s, qh, ch, sizes, st, part_sum, ids, cand_hdr,
                                n_slice, H, Lq, C, sm_scale);
@@ -450,9 +494,9 @@ hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int
     } else {
         auto select = [&](auto parents, auto keys) {
             if constexpr (parents)
-                if (one) return pass(both, no, parents, keys);
-            pass(first, no, parents, keys);
-            pass(second, no, parents, keys);
+                if (one) return pass(both, no, parents, keys, no);
+            pass(first, no, parents, keys, no);
+            pass(second, no, parents, keys, no);
         };
         if (parent && n_keys) select(yes, yes);
         else if (parent) select(yes, no);

@@ -148,6 +148,27 @@ def test_candidate_parts(sq, oracle, case, first):
     assert 0 < gk.sum() < w.B * w.H * w.C
 
 
+# Candidates made by the pass that scores them, or by a launch in front of it.
+CHILD_CASES = [
+    dict(B=130, H=4, L=2500, C=2048, C1=40, Lq=2),    # one slice a row, as many candidates as it holds
+    dict(B=130, H=4, L=2500, C=2049, C1=40, Lq=2),    # and one more: a launch in front
+    dict(B=1, H=2, L=4000, C=3000, C1=1024, Lq=40),   # the most coarse clusters, hardly a group of children each
+    dict(B=1, H=1, L=3000, C=700, C1=1, Lq=130),      # one coarse cluster, two blocks of tokens
+]
+
+
+@pytest.mark.parametrize("first", ["all", "some"])
+@pytest.mark.parametrize("case", CHILD_CASES, ids=lambda c: "B{B}H{H}C{C}C1_{C1}Lq{Lq}".format(**c))
+def test_children_of_the_kept_coarse_clusters(sq, oracle, case, first):
+    w = wl.make_workload("hier_prefill_children", seed=36, threads=4, U=5, keep_frac=0.2, coarse_keep_frac=0.5, causal_user=False,
+                         variable_fanout=True, **case)
+    T1, T2 = thresholds(w)
+    if first == "all" or w.C1 == 1:
+        T1 = np.full(w.H, -1.0, np.float32)
+    gk, _ = compare(oracle, w, T1, T2, run(sq, w, T1, T2), f"children {case} {first}", sample=80)
+    assert 0 < gk.sum() < w.B * w.H * w.C
+
+
 def test_first_level_keeping_everything_is_the_one_level_step(sq, oracle):
     w = wl.make_workload("hier_prefill_mean_all", B=1, H=2, L=4096, C=128, C1=8, Lq=50, U=20, keep_frac=0.2,
                          coarse_keep_frac=0.5, causal_user=True, seed=32, threads=2)
