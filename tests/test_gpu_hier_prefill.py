@@ -153,7 +153,7 @@ CHILD_CASES = [
     dict(B=130, H=4, L=2500, C=2048, C1=40, Lq=2),    # one slice a row, as many candidates as it holds
     dict(B=130, H=4, L=2500, C=2049, C1=40, Lq=2),    # and one more: a launch in front
     dict(B=1, H=2, L=4000, C=3000, C1=1024, Lq=40),   # the most coarse clusters, hardly a group of children each
-    dict(B=1, H=1, L=3000, C=700, C1=1, Lq=130),      # one coarse cluster, two blocks of tokens
+    dict(B=1, H=1, L=3000, C=700, C1=2, Lq=130),      # two coarse clusters, two blocks of tokens
 ]
 
 
@@ -163,7 +163,7 @@ def test_children_of_the_kept_coarse_clusters(sq, oracle, case, first):
     w = wl.make_workload("hier_prefill_children", seed=36, threads=4, U=5, keep_frac=0.2, coarse_keep_frac=0.5, causal_user=False,
                          variable_fanout=True, **case)
     T1, T2 = thresholds(w)
-    if first == "all" or w.C1 == 1:
+    if first == "all":
         T1 = np.full(w.H, -1.0, np.float32)
     gk, _ = compare(oracle, w, T1, T2, run(sq, w, T1, T2), f"children {case} {first}", sample=80)
     assert 0 < gk.sum() < w.B * w.H * w.C
