@@ -80,18 +80,32 @@ __global__ __launch_bounds__(256) void expand_ranges_kernel(DecodePlan plan, int
 constexpr int PF_LIST_CAP = 4096;         // fixed blocks per workgroup that are listed; a longer share is walked whole
 constexpr int PF_UMASK_WORDS = SELECT_MAX_C / 32;
 
-// s_um[v * W + 0..W) |= keep masks of the 32 queries of wave v, v = 0..waves-1, those below Lq, of query rows row0...; s_um zeroed
-// by the caller, barrier after it by the caller.  A mask word of eight queries per item: eight independent loads, one LDS atomic.
+// s_um[v * W + 0..W) = OR of the keep masks of the 32 queries of wave v, v = 0..waves-1, those below Lq, of query rows row0...  Two
+// barriers inside, the second at the end.  A mask word of eight queries per item: eight independent loads, one LDS atomic; the first
+// item's loads are under way while the words are cleared.
 __device__ __forceinline__ void pf_union_masks(uint32_t *s_um, const uint32_t *__restrict__ keep_mask, size_t row0, int q0,
                                                int waves, int Lq, int W, int tid, int threads)
 {
-    for (int idx = tid; idx < 4 * waves * W; idx += threads) {
-        const int g = idx / W, w = idx - g * W;
+    const int items = 4 * waves * W;
+    uint32_t m[8];
+    int g = 0, w = 0;
+    auto load = [&](int idx) {
+        g = idx / W;
+        w = idx - g * W;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) m[k] = keep_mask[(row0 + min(q0 + g * 8 + k, Lq - 1)) * W + w];   // (past the end: the last row again)
+    };
+    if (tid < items) load(tid);
+    for (int i = tid; i < waves * W; i += threads) s_um[i] = 0u;
+    __syncthreads();
+    for (int idx = tid; idx < items; idx += threads) {
         uint32_t acc = 0u;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) acc |= keep_mask[(row0 + min(q0 + g * 8 + k, Lq - 1)) * W + w];   // (past the end: the last row again)
+        for (int k = 0; k < 8; ++k) acc |= m[k];
         if (q0 + g * 8 < Lq && acc) atomicOr(&s_um[(g >> 2) * W + w], acc);
+        if (idx + threads < items) load(idx + threads);
     }
+    __syncthreads();
 }
 
 // Does a wave whose queries' masks OR to s_um need the block with table entry bi?  (A block that spans more
@@ -277,6 +291,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     __shared__ __align__(16) uint32_t s_tab[SHARED ? 1 : PF_TABS * PF_ROW_WORDS];
     __shared__ uint16_t s_list[SHARED ? 1 : PF_LIST_CAP];   // the fixed blocks this workgroup walks
     __shared__ int s_wc[PF_WAVES], s_act[PF_WAVES];
+    __shared__ int s_info[SHARED ? 1 : 64];                 // table entries of the first listed blocks
     __shared__ uint8_t s_need[SHARED ? 1 : PF_LIST_CAP];    // bit v: wave v has a query that kept a key of the listed block
     __shared__ __align__(16) uint32_t s_mw[SHARED ? 1 : PF_WAVES][NB][64];   // mask words of a wave's queries for the blocks at hand (sparse walk)
     __shared__ int32_t s_idx[SELECT ? pf_select_blocks(PF_WAVES) * PF_BN : 1];   // rows of the share's fixed blocks
@@ -346,84 +361,6 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     const int32_t *binfo = blk_info + (size_t)h * nblk_all;
     const uint32_t *mrow = keep_mask + (row0 + nqc) * W;    // mask row of this lane's query
 
-    // ---- the blocks of this share: fixed blocks (masked form: those in which a query of the workgroup kept a cluster, with the
-    // waves that need them; nobody's blocks are neither fetched nor staged), then user blocks -------------------------------
-    int n_list = (max(nblk_fixed - split, 0) + n_split - 1) / n_split;
-    const bool listed = !SHARED && n_list <= PF_LIST_CAP;
-    if constexpr (SELECT) {
-        pf_share_rows<PF_WAVES>(reinterpret_cast<const int *>(stage), s_idx, n_list, split, n_split, n_fixed, L);
-        __syncthreads();                                    // (the records lie where the tiles will be)
-    }
-    bool sparse = false;
-    if (listed) {
-        uint32_t *s_um = reinterpret_cast<uint32_t *>(stage);             // per wave: OR of the keep masks of its queries
-        static_assert(sizeof(stage) >= PF_WAVES * PF_UMASK_WORDS * 4, "the unions lie where the tiles will be");
-        for (int w = tid; w < PF_WAVES * W; w += PF_THREADS) s_um[w] = 0u;
-        __syncthreads();
-        pf_union_masks(s_um, keep_mask, row0, q0, PF_WAVES, Lq, W, tid, PF_THREADS);
-        __syncthreads();
-        int base = 0, active = 0;                           // blocks listed; (wave, block) pairs with a kept key, of this thread's blocks
-        for (int i0 = 0; i0 < n_list; i0 += PF_THREADS) {   // in order: a ballot per wave, the waves' counts in LDS
-            const int bb = split + (i0 + tid) * n_split;
-            int waves = 0;
-            if (i0 + tid < n_list) {
-                const int bi = binfo[bb];
-                for (int v = 0; v < PF_WAVES; ++v) waves |= (int)pf_block_needed(bi, s_um + v * W, W) << v;
-            }
-            const bool need = waves != 0;
-            active += __popc(waves);
-            const unsigned long long bal = __ballot(need);
-            if (lane == 0) s_wc[wave] = __popcll(bal);
-            __syncthreads();
-            int before = 0, total = 0;
-#pragma unroll
-            for (int w = 0; w < PF_WAVES; ++w) {
-                if (w < wave) before += s_wc[w];
-                total += s_wc[w];
-            }
-            if (need) {
-                const int at = base + before + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
-                s_list[at] = (uint16_t)bb;
-                s_need[at] = (uint8_t)waves;
-            }
-            base += total;
-            __syncthreads();
-        }
-        n_list = __builtin_amdgcn_readfirstlane(base);
-        const int act = (int)wave_sum((float)active);
-        if (lane == 0) s_act[wave] = act;
-        __syncthreads();
-        int all = 0;
-#pragma unroll
-        for (int w = 0; w < PF_WAVES; ++w) all += s_act[w];
-        all = __builtin_amdgcn_readfirstlane(all);
-        sparse = all * PF_SPARSE_DEN < n_list * min(PF_WAVES, (Lq - q0 + 31) >> 5) * PF_SPARSE_NUM;   // (of the waves with queries)
-    }
-    const int half = NB == 4 && sparse ? (n_list + 1) >> 1 : 0;   // (position 2 i + 1 is listed half a list behind position 2 i)
-    const int u_first = (split + n_split - nblk_fixed % n_split) % n_split;   // first user block of the share
-    const int n_mine = n_list + (max(nblk_user - u_first, 0) + n_split - 1) / n_split;
-    // The walk's next entries, one per lane: lane i holds position t_base + i (past the end: the last one again) as block | user
-    // flag << 31, and a fixed block's table entry.  Read with v_readlane, refilled every few dozen blocks: scalar values that
-    // cost one instruction each.
-    int t_base = 0, t_ent = 0, t_info = 0, t_need = 0;
-    auto fill_entries = [&](int base) PF_INLINE {
-        t_base = base;
-        const int i = min(base + lane, n_mine - 1);
-        const bool user = i >= n_list;
-        const int li = half ? (i >> 1) + (i & 1) * half : i;
-        const int blk = user ? u_first + (i - n_list) * n_split : listed ? (int)s_list[li] : split + i * n_split;
-        t_ent = user ? blk | (int)0x80000000 : blk;
-        if (!SHARED) {
-            t_info = binfo[user ? 0 : blk];
-            // (waited for here: left pending, it makes the compiler wait in every block, for the tiles on their way as well)
-            asm volatile("" : "+v"(t_info));
-            t_need = user || !listed ? 0xff : s_need[li];
-        }
-    };
-    auto ent = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_ent, i - t_base); };
-    auto inf = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_info, i - t_base); };
-    constexpr int T_KEEP = 56;                              // entries used of a fill: the loop looks up to seven ahead
-
     // ---- staging -----------------------------------------------------------------------------------------------------------
     // This thread's pieces of a 64-key block: piece i = key i*PF_RP + tid/16 (rows of 256 B), LDS slot tid%16 of that
     // row, i.e. the 16-byte chunk (tid%16) ^ swz(row) of the row in memory; row % 16 = (tid/16) % 16 for every piece.
@@ -454,15 +391,6 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
         }
         return x;
     };
-    auto rows_at = [&](int i) PF_INLINE {                   // of the block at position i
-        if constexpr (SELECT) {
-            Rows x{};
-#pragma unroll
-            for (int k = 0; k < PF_NP; ++k) x.r[k] = s_idx[min(i, max(n_list - 1, 0)) * PF_BN + k * PF_RP + trow];
-            return x;
-        } else
-            return rows_of(ent(i));
-    };
     typedef __attribute__((address_space(3))) void *lptr_t;
     auto lds_at = [&](const void *p) PF_INLINE { return __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t)p); };
     // Written as instructions: through the builtin the compiler may make a read of the CURRENT buffer wait for these
@@ -477,6 +405,112 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     };
     constexpr uint32_t V_AT = NB * PF_TILE;                 // byte offset of the V tiles
     auto loads_landed = [&]() PF_INLINE { __builtin_amdgcn_s_waitcnt(0x0f70); };   // vmcnt(0)
+
+    // ---- the blocks of this share: fixed blocks (masked form: those in which a query of the workgroup kept a cluster, with the
+    // waves that need them; nobody's blocks are neither fetched nor staged), then user blocks -------------------------------
+    int n_list = (max(nblk_fixed - split, 0) + n_split - 1) / n_split;
+    const bool listed = !SHARED && n_list <= PF_LIST_CAP;
+    // Masked form: the first blocks of the share are rarely left out, so their tiles are requested before the list is known: they land
+    // with the masks instead of a round trip after the list.  With that, the blocks' table entries requested in front of the unions and
+    // the first ones kept beside the list, whole steps, us: 16 heads x 200 tokens x 5000 keys 40.2 -> 39.1, 32 x 40 x 8000 42.5 -> 41.8,
+    // 4 x 100 x 16000 32.7 -> 31.8, 32 x 1024 x 32768 the same.
+    const bool ahead = !SHARED && n_list >= LK;
+    if (ahead)
+#pragma unroll
+        for (int b = 0; b < LK; ++b) {
+            const Aim aim = aim_at(split + b * n_split);
+#pragma unroll
+            for (int i = 0; i < PF_NP; ++i) {
+                fetch_piece(i, aim.k, aim.end, false, Rows{}, k_at, k_ch, b * PF_TILE);
+                if (b < LV) fetch_piece(i, aim.v, aim.end, false, Rows{}, v_at, v_ch, V_AT + b * PF_TILE);
+            }
+        }
+    if constexpr (SELECT) {
+        pf_share_rows<PF_WAVES>(reinterpret_cast<const int *>(stage), s_idx, n_list, split, n_split, n_fixed, L);
+        __syncthreads();                                    // (the records lie where the tiles will be)
+    }
+    bool sparse = false;
+    if (listed) {
+        // per wave: OR of the keep masks of its queries, in a tile that the first fetches leave alone
+        uint32_t *s_um = reinterpret_cast<uint32_t *>(stage + (NB == 4 ? LK * PF_TILE : V_AT + LV * PF_TILE));
+        static_assert(NB == 4 ? LK < NB : LV < NB, "");
+        static_assert(PF_TILE >= PF_WAVES * PF_UMASK_WORDS * 4, "the unions fit a tile");
+        int bi = tid < n_list ? binfo[split + tid * n_split] : 0;   // (requested in front of the unions' round trip)
+        pf_union_masks(s_um, keep_mask, row0, q0, PF_WAVES, Lq, W, tid, PF_THREADS);
+        int base = 0, active = 0;                           // blocks listed; (wave, block) pairs with a kept key, of this thread's blocks
+        for (int i0 = 0; i0 < n_list; i0 += PF_THREADS) {   // in order: a ballot per wave, the waves' counts in LDS
+            const int bb = split + (i0 + tid) * n_split;
+            int waves = 0;
+            if (i0 > 0) bi = i0 + tid < n_list ? binfo[bb] : 0;
+            if (i0 + tid < n_list) {
+                for (int v = 0; v < PF_WAVES; ++v) waves |= (int)pf_block_needed(bi, s_um + v * W, W) << v;
+            }
+            const bool need = waves != 0;
+            active += __popc(waves);
+            const unsigned long long bal = __ballot(need);
+            if (lane == 0) s_wc[wave] = __popcll(bal);
+            __syncthreads();
+            int before = 0, total = 0;
+#pragma unroll
+            for (int w = 0; w < PF_WAVES; ++w) {
+                if (w < wave) before += s_wc[w];
+                total += s_wc[w];
+            }
+            if (need) {
+                const int at = base + before + __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0));
+                s_list[at] = (uint16_t)bb;
+                s_need[at] = (uint8_t)waves;
+                if (at < 64) s_info[at] = bi;
+            }
+            base += total;
+            __syncthreads();
+        }
+        n_list = __builtin_amdgcn_readfirstlane(base);
+        const int act = (int)wave_sum((float)active);
+        if (lane == 0) s_act[wave] = act;
+        __syncthreads();
+        int all = 0;
+#pragma unroll
+        for (int w = 0; w < PF_WAVES; ++w) all += s_act[w];
+        all = __builtin_amdgcn_readfirstlane(all);
+        sparse = all * PF_SPARSE_DEN < n_list * min(PF_WAVES, (Lq - q0 + 31) >> 5) * PF_SPARSE_NUM;   // (of the waves with queries)
+    }
+    const int half = NB == 4 && sparse ? (n_list + 1) >> 1 : 0;   // (position 2 i + 1 is listed half a list behind position 2 i)
+    const int u_first = (split + n_split - nblk_fixed % n_split) % n_split;   // first user block of the share
+    const int n_mine = n_list + (max(nblk_user - u_first, 0) + n_split - 1) / n_split;
+    // The walk's next entries, one per lane: lane i holds position t_base + i (past the end: the last one again) as block | user
+    // flag << 31, and a fixed block's table entry.  Read with v_readlane, refilled every few dozen blocks: scalar values that
+    // cost one instruction each.
+    int t_base = 0, t_ent = 0, t_info = 0, t_need = 0;
+    auto fill_entries = [&](int base) PF_INLINE {
+        t_base = base;
+        const int i = min(base + lane, n_mine - 1);
+        const bool user = i >= n_list;
+        const int li = half ? (i >> 1) + (i & 1) * half : i;
+        const int blk = user ? u_first + (i - n_list) * n_split : listed ? (int)s_list[li] : split + i * n_split;
+        t_ent = user ? blk | (int)0x80000000 : blk;
+        if (!SHARED) {
+            // (the first entries' from LDS, behind the list; a user block's is not looked at)
+            if (base == 0 && listed && !half) t_info = user ? 0 : s_info[li & 63];
+            else t_info = binfo[user ? 0 : blk];
+            // (waited for here: left pending, it makes the compiler wait in every block, for the tiles on their way as well)
+            asm volatile("" : "+v"(t_info));
+            t_need = user || !listed ? 0xff : s_need[li];
+        }
+    };
+    auto ent = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_ent, i - t_base); };
+    auto inf = [&](int i) PF_INLINE { return __builtin_amdgcn_readlane(t_info, i - t_base); };
+    constexpr int T_KEEP = 56;                              // entries used of a fill: the loop looks up to seven ahead
+
+    auto rows_at = [&](int i) PF_INLINE {                   // of the block at position i
+        if constexpr (SELECT) {
+            Rows x{};
+#pragma unroll
+            for (int k = 0; k < PF_NP; ++k) x.r[k] = s_idx[min(i, max(n_list - 1, 0)) * PF_BN + k * PF_RP + trow];
+            return x;
+        } else
+            return rows_of(ent(i));
+    };
 
     // Masked form: what decides the visible keys travels ahead of the block: its table row to LDS (one wave fetches it), and
     // the two mask words of this lane's query that hold the block's window of clusters (loaded when the window moves to
@@ -635,6 +669,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
             fetch_tab(pos, e);
             if (needed(pos)) fetch_window(pos, tile);
         };
+        if (ahead) loads_landed();                          // (the same tiles are fetched, of other blocks)
         fetch_at(0, std::integral_constant<int, 0>{});
         if (NB == 4) fetch_at(1, std::integral_constant<int, 1>{});
         loads_landed();
@@ -711,10 +746,15 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
         };
         Aim aim_v{};                                        // of block it + LV (computed with its K, one iteration before)
         Rows rv = rows_at(LV), rk = rows_at(LK), rk1 = rows_at(LK + 1);   // blocks it + LV, it + LK, it + LK + 1
+        bool there = ahead;                                 // are the tiles that were requested those of the list's first blocks?
+#pragma unroll
+        for (int b = 0; b < LK; ++b) there = there && ent(b) == split + b * n_split;
+        if (ahead && !there) loads_landed();
 #pragma unroll
         for (int b = 0; b < LK; ++b) {
             const int e = ent(b);
             aim_v = aim_at(e);
+            if (there) continue;                            // (uniform)
             const Rows r = rows_at(b);
 #pragma unroll
             for (int i = 0; i < PF_NP; ++i) {
@@ -873,7 +913,8 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
             if (it > 0 && wave_on) any_nxt = start_scores(s_nxt, it + 1, uint2{0u, 0u});
         }
         for (; it < n_mine; it += NB) walks(std::true_type{});
-    }
+    } else if (ahead)
+        loads_landed();                                     // (nothing may be on its way to LDS behind the end)
 
     // ---- values that are not finite ------------------------------------------------------------------------------------------
     // The products of a block multiply the values of keys that a query does not see (and of rows past the end of a tensor) by 0,
