@@ -163,7 +163,8 @@ int sq_sparse_attn_prefill(const sq_shape_t *shape, const void *q, const void *K
 
 /*
  * How the prefill attention of a shape is divided: every workgroup has *waves (8 or 4) waves of 32 query tokens, and the key
- * blocks of its (sequence, head, group of tokens) are shared by *splits workgroups.  one_set != 0: the calls with one kept set
+ * blocks of its (sequence, head, group of tokens) are shared by *splits workgroups (with one kept set, a long context and few
+ * groups: on average, in proportion to the kept keys).  one_set != 0: the calls with one kept set
  * per (sequence, head) (sq_sparse_attn_prefill_shared and the steps on averaged scores); 0: per-query selection.  Host only;
  * results do not depend on it beyond the order of summation.
  */
