@@ -34,7 +34,8 @@
 // head) attend to ONE kept set.  The kept ranges are expanded into a list of key rows (the key-index tensor of
 // Section 4.2); the kernel walks that list 64 keys at a time, gathering K and V rows by index (the indices travel in
 // registers ahead of the rows), with no per-query masks: only the tail of the last block and the causal user keys are
-// hidden, so every executed tile is useful work.
+// hidden, so every executed tile is useful work.  The step on averaged scores makes the list of a share here (SELECT): where
+// prefill_selects() the launch in front that would make it for all of them is left out.
 #include <algorithm>
 #include <type_traits>
 #include <utility>
