@@ -1070,8 +1070,8 @@ int sq_prefill_mean_step(const sq_shape_t *sh, const void *q, const void *centro
     SQ_HIP(sq::launch_prefill_lookup(q, centroids, sizes, thresh, w.stats, nullptr, nullptr, w.part_sum, true, sh->B,
                                      sh->H, sh->Lq, sh->C, sh->sm_scale, s));
     const int parts = sq::lookup_parts(rows, sh->Lq, sh->C);
-    if (sq::prefill_selects(to_shape(sh))) {
-        const sq::PfSelect sel{w.part_sum, parts, thresh, sizes, offsets, keep_mask, n_keys};
+    if (sq::prefill_selects(to_shape(sh), false)) {
+        const sq::PfSelect sel{w.part_sum, parts, thresh, sizes, offsets, keep_mask, n_keys, nullptr, nullptr, rows};
         SQ_HIP(sq::launch_prefill_attn_select(q, K_fixed, V_fixed, K_user, V_user, sel, w.att.partials, out, lse, to_shape(sh), s));
     } else {
         SQ_HIP(sq::launch_mean_select(w.part_sum, parts, sh->Lq, thresh, sizes, offsets, nullptr, nullptr, false, keep_mask, n_keys,
@@ -1389,7 +1389,7 @@ int sq_hier_prefill_mean_step(const sq_shape_t *sh, int32_t C1, const void *q, c
     SQ_HIP(sq::launch_prefill_lookup(q, centroids1, sizes1, thresh1, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
                                      sh->B, sh->H, sh->Lq, C1, sh->sm_scale, s));
     const int parts1 = sq::lookup_parts(rows, sh->Lq, C1);
-    const sq::PfSelect coarse{w.step.part_sum, parts1, thresh1, sizes1, child_offsets, nullptr, nullptr};
+    const sq::PfSelect coarse{w.step.part_sum, parts1, thresh1, sizes1, child_offsets, nullptr, nullptr, nullptr, nullptr, rows};
     const bool children = sq::lookup_selects_children(rows, sh->Lq, sh->C, C1);
     if (!children)
         SQ_HIP(sq::launch_mean_select(w.step.part_sum, parts1, sh->Lq, thresh1, sizes1, child_offsets, nullptr, nullptr, true, nullptr,
@@ -1398,12 +1398,16 @@ int sq_hier_prefill_mean_step(const sq_shape_t *sh, int32_t C1, const void *q, c
     SQ_HIP(sq::launch_prefill_lookup(q, centroids2, sizes2, thresh2, w.step.stats, nullptr, nullptr, w.step.part_sum, true,
                                      sh->B, sh->H, sh->Lq, sh->C, sh->sm_scale, s, w.cand_id, w.cand_hdr, nullptr, nullptr, C1,
                                      nullptr, children ? &coarse : nullptr));
-    SQ_HIP(sq::launch_mean_select(w.step.part_sum, 0, sh->Lq, thresh2, sizes2,
-                                  offsets2, w.cand_id, w.cand_hdr, false, keep_mask2, n_keys, w.step.att.hdr,
-                                  w.step.att.key_idx, sh->L, rows, sh->H, sh->C, s));
     const PrefillSharedWs &att = w.step.att;
-    SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, att.hdr, att.key_idx, att.partials, out, lse,
-                                          to_shape(sh), s));
+    if (sq::prefill_selects(to_shape(sh), true)) {
+        const sq::PfSelect sel{w.step.part_sum, 0, thresh2, sizes2, offsets2, keep_mask2, n_keys, w.cand_id, w.cand_hdr, rows};
+        SQ_HIP(sq::launch_prefill_attn_select(q, K_fixed, V_fixed, K_user, V_user, sel, att.partials, out, lse, to_shape(sh), s));
+    } else {
+        SQ_HIP(sq::launch_mean_select(w.step.part_sum, 0, sh->Lq, thresh2, sizes2, offsets2, w.cand_id, w.cand_hdr, false, keep_mask2,
+                                      n_keys, att.hdr, att.key_idx, sh->L, rows, sh->H, sh->C, s));
+        SQ_HIP(sq::launch_prefill_attn_shared(q, K_fixed, V_fixed, K_user, V_user, att.hdr, att.key_idx, att.partials, out, lse,
+                                              to_shape(sh), s));
+    }
     g_err[0] = 0;
     return SQ_OK;
 }

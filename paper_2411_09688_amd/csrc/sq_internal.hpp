@@ -207,7 +207,7 @@ hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void 
 
 // The same with the kept set made by the attention launch itself, where prefill_selects(): part_sum [B*H, parts, C] are the parts of
 // the clusters' scores summed over the tokens (see launch_mean_select, which makes the same decisions).
-constexpr int PF_SELECT_MAX_C = 2048;
+constexpr int pf_select_max_c(int waves, bool candidates) { return candidates && waves == 8 ? 4096 : 2048; }
 constexpr int pf_select_blocks(int waves) { return waves == 8 ? 256 : 48; }   // fixed blocks of a share, at most: their rows lie in LDS
 struct PfSelect {
     const float *part_sum;
@@ -216,8 +216,11 @@ struct PfSelect {
     const int32_t *sizes, *offsets;
     uint32_t *keep_mask;                   // outputs, either may be null
     int32_t *n_keys;
+    const int32_t *cand_id;                // candidates (may be null): see launch_mean_select; parts is not used
+    const int2 *cand_hdr;
+    int rows;                              // B * H
 };
-bool prefill_selects(const Shape &sh);
+bool prefill_selects(const Shape &sh, bool candidates);
 hipError_t launch_prefill_attn_select(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                       const PfSelect &sel, float *partials, void *out, float *lse, const Shape &sh, hipStream_t s);
 

@@ -254,16 +254,16 @@ __device__ __forceinline__ PfDealt pf_deal(const PfDeal &deal, int piece, const 
 // together) and three barriers, about 3 us of the launch's prologue; the rows' searches run in parallel, a few per thread.
 // Rows of the keys of a share's n_list fixed blocks, split, split + n_split, ... of the list of kept keys: every key finds its cluster
 // among the records of mean_row_select.  (Behind the last key: that key again.)
-template <int PF_WAVES>
+template <int PF_WAVES, int MAX_C>
 __device__ __forceinline__ void pf_share_rows(const int *s, int32_t *s_idx, int n_list, int split, int n_split, int n_fixed, int L)
 {
-    const int *s_pos = s, *s_first = s + PF_SELECT_MAX_C;
-    const int kept = s[2 * PF_SELECT_MAX_C];
+    const int *s_pos = s, *s_first = s + MAX_C;
+    const int kept = s[2 * MAX_C];
     for (int i = threadIdx.x; i < n_list * PF_BN; i += 64 * PF_WAVES) {
         const int j = min((split + (i >> 6) * n_split) * PF_BN + (i & 63), n_fixed - 1);
         int c = 0;
 #pragma unroll
-        for (int step = PF_SELECT_MAX_C / 2; step > 0; step >>= 1)
+        for (int step = MAX_C / 2; step > 0; step >>= 1)
             if (c + step < kept && s_pos[c + step] <= j) c += step;
         s_idx[i] = min(max(s_first[c] + j - s_pos[c], 0), L - 1);   // (malformed offsets stay in the tensor)
     }
@@ -273,8 +273,9 @@ __device__ __forceinline__ void pf_share_rows(const int *s, int32_t *s_idx, int 
 // used.  Otherwise table / rows / blk_info are the block table (block_table_kernel).
 // SELECT (with SHARED): the kept set is made here, from the parts of the averaged scores (what mean_select_kernel does in a launch of
 // its own otherwise): every workgroup adds up its head's scores and decides all of its clusters, and the rows of its share's keys go to
-// a list in LDS.  The (sequence, head)'s first workgroup writes the mask and the count.
-template <bool SHARED, int PF_WAVES, bool SELECT>
+// a list in LDS.  The (sequence, head)'s first workgroup writes the mask and the count.  SELECTS: 1 of all clusters, 2 of the row's
+// candidates, 0 not.
+template <bool SHARED, int PF_WAVES, int SELECTS>
 __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kernel(
     const _Float16 *__restrict__ q, const _Float16 *__restrict__ Kf, const _Float16 *__restrict__ Vf,
     const _Float16 *__restrict__ Ku, const _Float16 *__restrict__ Vu, const uint32_t *__restrict__ keep_mask,
@@ -282,7 +283,9 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     _Float16 *__restrict__ out, float *__restrict__ lse, float *__restrict__ partials, int n_split, int B, int H, int L,
     int C, int Lq, int U, int causal_user, float sm_scale, PfSelect sel, PfDeal deal)
 {
+    constexpr bool SELECT = SELECTS != 0;
     static_assert(SHARED || !SELECT, "one kept set");
+    constexpr int SEL_C = pf_select_max_c(PF_WAVES, SELECTS == 2);
     constexpr int PF_BM = pf_bm(PF_WAVES), PF_THREADS = 64 * PF_WAVES;
     constexpr int PF_RP = PF_THREADS / 16;                  // rows of a key block the workgroup moves per pass (16 lanes per row)
     constexpr int PF_NP = PF_BN / PF_RP;                    // passes per block
@@ -350,7 +353,8 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     // keys of the fixed context this (sequence, head) walks: all of them, or the kept ones through the row list
     int n_fixed = L;
     if constexpr (SELECT)
-        n_fixed = min(mean_row_select<PF_WAVES, PF_SELECT_MAX_C, false>(sel, (size_t)b * H + h, h, C, Lq, unit % nqb == 0 && split == 0, reinterpret_cast<int *>(stage)), L);
+        n_fixed = min(mean_row_select<PF_WAVES, SEL_C, false, SELECTS == 2>(sel, (size_t)b * H + h, h, C, Lq, unit % nqb == 0 && split == 0,
+                                                                            reinterpret_cast<int *>(stage)), L);
     else if constexpr (SHARED)
         n_fixed = min(blk_info[2 * ((size_t)b * H + h) + 1], L);
     const int32_t *idx_bh = reinterpret_cast<const int32_t *>(table) + ((size_t)b * H + h) * (size_t)L;   // SHARED without SELECT only
@@ -427,7 +431,8 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
             }
         }
     if constexpr (SELECT) {
-        pf_share_rows<PF_WAVES>(reinterpret_cast<const int *>(stage), s_idx, n_list, split, n_split, n_fixed, L);
+        static_assert(sizeof(stage) >= mean_row_cand_words(SEL_C) * sizeof(int), "the records lie where the tiles will be");
+        pf_share_rows<PF_WAVES, SEL_C>(reinterpret_cast<const int *>(stage), s_idx, n_list, split, n_split, n_fixed, L);
         __syncthreads();                                    // (the records lie where the tiles will be)
     }
     bool sparse = false;
@@ -1137,7 +1142,7 @@ PfDeal prefill_deal(const Shape &sh, float *ws)
 
 namespace {
 
-template <bool SHARED, int WAVES, bool SELECT>
+template <bool SHARED, int WAVES, int SELECT>
 hipError_t launch_prefill_kernel(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                  const uint32_t *keep_mask, const uint32_t *table, const uint32_t *rows,
                                  const int32_t *blk_info, void *out, float *lse, float *partials, int n_split,
@@ -1161,7 +1166,7 @@ hipError_t launch_prefill_kernel(const void *q, const void *Kf, const void *Vf, 
 }
 
 // The attention launch and, where the blocks are split, the merge launch.
-template <bool SHARED, bool SELECT>
+template <bool SHARED, int SELECT>
 hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                   const uint32_t *keep_mask, const uint32_t *table, const uint32_t *rows,
                                   const int32_t *blk_info, void *out, float *lse, float *partials, const PfSelect &sel,
@@ -1218,7 +1223,7 @@ hipError_t launch_prefill_attn(const void *q, const void *Kf, const void *Vf, co
                                const uint32_t *keep_mask, const BlockTable &bt, float *partials, void *out, float *lse,
                                const Shape &sh, hipStream_t s)
 {
-    return launch_prefill_kernels<false, false>(q, Kf, Vf, Ku, Vu, keep_mask, bt.runs, bt.rows, bt.info, out, lse, partials, PfSelect{}, sh, s);
+    return launch_prefill_kernels<false, 0>(q, Kf, Vf, Ku, Vu, keep_mask, bt.runs, bt.rows, bt.info, out, lse, partials, PfSelect{}, sh, s);
 }
 
 hipError_t launch_expand_ranges(DecodePlan plan, int32_t *idx, int rows, int L, hipStream_t s)
@@ -1234,7 +1239,7 @@ hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void 
                                       const int2 *hdr, const int32_t *key_idx, float *partials, void *out, float *lse,
                                       const Shape &sh, hipStream_t s)
 {
-    return launch_prefill_kernels<true, false>(q, Kf, Vf, Ku, Vu, nullptr, reinterpret_cast<const uint32_t *>(key_idx), nullptr,
+    return launch_prefill_kernels<true, 0>(q, Kf, Vf, Ku, Vu, nullptr, reinterpret_cast<const uint32_t *>(key_idx), nullptr,
                                                reinterpret_cast<const int32_t *>(hdr), out, lse, partials, PfSelect{}, sh, s);
 }
 
@@ -1245,18 +1250,26 @@ hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void 
 //    1 x 1024 x 32768, 1638  41.4 / 37.3     1 x 16 x 2000, 40  19.4 / 15.7     4 x 1024 x 8000, 400  43.4 / 39.5
 //   2 x 32 x 500 x 20000, 500  127.9 / 124.9    32 x 16 x 32768, 1024  75.0 / 71.3    20 x 17 x 30000, 1500  49.8 / 47.9
 // Eight waves: 64 KB of rows beside 66 KB of tiles, one workgroup per compute unit as before; four: 12 KB, still two.
-bool prefill_selects(const Shape &sh)
+// A row's candidates: the same, up to 4096 clusters a head with eight waves (with four that many spill 61 registers) and not where the
+// shares are dealt in proportion (their lengths come from the list in front).  Both-level steps, a launch of its own / here:
+//   8 x 512 x 65536 3000  69.9 / 65.4    8 x 512 x 90000 4096  60.0 / 55.0    4 x 300 x 100000 4000  55.6 / 52.2    4 x 512 x 40000 1500  51.5 / 46.6
+//   8 x 16 x 32768 2048  36.2 / 31.1    2 x 40 x 60000 2000  36.0 / 31.1    1 x 100 x 33000 700  35.2 / 30.8    1 x 3 x 130000 4096  40.5 / 37.8
+bool prefill_selects(const Shape &sh, bool candidates)
 {
     const PfPlan plan = prefill_plan(true, sh);
     const long long blocks = ((long long)sh.L + PF_BN - 1) / PF_BN;
-    return sh.C <= PF_SELECT_MAX_C && (blocks + plan.n_split - 1) / plan.n_split <= pf_select_blocks(plan.waves);
+    if (candidates && prefill_deal(sh, nullptr).units) return false;
+    return sh.C <= pf_select_max_c(plan.waves, candidates) && (blocks + plan.n_split - 1) / plan.n_split <= pf_select_blocks(plan.waves);
 }
 
 hipError_t launch_prefill_attn_select(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,
                                       const PfSelect &sel, float *partials, void *out, float *lse, const Shape &sh, hipStream_t s)
 {
-    if (!prefill_selects(sh)) return hipErrorInvalidValue;
-    return launch_prefill_kernels<true, true>(q, Kf, Vf, Ku, Vu, nullptr, nullptr, nullptr, nullptr, out, lse, partials, sel, sh, s);
+    if (!prefill_selects(sh, sel.cand_id != nullptr)) return hipErrorInvalidValue;
+    auto launch = [&](auto selects) {
+        return launch_prefill_kernels<true, selects>(q, Kf, Vf, Ku, Vu, nullptr, nullptr, nullptr, nullptr, out, lse, partials, sel, sh, s);
+    };
+    return sel.cand_id ? launch(std::integral_constant<int, 2>{}) : launch(std::integral_constant<int, 1>{});
 }
 
 }  // namespace sq

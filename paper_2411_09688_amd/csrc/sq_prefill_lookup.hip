@@ -121,7 +121,7 @@ __global__ __launch_bounds__(256) void lookup_pass_kernel(
     int n_cand = 0;
     if constexpr (CHILDREN) {
         static_assert(sizeof(stage) >= mean_row_words(LK_COARSE_MAX) * sizeof(int), "the records lie where the centroids will be");
-        n_cand = mean_row_select<4, LK_COARSE_MAX, true>(coarse, bh, h, C1, Lq, false, reinterpret_cast<int *>(stage));
+        n_cand = mean_row_select<4, LK_COARSE_MAX, true, false>(coarse, bh, h, C1, Lq, false, reinterpret_cast<int *>(stage));
     } else if constexpr (CANDS)
         n_cand = cand_hdr[bh].y;
     const int C = CANDS ? min(n_cand, C_all) : C_all;

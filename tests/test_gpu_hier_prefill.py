@@ -215,6 +215,30 @@ def test_hier_prefill_mean_long_context_shape(sq, oracle):
     assert 0 < gk.sum()
 
 
+# The fine selection made by the attention launch itself, of the candidates (2048 clusters a head where it runs four waves, 4096 where
+# eight), or by a launch in front of it; some shapes with one share a unit, some with more.
+OWN_CASES = [
+    dict(B=64, H=5, L=3000, C=2048, C1=40, Lq=70),     # four waves, as many clusters as they take
+    dict(B=64, H=5, L=3000, C=2049, C1=40, Lq=70),     # and one more
+    dict(B=2, H=8, L=6000, C=4096, C1=64, Lq=300),     # eight waves, the same
+    dict(B=2, H=8, L=6000, C=4097, C1=64, Lq=300),
+    dict(B=1, H=1, L=5000, C=257, C1=16, Lq=1),        # one key in a group of its own; short shares
+]
+
+
+@pytest.mark.parametrize("first", ["all", "some", "none"])
+@pytest.mark.parametrize("case", OWN_CASES, ids=lambda c: "B{B}H{H}C{C}Lq{Lq}".format(**c))
+def test_fine_selection_inside_the_attention(sq, oracle, case, first):
+    w = wl.make_workload("hier_prefill_own", seed=39, threads=4, U=7, keep_frac=0.3, coarse_keep_frac=0.4, causal_user=False,
+                         variable_fanout=True, **case)
+    T1, T2 = thresholds(w)
+    if first != "some":
+        T1 = np.full(w.H, -1.0 if first == "all" else 2.0, np.float32)   # (an average of probabilities lies in [0, 1])
+    sample = min(80, w.B * w.H * w.Lq)
+    gk, _ = compare(oracle, w, T1, T2, run(sq, w, T1, T2), f"own selection {case} {first}", sample=sample)
+    assert (gk.sum() == 0) == (first == "none") and gk.sum() < w.B * w.H * w.C
+
+
 # ---- per-query selection through the hierarchy (sq_hier_prefill_step) -----------------------------------------------
 
 def run_per_query(sq, w, T1, T2, optional=True):
