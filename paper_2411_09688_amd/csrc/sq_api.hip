@@ -231,15 +231,16 @@ struct SharedStepWs {
     uint32_t *mask;
     sq::DecodePlan plan;
     float *partials;
-    int user_slot_base;
+    int user_slot_base, nuq;  // nuq: partial results of user keys per row, 0 where the work items hold the user keys
 };
 
-// G: query rows per (sequence, head) that share the head's K/V (1, or the group size of grouped-query attention).
-SharedStepWs carve_step_shared(Carver &cv, const sq_shape_t *sh, int G = 1)
+// G: query rows per (sequence, head) that share the head's K/V (1, or the group size of grouped-query attention).  user_pieces: the
+// user keys are attended to beside the selection, in pieces, and the work items hold none of them.
+SharedStepWs carve_step_shared(Carver &cv, const sq_shape_t *sh, int G, bool user_pieces)
 {
     const size_t rows = (size_t)sh->B * sh->H * G;
     const size_t urows = (size_t)sq::seq_groups_for(sh->B * G) * sh->H;
-    const size_t items = urows * ((size_t)sq::SG * sq::user_chunks_for(sh->U) + sq::chunk_cap_for(sh->L));
+    const size_t items = urows * ((user_pieces ? 0 : (size_t)sq::SG * sq::user_chunks_for(sh->U)) + sq::chunk_cap_for(sh->L));
     SharedStepWs w{};
     w.logits = cv.take<float>(rows * sh->C);
     w.n_ranges = cv.take<int32_t>(rows);
@@ -255,7 +256,8 @@ SharedStepWs carve_step_shared(Carver &cv, const sq_shape_t *sh, int G = 1)
     w.plan.total = cv.take<int>(2);
     w.plan.item = cv.take<int2>(items * sq::ITEM_STRIDE);
     w.user_slot_base = (int)((sq::SHARED_ATTN_GRID + urows) * sq::SG);
-    w.partials = cv.take<float>((w.user_slot_base + rows * (size_t)sq::user_pieces_for(sh->U)) * sq::PART_STRIDE);
+    w.nuq = user_pieces ? sq::user_pieces_for(sh->U) : 0;
+    w.partials = cv.take<float>((w.user_slot_base + rows * (size_t)w.nuq) * sq::PART_STRIDE);
     return w;
 }
 
@@ -287,6 +289,17 @@ bool step_is_shared(const sq_shape_t *sh, int G = 1)
 {
     if (sh->B * G < SHARED_MIN_ROWS) return false;
     return !step_is_indexed(sh, G) || (long long)sh->B * sh->H * G * ((long long)sh->L + sh->U) > SHARED_MIN_KEYS;
+}
+
+// User keys beside the selection: with one query row per K/V head and sequence (with more, every row would read them again), unless
+// the built-in buffer of sq_decode_step_noalloc holds the step with work items alone (16 sequences' pieces are up to 1.5 % larger).
+bool shared_step_has_pieces(const sq_shape_t *sh, int G)
+{
+    if (G != 1) return false;
+    Carver pieces(nullptr), items(nullptr);
+    carve_step_shared(pieces, sh, G, true);
+    carve_step_shared(items, sh, G, false);
+    return pieces.off <= SQ_NOALLOC_SCRATCH_BYTES || items.off > SQ_NOALLOC_SCRATCH_BYTES;
 }
 
 // Workspace of the two-level lookup.  C1 <= C2 is not known to sq_workspace_bytes, so level-1 buffers
@@ -565,7 +578,7 @@ size_t sq_workspace_bytes(const sq_shape_t *sh, int which)
         carve_decode(cv, sh);
         return cv.off;
     case SQ_CALL_DECODE_STEP:
-        if (sh->B >= SHARED_MIN_ROWS) carve_step_shared(cv, sh);   // (the per-row kernels below the line need less)
+        if (step_is_shared(sh)) carve_step_shared(cv, sh, 1, shared_step_has_pieces(sh, 1));
         else if (step_is_indexed(sh)) {
             Carver cv2(nullptr);
             carve_step_small(cv2, sh);
@@ -586,13 +599,15 @@ size_t sq_workspace_bytes(const sq_shape_t *sh, int which)
         carve_prefill_step(cv, sh);
         return cv.off;
     case SQ_CALL_GQA_DECODE_STEP: {                     // sized for the largest group (16 query heads per K/V head)
-        carve_step_shared(cv, sh, sq::SG);
+        carve_step_shared(cv, sh, sq::SG, false);
         Carver cv2(nullptr), cv3(nullptr);              // ... on any of the kernel families
         carve_step(cv2, sh, sq::SG);
         carve_step_index(cv3, sh, sq::SG);
         Carver cv4(nullptr);                            // (small rows: DS_GRID partials at most, whatever the group)
         cv4.take<float>((size_t)sq::DS_GRID * sq::PART_STRIDE);
-        return std::max(std::max(cv.off, cv2.off), std::max(cv3.off, cv4.off));
+        Carver cv5(nullptr);                            // (a group of one may have its user keys in pieces)
+        carve_step_shared(cv5, sh, 1, shared_step_has_pieces(sh, 1));
+        return std::max({cv.off, cv2.off, cv3.off, cv4.off, cv5.off});
     }
     case SQ_CALL_MULTILEVEL_SELECT:
         carve_hier(cv, sh);
@@ -609,7 +624,7 @@ size_t sq_workspace_bytes(const sq_shape_t *sh, int which)
         carve_hier_prefill(cv, sh);
         return cv.off;
     case SQ_CALL_GQA_MEAN_DECODE_STEP:                // sized for the largest group
-        carve_step_shared(cv, sh, sq::SG);
+        carve_step_shared(cv, sh, sq::SG, false);
         return cv.off;
     case SQ_CALL_HIER_PREFILL_MEAN_STEP:
         carve_hier_prefill_mean(cv, sh);
@@ -711,12 +726,11 @@ int decode_step_shared(const sq_shape_t *sh, int G, const void *q, const void *c
                        const void *K_user, const void *V_user, void *out, float *lse, uint32_t *keep_mask,
                        int32_t *n_keys, Carver &cv, hipStream_t s)
 {
-    SharedStepWs w = carve_step_shared(cv, sh, G);
+    SharedStepWs w = carve_step_shared(cv, sh, G, shared_step_has_pieces(sh, G));
     uint32_t *mask = keep_mask ? keep_mask : w.mask;
     // the G query heads of a (sequence, K/V head) are G query rows of that head: logits [B, H, G, C]
     SQ_HIP(sq::launch_score(q, centroids, w.logits, w.plan.total, sh->B, sh->H, G, sh->C, sh->sm_scale, s));
-    const sq::UserAttn ua = G == 1 ? make_user_pieces(sh, G, q, K_user, V_user, w.partials, w.user_slot_base, sq::user_pieces_for(sh->U))
-                                   : sq::UserAttn{};
+    const sq::UserAttn ua = w.nuq ? make_user_pieces(sh, G, q, K_user, V_user, w.partials, w.user_slot_base, w.nuq) : sq::UserAttn{};
     SQ_HIP(sq::launch_union_schedule(w.logits, thresh, sizes, offsets, mask, w.n_ranges, n_keys ? n_keys : w.n_keys,
                                      w.plan, ua.q ? 0 : sh->U, sh->B, G, sh->H, sh->C, s, &ua));
     sq::Shape shp = to_shape(sh);
@@ -849,7 +863,7 @@ int sq_gqa_mean_decode_step(const sq_shape_t *sh, int32_t G, const void *q, cons
     if (int rc = check_device(__func__)) return rc;
     Carver cv(ws);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    SharedStepWs w = carve_step_shared(cv, sh, G);
+    SharedStepWs w = carve_step_shared(cv, sh, G, false);
     SQ_HIP(sq::launch_score(q, centroids, w.logits, w.plan.total, sh->B, sh->H, G, sh->C, sh->sm_scale, s));
     SQ_HIP(sq::launch_group_mean_logits(w.logits, sizes, sh->B * sh->H, sh->H, G, sh->C, s));
     // The G rows of a group now select the same clusters: the union of a group of 16 rows streams each kept key once.

@@ -182,7 +182,7 @@ hipError_t launch_decode_attn(const void *q, const void *Kf, const void *Vf, con
 
 // Shared-context decode: per-sequence selection (keep_masks, n_ranges, n_keys: [B*H] rows) and the work items of
 // every union row in one launch (needs the two counters at plan.total zeroed), and the partial + merge kernels.  partials: (SHARED_ATTN_GRID + union
-// rows) * SG slots of PART_STRIDE floats.
+// rows) * SG slots of PART_STRIDE floats, then nuq slots per row where the user keys are attended to beside the selection.
 hipError_t launch_union_schedule(const float *logits, const float *thresh, const int32_t *sizes,
                                  const int32_t *offsets, uint32_t *keep_masks, int32_t *n_ranges, int32_t *n_keys,
                                  DecodePlan plan, int U, int B, int G, int H, int C, hipStream_t s,

@@ -69,6 +69,27 @@ def test_prefill_workspace_is_bounded(sq, H, L, Lq):
     assert table <= sq.workspace_bytes(sh, sq.SQ_CALL_ATTN_PREFILL) <= table + 131072 * 528 + 1024
 
 
+def test_shared_decode_workspace_holds_the_user_keys_once(sq):
+    """User keys of a step over a shared context cost either 528 bytes of partial results per 64 keys and row (one query row per K/V
+    head) or 1040 bytes of work items per 128 keys and row of a group of 16, never both."""
+    for B, H, U in ((8, 8, 4096), (16, 8, 32768), (17, 4, 100)):
+        with_u, none = (sq.make_shape(B, H, 32768, 1024, 1, u, 0.1) for u in (U, 0))
+        more = {c: sq.workspace_bytes(with_u, c) - sq.workspace_bytes(none, c) for c in (sq.SQ_CALL_DECODE_STEP, sq.SQ_CALL_GQA_MEAN_DECODE_STEP)}
+        assert more[sq.SQ_CALL_DECODE_STEP] <= B * H * ((U + 63) // 64) * 528 + 256
+        assert more[sq.SQ_CALL_GQA_MEAN_DECODE_STEP] <= B * H * 16 * ((U + 127) // 128) * 1040 + 256
+
+
+@pytest.mark.parametrize("B,H,L,C_,U", [(20, 4, 190, 7, 7578), (32, 4, 80048, 1122, 3319), (9, 2, 3354, 579, 27181),
+                                        (16, 8, 16384, 512, 8384), (16, 8, 16384, 512, 8448)])
+def test_noalloc_step_takes_what_fits_with_work_items(sq, B, H, L, C_, U):
+    """The step's intermediate state with its user keys in work items fits the built-in buffer: so does the step."""
+    urows = (B + 15) // 16 * H
+    tables = B * H * (C_ * 4 + 8 + (C_ + 31) // 32 * 4) + urows * (C_ * 16 + 20) + (768 + urows) * 16 * 528 + 12 * 256
+    items = urows * (16 * ((U + 127) // 128) + (L + 127) // 128) * 1040
+    assert tables + items <= sq.SQ_NOALLOC_SCRATCH_BYTES
+    assert sq.workspace_bytes(sq.make_shape(B, H, L, C_, 1, U, 0.1), sq.SQ_CALL_DECODE_STEP) <= sq.SQ_NOALLOC_SCRATCH_BYTES
+
+
 def test_host_side_validation(sq):
     L = sq.lib()
     buf = (C.c_char * 4096)()
