@@ -291,11 +291,12 @@ bool step_is_shared(const sq_shape_t *sh, int G = 1)
     return !step_is_indexed(sh, G) || (long long)sh->B * sh->H * G * ((long long)sh->L + sh->U) > SHARED_MIN_KEYS;
 }
 
-// User keys beside the selection: with one query row per K/V head and sequence (with more, every row would read them again), unless
+// User keys beside the selection: with one query row per K/V head and sequence (with more, every row would read them again), up to a
+// number of them (see there), unless
 // the built-in buffer of sq_decode_step_noalloc holds the step with work items alone (16 sequences' pieces are up to 1.5 % larger).
 bool shared_step_has_pieces(const sq_shape_t *sh, int G)
 {
-    if (G != 1) return false;
+    if (G != 1 || !sq::union_takes_user_keys((long long)sh->B * sh->H, sh->U, sh->C)) return false;
     Carver pieces(nullptr), items(nullptr);
     carve_step_shared(pieces, sh, G, true);
     carve_step_shared(items, sh, G, false);

@@ -325,6 +325,23 @@ hipError_t launch_cand_select(CandSelect cs, const float *thresh, uint32_t *keep
 // user_pieces_for(U) partial results at slots user->slot_base + r * nuq + (0 .. nuq - 1) of `partials`.
 constexpr int USER_PIECE = 64;
 inline int user_pieces_for(int U) { return (U + USER_PIECE - 1) / USER_PIECE; }
+// The same pieces beside the two launches of a union selection (see launch_select): up to this many of all rows.  What the launches hide
+// is fixed, a piece's partial result (528 bytes written and read again for 32 KB of keys and values) is not, and a row of more than 1024
+// clusters is selected in several steps, which hide more.  Whole steps, us, user keys in work items / in pieces:
+//   sequences x heads, clusters    8192 pieces      16384            32768            65536           131072
+//   16 x  8,  256                  82.9 / 80.6    122.8 / 123.6    203.6 / 212.2    363 / 388          -
+//    8 x 20,  400                  75.0 / 71.6    115.8 / 114.9    193.8 / 202.5    356 / 379          -
+//    9 x  5,  700                  75.6 / 74.2    115.4 / 117.6    197.0 / 207.8    358 / 388          -
+//   16 x 32, 1024                 137.9 / 133.2   178.4 / 175.5    260.2 / 265.3    420.6 / 439     1374 / 1509 (at 262144)
+//   16 x 16, 1500                     -           161.8 / 149.6    243.3 / 237.0    405.7 / 415      720 / 764
+//   12 x 12, 2000                 124.5 / 116.0   167.5 / 153.4    247.7 / 235.6    411.7 / 412.2      -
+//   16 x  8, 2500                     -           178.4 / 165.0    259.8 / 243.0    421.3 / 419.1    741 / 773
+//    9 x  8, 4096                     -           188.4 / 175.6    272.2 / 253.0    429.3 / 418.3    745 / 780
+//   16 x  2, 8192                 190.3 / 179.7   230.6 / 218.0    317.4 / 300.4    480.4 / 452.8      -
+inline bool union_takes_user_keys(long long rows, int U, int C)
+{
+    return rows * user_pieces_for(U) <= (C > 1024 ? 30720 + 13 * C : C > 716 ? 20 * C : 14336);
+}
 hipError_t launch_decode_attn_index(const void *q, const void *Kf, const void *Vf, KeyIndexPlan plan, float *partials,
                                     void *out, float *lse, int rows, int H, int G, float sm_scale, const UserAttn *user,
                                     hipStream_t s);

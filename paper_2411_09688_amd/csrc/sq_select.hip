@@ -877,7 +877,8 @@ hipError_t launch_select(const float *logits, const float *row_max, const float 
         // union row and queue for its vector ALUs, so they get a launch of their own, four rows per workgroup
         // across the chip (the same function, the same bits); the union kernel then reads the mask words.
         opt.masks_ready = 0;
-        // The rows' user keys ride along (one query row per K/V head and sequence: with more, every row would read them again, 2 to
+        // The rows' user keys ride along, up to a number of them (union_takes_user_keys; one query row per K/V head and sequence: with more,
+        // every row would read them again, 2 to
         // 5 % slower): both launches are chains of round trips that leave the memory system idle, while the attention behind them
         // takes as long as its bytes.  The union launch, one workgroup per compute unit for a few rows, takes what its idle compute
         // units read in its own time, the mask launch the rest.  Whole steps, us, none / all in the mask launch / in halves / all in

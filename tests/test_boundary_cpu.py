@@ -79,6 +79,17 @@ def test_shared_decode_workspace_holds_the_user_keys_once(sq):
         assert more[sq.SQ_CALL_GQA_MEAN_DECODE_STEP] <= B * H * 16 * ((U + 127) // 128) * 1040 + 256
 
 
+@pytest.mark.parametrize("B,H,C_,pieces", [(16, 32, 1024, 20 * 1024), (16, 8, 256, 14336), (9, 8, 700, 14336), (8, 32, 800, 20 * 800),
+                                           (16, 8, 1025, 30720 + 13 * 1025), (12, 12, 4096, 30720 + 13 * 4096)])
+def test_shared_decode_takes_user_keys_beside_the_selection_up_to_a_line(sq, B, H, C_, pieces):
+    """The workspace shows which form a step takes: 528 bytes per row and 64 user keys, or 1040 per row of a group and 128."""
+    last = pieces // (B * H) * 64
+    for U, beside in ((last, True), (last + 1, False), (2 * last, False)):
+        with_u, none = (sq.workspace_bytes(sq.make_shape(B, H, 32768, C_, 1, u, 0.1), sq.SQ_CALL_DECODE_STEP) for u in (U, 0))
+        want = B * H * ((U + 63) // 64) * 528 if beside else H * 16 * ((U + 127) // 128) * 1040
+        assert abs(with_u - none - want) <= 256, (U, beside)
+
+
 @pytest.mark.parametrize("B,H,L,C_,U", [(20, 4, 190, 7, 7578), (32, 4, 80048, 1122, 3319), (9, 2, 3354, 579, 27181),
                                         (16, 8, 16384, 512, 8384), (16, 8, 16384, 512, 8448)])
 def test_noalloc_step_takes_what_fits_with_work_items(sq, B, H, L, C_, U):

@@ -325,6 +325,30 @@ def test_shared_context_user_pieces(sq, oracle, U):
     step_against_oracle(sq, oracle, w, f"shared_pieces U={U}")
 
 
+@pytest.mark.parametrize("over", [0, 1])
+def test_shared_context_user_keys_on_both_sides_of_the_line(sq, over):
+    """The most user keys that are attended to beside the selection (14336 pieces of 64), and one more: in work items.  Nothing of the
+    context is kept, so that a row is the dense attention over its user keys: float32 sums over the inputs' fp16 values."""
+    B, H, L, C, U = 16, 8, 4000, 50, 7168 + over
+    g = torch.Generator(device="cuda").manual_seed(23)
+    rnd = lambda *s: torch.randn(*s, generator=g, device="cuda").half()  # noqa: E731
+    q, cent, K, V, Ku, Vu = rnd(B, H, 1, 128), rnd(H, C, 128), rnd(H, L, 128), rnd(H, L, 128), rnd(B, H, U, 128), rnd(B, H, U, 128)
+    sizes = torch.full((H, C), L // C, dtype=torch.int32, device="cuda")
+    offsets = (torch.arange(C + 1, device="cuda", dtype=torch.int32) * (L // C)).expand(H, C + 1).contiguous()
+    sh = sq.make_shape(B, H, L, C, 1, U, 128 ** -0.5)
+    out, lse = torch.full_like(q, 7.0), torch.full((B, H, 1), 7.0, device="cuda")
+    mask, nk = torch.full((B, H, 1, 2), 7, dtype=torch.int32, device="cuda"), torch.full((B, H, 1), 7, dtype=torch.int32, device="cuda")
+    sq.sq_decode_step(sh, q, cent, sizes, offsets, torch.full((H,), 2.0, device="cuda"), K, V, Ku, Vu, out, lse, mask, nk,
+                      sq.workspace(sh, sq.SQ_CALL_DECODE_STEP, "cuda:0"))
+    torch.cuda.synchronize()
+    assert not mask.any() and not nk.any()
+    x = (q.float() * Ku.float()).sum(-1) * 128 ** -0.5
+    want_lse = torch.logsumexp(x, -1, keepdim=True)
+    want = (torch.exp(x - want_lse).unsqueeze(-1) * Vu.float()).sum(2, keepdim=True)
+    assert (lse - want_lse).abs().max().item() <= 1e-4
+    assert (out.float() - want).abs().max().item() <= ATTN_ATOL
+
+
 def test_shared_context_step_extremes(sq, oracle):
     base = dict(B=10, H=2, L=1024, C=32, Lq=1, U=33, keep_frac=0.5, seed=12, threads=2)
     # every sequence keeps everything: each key is owned by all sequences of the group
