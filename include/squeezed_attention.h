@@ -171,6 +171,18 @@ int sq_sparse_attn_prefill(const sq_shape_t *shape, const void *q, const void *K
 int sq_prefill_plan(const sq_shape_t *shape, int one_set, int32_t *waves, int32_t *splits);
 
 /*
+ * Which launches make the kept set of a call with one kept set per (sequence, head), `which` one of SQ_CALL_ATTN_PREFILL_SHARED,
+ * SQ_CALL_PREFILL_MEAN_STEP and SQ_CALL_HIER_PREFILL_MEAN_STEP (C1: its coarse clusters; not used otherwise).  *form is the sum of
+ * SQ_FORM_SELECTS (the attention launch selects; otherwise a launch in front of it does, or the ranges are the caller's),
+ * SQ_FORM_CHILDREN (the pass over the candidates lists them itself) and SQ_FORM_DEALT (the shares of the key blocks are dealt in
+ * proportion to the kept keys).  Host only.
+ */
+#define SQ_FORM_SELECTS 1
+#define SQ_FORM_CHILDREN 2
+#define SQ_FORM_DEALT 4
+int sq_prefill_form(const sq_shape_t *shape, int which, int32_t C1, int32_t *form);
+
+/*
  * Prefill selection as the paper does it (Appendix D, "Prefill Stage"): the cluster scores of Eq. 1,
  * S_i(t) = exp(x_i(t) - m(t)) / D(t), are averaged over the Lq query tokens of a (sequence, head) and
  * cluster i is kept iff N_i > 0 and the average is > thresh[h] (strict): ONE kept set for all query

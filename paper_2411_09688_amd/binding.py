@@ -25,7 +25,7 @@ SQ_OK, SQ_ERR_INVALID_ARG, SQ_ERR_UNSUPPORTED, SQ_ERR_WORKSPACE, SQ_ERR_HIP = 0,
 SQ_MAX_LEVELS = 4
 
 EXPORTS = ("sq_workspace_bytes", "sq_last_error", "sq_version", "sq_centroid_score", "sq_select",
-           "sq_sparse_attn_decode", "sq_sparse_attn_prefill", "sq_prefill_plan", "sq_hier_select", "sq_decode_step",
+           "sq_sparse_attn_decode", "sq_sparse_attn_prefill", "sq_prefill_plan", "sq_prefill_form", "sq_hier_select", "sq_decode_step",
            "sq_hier_decode_step", "sq_decode_step_noalloc", "sq_select_mean", "sq_sparse_attn_prefill_shared", "sq_prefill_step",
            "sq_prefill_mean_step", "sq_gqa_decode_step", "sq_multilevel_select", "sq_multilevel_decode_step",
            "sq_kmeans_normalize", "sq_kmeans_step", "sq_cluster_layout", "sq_cluster_nest", "sq_calibrate_threshold", "sq_hier_prefill_mean_step", "sq_hier_prefill_step", "sq_gqa_mean_decode_step", "sq_profile_begin",
@@ -70,6 +70,7 @@ def lib() -> C.CDLL:
         L.sq_sparse_attn_decode.argtypes = [sp] + [vp] * 10 + [vp, sz, vp]
         L.sq_sparse_attn_prefill.argtypes = [sp] + [vp] * 9 + [vp, sz, vp]
         L.sq_prefill_plan.argtypes = [sp, C.c_int, C.POINTER(C.c_int32), C.POINTER(C.c_int32)]
+        L.sq_prefill_form.argtypes = [sp, C.c_int, C.c_int32, C.POINTER(C.c_int32)]
         L.sq_select_mean.argtypes = [sp] + [vp] * 10 + [vp, sz, vp]
         L.sq_sparse_attn_prefill_shared.argtypes = [sp] + [vp] * 10 + [vp, sz, vp]
         L.sq_prefill_step.argtypes = [sp] + [vp] * 13 + [vp, sz, vp]
@@ -192,6 +193,16 @@ def sq_prefill_plan(shape, one_set=False):
     waves, splits = C.c_int32(), C.c_int32()
     _check(lib().sq_prefill_plan(C.byref(shape), int(one_set), C.byref(waves), C.byref(splits)))
     return waves.value, splits.value
+
+
+SQ_FORM_SELECTS, SQ_FORM_CHILDREN, SQ_FORM_DEALT = 1, 2, 4
+
+
+def sq_prefill_form(shape, which, C1=0):
+    """Which launches make the kept set of a call with one kept set per (sequence, head): a sum of SQ_FORM_*."""
+    form = C.c_int32()
+    _check(lib().sq_prefill_form(C.byref(shape), which, C1, C.byref(form)))
+    return form.value
 
 
 def sq_select_mean(shape, logits, row_max, denom, thresh, sizes, offsets, keep_mask, ranges, n_ranges, n_keys, ws,

@@ -940,6 +940,23 @@ int sq_prefill_plan(const sq_shape_t *sh, int one_set, int32_t *waves, int32_t *
     return SQ_OK;
 }
 
+int sq_prefill_form(const sq_shape_t *sh, int which, int32_t C1, int32_t *form)
+{
+    if (int rc = check_shape(sh, __func__, false)) return rc;
+    if (!form) return fail(SQ_ERR_INVALID_ARG, "%s: form is NULL", __func__);
+    const bool hier = which == SQ_CALL_HIER_PREFILL_MEAN_STEP;
+    if (which != SQ_CALL_ATTN_PREFILL_SHARED && which != SQ_CALL_PREFILL_MEAN_STEP && !hier)
+        return fail(SQ_ERR_INVALID_ARG, "%s: which = %d is not a call with one kept set", __func__, which);
+    if (hier && (C1 < 1 || C1 > sh->C)) return fail(SQ_ERR_INVALID_ARG, "%s: C1 = %d, C = %d", __func__, C1, sh->C);
+    const sq::Shape shp = to_shape(sh);
+    *form = which != SQ_CALL_ATTN_PREFILL_SHARED && sq::prefill_selects(shp, hier) ? SQ_FORM_SELECTS
+            : sq::prefill_deal(shp, nullptr).units                                 ? SQ_FORM_DEALT
+                                                                                   : 0;
+    if (hier && sq::lookup_selects_children(sh->B * sh->H, sh->Lq, sh->C, C1)) *form |= SQ_FORM_CHILDREN;
+    g_err[0] = 0;
+    return SQ_OK;
+}
+
 int sq_sparse_attn_prefill(const sq_shape_t *sh, const void *q, const void *K_fixed, const void *V_fixed,
                            const int32_t *offsets, const uint32_t *keep_mask, const void *K_user, const void *V_user,
                            void *out, float *lse, void *ws, size_t ws_bytes, void *stream)

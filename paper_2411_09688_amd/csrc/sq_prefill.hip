@@ -1243,23 +1243,32 @@ hipError_t launch_prefill_attn_shared(const void *q, const void *Kf, const void 
                                                reinterpret_cast<const int32_t *>(hdr), out, lse, partials, PfSelect{}, sh, s);
 }
 
-// Where the attention launch makes the kept set itself: whenever the records and the rows of a share's keys find room in LDS, since a
-// workgroup's few loads of scores (about 3 us, traced) cost less than a launch in front (5 to 7 us) and the two round trips to
-// the list it leaves (2 us) for every shape measured.  Whole steps, us, a launch of its own / here:
+// Where the attention launch makes the kept set itself: where the records and the rows of a share's keys find room in LDS and the launch
+// is about one round of workgroups, since a workgroup's few loads of scores (about 3 us, traced) cost less than a launch in front (5 to
+// 7 us) and the two round trips to the list it leaves (2 us).  Whole steps, us, a launch of its own / here:
 //   32 heads x 1024 tokens x 32768 keys, 1024 clusters 140.3 / 137.4    20 x 150 x 20011, 613 37.7 / 34.8    32 x 16 x 2000, 32 23.8 / 19.1
 //    1 x 1024 x 32768, 1638  41.4 / 37.3     1 x 16 x 2000, 40  19.4 / 15.7     4 x 1024 x 8000, 400  43.4 / 39.5
 //   2 x 32 x 500 x 20000, 500  127.9 / 124.9    32 x 16 x 32768, 1024  75.0 / 71.3    20 x 17 x 30000, 1500  49.8 / 47.9
+// Every further round pays the 3 us again, and more where the scores come in many parts (the longer the prompt, the more, up to 512):
+//    4 x 4096 x 8000, 400 (64 workgroups) 80.6 / 74.6    8 x 8192 x 8000, 400 (256) 294 / 289    one head x 16384 x 32768, 1024 (512 parts) 239 / 226
+//   20 x 6000 x 4000, 200 (480, 25 parts) 98.9 / 98.2    12 x 10000 x 8000, 300 (480, 42) 150.9 / 151.0    3 x 32 x 1100 x 4000, 128 (480) 92.3 / 90.9
+//    5 x 20000 x 16384, 1000 (395, 102) 229 / 239    3 x 40000 x 16384, 1000 (471, 157) 266 / 281    16 x 8192 x 16384, 1024 (512, 32) 262 / 268
+//   20 x 8192 x 16384, 1024 (640) 338 / 349    32 x 8192 x 16384, 1024 (1024) 563 / 573    32 x 16384 x 16384, 1024 (2048) 989 / 1021
 // Eight waves: 64 KB of rows beside 66 KB of tiles, one workgroup per compute unit as before; four: 12 KB, still two.
 // A row's candidates: the same, up to 4096 clusters a head with eight waves (with four that many spill 61 registers) and not where the
 // shares are dealt in proportion (their lengths come from the list in front).  Both-level steps, a launch of its own / here:
 //   8 x 512 x 65536 3000  69.9 / 65.4    8 x 512 x 90000 4096  60.0 / 55.0    4 x 300 x 100000 4000  55.6 / 52.2    4 x 512 x 40000 1500  51.5 / 46.6
 //   8 x 16 x 32768 2048  36.2 / 31.1    2 x 40 x 60000 2000  36.0 / 31.1    1 x 100 x 33000 700  35.2 / 30.8    1 x 3 x 130000 4096  40.5 / 37.8
+//   24 x 4096 x 16384 1000 (384 workgroups) 201.5 / 197.9    32 x 4096 x 32768 2000 (512) 377.3 / 379.6    32 x 8192 x 16384 1000 (1024) 411 / 416
 bool prefill_selects(const Shape &sh, bool candidates)
 {
     const PfPlan plan = prefill_plan(true, sh);
     const long long blocks = ((long long)sh.L + PF_BN - 1) / PF_BN;
     if (candidates && prefill_deal(sh, nullptr).units) return false;
-    return sh.C <= pf_select_max_c(plan.waves, candidates) && (blocks + plan.n_split - 1) / plan.n_split <= pf_select_blocks(plan.waves);
+    if (sh.C > pf_select_max_c(plan.waves, candidates) || (blocks + plan.n_split - 1) / plan.n_split > pf_select_blocks(plan.waves)) return false;
+    const long long bm = pf_bm(plan.waves), slots = 256 * 8 / plan.waves;
+    const long long groups = (long long)sh.B * sh.H * ((sh.Lq + bm - 1) / bm) * plan.n_split;
+    return groups <= slots || (8 * groups <= 15 * slots && (candidates || lookup_parts(sh.B * sh.H, sh.Lq, sh.C) <= 64));
 }
 
 hipError_t launch_prefill_attn_select(const void *q, const void *Kf, const void *Vf, const void *Ku, const void *Vu,

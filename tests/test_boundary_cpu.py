@@ -101,6 +101,21 @@ def test_noalloc_step_takes_what_fits_with_work_items(sq, B, H, L, C_, U):
     assert sq.workspace_bytes(sq.make_shape(B, H, L, C_, 1, U, 0.1), sq.SQ_CALL_DECODE_STEP) <= sq.SQ_NOALLOC_SCRATCH_BYTES
 
 
+@pytest.mark.parametrize("B,H,L,C_,Lq,C1,inside", [
+    (1, 32, 32768, 1024, 1024, 0, True), (1, 20, 20011, 613, 150, 0, True),
+    (1, 1, 32768, 1024, 16384, 0, True),                      # one round of workgroups: any number of parts
+    (480, 1, 2000, 100, 200, 0, True), (481, 1, 2000, 100, 200, 0, False),   # eight waves: 15/8 of a round
+    (960, 1, 400, 20, 4, 0, True), (961, 1, 400, 20, 4, 0, False),           # four waves
+    (1, 8, 8000, 400, 15360, 0, True),                        # 480 workgroups, 64 parts
+    (1, 5, 16384, 1000, 20000, 0, False),                     # 395 workgroups, 102 parts
+    (1, 32, 16384, 1024, 8192, 0, False), (1, 24, 16384, 1000, 4096, 32, True), (1, 32, 16384, 1000, 8192, 32, False),
+])
+def test_the_attention_launch_selects_in_about_one_round(sq, B, H, L, C_, Lq, C1, inside):
+    sh = sq.make_shape(B, H, L, C_, Lq, 64, 0.1, causal_user=True)
+    which = sq.SQ_CALL_HIER_PREFILL_MEAN_STEP if C1 else sq.SQ_CALL_PREFILL_MEAN_STEP
+    assert bool(sq.sq_prefill_form(sh, which, C1) & sq.SQ_FORM_SELECTS) == inside, sq.sq_prefill_plan(sh, one_set=True)
+
+
 def test_host_side_validation(sq):
     L = sq.lib()
     buf = (C.c_char * 4096)()

@@ -223,6 +223,7 @@ OWN_CASES = [
     dict(B=2, H=8, L=6000, C=4096, C1=64, Lq=300),     # eight waves, the same
     dict(B=2, H=8, L=6000, C=4097, C1=64, Lq=300),
     dict(B=1, H=1, L=5000, C=257, C1=16, Lq=1),        # one key in a group of its own; short shares
+    dict(B=31, H=31, L=600, C=50, C1=8, Lq=2),         # more than 15/8 of a round of workgroups
 ]
 
 

@@ -54,6 +54,8 @@ ROUTES = [
     dict(B=200, H=1, L=64 * 256 + 1, C=300, Lq=150, U=5),   # and one block more
     dict(B=500, H=1, L=64 * 48, C=150, Lq=3, U=7),          # four waves: 48 blocks
     dict(B=500, H=1, L=64 * 48 + 1, C=150, Lq=3, U=7),
+    dict(B=30, H=32, L=400, C=20, Lq=4, U=3),               # four waves: 15/8 of a round of workgroups
+    dict(B=31, H=31, L=400, C=20, Lq=4, U=3),               # and one workgroup more
 ]
 
 
