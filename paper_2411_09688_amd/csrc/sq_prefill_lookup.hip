@@ -442,11 +442,14 @@ size_t lookup_part_floats(int BH, int C)
 // (6.5 us, and the round trip to the list it leaves), whole two-level steps, us, own launch / inside, by heads x tokens x keys, fine /
 // coarse clusters: 8 x 512 x 262144, 16384 / 256 99.0 / 94.6, 1 x 512 x 262144, 16384 / 256 57.7 / 52.7, 4 x 300 x 200000, 10000 / 100
 // 68.2 / 63.5, 8 x 200 x 131072, 6000 / 64 69.9 / 64.8, 8 x 300 x 40000, 2000 / 40 56.7 / 52.3, 1 x 64 x 100000, 4000 / 64 38.4 / 32.4.
-// The line is what a slice holds in LDS: 8 KB of candidates beside 32 KB of centroids, three workgroups per compute unit.
+// Every further round of workgroups (three a compute unit) pays the 2 us again: 16 x 8192 x 32768, 2000 / 64 (1024 workgroups) 347.7 / 350.3,
+// 32 x 4096 (1024) 348.1 / 351.1, 32 x 6000, 2000 / 1000 (1504) 506.9 / 510.5, 32 x 16384 x 16384, 1000 / 32 (4096) 822.6 / 827.2;
+// 20 x 8192 x 40000, 1500 / 64 (1280) 494.2 / 490.7.
+// The other line is what a slice holds in LDS: 8 KB of candidates beside 32 KB of centroids, three workgroups per compute unit.
 bool lookup_selects_children(int BH, int Lq, int C, int C1)
 {
     const int groups = (C + LK_G - 1) / LK_G, n_slice = lookup_slices(BH, Lq, C);
-    return C1 <= LK_COARSE_MAX && (groups + n_slice - 1) / n_slice <= LK_MAX_GROUPS;
+    return (long long)BH * ((Lq + LK_BT - 1) / LK_BT) * n_slice <= 3 * 256 && C1 <= LK_COARSE_MAX && (groups + n_slice - 1) / n_slice <= LK_MAX_GROUPS;
 }
 
 hipError_t launch_prefill_lookup(const void *q, const void *centroids, const int32_t *sizes, const float *thresh,

@@ -116,6 +116,14 @@ def test_the_attention_launch_selects_in_about_one_round(sq, B, H, L, C_, Lq, C1
     assert bool(sq.sq_prefill_form(sh, which, C1) & sq.SQ_FORM_SELECTS) == inside, sq.sq_prefill_plan(sh, one_set=True)
 
 
+@pytest.mark.parametrize("H,C_,Lq,C1,inside", [(8, 16384, 512, 256, True), (1, 3000, 40, 1024, True), (1, 3000, 40, 1025, False),
+                                               (12, 2000, 64 * 128, 64, True), (12, 2000, 64 * 128 + 1, 64, False), (32, 1000, 16384, 32, False)])
+def test_the_pass_over_the_candidates_lists_them_in_one_round(sq, H, C_, Lq, C1, inside):
+    """Up to 768 workgroups (blocks of 128 tokens of all heads) and 1024 coarse clusters."""
+    sh = sq.make_shape(1, H, 32768, C_, Lq, 64, 0.1, causal_user=True)
+    assert bool(sq.sq_prefill_form(sh, sq.SQ_CALL_HIER_PREFILL_MEAN_STEP, C1) & sq.SQ_FORM_CHILDREN) == inside
+
+
 def test_host_side_validation(sq):
     L = sq.lib()
     buf = (C.c_char * 4096)()

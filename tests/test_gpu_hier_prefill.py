@@ -153,7 +153,10 @@ CHILD_CASES = [
     dict(B=130, H=4, L=2500, C=2048, C1=40, Lq=2),    # one slice a row, as many candidates as it holds
     dict(B=130, H=4, L=2500, C=2049, C1=40, Lq=2),    # and one more: a launch in front
     dict(B=1, H=2, L=4000, C=3000, C1=1024, Lq=40),   # the most coarse clusters, hardly a group of children each
+    dict(B=1, H=2, L=4000, C=3000, C1=1025, Lq=40),   # and one more: a launch in front
     dict(B=1, H=1, L=3000, C=700, C1=2, Lq=130),      # two coarse clusters, two blocks of tokens
+    dict(B=24, H=32, L=600, C=50, C1=8, Lq=3),        # one round of workgroups
+    dict(B=31, H=25, L=600, C=50, C1=8, Lq=3),        # and more
 ]
 
 
