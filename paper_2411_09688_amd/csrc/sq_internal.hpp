@@ -239,7 +239,8 @@ size_t prefill_partial_floats(bool shared, const Shape &sh);
 constexpr int PF_DEAL_MIN_SPLIT = 4, PF_DEAL_MIN_BLOCKS = 16;   // shares a unit and blocks a share (an eighth of the context), at least
 struct PfDeal {
     int units, shares;
-    int2 *dealt;                           // [units]: first share, shares; behind the partial results [shares, 32 * waves]
+    int rows;                              // of a share's partial results: a unit's query tokens, a multiple of 8
+    int2 *dealt;                           // [units]: first share, shares; behind the partial results [shares, rows]
     size_t words;                          // of both
 };
 PfDeal prefill_deal(const Shape &sh, float *ws);

@@ -944,7 +944,7 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     const float inv = empty ? 0.0f : 1.0f / lt;
     _Float16 *orow = out + (row0 + nq) * D;
     const bool dealt = SHARED && !SELECT && deal.units != 0;   // (uniform)
-    float *pr = partials + ((dealt ? (size_t)share0 * PF_BM + (size_t)(nq - q0) * n_split : (row0 + nq) * (size_t)n_split) + split) * PART_STRIDE;
+    float *pr = partials + ((dealt ? (size_t)share0 * deal.rows + (size_t)(nq - q0) * n_split : (row0 + nq) * (size_t)n_split) + split) * PART_STRIDE;
     if (n_split > 1) {                                      // this share's (m, l, o) for the merge launch; m in natural units
         if (!again)
 #pragma unroll
@@ -986,10 +986,10 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
 // Traced, a wave per row that found the maximum first / eight shares a round, the last of them taken again to fill it / this kernel:
 // 32768 rows x 2 shares 11.7 / 8.2 / 7.8 us, 7992 x 7 7.2 / 6.4 / 5.9, 4096 x 16 8.0 / 7.7 / 7.3; 4096 x 10 6.5 / 5.4, 3000 x 11
 // 4.9 / 4.5, 3000 x 17 8.2 / 7.1, 1000 x 24 5.2 / 4.1, 100 x 63 4.0 / 3.9 (the last two of the three).
-// DEALT: rows are units times bm positions, and the attention launch named every unit's first share and number of shares.
+// DEALT: rows are units times deal.rows positions, and the attention launch named every unit's first share and number of shares.
 struct PfMerge {
     PfDeal deal;
-    int bm, nqb, B, H, Lq;
+    int nqb, B, H, Lq;
 };
 template <int AHEAD, int GROUPS, bool ONE, bool DEALT>
 __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restrict__ partials, _Float16 *__restrict__ out,
@@ -998,12 +998,12 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
     const int half = threadIdx.x >> 5, lane = threadIdx.x & 31, group = half % GROUPS;
     size_t row = (size_t)blockIdx.x * (8 / GROUPS) + half / GROUPS;
     const float *pr = partials + min(row, rows - 1) * (size_t)n_split * PART_STRIDE;
-    if constexpr (DEALT) {                                  // (a workgroup's rows are of one unit: bm is a multiple of 8)
-        const int unit = (int)(row / mg.bm), r = (int)(row - (size_t)unit * mg.bm), nq = unit % mg.nqb * mg.bm + r;
+    if constexpr (DEALT) {                                  // (a workgroup's rows are of one unit: deal.rows is a multiple of 8)
+        const int unit = (int)(row / mg.deal.rows), r = (int)(row - (size_t)unit * mg.deal.rows), nq = unit % mg.nqb * mg.deal.rows + r;
         const int2 d = mg.deal.dealt[unit];
         n_split = d.y;
-        if (n_split == 1) return;                           // (its only share wrote the outputs)
-        pr = partials + ((size_t)d.x * mg.bm + (size_t)r * n_split) * PART_STRIDE;
+        if (n_split == 1 || nq - half / GROUPS >= mg.Lq) return;   // (its only share wrote the outputs; no row of the workgroup is a query)
+        pr = partials + ((size_t)d.x * mg.deal.rows + (size_t)r * n_split) * PART_STRIDE;
         rows = (size_t)mg.B * mg.H * mg.Lq;
         row = nq < mg.Lq ? ((size_t)(unit / mg.nqb % mg.B) * mg.H + unit / (mg.nqb * mg.B)) * mg.Lq + nq : rows;
     }
@@ -1134,7 +1134,8 @@ PfDeal prefill_deal(const Shape &sh, float *ws)
     if (units > 64 || sh.B * sh.H == 1 || plan.n_split < PF_DEAL_MIN_SPLIT || (long long)sh.L < 8ll * PF_BN * PF_DEAL_MIN_BLOCKS * plan.n_split) return d;
     d.units = (int)units;
     d.shares = (int)units * plan.n_split;
-    const size_t floats = (size_t)d.shares * bm * PART_STRIDE;
+    d.rows = std::min(bm, (sh.Lq + 7) / 8 * 8);
+    const size_t floats = (size_t)d.shares * d.rows * PART_STRIDE;
     d.dealt = reinterpret_cast<int2 *>(ws + floats);
     d.words = floats + 2 * (size_t)units;
     return d;
@@ -1180,14 +1181,15 @@ hipError_t launch_prefill_kernels(const void *q, const void *Kf, const void *Vf,
                                                                                     out, lse, partials, plan.n_split, sel, deal, sh, s);
     if (e != hipSuccess || plan.n_split == 1) return e;
     const int bm = pf_bm(plan.waves);
-    const size_t n = deal.units ? (size_t)deal.units * bm : (size_t)sh.B * sh.H * sh.Lq;
+    const size_t rows_out = (size_t)sh.B * sh.H * sh.Lq, n = deal.units ? (size_t)deal.units * deal.rows : rows_out;
     auto merge = [&](auto kernel, int groups) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)((n * groups + 7) / 8)), dim3(256), 0, s, partials, (_Float16 *)out, lse,
-                           plan.n_split, n, PfMerge{deal, bm, (sh.Lq + bm - 1) / bm, sh.B, sh.H, sh.Lq});
+                           plan.n_split, n, PfMerge{deal, (sh.Lq + bm - 1) / bm, sh.B, sh.H, sh.Lq});
     };
     if (deal.units) {                                       // (a unit's shares are known there)
-        n >= 4096 ? merge(prefill_merge_kernel<8, 1, false, true>, 1) : n >= 1024 ? merge(prefill_merge_kernel<8, 2, false, true>, 2)
-                                                                                : merge(prefill_merge_kernel<8, 8, false, true>, 8);
+        rows_out >= 4096   ? merge(prefill_merge_kernel<8, 1, false, true>, 1)
+        : rows_out >= 1024 ? merge(prefill_merge_kernel<8, 2, false, true>, 2)
+                           : merge(prefill_merge_kernel<8, 8, false, true>, 8);
         return hipGetLastError();
     }
     // Several half waves per row where the rows are few; a half wave takes its shares in rounds of at most eight, as even as they go.

@@ -124,6 +124,18 @@ def test_the_pass_over_the_candidates_lists_them_in_one_round(sq, H, C_, Lq, C1,
     assert bool(sq.sq_prefill_form(sh, sq.SQ_CALL_HIER_PREFILL_MEAN_STEP, C1) & sq.SQ_FORM_CHILDREN) == inside
 
 
+@pytest.mark.parametrize("B,H", [(1, 8), (4, 1), (1, 2)])
+def test_dealt_shares_hold_the_tokens_there_are(sq, B, H):
+    """Shares in proportion to the kept keys: 528 bytes of partial results per share and query token, tokens rounded up to eight."""
+    size = {}
+    for Lq in (1, 8, 9, 16):
+        sh = sq.make_shape(B, H, 524288, 16384, Lq, 1, 0.1)
+        assert sq.sq_prefill_form(sh, sq.SQ_CALL_ATTN_PREFILL_SHARED) == sq.SQ_FORM_DEALT
+        size[Lq] = sq.workspace_bytes(sh, sq.SQ_CALL_ATTN_PREFILL_SHARED)
+    splits = sq.sq_prefill_plan(sh, one_set=True)[1]
+    assert size[1] == size[8] and size[9] == size[16] and abs(size[16] - size[8] - B * H * splits * 8 * 528) <= 256
+
+
 def test_host_side_validation(sq):
     L = sq.lib()
     buf = (C.c_char * 4096)()

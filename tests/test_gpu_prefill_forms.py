@@ -165,6 +165,8 @@ DEALT = [
     dict(B=1, H=32, L=64 * 512, C=300, Lq=300, U=300),       # 64 units, four shares each on average
     dict(B=2, H=8, L=64 * 1024 + 5, C=400, Lq=257, U=10),    # 32 units, a unit of one query among every two
     dict(B=3, H=1, L=500000, C=200, Lq=200, U=0),            # three units, 59 shares each, no user keys
+    dict(B=8, H=1, L=524288, C=200, Lq=5, U=5),              # short prompts: eight rows a share, five of them queries
+    dict(B=4, H=1, L=524288, C=200, Lq=40, U=40),
 ]
 
 
