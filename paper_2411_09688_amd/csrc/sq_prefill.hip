@@ -986,7 +986,10 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
 // Traced, a wave per row that found the maximum first / eight shares a round, the last of them taken again to fill it / this kernel:
 // 32768 rows x 2 shares 11.7 / 8.2 / 7.8 us, 7992 x 7 7.2 / 6.4 / 5.9, 4096 x 16 8.0 / 7.7 / 7.3; 4096 x 10 6.5 / 5.4, 3000 x 11
 // 4.9 / 4.5, 3000 x 17 8.2 / 7.1, 1000 x 24 5.2 / 4.1, 100 x 63 4.0 / 3.9 (the last two of the three).
-// DEALT: rows are units times deal.rows positions, and the attention launch named every unit's first share and number of shares.
+// DEALT: rows are units times deal.rows positions, and the attention launch named every unit's first share and number of shares.  Only
+// the device knows how many: a workgroup, whose rows are of one unit, branches to the form with rounds as even as they go.  (Traced, a
+// fixed eight shares a round / this: 16384 rows x 4 shares on average 9.6 / 9.0 us, 5140 x 8 7.9 / 7.1, 4096 x 16 9.1 / 8.8; known on the
+// host, without dealing: 6.6, 4.6.)
 struct PfMerge {
     PfDeal deal;
     int nqb, B, H, Lq;
@@ -999,13 +1002,15 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
     size_t row = (size_t)blockIdx.x * (8 / GROUPS) + half / GROUPS;
     const float *pr = partials + min(row, rows - 1) * (size_t)n_split * PART_STRIDE;
     if constexpr (DEALT) {                                  // (a workgroup's rows are of one unit: deal.rows is a multiple of 8)
-        const int unit = (int)(row / mg.deal.rows), r = (int)(row - (size_t)unit * mg.deal.rows), nq = unit % mg.nqb * mg.deal.rows + r;
+        const int first = (int)blockIdx.x * (8 / GROUPS), unit = first / mg.deal.rows;   // (uniform, as all that follows from them)
+        const int r0 = first - unit * mg.deal.rows, q0 = unit % mg.nqb * mg.deal.rows, bh = unit / mg.nqb % mg.B * mg.H + unit / (mg.nqb * mg.B);
         const int2 d = mg.deal.dealt[unit];
-        n_split = d.y;
-        if (n_split == 1 || nq - half / GROUPS >= mg.Lq) return;   // (its only share wrote the outputs; no row of the workgroup is a query)
+        n_split = __builtin_amdgcn_readfirstlane(d.y);
+        if (n_split == 1 || q0 + r0 >= mg.Lq) return;       // (its only share wrote the outputs; no row of the workgroup is a query)
+        const int r = r0 + half / GROUPS;
         pr = partials + ((size_t)d.x * mg.deal.rows + (size_t)r * n_split) * PART_STRIDE;
         rows = (size_t)mg.B * mg.H * mg.Lq;
-        row = nq < mg.Lq ? ((size_t)(unit / mg.nqb % mg.B) * mg.H + unit / (mg.nqb * mg.B)) * mg.Lq + nq : rows;
+        row = q0 + r < mg.Lq ? (size_t)bh * mg.Lq + q0 + r : rows;
     }
     float M = SQ_NEG_INF, l = 0.0f;
     f4 o = {0.f, 0.f, 0.f, 0.f};
@@ -1026,29 +1031,40 @@ __global__ __launch_bounds__(256) void prefill_merge_kernel(const float *__restr
         }
         M = top;
     };
-    for (int s0 = group; ONE ? s0 == group : s0 < n_split; s0 += AHEAD * GROUPS) {
-        float m[AHEAD], n[AHEAD];
-        f4 v[AHEAD];
-        constexpr auto full = [](int k) { return ONE && (GROUPS == 1 || k < AHEAD - 1); };
+    auto take = [&](auto ahead) PF_INLINE {                 // all of the half wave's shares, `ahead` of them in a round
+        constexpr int A = ahead;
+        for (int s0 = group; ONE ? s0 == group : s0 < n_split; s0 += A * GROUPS) {
+            float m[A], n[A];
+            f4 v[A];
+            constexpr auto full = [](int k) { return ONE && (GROUPS == 1 || k < A - 1); };
 #pragma unroll
-        for (int k = 0; k < AHEAD; ++k) {
-            const float *p = pr + (size_t)(full(k) ? s0 + k * GROUPS : min(s0 + k * GROUPS, n_split - 1)) * PART_STRIDE;
-            const float2 ml = *reinterpret_cast<const float2 *>(p);
-            m[k] = ml.x;
-            n[k] = ml.y;
-            v[k] = *reinterpret_cast<const f4 *>(p + 4 + 4 * lane);
+            for (int k = 0; k < A; ++k) {
+                const float *p = pr + (size_t)(full(k) ? s0 + k * GROUPS : min(s0 + k * GROUPS, n_split - 1)) * PART_STRIDE;
+                const float2 ml = *reinterpret_cast<const float2 *>(p);
+                m[k] = ml.x;
+                n[k] = ml.y;
+                v[k] = *reinterpret_cast<const f4 *>(p + 4 + 4 * lane);
+            }
+            __builtin_amdgcn_sched_barrier(0);              // (all of them under way)
+#pragma unroll
+            for (int k = 0; k < A; ++k) {                   // past the end: zeros, no share's values, which may be infinite or NaN
+                const bool there = full(k) || s0 + k * GROUPS < n_split;
+                m[k] = there ? m[k] : SQ_NEG_INF;
+                n[k] = there ? n[k] : 0.0f;
+#pragma unroll
+                for (int d = 0; d < 4; ++d) v[k][d] = there ? v[k][d] : 0.0f;
+            }
+            fold(m, n, v);
         }
-        __builtin_amdgcn_sched_barrier(0);                  // (all of them under way)
-#pragma unroll
-        for (int k = 0; k < AHEAD; ++k) {                   // past the end: zeros, no share's values, which may be infinite or NaN
-            const bool there = full(k) || s0 + k * GROUPS < n_split;
-            m[k] = there ? m[k] : SQ_NEG_INF;
-            n[k] = there ? n[k] : 0.0f;
-#pragma unroll
-            for (int d = 0; d < 4; ++d) v[k][d] = there ? v[k][d] : 0.0f;
-        }
-        fold(m, n, v);
-    }
+    };
+    if constexpr (DEALT) {                                  // rounds as even as they go (uniform)
+        const int per = (n_split + GROUPS - 1) / GROUPS, rounds = (per + AHEAD - 1) / AHEAD, ahead = (per + rounds - 1) / rounds;
+        static_for<AHEAD + 1>([&](auto a) PF_INLINE {
+            if constexpr (a > 0)
+                if (ahead == a) take(a);
+        });
+    } else
+        take(std::integral_constant<int, AHEAD>{});
     if constexpr (GROUPS > 1) {
         __shared__ __align__(16) float s_part[8][PART_STRIDE];
         if (lane == 0) {
@@ -1121,8 +1137,14 @@ size_t prefill_partial_floats(bool shared, const Shape &sh)
     return s > 1 ? (size_t)sh.B * sh.H * sh.Lq * s * PART_STRIDE : 0;
 }
 
-// Dealing costs a workgroup about a microsecond in front of its first load and pays where shares are long; heads differ by a factor of
-// three at the measured thresholds.  Whole two-level steps, us, even / in proportion, by heads x tokens x keys (blocks a share, an eighth
+// Dealing costs a workgroup about a microsecond in front of its first load and the merge two, and pays where shares are long and heads
+// keep different numbers of keys, which only the device knows.  Whole one-level steps, us, even / in proportion, by the share of the keys
+// kept (heads alike up to 1/16, apart from 1/8 on):     1/32            1/16           0.09          1/8          0.2          0.3
+//   20 heads x 257 tokens x  65536 keys            66.6 / 68.6    71.2 / 74.2    84.9 / 83.5   114 / 98    152 / 127    188 / 157
+//   32       x 512        x 100000                  114 / 117      144 / 150      168 / 173    197 / 200   404 / 309    554 / 403
+//   16       x 300        x 131072                 70.8 / 72.4    84.7 / 86.7     126 / 106    173 / 129   236 / 169    293 / 210
+//   16       x 400        x 200000                 99.3 / 100.3    123 / 124      279 / 177    408 / 236   506 / 318    579 / 400
+// Two-level steps, whose heads differ by a factor of three at the measured thresholds, us, even / in proportion, by heads x tokens x keys (blocks a share, an eighth
 // of the context): 8 x 512 x 262144, 1/16 kept 104.7 / 98.8, 0.09 kept 123.7 / 114.5 (32); 4 x 300 x 200000 67.8 / 68.4 (12); 8 x 200 x
 // 131072 69.0 / 67.6, 8 x 512 x 65536 73.5 / 74.0, one head x 512 x 262144 57.6 / 58.7 (8; one head's units keep the same keys).
 PfDeal prefill_deal(const Shape &sh, float *ws)

@@ -283,6 +283,11 @@ MERGE_CASES = [
     (False, 12, dict(B=1, H=20, L=3000, C=99, Lq=60, U=60)),
     (False, 20, dict(B=1, H=2, L=900, C=30, Lq=200, U=300)),
     (False, 20, dict(B=1, H=4, L=6000, C=99, Lq=369, U=369)),
+    # shares in proportion to the kept keys: one, two and eight half waves a row, workgroups of eight and of four waves
+    (True, 8, dict(B=1, H=16, L=65541, C=300, Lq=300, U=300)),
+    (True, 8, dict(B=1, H=20, L=65536, C=300, Lq=257, U=257)),
+    (True, 16, dict(B=1, H=4, L=131072, C=300, Lq=1000, U=600)),
+    (True, 61, dict(B=1, H=2, L=524288, C=300, Lq=5, U=50)),
 ]
 
 
@@ -307,6 +312,7 @@ def test_values_that_are_not_finite_stay_in_their_rows(sq, one_set, splits, case
         gk, P = masked_problem(sq, w, 0.3, np.random.default_rng(6))
         assert ((gk * w.sizes[None, :, None]).sum(-1) > 0).all()
     assert sq.sq_prefill_plan(P.shape, one_set=one_set)[1] == splits
+    assert (sq.sq_prefill_form(P.shape, sq.SQ_CALL_ATTN_PREFILL_SHARED) == sq.SQ_FORM_DEALT) == (w.L >= 65536)
 
     def attend():
         if not one_set:

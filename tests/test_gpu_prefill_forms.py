@@ -161,25 +161,36 @@ def test_merges_one_kept_set(sq, oracle, waves, splits, case):
     test_one_kept_set(sq, oracle, waves, splits, case, 0.02)             # (shares without a key among them)
 
 
+# (waves, shares on average, dealt in proportion).  The merge takes one half wave a row from 4096 rows on, two from 1024 on, else eight.
 DEALT = [
-    dict(B=1, H=32, L=64 * 512, C=300, Lq=300, U=300),       # 64 units, four shares each on average
-    dict(B=2, H=8, L=64 * 1024 + 5, C=400, Lq=257, U=10),    # 32 units, a unit of one query among every two
-    dict(B=3, H=1, L=500000, C=200, Lq=200, U=0),            # three units, 59 shares each, no user keys
-    dict(B=8, H=1, L=524288, C=200, Lq=5, U=5),              # short prompts: eight rows a share, five of them queries
-    dict(B=4, H=1, L=524288, C=200, Lq=40, U=40),
+    (8, 4, True, dict(B=1, H=32, L=64 * 512, C=300, Lq=300, U=300)),       # 64 units
+    (8, 8, True, dict(B=2, H=8, L=64 * 1024 + 5, C=400, Lq=257, U=10)),    # 32 units, a unit of one query among every two
+    (8, 62, False, dict(B=3, H=1, L=500000, C=200, Lq=200, U=0)),          # a little short of 16 blocks a share: even shares
+    (8, 64, True, dict(B=3, H=1, L=524288, C=200, Lq=200, U=0)),           # three units, no user keys; 600 rows
+    (8, 42, True, dict(B=3, H=1, L=524288, C=200, Lq=512, U=512)),         # 1536 rows
+    (4, 61, True, dict(B=8, H=1, L=524288, C=200, Lq=5, U=5)),             # short prompts: eight rows a share, five of them queries
+    (8, 61, True, dict(B=4, H=1, L=524288, C=200, Lq=40, U=40)),
+    (4, 10, True, dict(B=5, H=2, L=64 * 2048, C=300, Lq=520, U=50)),       # four waves; 5200 rows
+    (4, 32, True, dict(B=5, H=1, L=64 * 4096, C=300, Lq=257, U=0)),        # 1285 rows, a unit of one query among every three
+    (4, 54, True, dict(B=3, H=1, L=524288, C=200, Lq=257, U=0)),           # 771 rows
 ]
 
 
-@pytest.mark.parametrize("case", DEALT, ids=lambda c: "B{B}H{H}L{L}Lq{Lq}".format(**c))
-def test_shares_in_proportion(sq, oracle, case):
-    """Long contexts of few units: the shares follow the rows' numbers of kept keys, which go from none over one cluster to all."""
+@pytest.mark.parametrize("keep", ["some", "none"])
+@pytest.mark.parametrize("waves,splits,dealt,case", DEALT, ids=lambda v: "B{B}H{H}L{L}Lq{Lq}".format(**v) if isinstance(v, dict) else str(v))
+def test_shares_in_proportion(sq, oracle, waves, splits, dealt, case, keep):
+    """Long contexts of few units: the shares follow the rows' numbers of kept keys, which go from none over one cluster to all; with
+    nothing kept and no user keys, a unit's shares are those of units without a block."""
     w = wl.make_workload("prefill_dealt", seed=53, threads=4, keep_frac=0.3, causal_user=True, **case)
     rng = np.random.default_rng(16)
     share = np.resize([0.0, 0.02, 0.5, 1.0, 0.1], (w.B, w.H))
     kept = rng.random((w.B, w.H, w.C)) < share[..., None]
     kept[share == 0.02] = np.arange(w.C) == 7                 # one cluster
+    if keep == "none":
+        kept[:] = False
     P = sq.upload(w)
-    assert sq.sq_prefill_plan(P.shape, one_set=True)[1] >= 4
+    assert sq.sq_prefill_plan(P.shape, one_set=True) == (waves, splits)
+    assert sq.sq_prefill_form(P.shape, sq.SQ_CALL_ATTN_PREFILL_SHARED) == (sq.SQ_FORM_DEALT if dealt else 0)
     ranges, nr = np.zeros((w.B, w.H, w.C, 2), np.int32), np.zeros((w.B, w.H), np.int32)
     for b in range(w.B):
         for h in range(w.H):
