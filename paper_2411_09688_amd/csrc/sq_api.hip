@@ -365,11 +365,9 @@ struct KmeansWs {
 KmeansWs carve_kmeans(Carver &cv, const sq_shape_t *sh)
 {
     const size_t heads = (size_t)sh->B * sh->H;
-    const int PL = sq::kmeans_part_len(sh->L);
-    const size_t parts = (size_t)(sh->L + PL - 1) / PL;
     KmeansWs w{};
     w.hn = cv.take<float>(heads * sh->C);
-    w.hist = cv.take<int32_t>(heads * parts * ((sh->C + 1) & ~1));   // (or two parts' counts of 16 bits in the place of one)
+    w.hist = cv.take<int32_t>(sq::kmeans_hist_ints((int)heads, sh->L, sh->C));
     return w;
 }
 

@@ -245,9 +245,8 @@ struct PfDeal {
 };
 PfDeal prefill_deal(const Shape &sh, float *ws);
 
-// Offline clustering (sq_kmeans.hip).  hn: [heads * C] floats; hist: [heads * parts * C] ints with
-// parts = ceil(L / kmeans_part_len(L)).
-int kmeans_part_len(int L);
+// Offline clustering (sq_kmeans.hip).  hn: [heads * C] floats; hist: kmeans_hist_ints() ints, the parts' counts of every centre.
+size_t kmeans_hist_ints(int heads, int L, int C);
 hipError_t launch_normalize_rows(const void *K, void *X, size_t rows, hipStream_t s);
 hipError_t launch_kmeans_step(const void *X, const void *centers_in, void *centers_out, int32_t *assign,
                               int32_t *sizes, int32_t *offsets, int32_t *perm, float *hn, int32_t *hist, int heads,

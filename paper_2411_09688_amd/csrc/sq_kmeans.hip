@@ -83,13 +83,13 @@ __global__ __launch_bounds__(256) void half_norm_kernel(const _Float16 *__restri
     if (l16 == 0 && row < rows) nhn[row] = -(0.5f * ss);
 }
 
-// HIST: the workgroup's keys are a part of the grouping below, and it leaves their histogram, 16 bits a centre, too.
+// HIST: the workgroup's keys are a part of the grouping below, and it leaves their histogram, too: 16 bits a centre in a row of Cs.
 template <bool HIST>
 __global__ __launch_bounds__(256, 3) void kmeans_assign_kernel(const _Float16 *__restrict__ X,
                                                                const _Float16 *__restrict__ cent,
                                                                const float *__restrict__ nhn,
                                                                int32_t *__restrict__ assign, uint32_t *__restrict__ hist,
-                                                               int L, int C)
+                                                               int L, int C, int Cs)
 {
     __shared__ __align__(16) KmStage stage[KM_STAGES];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -202,7 +202,7 @@ __global__ __launch_bounds__(256, 3) void kmeans_assign_kernel(const _Float16 *_
     }
     take(cur, cur_c0);
     uint32_t *s_cnt = reinterpret_cast<uint32_t *>(stage);    // two centres a word, where the groups were
-    const int words = (C + 1) >> 1;
+    const int words = Cs >> 1;
     if constexpr (HIST) {
         static_assert(sizeof(stage) >= SELECT_MAX_C * 2, "a count of 16 bits for every centre");
         __syncthreads();                                      // (the last group is read)
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(256) void kmeans_hist_kernel(const int32_t *__restr
 }
 
 // Grouping, step 2: per centre, the part counts become exclusive prefixes over the parts and their total the cluster size.  A
-// workgroup takes 64 centres, each of its four waves a quarter of the parts (at most 64, see kmeans_part_len).  5.8 us at 32 heads x
+// workgroup takes 64 centres, each of its four waves a quarter of the parts (at most 64, see kmeans_part_len, or 128 of 16 bits).  5.8 us at 32 heads x
 // 1024 centres x 64 parts, where one workgroup per head, which also scanned the sizes into offsets, took 9.4.
 // CT: type of the counts, 16 bits where the keys of a head are at most 2^15 in at most 128 parts.  Cs: counts of a part's row.
 template <typename CT>
@@ -482,11 +482,37 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const _Float16 *__rest
         *reinterpret_cast<const h8 *>(src + ((size_t)h * L + k) * D + piece * 8);
 }
 
-int kmeans_part_len(int L)
+static int kmeans_part_len(int L)
 {
     const int want = (L + 63) / 64;                           // at most 64 parts per head
     const int pl = ((want + 255) / 256) * 256;
     return pl < 512 ? 512 : pl;
+}
+
+// Counts of a part's row of 16 bits: whole lines of 128 bytes, since workgroups on different XCDs write neighbouring rows (rows of C,
+// whole steps, us, rows of C / of lines: 32 heads x 32768 keys x 1638 centres 429.0 / 419.2, x 1900 484.0 / 472.9, 8 x 32768 x 6553
+// 414.4 / 407.6, 24 x 32768 x 1638 328.7 / 322.6; with the launch that counted the ids again 428.3, 479.2, 417.7, 327.9).
+// Below 256 centres the rows are a small part of the step and the lines would be mostly padding.
+static int kmeans_hist_row(int C) { return C < 256 ? (C + 1) & ~1 : (C + 63) & ~63; }
+
+// Does the assignment leave the histograms?  The launch that counted the ids again is a launch's time where there is little to count;
+// what it costs the assignment is a microsecond a workgroup, under the others' products, and the rows of 256 keys in 16 bits are as many
+// bytes as those of 512 in 32.  Whole step, us, with that launch / here: 32 heads x 32768 keys x 1024 centres 287.1 / 283.2, 16 x 30000 x
+// 800 129.9 / 127.0, 4 x 32768 x 1638 79.0 / 75.7, 1 x 20000 x 500 34.0 / 30.4, 32 x 3000 x 130 35.4 / 32.1, 1 x 2000 x 40 23.1 / 20.0.
+// The lines are the scan's 128 parts (and every prefix has to fit 16 bits), and 2^23 counts (16 MB): with more they leave the L2s before
+// they are read, 8 x 32768 x 8192 506.5 / 499.1, 4 x 32768 x 16384 522 / 515, 32 x 32768 x 2048 505.5 / 501.7, but
+// 32 x 32768 x 4096 933 / 943, 16 x 32768 x 6000 706 / 722, 12 x 32768 x 8192 719 / 728, 6 x 32768 x 16384 738 / 764.
+static bool kmeans_fused(int heads, int L, int C)
+{
+    const long long parts = (L + KM_ROWS_PER_WG - 1) / KM_ROWS_PER_WG;
+    return parts <= KM_FUSED_PARTS && heads * parts * kmeans_hist_row(C) <= 1ll << 23;
+}
+
+size_t kmeans_hist_ints(int heads, int L, int C)
+{
+    const size_t PL = kmeans_part_len(L), counted = (size_t)heads * ((L + PL - 1) / PL) * C;   // (cluster_nest counts them always)
+    if (!kmeans_fused(heads, L, C)) return counted;
+    return std::max(counted, (size_t)heads * ((L + KM_ROWS_PER_WG - 1) / KM_ROWS_PER_WG) * kmeans_hist_row(C) / 2);
 }
 
 hipError_t launch_normalize_rows(const void *K, void *X, size_t rows, hipStream_t s)
@@ -521,24 +547,19 @@ hipError_t launch_kmeans_step(const void *X, const void *centers_in, void *cente
 {
     hipLaunchKernelGGL(half_norm_kernel, dim3((H * C + 15) / 16), dim3(256), 0, s, (const _Float16 *)centers_in, hn, H * C);
     const dim3 grid_a((L + KM_ROWS_PER_WG - 1) / KM_ROWS_PER_WG, H);
-    // The launch that counted the ids again is a launch's time where there is little to count; what it costs the assignment is a
-    // microsecond a workgroup, under the others' products, and the rows of 256 keys in 16 bits are as many bytes as those of 512 in 32.
-    // Whole step, us, with that launch / here: 32 heads x 32768 keys x 1024 centres 287.1 / 283.2, 16 x 30000 x 800 129.9 / 127.0,
-    // 4 x 32768 x 1638 79.0 / 75.7, 1 x 20000 x 500 34.0 / 30.4, 32 x 3000 x 130 35.4 / 32.1, 1 x 2000 x 40 23.1 / 20.0.  The line is
-    // the scan's 128 parts (and every prefix has to fit 16 bits).
-    const bool fused = L <= KM_FUSED_PARTS * KM_ROWS_PER_WG;
+    const bool fused = kmeans_fused(H, L, C);
     auto assign_kernel = [&](auto kernel) {
         hipEvent_t ev0, ev1;
         if (profile_pair(&ev0, &ev1))
             hipExtLaunchKernelGGL(kernel, grid_a, dim3(256), 0, s, ev0, ev1, 0, (const _Float16 *)X, (const _Float16 *)centers_in,
-                                  (const float *)hn, assign, reinterpret_cast<uint32_t *>(hist), L, C);
+                                  (const float *)hn, assign, reinterpret_cast<uint32_t *>(hist), L, C, kmeans_hist_row(C));
         else
             hipLaunchKernelGGL(kernel, grid_a, dim3(256), 0, s, (const _Float16 *)X, (const _Float16 *)centers_in, (const float *)hn,
-                               assign, reinterpret_cast<uint32_t *>(hist), L, C);
+                               assign, reinterpret_cast<uint32_t *>(hist), L, C, kmeans_hist_row(C));
     };
     if (fused) {
         assign_kernel(kmeans_assign_kernel<true>);
-        launch_scan_scatter(assign, sizes, offsets, perm, reinterpret_cast<uint16_t *>(hist), H, L, C, (C + 1) & ~1, KM_ROWS_PER_WG, s);
+        launch_scan_scatter(assign, sizes, offsets, perm, reinterpret_cast<uint16_t *>(hist), H, L, C, kmeans_hist_row(C), KM_ROWS_PER_WG, s);
     } else {
         assign_kernel(kmeans_assign_kernel<false>);
         launch_group(assign, sizes, offsets, perm, hist, H, L, C, s);

@@ -200,3 +200,16 @@ def test_noalloc_step_rejects_oversized_shapes_on_the_host(sq):
     assert rc == sq.SQ_ERR_WORKSPACE and b"built-in" in L.sq_last_error()
     fits = sq.make_shape(1, 32, 32768, 1024, 1, 512, 0.0884)
     assert sq.workspace_bytes(fits, sq.SQ_CALL_DECODE_STEP) <= sq.SQ_NOALLOC_SCRATCH_BYTES
+
+
+@pytest.mark.parametrize("H,L,C_", [(32, 32768, 1024), (32, 32768, 1638), (8, 32768, 8192), (12, 32768, 8192), (32, 32769, 1900), (3, 256, 1), (1, 513, 65), (2, 513, 257)])
+def test_kmeans_workspace_rows_of_whole_lines(sq, H, L, C_):
+    """Counts of the parts: 16 bits in rows of whole 128-byte lines (of words below 256 centres) for parts of 256 keys, up to 32768 keys and 2^23 counts, and in any
+    case room for 32 bits and parts of 512 keys (or 64 parts); a half norm per centre."""
+    to, parts = 2 if C_ < 256 else 64, (L + 255) // 256
+    row = (C_ + to - 1) // to * to
+    want = H * ((L + 511) // 512 if L <= 32768 else (L + 767) // 768) * C_ * 4
+    if parts <= 128 and H * parts * row <= 1 << 23:
+        want = max(want, H * parts * row * 2)
+    up = lambda n: (n + 255) // 256 * 256  # noqa: E731
+    assert sq.workspace_bytes(sq.make_shape(1, H, L, C_, 1, 0, 1.0), sq.SQ_CALL_KMEANS_STEP) == up(H * C_ * 4) + up(want)

@@ -179,10 +179,11 @@ def test_means_of_clusters_in_any_order(sq, H, L, C, members, order):
         np.testing.assert_allclose(got[h], want, rtol=6e-4, atol=1e-3)
 
 
-@pytest.mark.parametrize("H,L,C", [(2, 32768, 33), (2, 32769, 33), (3, 256, 1), (1, 9001, 9001)])
+@pytest.mark.parametrize("H,L,C", [(2, 32768, 33), (2, 32769, 33), (3, 256, 1), (1, 9001, 9001), (3, 700, 255), (3, 700, 256), (3, 700, 257)])
 def test_histograms_left_by_the_assignment(sq, H, L, C):
     """The most keys whose histograms the assignment leaves, and one more; one cluster that takes all but the last keys, so that the
-    counts of a part and the prefixes reach their largest; an odd number of centres, many of them."""
+    counts of a part and the prefixes reach their largest; an odd number of centres, many of them; rows of counts that fill lines of 128
+    bytes, and that do not."""
     rng = np.random.default_rng(16)
     X = np.broadcast_to(rng.standard_normal((H, 1, 128)), (H, L, 128)) + 0.01 * rng.standard_normal((H, L, 128))
     X[:, -min(L // 2, 5):] *= -1
