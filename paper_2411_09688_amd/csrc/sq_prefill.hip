@@ -418,8 +418,10 @@ __global__ __launch_bounds__(64 * PF_WAVES, 8 / PF_WAVES) void prefill_attn_kern
     // Masked form: the first blocks of the share are rarely left out, so their tiles are requested before the list is known: they land
     // with the masks instead of a round trip after the list.  With that, the blocks' table entries requested in front of the unions and
     // the first ones kept beside the list, whole steps, us: 16 heads x 200 tokens x 5000 keys 40.2 -> 39.1, 32 x 40 x 8000 42.5 -> 41.8,
-    // 4 x 100 x 16000 32.7 -> 31.8, 32 x 1024 x 32768 the same.
-    const bool ahead = !SHARED && n_list >= LK;
+    // 4 x 100 x 16000 32.7 -> 31.8, 32 x 1024 x 32768 the same.  Of fewer queries than a wave holds many blocks are left out where a
+    // per cent or so of the keys is kept, and the list waits for tiles in vain: 8 x 16 x 100000, 1/100 kept, 72.4 without, 75.0 with
+    // them, 8 x 3 x 100000, 1/20 68.1 / 70.6, one head x 1 x 500000, 1/500 52.0 / 54.1; 16 x 20 x 5000, 0.15 27.0 / 26.5.
+    const bool ahead = !SHARED && n_list >= LK && Lq >= 32;
     if (ahead)
 #pragma unroll
         for (int b = 0; b < LK; ++b) {

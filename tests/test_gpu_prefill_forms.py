@@ -61,6 +61,8 @@ MASKED = [
     (8, 5, dict(B=2, H=12, L=3001, C=99, Lq=333, U=333)),
     (4, 6, dict(B=2, H=40, L=4096, C=100, Lq=120, U=120)),
     (8, 2, dict(B=1, H=32, L=64 * 150, C=300, Lq=1000, U=64)),           # 75 listed blocks
+    (4, 12, dict(B=1, H=40, L=20000, C=300, Lq=31, U=31)),               # the first tiles wait for the list
+    (4, 12, dict(B=1, H=40, L=20000, C=300, Lq=32, U=32)),               # and leave before it
 ]
 
 
