@@ -166,7 +166,9 @@ int sq_sparse_attn_prefill(const sq_shape_t *shape, const void *q, const void *K
  * blocks of its (sequence, head, group of tokens) are shared by *splits workgroups (with one kept set, a long context and few
  * groups: on average, in proportion to the kept keys).  one_set != 0: the calls with one kept set
  * per (sequence, head) (sq_sparse_attn_prefill_shared and the steps on averaged scores); 0: per-query selection.  Host only;
- * results do not depend on it beyond the order of summation.
+ * results do not depend on it beyond the order of summation.  Where the shares are in proportion (SQ_FORM_DEALT below), a row's
+ * order of summation follows the kept counts of all (sequence, head)s of the call, so that its bits are the same again only in a call
+ * whose other rows keep as many keys; everywhere else they follow from the shape and the row alone.
  */
 int sq_prefill_plan(const sq_shape_t *shape, int one_set, int32_t *waves, int32_t *splits);
 

@@ -120,9 +120,10 @@ struct SelectOpts {
     const int2 *cand_items;          //   items) of the row: the row is then staged from these streams alone
 };
 
-// Dense attention over the rows' user keys as a rider on the selection launch (see sq_user_attn.hpp): q [rows, d],
-// user keys [rows / G, U, d]; row r leaves nuq = ceil(U / KPC) partial results, one per chunk of user keys, at slots
-// slot_base + r * nuq + (0 .. nuq - 1) of `partials`.  q == nullptr: none.
+// Dense attention over the rows' user keys as a rider on another launch (see sq_user_attn.hpp): q [rows, d], user keys
+// [rows / G, U, d]; row r leaves nuq partial results, one per chunk of KPC user keys (work-list steps) or per piece of USER_PIECE
+// (steps through the key-index list or over a shared context), at slots slot_base + r * nuq + (0 .. nuq - 1) of `partials`.
+// q == nullptr: none.
 struct UserAttn {
     const _Float16 *q, *Ku, *Vu;
     float *partials;

@@ -4,7 +4,7 @@
 //   half norms  hn_c = |c|^2 / 2 of the current centres                         (one wave per centre)
 //   assignment  a(x) = argmin_c |x - c|^2 = argmax_c (x . c - hn_c)              (matrix cores, below)
 //   grouping    stable counting sort of the key indices by centre id: per-part histograms (left by the assignment's workgroups
-//               up to 32768 keys), a scan over parts and centres, and a scatter in key order -- sizes, offsets and the member
+//               up to 32768 keys and 2^23 counts), a scan over parts and centres, and a scatter in key order -- sizes, offsets and the member
 //               list of every cluster
 //   update      centre = mean of its members' vectors (a cluster without members keeps its centre)
 //

@@ -251,7 +251,8 @@ __device__ __forceinline__ PfDealt pf_deal(const PfDeal &deal, int piece, const 
 
 // ---- the kept set made by the attention launch ----------------------------------------------------------------------------
 // (mean_row_select.)  Bound by a chain of one round of loads (the clusters' sizes, offsets and up to eight parts of their scores
-// together) and three barriers, about 3 us of the launch's prologue; the rows' searches run in parallel, a few per thread.
+// together; a further round for every eight parts more, and two in front for candidates, their number and their ids) and three barriers,
+// about 3 us of the launch's prologue; the rows' searches run in parallel, a few per thread.
 // Rows of the keys of a share's n_list fixed blocks, split, split + n_split, ... of the list of kept keys: every key finds its cluster
 // among the records of mean_row_select.  (Behind the last key: that key again.)
 template <int PF_WAVES, int MAX_C>

@@ -213,3 +213,12 @@ def test_kmeans_workspace_rows_of_whole_lines(sq, H, L, C_):
         want = max(want, H * parts * row * 2)
     up = lambda n: (n + 255) // 256 * 256  # noqa: E731
     assert sq.workspace_bytes(sq.make_shape(1, H, L, C_, 1, 0, 1.0), sq.SQ_CALL_KMEANS_STEP) == up(H * C_ * 4) + up(want)
+
+
+def test_prefill_form_checks_its_arguments(sq):
+    sh = sq.make_shape(1, 8, 262144, 16384, 512, 512, 0.1, causal_user=True)
+    assert sq.sq_prefill_form(sh, sq.SQ_CALL_HIER_PREFILL_MEAN_STEP, 256) == sq.SQ_FORM_CHILDREN | sq.SQ_FORM_DEALT
+    for which, C1 in ((sq.SQ_CALL_DECODE_STEP, 0), (sq.SQ_CALL_HIER_PREFILL_MEAN_STEP, 0), (sq.SQ_CALL_HIER_PREFILL_MEAN_STEP, 16385)):
+        with pytest.raises(sq.SqError):
+            sq.sq_prefill_form(sh, which, C1)
+    assert sq.lib().sq_prefill_form(C.byref(sh), sq.SQ_CALL_PREFILL_MEAN_STEP, 0, None) == sq.SQ_ERR_INVALID_ARG
